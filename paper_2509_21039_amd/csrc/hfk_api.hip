@@ -48,6 +48,12 @@ int device_cu_count()
     return cus;
 }
 
+int term_limit(double tau)
+{
+    if (!(tau > 0.0)) return -1000000;
+    return (int)floor(log2(tau < 1e-10 ? tau : 1e-10) + log2(1e-10));
+}
+
 // Per-workgroup copies of F are used while they stay within this many bytes in total.
 constexpr double kPrivateBudget = 16.0e9;
 // Ket-side Coulomb vectors: one per workgroup within this budget, else fewer copies that
@@ -108,6 +114,8 @@ Layout make_layout(int64_t n, int g, int prec, int with_grad, int groups, bool a
     L.bra_f = take(sizeof(float) * 8 * g2 * PC);
     L.boys_g = take(sizeof(double) * kBoysGrid * kBoysStrideG);
     L.boys_g_f = take(sizeof(double) * kBoysGridF * kBoysStrideF);
+    L.bexp = take(sizeof(short) * g2 * PC);
+    L.kexp = take(sizeof(int) * g2 * ((PC + kWaveKets - 1) / kWaveKets));
     L.nitems = take(sizeof(long long) * PC);
     L.lim = take(sizeof(int) * PC);
     L.item_off = take(sizeof(long long) * (PC + 1));

@@ -61,6 +61,16 @@ __device__ inline void pair_prims_atoms(const Basis &b, int64_t i, int64_t j, co
     }
 }
 
+// Binary exponent e with u < 2^e of a primitive pair's bound (see term_limit).
+__device__ inline short term_exponent(double u)
+{
+    if (!(u <= 1e300)) return (short)kTermAlways;
+    if (!(u > 0.0)) return (short)kTermNever;
+    int e;
+    (void)frexp(u, &e);
+    return (short)e;
+}
+
 // Reciprocal square root in FP64: the hardware estimate (relative error ~5e-8) refined by
 // one Newton step, y (1 + e/2) with e = 1 - x y^2, leaving ~1.5 e^2 ~ 4e-15.
 __device__ inline double rsqrt_fp64(double x)
@@ -178,6 +188,67 @@ __device__ inline double boys_eval_d(const double *__restrict__ tab, unsigned of
 // Wave-uniform tables read through the constant address space are fetched with scalar
 // loads (they are never written while a kernel runs).
 template <typename T> using cptr = const __attribute__((address_space(4))) T *;
+
+// Term masks of the quartet kernels.  Lane ab < G^2 holds the bra's exponent e_ab (kTermNone
+// in the other lanes); kexp points at the maxima over the wave's kets of the G ket primitive
+// pairs of one row cb.  need[d] has bit ab set if some ket primitive pair d' <= d of the row
+// is not negligible beside bra primitive pair ab, so need[G-1] lists the bra primitive pairs
+// with anything to do in the row, and the first d with the bit set is where the row's terms
+// start: leading (tight) primitives fall away first, and the terms that stay are added in
+// the order of the full sum.
+template <int G> struct TermMask {
+    using T = unsigned;
+};
+template <> struct TermMask<6> {
+    using T = unsigned long long;
+};
+template <int G>
+__device__ inline void term_masks(int ebra, cptr<int> kexp, int limit, typename TermMask<G>::T *need)
+{
+    using T = typename TermMask<G>::T;
+    int e[G];
+#pragma unroll
+    for (int d = 0; d < G; ++d) e[d] = kexp[d];
+    T m = 0;
+#pragma unroll
+    for (int d = 0; d < G; ++d) {
+        m |= (T)__builtin_amdgcn_ballot_w64(ebra > limit - e[d]);
+        need[d] = m;
+    }
+}
+__device__ inline int term_first(unsigned m) { return __builtin_ctz(m); }
+__device__ inline int term_first(unsigned long long m) { return __builtin_ctzll(m); }
+
+// Calls body(integral_constant<ND>, ab) for every bra primitive pair ab listed in need, in
+// ascending order, with ND >= the terms that pair needs of a row (its last ND): every count
+// for G <= 4, every second one above (code size).
+template <int ND> struct TermCount {
+    static constexpr int value = ND;
+};
+template <int G, int ND, typename T, typename Body>
+__device__ __attribute__((always_inline)) inline void term_dispatch(const T *need, T bit, int ab, Body &&body)
+{
+    constexpr int kStep = G <= 4 ? 1 : 2;
+    if constexpr (ND - kStep < 1) {
+        body(TermCount<ND>{}, ab);
+    } else {
+        // terms before the last ND - kStep: d < G - ND + kStep
+        if (need[G - ND + kStep - 1] & bit)
+            body(TermCount<ND>{}, ab);
+        else
+            term_dispatch<G, ND - kStep>(need, bit, ab, body);
+    }
+}
+template <int G, typename T, typename Body>
+__device__ __attribute__((always_inline)) inline void for_terms(const T *need, Body &&body)
+{
+    for (T m = need[G - 1]; m;) {
+        const int ab = term_first(m);
+        const T bit = m & (~m + 1);
+        m ^= bit;
+        term_dispatch<G, G>(need, bit, ab, body);
+    }
+}
 
 // Buffer loads from an SoA table [C][g2][pcap] with the ket t as a 32-bit lane offset.  A
 // resource covers `rows` consecutive primitive-pair rows of one component starting at row

@@ -195,6 +195,8 @@ struct Layout {
     size_t bgw, bgw_f;                     // gradient: [pcap][g2][kGW] bra weights mu S, fa S, fb S, fa fb S, fb^2 S
     size_t bra, bra_f;                     // [pcap][g2][8] Px Py Pz S -2Px -2Py -2Pz |P|^2 (wave-uniform bra data)
     size_t boys_g, boys_g_f;               // gradient tables: H of degree 7 (FP64), g(T) = -(4/sqrt(pi)) F1(T) (FP32 grid)
+    size_t bexp;                           // [pcap][g2] binary exponents bounding every primitive pair (term screen)
+    size_t kexp;                           // [pcap / kWaveKets, rounded up][g2] their maxima over the kets of a wave
     size_t nitems, lim, item_off, scan_tmp;
     size_t gcnt, goff;                     // per bra group: blocks, and their exclusive prefix
     int64_t ngroups;                       // bra groups of 2^gshift bras
@@ -275,6 +277,19 @@ hipError_t launch_dens_check_batched(DevHeader *hdr, int64_t nmol, const long lo
 // bases; kmu/kfa: per-atom gradient tables or NULL) past the last pair.
 hipError_t launch_pair_pad(const DevHeader *hdr, int64_t pcap, int g2, bool atoms, int *pk, int *pl, double *pq,
                            double *pd, double *prim, float *prim_f, double *kmu, double *kfa, hipStream_t st);
+
+// Screen of primitive terms.  A primitive pair is bounded by u = |S_ab| p^(1/4) (times
+// max(1, 2 mu R, sqrt p) in the gradient's tables, for the derivative terms), so that a
+// primitive quartet is at most u_ab u_cd: S_ab S_cd E(r) with E <= (2/sqrt(pi)) sqrt(rho) and
+// sqrt(rho) = sqrt(p q / (p + q)) <= (p q)^(1/4) / sqrt(2).  The tables hold the binary
+// exponent e with u < 2^e, and the quartet kernels leave out a primitive quartet when
+// e_ab + e_cd <= term_limit(tau), that is when it is below 1e-10 min(tau, 1e-10): ten decimal
+// orders under the screen of whole quartets, and so little that the sums over a wave's
+// primitives do not change in FP64 beyond their own rounding.  tau = 0 leaves nothing out.
+constexpr int kTermNever = -30000;    // exponent of a zero bound (left out unless tau = 0)
+constexpr int kTermAlways = 15000;    // of a bound that is not finite (never left out)
+constexpr int kTermNone = -(1 << 28); // lanes without a bra primitive pair (under every limit, tau = 0 too)
+int term_limit(double tau);
 
 int device_cu_count();
 

@@ -300,7 +300,7 @@ __global__ __launch_bounds__(256) void k_pair_scatter(Basis b, const BasisDev *_
                                                       float *__restrict__ bra_f, double *__restrict__ bip,
                                                       float *__restrict__ bip_f, double *__restrict__ kmu,
                                                       double *__restrict__ kfa, double *__restrict__ bgw,
-                                                      float *__restrict__ bgw_f,
+                                                      float *__restrict__ bgw_f, short *__restrict__ bexp,
                                                       const int *__restrict__ slot)
 {
     const int64_t npair = n * (n + 1) / 2;
@@ -353,6 +353,17 @@ __global__ __launch_bounds__(256) void k_pair_scatter(Basis b, const BasisDev *_
         bf[0] = (float)px[ab]; bf[1] = (float)py[ab]; bf[2] = (float)pz[ab]; bf[3] = (float)ps[ab];
         bf[4] = (float)(-2.0 * px[ab]); bf[5] = (float)(-2.0 * py[ab]); bf[6] = (float)(-2.0 * pz[ab]);
         bf[7] = (float)p2;
+    }
+    {
+        // exponents of the term screen
+        const double r = sqrt((A[0] - B[0]) * (A[0] - B[0]) + (A[1] - B[1]) * (A[1] - B[1]) +
+                              (A[2] - B[2]) * (A[2] - B[2]));
+        for (int ab = 0; ab < g2; ++ab) {
+            const double p_ab = b.aexp ? pp[ab] : bd->p[ab], sp = sqrt(p_ab);
+            double u = fabs(ps[ab]) * sqrt(sp);
+            if (bgw) u *= fmax(1.0, fmax(sp, 2.0 * r * (b.aexp ? mu[ab] : bd->mu[ab])));
+            bexp[(int64_t)pos * g2 + ab] = term_exponent(u);
+        }
     }
     if (bip) {
         for (int ab = 0; ab < g2; ++ab) {
@@ -475,15 +486,30 @@ hipError_t launch_pair_pad(const DevHeader *hdr, int64_t pcap, int g2, bool atom
 }
 
 // Ket range of every bra s (in bucketed order): kets t < lim_s with
-// lim_s = min(s + 1, end of the band holding tau / Q_s); items of kItemKets kets.
+// lim_s = min(s + 1, end of the band holding tau / Q_s); items of kItemKets kets.  A workgroup
+// covers the kWaveKets kets that one wave of the quartet kernels takes, and leaves the maxima
+// of their term exponents in kexp.
+static_assert(kWaveKets == 256, "one workgroup of k_limits per wave's share of kets");
 __global__ __launch_bounds__(256) void k_limits(const DevHeader *__restrict__ hdr, double tau,
                                                 const double *__restrict__ pq,
                                                 const long long *__restrict__ boff,
                                                 long long *__restrict__ nitems, int *__restrict__ lims,
-                                                int64_t pcap)
+                                                int64_t pcap, int g2, const short *__restrict__ bexp,
+                                                int *__restrict__ kexp)
 {
     const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t S = hdr->sig_pairs;
+    if ((int64_t)blockIdx.x * kWaveKets < S) {
+        __shared__ int emax[kMaxG2];
+        for (int ab = threadIdx.x; ab < g2; ab += blockDim.x) emax[ab] = kTermNever;
+        __syncthreads();
+        // consecutive lanes read consecutive exponents of the workgroup's kets
+        const int64_t at = (int64_t)blockIdx.x * kWaveKets;
+        const int cnt = (int)(S - at < kWaveKets ? S - at : kWaveKets) * g2;
+        for (int x = threadIdx.x; x < cnt; x += blockDim.x) atomicMax(&emax[x % g2], (int)bexp[at * g2 + x]);
+        __syncthreads();
+        for (int ab = threadIdx.x; ab < g2; ab += blockDim.x) kexp[(int64_t)blockIdx.x * g2 + ab] = emax[ab];
+    }
     if (s >= pcap) return;
     long long ni = 0;
     if (s < S) {
@@ -817,7 +843,7 @@ hipError_t launch_pairs(const Layout &L, const Basis &b, char *ws, const double 
                        (float *)(ws + L.bra_f), L.atoms ? (double *)(ws + L.bip) : nullptr,
                        L.atoms ? (float *)(ws + L.bip_f) : nullptr, L.pmu ? (double *)(ws + L.pmu) : nullptr,
                        L.pmu ? (double *)(ws + L.pfa) : nullptr, L.bgw ? (double *)(ws + L.bgw) : nullptr,
-                       L.bgw ? (float *)(ws + L.bgw_f) : nullptr, slot);
+                       L.bgw ? (float *)(ws + L.bgw_f) : nullptr, (short *)(ws + L.bexp), slot);
     hipLaunchKernelGGL(k_pair_pad, dim3((unsigned)((L.pcap + 255) / 256)), dim3(256), 0, st, hdr, L.pcap, L.g2,
                        true, L.atoms ? 5 : -1, L.atoms ? 4 : -1,
                        (int *)(ws + L.pk), (int *)(ws + L.pl), (double *)(ws + L.pq), (double *)(ws + L.pd),
@@ -825,7 +851,7 @@ hipError_t launch_pairs(const Layout &L, const Basis &b, char *ws, const double 
                        L.pmu ? (double *)(ws + L.pfa) : nullptr);
     hipLaunchKernelGGL(k_limits, dim3((unsigned)((L.pcap + 255) / 256)), dim3(256), 0, st, hdr, tau,
                        (const double *)(ws + L.pq), off, (long long *)(ws + L.nitems), (int *)(ws + L.lim),
-                       L.pcap);
+                       L.pcap, L.g2, (const short *)(ws + L.bexp), (int *)(ws + L.kexp));
     e = launch_scan((const long long *)(ws + L.nitems), L.pcap, (long long *)(ws + L.item_off),
                     (long long *)(ws + L.scan_tmp), &hdr->items, st);
     if (e != hipSuccess) return e;
