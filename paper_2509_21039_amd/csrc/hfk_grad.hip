@@ -61,6 +61,9 @@ struct GradArgs {
     int gshift;                 // log2 of the bras per group
     int tile;               // items per block
     const int *lim;
+    const short *bexp;          // [pcap][g2] term exponents of the bras
+    const int *kexp;            // [ket block of a wave][g2] maxima of the kets' exponents
+    int tlim;                   // term_limit(tau)
     const double *dens;
     const double *xdens;    // X of the two-density contraction, or NULL (Gamma from D alone)
     const double *xyz;
@@ -186,7 +189,7 @@ void k_grad(GradArgs a)
         const cptr<double> cmu = (cptr<double>)bd->mu;
         const cptr<double> cfa = (cptr<double>)bd->fa;
         const cptr<double> cfb = (cptr<double>)bd->fb;
-        int cur = -1, bi = 0, bj = 0, lim = 0;
+        int cur = -1, bi = 0, bj = 0, lim = 0, ebra = kTermNone;
         double qs = 0.0, ds = 0.0;
         double gA[3] = {0, 0, 0}, gB[3] = {0, 0, 0};
         for (long long m = m0; m <= m1; ++m) {
@@ -212,9 +215,11 @@ void k_grad(GradArgs a)
                 qs = a.pq[s];
                 ds = a.pd[s];
                 lim = a.lim[s];
+                ebra = lane < G2 ? (int)a.bexp[(int64_t)s * G2 + lane] : kTermNone;
             }
             const long long wbase = (m - a.item_off[s]) * kItemKets + (long long)wave * kWaveKets;
             if (wbase >= lim) continue;
+            const cptr<int> kexp = (cptr<int>)(a.kexp + __builtin_amdgcn_readfirstlane((int)(wbase / kWaveKets)) * G2);
             int *perm = wperm[wave];
             const int nvalid = pack_kets(wbase, lane, perm,
                                          [&](long long t) { return t < lim && qs * a.pq[t] >= a.tau; });
@@ -236,6 +241,9 @@ void k_grad(GradArgs a)
                 for (int cb = 0; cb < G; ++cb) {
                     R kx[G], ky[G], kz[G], ks[G], kp[G], kq[G];
                     R kms[G], kds[G], kcs[G], kcds[G];   // S_cd times mu_cd, fd, fc, fc fd
+                    typename TermMask<G>::T need[G];
+                    term_masks<G>(ebra, kexp + cb * G, a.tlim, need);
+                    if (!need[G - 1]) continue;
                     // buffer loads of the ket table: component and this cb's rows in the
                     // resource, the row as a scalar offset, the ket as a 32-bit lane offset
                     const unsigned tb = (unsigned)t * (unsigned)sizeof(R);
@@ -245,6 +253,7 @@ void k_grad(GradArgs a)
                     };
 #pragma unroll
                     for (int d = 0; d < G; ++d) {
+                        if (G <= 4 && !need[d]) continue;   // no bra primitive pair reads it
                         kx[d] = ld(0, d);
                         ky[d] = ld(1, d);
                         kz[d] = ld(2, d);
@@ -259,6 +268,7 @@ void k_grad(GradArgs a)
                     for (int d = 0; d < G; ++d) {
                         const int cd = cb * G + d;
                         if constexpr (kAtoms) {
+                            if (G <= 4 && !need[d]) continue;
                             const double mu = a.kmu[(int64_t)cd * a.pcap + t];
                             const double fc = a.kfa[(int64_t)cd * a.pcap + t];
                             const double fd = 1.0 - fc;
@@ -274,8 +284,8 @@ void k_grad(GradArgs a)
                             kw[4 * d + 3] = (R)(fc * fd);
                         }
                     }
-#pragma unroll 1
-                    for (int ab = 0; ab < G2; ++ab) {
+                    for_terms<G>(need, [&](auto nd, int ab) __attribute__((always_inline)) {
+                        constexpr int D0 = G - decltype(nd)::value;   // first term of the row
                         // every scalar of this bra primitive in one batch of scalar loads: the
                         // centre and charge, the weights mu S, fa S, fb S, fa fb S, fb^2 S, and
                         // the switch data
@@ -292,9 +302,9 @@ void k_grad(GradArgs a)
                         } else {
                             const cptr<R> up = rsg + 4 * (ab * G2 + cb * G);
 #pragma unroll
-                            for (int c = 0; c < 4 * G; ++c) u[c] = up[c];
+                            for (int c = 4 * D0; c < 4 * G; ++c) u[c] = up[c];
 #pragma unroll
-                            for (int c = 0; c < 4 * G; ++c) asm volatile("" ::"s"(u[c]));
+                            for (int c = 4 * D0; c < 4 * G; ++c) asm volatile("" ::"s"(u[c]));
                         }
                         const R px = b[0], py = b[1], pz = b[2], sab = b[3];
                         R U = R(0), Y = R(0), X0 = R(0), X1 = R(0), Xc = R(0), Xcd = R(0);
@@ -303,7 +313,7 @@ void k_grad(GradArgs a)
                         // overwrite theirs from the table under exec masks
                         R r2[G], E[G], W[G];
 #pragma unroll
-                        for (int d = 0; d < G; ++d) {
+                        for (int d = D0; d < G; ++d) {
                             if (kExpand) {
                                 r2[d] = fma(b[4], kx[d], fma(b[5], ky[d], fma(b[6], kz[d], kq[d] + b[7])));
                             } else {
@@ -315,7 +325,7 @@ void k_grad(GradArgs a)
                             W[d] = GradScale<R>::w_far(y);
                         }
 #pragma unroll
-                        for (int d = 0; d < G; ++d) {
+                        for (int d = D0; d < G; ++d) {
                             const R sw = kAtoms ? bsw + kp[d] : u[4 * d];
                             if (r2[d] < sw) {
                                 R q1, q2, q3;
@@ -341,7 +351,7 @@ void k_grad(GradArgs a)
                             }
                         }
 #pragma unroll
-                        for (int d = 0; d < G; ++d) {
+                        for (int d = D0; d < G; ++d) {
                             if constexpr (kAtoms) {
                                 U = fma(ks[d], E[d], U);
                                 Y = fma(kms[d], E[d], Y);
@@ -371,7 +381,7 @@ void k_grad(GradArgs a)
                         wC = fma(sab, Xc, wC);
                         wCB = fma(bw[2], Xc, wCB);
                         wCD = fma(sab, Xcd, wCD);
-                    }
+                    });
                 }
                 {
                     // back from the accumulators' scales (E times kE, W times kW)
@@ -599,6 +609,9 @@ hipError_t launch_grad(const Layout &L, const Basis &b, char *ws, const double *
     a.bgw_f = (const float *)(ws + L.bgw_f);
     a.item_off = (const long long *)(ws + L.item_off);
     a.lim = (const int *)(ws + L.lim);
+    a.bexp = (const short *)(ws + L.bexp);
+    a.kexp = (const int *)(ws + L.kexp);
+    a.tlim = term_limit(tau);
     a.goff = (const long long *)(ws + L.goff);
     a.ngroups = L.ngroups;
     a.gshift = L.gshift;

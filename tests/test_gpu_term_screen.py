@@ -58,3 +58,22 @@ def test_forward_vs_oracle(torch_dev, atoms, precision, g, order, tau, spacing):
     Gr, Er, _ = (oracle.fock_atoms if atoms else oracle.fock)(s.xyz, s.dens, e, c, tau)
     assert_close(G.cpu().numpy(), Gr, TOL[precision])
     assert rel(float(E2.item()), Er) < TOL[precision]
+
+
+@pytest.mark.parametrize("atoms", [False, True])
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("g,order,tau,spacing", [
+    (1, "tight_first", 1e-10, 3.0), (2, "diffuse_first", 1e-10, 3.0), (3, "tight_first", 1e-12, 4.0),
+    (3, "shuffled", 1e-8, 3.0), (4, "tight_first", 1e-10, 3.0), (5, "diffuse_first", 1e-8, 4.0)])
+def test_gradient_vs_oracle(torch_dev, atoms, precision, g, order, tau, spacing):
+    # the derivative bounds carry max(1, 2 mu R, sqrt p) per pair, so the same count holds
+    import paper_2509_21039_amd as hfk
+    torch, dev = torch_dev
+    s, e, c = _system(g, order, tau, spacing, atoms)
+    announce("term screen gradient g=%d %s tau=%g spacing=%g atoms=%d %s" % (g, order, tau, spacing, atoms, precision))
+    dx, _, E2 = hfk.fock_grad(torch.tensor(s.xyz, device=dev), torch.tensor(s.dens, device=dev), e, c, tau, precision,
+                              want_dens=False)
+    gr, Er, _ = (oracle.grad_atoms if atoms else oracle.grad)(s.xyz, s.dens, e, c, tau)
+    # the FP64 gradient's rows are of degree 7 with a derivative near 3e-12 (tolerance of the gradient tests)
+    assert_close(dx.cpu().numpy(), gr, 1e-10 if precision == "fp64" else TOL["mixed"])
+    assert rel(float(E2.item()), Er) < TOL[precision]
