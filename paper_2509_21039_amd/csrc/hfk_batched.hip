@@ -48,6 +48,9 @@ struct BArgs {
     const double *kfa;
     const long long *item_off;
     const int *lim;
+    const short *bexp;      // [pcap][g2] term exponents of the bras
+    const int *kexp;        // [64 kets][g2] maxima of the kets' exponents
+    int tlim;               // term_limit(tau)
     const int *klo;
     const int *mol_n;
     const long long *mol_aoff;
@@ -187,7 +190,8 @@ __global__ __launch_bounds__(256) void k_b_pair_scatter(
     int64_t pcap, const double *__restrict__ q, const int *__restrict__ bucket_of, int *__restrict__ cur,
     int *__restrict__ pk, int *__restrict__ pl, int *__restrict__ pm, double *__restrict__ pq, double *__restrict__ pd,
     double *__restrict__ prim, float *__restrict__ prim_f, double *__restrict__ bra, float *__restrict__ bra_f,
-    double *__restrict__ bip, float *__restrict__ bip_f, double *__restrict__ kmu, double *__restrict__ kfa)
+    double *__restrict__ bip, float *__restrict__ bip_f, double *__restrict__ kmu, double *__restrict__ kfa,
+    short *__restrict__ bexp, bool grad)
 {
     const long long p = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= ptot) return;
@@ -235,6 +239,14 @@ __global__ __launch_bounds__(256) void k_b_pair_scatter(
             bf[c] = (float)row[c];
         }
     }
+    {
+        // exponents of the term screen
+        const double r = sqrt((A[0] - B[0]) * (A[0] - B[0]) + (A[1] - B[1]) * (A[1] - B[1]) +
+                              (A[2] - B[2]) * (A[2] - B[2]));
+        for (int ab = 0; ab < g2; ++ab)
+            bexp[(int64_t)pos * g2 + ab] =
+                term_exponent(term_bound(ps[ab], b.aexp ? pp[ab] : bd->p[ab], b.aexp ? mu[ab] : bd->mu[ab], r, grad));
+    }
     if (bip) {
         for (int ab = 0; ab < g2; ++ab) {
             const double sw = kTswitch / pp[ab];
@@ -259,13 +271,16 @@ __global__ void k_b_pad(const DevHeader *__restrict__ hdr, int64_t pcap, int *__
 }
 
 // Ket range of every bra s: kets t in [klo_s, lim_s), klo_s the first pair of its molecule,
-// lim_s = min(s + 1, end of the molecule's band holding tau / Q_s).
+// lim_s = min(s + 1, end of the molecule's band holding tau / Q_s).  A workgroup also leaves
+// the maxima of its pairs' term exponents over every 64 consecutive pairs in kexp.
 __global__ __launch_bounds__(256) void k_b_limits(const DevHeader *__restrict__ hdr, double tau,
                                                   const double *__restrict__ pq, const int *__restrict__ pm,
                                                   const long long *__restrict__ boff, long long *__restrict__ nitems,
-                                                  int *__restrict__ lims, int *__restrict__ klo, int64_t pcap)
+                                                  int *__restrict__ lims, int *__restrict__ klo, int64_t pcap,
+                                                  int g2, const short *__restrict__ bexp, int *__restrict__ kexp)
 {
     const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    block_term_maxima<kWave, 256>(hdr->sig_pairs, g2, bexp, kexp);
     if (s >= pcap) return;
     long long ni = 0;
     if (s < hdr->sig_pairs) {
@@ -436,8 +451,8 @@ __global__ __launch_bounds__(kBatchMaxThreads) void k_batched(BArgs a)
     __syncthreads();
     {
     int s = s_first, curbra = -1;
-    int bi = 0, bj = 0, lim = 0, klo = 0;
-    double qs = 0.0, ds = 0.0, Ax = 0.0, Ay = 0.0, Az = 0.0, Bx = 0.0, By = 0.0, Bz = 0.0;
+    int bi = 0, bj = 0, lim = 0, klo = 0, ebra = kTermNone;
+    double qs = 0.0, ds = 0.0;
     double jb = 0.0, gA[3] = {0, 0, 0}, gB[3] = {0, 0, 0};
     // folds this wave's bra-side sums into the LDS accumulators
     auto flush_bra = [&]() {
@@ -463,18 +478,21 @@ __global__ __launch_bounds__(kBatchMaxThreads) void k_batched(BArgs a)
         if (s != curbra) {
             if (curbra >= 0) flush_bra();
             curbra = s;
-            bi = a.pk[s];
-            bj = a.pl[s];
-            qs = a.pq[s];
-            ds = a.pd[s];
-            lim = a.lim[s];
-            klo = a.klo[s];
-            const double *xa = a.xyz + 3 * (aoff + bi), *xb = a.xyz + 3 * (aoff + bj);
-            Ax = xa[0]; Ay = xa[1]; Az = xa[2];
-            Bx = xb[0]; By = xb[1]; Bz = xb[2];
+            // scalar loads: the bra's data stays in scalar registers
+            bi = ((cptr<int>)a.pk)[s];
+            bj = ((cptr<int>)a.pl)[s];
+            qs = ((cptr<double>)a.pq)[s];
+            ds = ((cptr<double>)a.pd)[s];
+            lim = ((cptr<int>)a.lim)[s];
+            klo = ((cptr<int>)a.klo)[s];
+            ebra = lane < G2 ? (int)a.bexp[(int64_t)s * G2 + lane] : kTermNone;
         }
         const long long t0 = klo + (m - a.item_off[s]) * kKetsPerItem + (u % kUnitsPerItem) * kWave;
         if (t0 >= lim) continue;
+        // the unit's 64 kets lie in one or two aligned blocks of 64
+        const int kb0 = __builtin_amdgcn_readfirstlane((int)(t0 / kWave));
+        const int kb1 = __builtin_amdgcn_readfirstlane((int)(((t0 + kWave < lim ? t0 + kWave : lim) - 1) / kWave));
+        const cptr<int> kexp0 = (cptr<int>)(a.kexp + (int64_t)kb0 * G2), kexp1 = (cptr<int>)(a.kexp + (int64_t)kb1 * G2);
         const long long tk = t0 + lane;
         const bool valid = (tk < lim) && (qs * a.pq[tk] >= a.tau);
         const long long t = valid ? tk : S;   // lanes without a kept quartet read the first pad entry
@@ -488,6 +506,9 @@ __global__ __launch_bounds__(kBatchMaxThreads) void k_batched(BArgs a)
         R wA = R(0), wAB = R(0), wB = R(0), wBB = R(0), wAD = R(0), wBD = R(0), wC = R(0), wCB = R(0), wCD = R(0);
 #pragma unroll 1
         for (int cb = 0; cb < G; ++cb) {
+            typename TermMask<G>::T need[G];
+            term_masks<G>(ebra, kexp0 + cb * G, kexp1 + cb * G, a.tlim, need);
+            if (!need[G - 1]) continue;
             R kx[G], ky[G], kz[G], ks[G], kp[G];
             R kms[G], kds[G], kcs[G], kcds[G];   // S_cd times mu_cd, fd, fc, fc fd
             // buffer loads of the ket table: component and this cb's rows in the resource,
@@ -499,6 +520,7 @@ __global__ __launch_bounds__(kBatchMaxThreads) void k_batched(BArgs a)
             };
 #pragma unroll
             for (int d = 0; d < G; ++d) {
+                if (G <= 4 && !need[d]) continue;   // no bra primitive pair reads it
                 kx[d] = ld(0, d);
                 ky[d] = ld(1, d);
                 kz[d] = ld(2, d);
@@ -508,6 +530,7 @@ __global__ __launch_bounds__(kBatchMaxThreads) void k_batched(BArgs a)
             if (kGrad) {
 #pragma unroll
                 for (int d = 0; d < G; ++d) {
+                    if (G <= 4 && !need[d]) continue;
                     const int cd = cb * G + d;
                     double mu, fc;
                     if constexpr (kAtoms) {
@@ -524,8 +547,8 @@ __global__ __launch_bounds__(kBatchMaxThreads) void k_batched(BArgs a)
                     kcds[d] = (R)(fc * fd) * ks[d];
                 }
             }
-#pragma unroll 1
-            for (int ab = 0; ab < G2; ++ab) {
+            for_terms<G>(need, [&](auto nd, int ab) __attribute__((always_inline)) {
+                constexpr int D0 = G - decltype(nd)::value;   // first term of the row
                 // every scalar of this bra primitive in one batch of scalar loads:
                 // Px Py Pz S mu*S fa*S fb*S fa*fb*S fb^2*S, and the switch data
                 const cptr<R> bp = bra + kBBra * ab;
@@ -538,9 +561,9 @@ __global__ __launch_bounds__(kBatchMaxThreads) void k_batched(BArgs a)
                 } else {
                     const cptr<R> up = rsg + 4 * (ab * G2 + cb * G);
 #pragma unroll
-                    for (int c = 0; c < 4 * G; ++c) u[c] = up[c];
+                    for (int c = 4 * D0; c < 4 * G; ++c) u[c] = up[c];
 #pragma unroll
-                    for (int c = 0; c < 4 * G; ++c) asm volatile("" ::"s"(u[c]));
+                    for (int c = 4 * D0; c < 4 * G; ++c) asm volatile("" ::"s"(u[c]));
                 }
                 const R px = b[0], py = b[1], pz = b[2];
                 R U = R(0), Y = R(0), X0 = R(0), X1 = R(0), Xc = R(0), Xcd = R(0);
@@ -549,7 +572,7 @@ __global__ __launch_bounds__(kBatchMaxThreads) void k_batched(BArgs a)
                 // overwrite theirs from the table under exec masks
                 R r2[G], E[G], W[G];
 #pragma unroll
-                for (int d = 0; d < G; ++d) {
+                for (int d = D0; d < G; ++d) {
                     const R dx = px - kx[d], dy = py - ky[d], dz = pz - kz[d];
                     r2[d] = dx * dx + dy * dy + dz * dz;
                     const R y = GradScale<R>::e_far(r2[d]);
@@ -557,7 +580,7 @@ __global__ __launch_bounds__(kBatchMaxThreads) void k_batched(BArgs a)
                     W[d] = kGrad ? GradScale<R>::w_far(y) : R(0);
                 }
 #pragma unroll
-                for (int d = 0; d < G; ++d) {
+                for (int d = D0; d < G; ++d) {
                     // switch radius^2 kTswitch / rho (per-atom bases: sum of the stored halves)
                     const R sw = kAtoms ? bsw + kp[d] : u[4 * d];
                     if (r2[d] < sw) {
@@ -579,17 +602,17 @@ __global__ __launch_bounds__(kBatchMaxThreads) void k_batched(BArgs a)
                             // degree-7 rows of H; g = 2 H': W on the grid is (2 kW / kE) dE/dd
                             double de;
                             E[d] = q2 * boys_eval_d(tHG, off, dd, de);
-                            if (kGrad) W[d] = q3 * (R(2.0 * GradScale<R>::kW / GradScale<R>::kE) * de);
+                            if constexpr (kGrad) W[d] = q3 * (R(2.0 * GradScale<R>::kW / GradScale<R>::kE) * de);
                         } else {
                             E[d] = q2 * boys_eval<R>(tHG, off, dd);
-                            if (kGrad) W[d] = q3 * boys_eval<R>(tHG + BG::g_off, off, dd);
+                            if constexpr (kGrad) W[d] = q3 * boys_eval<R>(tHG + BG::g_off, off, dd);
                         }
                     }
                 }
 #pragma unroll
-                for (int d = 0; d < G; ++d) {
+                for (int d = D0; d < G; ++d) {
                     U = fma(ks[d], E[d], U);
-                    if (kGrad) {
+                    if constexpr (kGrad) {
                         Y = fma(kms[d], E[d], Y);
                         X0 = fma(ks[d], W[d], X0);
                         X1 = fma(kds[d], W[d], X1);
@@ -598,7 +621,7 @@ __global__ __launch_bounds__(kBatchMaxThreads) void k_batched(BArgs a)
                     }
                 }
                 eri = fma(b[3], U, eri);
-                if (kGrad) {
+                if constexpr (kGrad) {
                     sX = fma(b[4], U, sX);
                     sZ = fma(b[3], Y, sZ);
                     wA = fma(b[5], X0, wA);
@@ -611,7 +634,7 @@ __global__ __launch_bounds__(kBatchMaxThreads) void k_batched(BArgs a)
                     wCB = fma(b[6], Xc, wCB);
                     wCD = fma(b[3], Xcd, wCD);
                 }
-            }
+            });
         }
         {
             // back from the accumulators' scales (E times kE, W times kW)
@@ -642,7 +665,7 @@ __global__ __launch_bounds__(kBatchMaxThreads) void k_batched(BArgs a)
             if (kGrad) {
                 const double gam = deg * (4.0 * ds * dt - Dik * Djl - Dil * Djk);
                 const double *xc = a.xyz + 3 * (aoff + k), *xd = a.xyz + 3 * (aoff + l);
-                const double A[3] = {Ax, Ay, Az}, B[3] = {Bx, By, Bz};
+                const cptr<double> A = (cptr<double>)a.xyz + 3 * (aoff + bi), B = (cptr<double>)a.xyz + 3 * (aoff + bj);
 #pragma unroll
                 for (int c = 0; c < 3; ++c) {
                     const double rac = A[c] - xc[c], rba = B[c] - A[c], rdc = xd[c] - xc[c];
@@ -840,6 +863,8 @@ BLayout make_blayout(int64_t nmol, const int64_t *atom_off, int g, int with_grad
     L.bra = take(sizeof(double) * kBBra * g2 * PC);
     L.bra_f = take(sizeof(float) * kBBra * g2 * PC);
     L.nitems = take(sizeof(long long) * PC);
+    L.bexp = take(sizeof(short) * (size_t)L.g2 * (size_t)L.pcap);
+    L.kexp = take(sizeof(int) * (size_t)L.g2 * (size_t)(L.pcap / kWave + 1));
     L.lim = take(sizeof(int) * PC);
     L.klo = take(sizeof(int) * PC);
     L.item_off = take(sizeof(long long) * (PC + 1));
@@ -922,7 +947,7 @@ hipError_t launch_batched(const BLayout &L, const Basis &b, char *ws, const int6
                        (double *)(ws + L.pd), (double *)(ws + L.prim), (float *)(ws + L.prim_f), (double *)(ws + L.bra),
                        (float *)(ws + L.bra_f), L.atoms ? (double *)(ws + L.bip) : nullptr,
                        L.atoms ? (float *)(ws + L.bip_f) : nullptr, L.kmu ? (double *)(ws + L.kmu) : nullptr,
-                       L.kmu ? (double *)(ws + L.kfa) : nullptr);
+                       L.kmu ? (double *)(ws + L.kfa) : nullptr, (short *)(ws + L.bexp), d_xyz != nullptr);
     const unsigned nbc = (unsigned)((L.pcap + 255) / 256);
     e = launch_pair_pad(hdr, L.pcap, L.g2, L.atoms, (int *)(ws + L.pk), (int *)(ws + L.pl), (double *)(ws + L.pq),
                         (double *)(ws + L.pd), (double *)(ws + L.prim), (float *)(ws + L.prim_f),
@@ -931,7 +956,7 @@ hipError_t launch_batched(const BLayout &L, const Basis &b, char *ws, const int6
     hipLaunchKernelGGL(k_b_pad, dim3(nbc), dim3(256), 0, st, hdr, L.pcap, (int *)(ws + L.pm));
     hipLaunchKernelGGL(k_b_limits, dim3(nbc), dim3(256), 0, st, hdr, tau, (const double *)(ws + L.pq),
                        (const int *)(ws + L.pm), boff, (long long *)(ws + L.nitems), (int *)(ws + L.lim),
-                       (int *)(ws + L.klo), L.pcap);
+                       (int *)(ws + L.klo), L.pcap, L.g2, (const short *)(ws + L.bexp), (int *)(ws + L.kexp));
     e = launch_scan((const long long *)(ws + L.nitems), L.pcap, (long long *)(ws + L.item_off),
                     (long long *)(ws + L.scan_tmp), &hdr->items, st);
     if (e != hipSuccess) return e;
@@ -975,6 +1000,9 @@ hipError_t launch_batched(const BLayout &L, const Basis &b, char *ws, const int6
     a.kfa = L.kmu ? (const double *)(ws + L.kfa) : nullptr;
     a.item_off = (const long long *)(ws + L.item_off);
     a.lim = (const int *)(ws + L.lim);
+    a.bexp = (const short *)(ws + L.bexp);
+    a.kexp = (const int *)(ws + L.kexp);
+    a.tlim = term_limit(tau);
     a.klo = (const int *)(ws + L.klo);
     a.mol_n = d_n;
     a.mol_aoff = d_aoff;

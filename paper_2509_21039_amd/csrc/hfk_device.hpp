@@ -71,6 +71,36 @@ __device__ inline short term_exponent(double u)
     return (short)e;
 }
 
+// Bound u of a primitive pair with charge S, exponent sum p, mu and atoms r apart (grad: the
+// derivative terms too).
+__device__ inline double term_bound(double S, double p, double mu, double r, bool grad)
+{
+    const double sp = sqrt(p), u = fabs(S) * sqrt(sp);
+    return grad ? u * fmax(1.0, fmax(sp, 2.0 * r * mu)) : u;
+}
+
+// Called by a whole workgroup of kThreads threads, for kThreads consecutive pairs: the maxima
+// of the term exponents of every kBlock of them, into kexp[block][g2].
+template <int kBlock, int kThreads>
+__device__ inline void block_term_maxima(int64_t pairs, int g2, const short *__restrict__ bexp,
+                                         int *__restrict__ kexp)
+{
+    constexpr int kSub = kThreads / kBlock;
+    const int64_t at = (int64_t)blockIdx.x * kThreads;
+    if (at >= pairs) return;   // the same for the whole workgroup
+    __shared__ int emax[kSub * kMaxG2];
+    for (int x = threadIdx.x; x < kSub * g2; x += kThreads) emax[x] = kTermNever;
+    __syncthreads();
+    // consecutive lanes read consecutive exponents
+    const int cnt = (int)(pairs - at < kThreads ? pairs - at : kThreads) * g2;
+    for (int x = threadIdx.x; x < cnt; x += kThreads)
+        atomicMax(&emax[x / (kBlock * g2) * g2 + x % g2], (int)bexp[at * g2 + x]);
+    __syncthreads();
+    for (int x = threadIdx.x; x < kSub * g2; x += kThreads) {
+        if (at + (int64_t)(x / g2) * kBlock < pairs) kexp[(int64_t)blockIdx.x * kSub * g2 + x] = emax[x];
+    }
+}
+
 // Reciprocal square root in FP64: the hardware estimate (relative error ~5e-8) refined by
 // one Newton step, y (1 + e/2) with e = 1 - x y^2, leaving ~1.5 e^2 ~ 4e-15.
 __device__ inline double rsqrt_fp64(double x)
@@ -209,6 +239,21 @@ __device__ inline void term_masks(int ebra, cptr<int> kexp, int limit, typename 
     int e[G];
 #pragma unroll
     for (int d = 0; d < G; ++d) e[d] = kexp[d];
+    T m = 0;
+#pragma unroll
+    for (int d = 0; d < G; ++d) {
+        m |= (T)__builtin_amdgcn_ballot_w64(ebra > limit - e[d]);
+        need[d] = m;
+    }
+}
+// The same over kets that lie in two blocks.
+template <int G>
+__device__ inline void term_masks(int ebra, cptr<int> kexp0, cptr<int> kexp1, int limit, typename TermMask<G>::T *need)
+{
+    using T = typename TermMask<G>::T;
+    int e[G];
+#pragma unroll
+    for (int d = 0; d < G; ++d) e[d] = kexp0[d] > kexp1[d] ? kexp0[d] : kexp1[d];
     T m = 0;
 #pragma unroll
     for (int d = 0; d < G; ++d) {

@@ -238,6 +238,7 @@ struct BLayout {
     size_t mol_n, mol_aoff, mol_poff, mol_doff, mol_toff, cent, qmax;
     size_t q, bucket_of, bcnt, boff, bcur;
     size_t pk, pl, pm, pq, pd, prim, prim_f, bra, bra_f;
+    size_t bexp, kexp;                  // term screen, as in Layout (maxima over 64 kets)
     size_t nitems, lim, klo, item_off, scan_tmp;
     size_t facc, gacc;
     size_t mol_i0, mol_i1;              // per molecule: first and end item

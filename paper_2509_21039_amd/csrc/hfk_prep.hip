@@ -359,9 +359,8 @@ __global__ __launch_bounds__(256) void k_pair_scatter(Basis b, const BasisDev *_
         const double r = sqrt((A[0] - B[0]) * (A[0] - B[0]) + (A[1] - B[1]) * (A[1] - B[1]) +
                               (A[2] - B[2]) * (A[2] - B[2]));
         for (int ab = 0; ab < g2; ++ab) {
-            const double p_ab = b.aexp ? pp[ab] : bd->p[ab], sp = sqrt(p_ab);
-            double u = fabs(ps[ab]) * sqrt(sp);
-            if (bgw) u *= fmax(1.0, fmax(sp, 2.0 * r * (b.aexp ? mu[ab] : bd->mu[ab])));
+            const double u = term_bound(ps[ab], b.aexp ? pp[ab] : bd->p[ab], b.aexp ? mu[ab] : bd->mu[ab], r,
+                                        bgw != nullptr);
             bexp[(int64_t)pos * g2 + ab] = term_exponent(u);
         }
     }
@@ -499,17 +498,7 @@ __global__ __launch_bounds__(256) void k_limits(const DevHeader *__restrict__ hd
 {
     const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t S = hdr->sig_pairs;
-    if ((int64_t)blockIdx.x * kWaveKets < S) {
-        __shared__ int emax[kMaxG2];
-        for (int ab = threadIdx.x; ab < g2; ab += blockDim.x) emax[ab] = kTermNever;
-        __syncthreads();
-        // consecutive lanes read consecutive exponents of the workgroup's kets
-        const int64_t at = (int64_t)blockIdx.x * kWaveKets;
-        const int cnt = (int)(S - at < kWaveKets ? S - at : kWaveKets) * g2;
-        for (int x = threadIdx.x; x < cnt; x += blockDim.x) atomicMax(&emax[x % g2], (int)bexp[at * g2 + x]);
-        __syncthreads();
-        for (int ab = threadIdx.x; ab < g2; ab += blockDim.x) kexp[(int64_t)blockIdx.x * g2 + ab] = emax[ab];
-    }
+    block_term_maxima<kWaveKets, 256>(S, g2, bexp, kexp);
     if (s >= pcap) return;
     long long ni = 0;
     if (s < S) {
