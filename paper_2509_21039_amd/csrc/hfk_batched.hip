@@ -341,8 +341,8 @@ __global__ __launch_bounds__(256) void k_b_blocks(DevHeader *__restrict__ hdr, i
 
 // Work within a block.  A block is a range of items of one molecule (all of them for an
 // owned block).  Each item (bra s, 256 kets) is cut into four units of 64 kets, and the
-// waves of the workgroup take the block's units round-robin, each on its own: a wave walks
-// its units in item order, keeps its bra's data while the bra stays the same, and folds its
+// waves of the workgroup take consecutive shares of the block's units, each on its own: a wave
+// walks its units in item order, keeps its bra's data while the bra stays the same, and folds its
 // bra-side sums into LDS when the bra changes.  The waves meet only at the start and the
 // end of a block (LDS cleared, then the molecule's accumulators written out), so a bra with
 // few kets occupies one wave, not the workgroup.  The wave count per workgroup is set at
@@ -472,7 +472,10 @@ __global__ __launch_bounds__(kBatchMaxThreads) void k_batched(BArgs a)
         }
     };
     const long long nunits = (m1 - m0) * kUnitsPerItem;
-    for (long long u = wave; u < nunits; u += nwaves) {
+    // consecutive units per wave: a bra's units mostly meet in one wave, which folds its sums
+    // once; dealt out round-robin, a bra of ten units cost eight folds of seven wave sums
+    const long long uend = nunits * (wave + 1) / nwaves;
+    for (long long u = nunits * wave / nwaves; u < uend; ++u) {
         const long long m = m0 + u / kUnitsPerItem;
         while (a.item_off[s + 1] <= m) ++s;
         if (s != curbra) {

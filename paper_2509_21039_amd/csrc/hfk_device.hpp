@@ -335,12 +335,32 @@ __device__ inline int q_band(double q)
     return x < 0.0 ? 0 : (int)x;
 }
 
-// Wave-wide sum (64 lanes) of a double through cross-lane shuffles.
+// Lane permutation within rows of 16 lanes of a double (DPP moves of its halves).
+template <int kCtrl>
+__device__ inline double dpp_move(double v)
+{
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_mov_dpp((int)b, kCtrl, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), kCtrl, 0xf, 0xf, true);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+__device__ inline double read_lane(double v, int lane)
+{
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_readlane((int)b, lane), hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+
+// Wave-wide sum (64 lanes) of a double, the same in every lane: DPP within rows of 16 (swap of
+// neighbours, of pairs, mirrored halves, mirrored row), then the four row sums.  No LDS
+// permutes, of which a shuffle butterfly takes twelve.  Called with every lane active.
 __device__ inline double wave_sum(double v)
 {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
+    v += dpp_move<0xb1>(v);    // quad_perm [1, 0, 3, 2]
+    v += dpp_move<0x4e>(v);    // quad_perm [2, 3, 0, 1]
+    v += dpp_move<0x141>(v);   // row_half_mirror
+    v += dpp_move<0x140>(v);   // row_mirror
+    return (read_lane(v, 0) + read_lane(v, 16)) + (read_lane(v, 32) + read_lane(v, 48));
 }
 
 __device__ inline int lane_id() { return (int)__lane_id(); }
