@@ -48,10 +48,10 @@ int device_cu_count()
     return cus;
 }
 
-int term_limit(double tau)
+int term_limit(double tau, int prec)
 {
     if (!(tau > 0.0)) return -1000000;
-    return (int)floor(log2(tau < 1e-10 ? tau : 1e-10) + log2(1e-10));
+    return (int)floor(log2(tau < 1e-10 ? tau : 1e-10) + log2(prec == HFK_MIXED ? 1e-6 : 1e-10));
 }
 
 // Per-workgroup copies of F are used while they stay within this many bytes in total.

@@ -1005,7 +1005,7 @@ hipError_t launch_batched(const BLayout &L, const Basis &b, char *ws, const int6
     a.lim = (const int *)(ws + L.lim);
     a.bexp = (const short *)(ws + L.bexp);
     a.kexp = (const int *)(ws + L.kexp);
-    a.tlim = term_limit(tau);
+    a.tlim = term_limit(tau, prec);
     a.klo = (const int *)(ws + L.klo);
     a.mol_n = d_n;
     a.mol_aoff = d_aoff;

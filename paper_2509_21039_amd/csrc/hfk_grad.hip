@@ -611,7 +611,7 @@ hipError_t launch_grad(const Layout &L, const Basis &b, char *ws, const double *
     a.lim = (const int *)(ws + L.lim);
     a.bexp = (const short *)(ws + L.bexp);
     a.kexp = (const int *)(ws + L.kexp);
-    a.tlim = term_limit(tau);
+    a.tlim = term_limit(tau, prec);
     a.goff = (const long long *)(ws + L.goff);
     a.ngroups = L.ngroups;
     a.gshift = L.gshift;

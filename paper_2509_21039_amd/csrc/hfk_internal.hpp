@@ -284,13 +284,15 @@ hipError_t launch_pair_pad(const DevHeader *hdr, int64_t pcap, int g2, bool atom
 // primitive quartet is at most u_ab u_cd: S_ab S_cd E(r) with E <= (2/sqrt(pi)) sqrt(rho) and
 // sqrt(rho) = sqrt(p q / (p + q)) <= (p q)^(1/4) / sqrt(2).  The tables hold the binary
 // exponent e with u < 2^e, and the quartet kernels leave out a primitive quartet when
-// e_ab + e_cd <= term_limit(tau), that is when it is below 1e-10 min(tau, 1e-10): ten decimal
-// orders under the screen of whole quartets, and so little that the sums over a wave's
-// primitives do not change in FP64 beyond their own rounding.  tau = 0 leaves nothing out.
+// e_ab + e_cd <= term_limit(tau, prec), that is when it is below 1e-10 min(tau, 1e-10): ten
+// decimal orders under the screen of whole quartets, and so little that the sums do not change
+// in FP64 beyond their own rounding.  With FP32 integrals the line is at 1e-6 min(tau, 1e-10):
+// a matrix element of 1e5 quartets moves by 1e-11 at most, where FP32 rounding leaves 1e-8.
+// tau = 0 leaves nothing out.
 constexpr int kTermNever = -30000;    // exponent of a zero bound (left out unless tau = 0)
 constexpr int kTermAlways = 15000;    // of a bound that is not finite (never left out)
 constexpr int kTermNone = -(1 << 28); // lanes without a bra primitive pair (under every limit, tau = 0 too)
-int term_limit(double tau);
+int term_limit(double tau, int prec);
 
 int device_cu_count();
 
