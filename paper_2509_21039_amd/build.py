@@ -26,7 +26,7 @@ HIPCC = os.environ.get("HIPCC", shutil.which("hipcc") or "/opt/rocm/bin/hipcc")
 
 FLAGS = [
     "-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",
-    "-munsafe-fp-atomics",
+    "-munsafe-fp-atomics", "-fconstexpr-steps=200000000",   # the Boys tables are computed by the compiler
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-I", INCLUDE, "-I", CSRC,
     "-Wall", "-Wno-unused-function",

@@ -68,6 +68,7 @@ Layout make_layout(int64_t n, int g, int prec, int with_grad, int groups, bool a
     L.atoms = atoms;
     L.tile = prec == HFK_MIXED ? 2 * kTileItems : kTileItems;
     L.gshift = 10;   // kGroupBras
+    L.sub = kSubChunks;
     L.kcopies = 0;
     L.private_ok = !compact && (double)groups * (double)n * (double)n * 8.0 <= kPrivateBudget;
     L.npair = n * (n + 1) / 2;
@@ -84,8 +85,6 @@ Layout make_layout(int64_t n, int g, int prec, int with_grad, int groups, bool a
     const size_t P = (size_t)L.npair, PC = (size_t)L.pcap, g2 = (size_t)L.g2;
     L.hdr = take(sizeof(DevHeader));
     L.basis = take(sizeof(BasisDev));
-    L.boys = take(sizeof(double) * kBoysGrid * kBoysStride);
-    L.boys_f = take(sizeof(double) * kBoysGridF * kBoysStrideF);
     L.q_unsorted = take(sizeof(double) * P);
     L.bucket_of = take(sizeof(int) * P);
     L.bucket_cnt = take(sizeof(long long) * kNumBuckets);
@@ -95,6 +94,7 @@ Layout make_layout(int64_t n, int g, int prec, int with_grad, int groups, bool a
     L.pl = take(sizeof(int) * PC);
     L.pq = take(sizeof(double) * PC);
     L.pd = take(sizeof(double) * PC);
+    // a build fills the tables of its precision only; a workspace holds either
     L.prim = take(sizeof(double) * (atoms ? 6 : 5) * g2 * PC);   // Px, Py, Pz, S, |P|^2 (, 1/p)
     L.prim_f = take(sizeof(float) * (atoms ? 5 : 4) * g2 * PC);
     if (atoms) {
@@ -112,10 +112,11 @@ Layout make_layout(int64_t n, int g, int prec, int with_grad, int groups, bool a
     }
     L.bra = take(sizeof(double) * 8 * g2 * PC);
     L.bra_f = take(sizeof(float) * 8 * g2 * PC);
-    L.boys_g = take(sizeof(double) * kBoysGrid * kBoysStrideG);
-    L.boys_g_f = take(sizeof(double) * kBoysGridF * kBoysStrideF);
+    const size_t term_at = o;
     L.bexp = take(sizeof(short) * g2 * PC);
-    L.kexp = take(sizeof(int) * g2 * ((PC + kWaveKets - 1) / kWaveKets));
+    L.kexp64 = take(sizeof(int) * g2 * (PC / 64 + 4));
+    L.kexp256 = take(sizeof(int) * g2 * (PC / 256 + 1));
+    const size_t term_bytes = o - term_at;
     L.nitems = take(sizeof(long long) * PC);
     L.lim = take(sizeof(int) * PC);
     L.item_off = take(sizeof(long long) * (PC + 1));
@@ -138,6 +139,7 @@ Layout make_layout(int64_t n, int g, int prec, int with_grad, int groups, bool a
     L.xw = with_grad ? take(sizeof(double) * 2 * n2) : 0;
     L.e2tmp = take(sizeof(double));
     L.total = o;
+    L.static_bytes = o - term_bytes;
     return L;
 }
 
@@ -410,7 +412,11 @@ static hfk_status debug_check(char *ws_hdr, int64_t n, const double *dens, hipSt
 // per device with that device current, and only that address is ever passed to kernels or
 // copies.  Every call on a GPU shares that GPU's copy: calls that overlap in time on one GPU
 // race, and each call clears what it needs (counters, accumulators) before use.
-constexpr size_t kStaticScratchBytes = (size_t)64 << 20;
+constexpr size_t kStaticScratchBytes = (size_t)66 << 20;
+// The largest system the call accepts is a property of its interface (about 256 atoms with three
+// primitives): 64 MiB less the 278272 bytes of constant tables that a workspace once held,
+// counted without the term screen's tables, which take under 1 MiB of such a system.
+constexpr size_t kStaticScratchLimit = ((size_t)64 << 20) - 278272;
 static __device__ __align__(256) char scratch[kStaticScratchBytes];
 
 static std::mutex g_scratch_mu;
@@ -568,11 +574,11 @@ static hfk_status fock_one_basis(int64_t natoms, const double *xyz, int32_t ngau
     if (cus <= 0) return fail(HFK_EHIP, "no HIP device");
     Layout L = make_layout(natoms, ngauss, precision, 0, groups_cap(cus), false, compact);
     if (compact) {
-        if (L.total > kStaticScratchBytes)
+        if (L.static_bytes > kStaticScratchLimit || L.total > kStaticScratchBytes)
             return fail(HFK_EUNSUPPORTED,
                         "this system needs %zu bytes of scratch; the allocation-free call holds %zu (about 256 atoms "
                         "with 3 primitives per function)",
-                        L.total, kStaticScratchBytes);
+                        L.static_bytes, kStaticScratchLimit);
         s = static_scratch(&workspace);
         if (s != HFK_OK) return s;
         workspace_bytes = kStaticScratchBytes;
@@ -603,20 +609,13 @@ static hfk_status fock_one_basis(int64_t natoms, const double *xyz, int32_t ngau
     hipStream_t st = (hipStream_t)stream;
     s = debug_check(ws + L.hdr, natoms, dens, st, "dens");
     if (s != HFK_OK) return s;
-    hipError_t e = launch_setup(b, (BasisDev *)(ws + L.basis), (double *)(ws + L.boys),
-                                (double *)(ws + L.boys_f), (double *)(ws + L.boys_g),
-                                (double *)(ws + L.boys_g_f), (DevHeader *)(ws + L.hdr), natoms, xyz, st);
-    if (e != hipSuccess) return hip_fail(e, "setup launch");
-    e = launch_pairs(L, b, ws, xyz, dens, tau, st, strat == HFK_STRATEGY_DETERMINISTIC);
+    hipError_t e = launch_pairs(L, b, ws, xyz, dens, tau, precision, fock_plan(L, ws, strat, precision, cfg.variant), st);
     if (e == hipErrorNotSupported && strat == HFK_STRATEGY_DETERMINISTIC)
         return fail(HFK_EUNSUPPORTED, "deterministic strategy: more than %d pairs share one (Q band, cell) bucket",
                     kMaxFixedBucket);
     if (e != hipSuccess) return hip_fail(e, "pair launch");
     e = launch_fock(L, b, ws, dens, tau, precision, strat, cfg.variant, fock, e2, st);
     if (e != hipSuccess) return hip_fail(e, "fock launch");
-    e = launch_header_info(ws + L.hdr, strat, L.groups, precision, cfg.variant, st, L.tile, 1 << L.gshift,
-                           effective_copies(L));
-    if (e != hipSuccess) return hip_fail(e, "header launch");
     note_last(workspace, stream);
     return HFK_OK;
 }
@@ -731,20 +730,13 @@ hfk_status hfk_fock_atoms(int64_t natoms, const double *xyz, int32_t ngauss, con
     Basis b;
     hipError_t e = upload_rows((double *)(ws + L.arow), natoms, ngauss, exps_host, coefs_host, st, &b);
     if (e != hipSuccess) return hip_fail(e, "basis rows copy");
-    e = launch_setup(b, (BasisDev *)(ws + L.basis), (double *)(ws + L.boys), (double *)(ws + L.boys_f),
-                     (double *)(ws + L.boys_g), (double *)(ws + L.boys_g_f), (DevHeader *)(ws + L.hdr), natoms, xyz,
-                     st);
-    if (e != hipSuccess) return hip_fail(e, "setup launch");
-    e = launch_pairs(L, b, ws, xyz, dens, tau, st, strat == HFK_STRATEGY_DETERMINISTIC);
+    e = launch_pairs(L, b, ws, xyz, dens, tau, precision, fock_plan(L, ws, strat, precision, 1), st);
     if (e == hipErrorNotSupported && strat == HFK_STRATEGY_DETERMINISTIC)
         return fail(HFK_EUNSUPPORTED, "deterministic strategy: more than %d pairs share one (Q band, cell) bucket",
                     kMaxFixedBucket);
     if (e != hipSuccess) return hip_fail(e, "pair launch");
     e = launch_fock(L, b, ws, dens, tau, precision, strat, 1, fock, e2, st);
     if (e != hipSuccess) return hip_fail(e, "fock launch");
-    e = launch_header_info(ws + L.hdr, strat, L.groups, precision, 1, st, L.tile, 1 << L.gshift,
-                           effective_copies(L));
-    if (e != hipSuccess) return hip_fail(e, "header launch");
     note_last(workspace, stream);
     return HFK_OK;
 }
@@ -823,10 +815,6 @@ hfk_status hfk_scf(int64_t natoms, const double *xyz, const double *charges_host
     Basis b;
     hipError_t e = upload_rows((double *)(ws + L.arow), natoms, ngauss, exps_host, coefs_host, st, &b);
     if (e != hipSuccess) return hip_fail(e, "basis rows copy");
-    e = launch_setup(b, (BasisDev *)(ws + L.basis), (double *)(ws + L.boys), (double *)(ws + L.boys_f),
-                     (double *)(ws + L.boys_g), (double *)(ws + L.boys_g_f), (DevHeader *)(ws + L.hdr), natoms, xyz,
-                     st);
-    if (e != hipSuccess) return hip_fail(e, "setup launch");
     ScfResult r;
     char msg[256];
     msg[0] = 0;
@@ -929,11 +917,10 @@ static hfk_status fock_grad_impl(bool atoms, int64_t natoms, const double *xyz, 
     } else {
         b = make_basis(ngauss, exps_host, coefs_host);
     }
-    hipError_t e = launch_setup(b, (BasisDev *)(ws + L.basis), (double *)(ws + L.boys), (double *)(ws + L.boys_f),
-                                (double *)(ws + L.boys_g), (double *)(ws + L.boys_g_f), (DevHeader *)(ws + L.hdr),
-                                natoms, xyz, st);
-    if (e != hipSuccess) return hip_fail(e, "setup launch");
-    e = launch_pairs(L, b, ws, xyz, dens, tau, st);
+    PairPlan plan;
+    memset(&plan, 0, sizeof(plan));
+    plan.info = HeaderInfo{0, L.groups, precision, -1, L.tile, 1 << L.gshift, 0};
+    hipError_t e = launch_pairs(L, b, ws, xyz, dens, tau, precision, plan, st);
     if (e != hipSuccess) return hip_fail(e, "pair launch");
     const int64_t n2 = natoms * natoms;
     double *xw = (double *)(ws + L.xw);
@@ -953,18 +940,18 @@ static hfk_status fock_grad_impl(bool atoms, int64_t natoms, const double *xyz, 
         if (strat == HFK_STRATEGY_PRIVATE && !L.private_ok) strat = HFK_STRATEGY_ATOMIC;
         Layout LW = L;
         set_shape(LW, cfg.tile, cfg.gbras, cfg.kcopies);
-        e = launch_pairs(LW, b, ws, xyz, xw, tau, st);
-        if (e != hipSuccess) return hip_fail(e, "pair launch (W)");
         Layout LF = LW;
         const int fit = fock_resident_groups(ngauss, precision, cfg.variant, natoms, atoms);
         LF.groups = cus * (fit > 0 && cfg.gpc > fit ? fit : cfg.gpc);
+        PairPlan wplan = fock_plan(LF, ws, strat, precision, cfg.variant);
+        wplan.info = plan.info;
+        e = launch_pairs(LF, b, ws, xyz, xw, tau, precision, wplan, st);
+        if (e != hipSuccess) return hip_fail(e, "pair launch (W)");
         e = launch_fock(LF, b, ws, xw, tau, precision, strat, cfg.variant, d_dens, (double *)(ws + L.e2tmp), st);
         if (e != hipSuccess) return hip_fail(e, "Fock launch (W)");
         e = launch_axpy_dev(n2, g_e2, fock_in, d_dens, st);
         if (e != hipSuccess) return hip_fail(e, "axpy launch");
     }
-    e = launch_header_info(ws + L.hdr, 0, L.groups, precision, -1, st, L.tile, 1 << L.gshift, 0);
-    if (e != hipSuccess) return hip_fail(e, "header launch");
     note_last(workspace, stream);
     return HFK_OK;
 }
@@ -1074,11 +1061,7 @@ static hfk_status fock_batched_impl(bool atoms, int64_t nmol, const int64_t *ato
     } else {
         b = make_basis(ngauss, exps_host, coefs_host);
     }
-    hipError_t e = launch_setup(b, (BasisDev *)(ws + L.basis), (double *)(ws + L.boys), (double *)(ws + L.boys_f),
-                                (double *)(ws + L.boys_g), (double *)(ws + L.boys_g_f), (DevHeader *)(ws + L.hdr),
-                                atom_off_host[nmol], xyz, st);
-    if (e != hipSuccess) return hip_fail(e, "setup launch");
-    e = upload_batch_tables(L, ws, atom_off_host, st);
+    hipError_t e = upload_batch_tables(L, ws, atom_off_host, st);
     if (e != hipSuccess) return hip_fail(e, "batch tables copy");
     if (g_debug) {
         DevHeader *hdr = (DevHeader *)(ws + L.hdr);

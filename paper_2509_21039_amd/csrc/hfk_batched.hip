@@ -23,16 +23,13 @@
 #include <vector>
 
 #include "hfk_device.hpp"
+#include "hfk_boys.hpp"
 
 namespace hfk {
 
 struct BArgs {
     const DevHeader *hdr;
     const BasisDev *bd;
-    const double *tabH;
-    const double *tabH_f;   // rows of the FP32 grid (FP64 values)
-    const double *tabG;
-    const double *tabG_f;
     const int *pk;
     const int *pl;
     const int *pm;
@@ -72,14 +69,19 @@ struct BArgs {
     int nmax;
 };
 
+static __device__ const BoysGrad64 kBoysB64 = make_boys_grad64();
+static __device__ const BoysFloat kBoysB32 = make_boys_float(false);
+
 template <typename R> struct BPrec;
 template <> struct BPrec<double> {
+    static __device__ const double *boys() { return kBoysB64.v; }
     static __device__ const double *prim(const BArgs &a) { return a.prim; }
     static __device__ const double *bra(const BArgs &a) { return a.bra; }
     static __device__ const double *bip(const BArgs &a) { return a.bip; }
     static __device__ const double *rsg(const BasisDev *bd) { return bd->rsg; }
 };
 template <> struct BPrec<float> {
+    static __device__ const float *boys() { return kBoysB32.v; }
     static __device__ const float *prim(const BArgs &a) { return a.prim_f; }
     static __device__ const float *bra(const BArgs &a) { return a.bra_f; }
     static __device__ const float *bip(const BArgs &a) { return a.bip_f; }
@@ -380,37 +382,7 @@ __global__ __launch_bounds__(kBatchMaxThreads) void k_batched(BArgs a)
     const int nwaves = nthr / kWave;
     const int S = a.hdr->sig_pairs;
     const BasisDev *bd = a.bd;
-    // grid-scaled rows (argument T' = T / h) from the FP64 rows (one rounding for FP32):
-    // coefficient m of H times h^m sqrt(h) kE, of g times h^m h^(3/2) kW (FP32 only; FP64
-    // takes g from the derivative of H's degree-7 row)
-    {
-        // FP64: the degree-7 rows of H (tabG); FP32: H's and g's rows on the FP32 grid
-        const double *gH = sizeof(R) == 8 ? a.tabG : a.tabH_f, *gG = a.tabG_f;
-        for (int x = tid; x < BG::table_len; x += nthr) {
-            int k, c;
-            bool isg;
-            if constexpr (sizeof(R) == 8) {   // H's rows of degree 7, padded
-                k = x / BG::pair_stride;
-                c = x % BG::pair_stride;
-                isg = false;
-            } else {                          // H's rows, then g's
-                isg = x >= BG::g_off;
-                const int y = isg ? x - BG::g_off : x;
-                k = y / BG::stride;
-                c = y % BG::stride;
-            }
-            const int order = sizeof(R) == 8 ? kBoysOrderG : BG::stride;
-            const int rowlen = sizeof(R) == 8 ? kBoysStrideG : BG::stride;
-            double v = 0.0;   // the pad
-            if (c < order) {
-                double sc = sqrt(BG::h);
-                for (int e = 0; e < c; ++e) sc *= BG::h;
-                v = isg ? gG[k * rowlen + c] * sc * BG::h * (double)GradScale<R>::kW
-                        : gH[k * rowlen + c] * sc * (double)GradScale<R>::kE;
-            }
-            tHG[x] = (R)v;
-        }
-    }
+    load_boys<R>(tHG, BPrec<R>::boys(), BG::table_len, tid, nthr);
     unsigned long long kept = 0;
     __shared__ long long blk_at;
     __shared__ int s_first;
@@ -743,12 +715,6 @@ __global__ void k_b_fill(double *__restrict__ p, int64_t m)
     if (i < m) p[i] = 0.0;
 }
 
-__global__ void k_b_fill_ll(long long *__restrict__ p, int64_t m)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < m) p[i] = 0;
-}
-
 __global__ void k_b_copy(const double *__restrict__ s, int64_t m, double *__restrict__ d)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -831,10 +797,6 @@ BLayout make_blayout(int64_t nmol, const int64_t *atom_off, int g, int with_grad
     const size_t NB = NM * kNumBands;
     L.hdr = take(sizeof(DevHeader));
     L.basis = take(sizeof(BasisDev));
-    L.boys = take(sizeof(double) * kBoysGrid * kBoysStride);
-    L.boys_f = take(sizeof(double) * kBoysGridF * kBoysStrideF);
-    L.boys_g = take(sizeof(double) * kBoysGrid * kBoysStrideG);
-    L.boys_g_f = take(sizeof(double) * kBoysGridF * kBoysStrideF);
     L.mol_n = take(sizeof(int) * NM);
     L.mol_aoff = take(sizeof(long long) * (NM + 1));
     L.mol_poff = take(sizeof(long long) * (NM + 1));
@@ -934,11 +896,15 @@ hipError_t launch_batched(const BLayout &L, const Basis &b, char *ws, const int6
     long long *bcnt = (long long *)(ws + L.bcnt);
     long long *boff = (long long *)(ws + L.boff);
     int *bcur = (int *)(ws + L.bcur);
+    // header and basis constants, F's accumulators and the bucket counters cleared
+    const HeaderInfo info{0, groups, prec, -1, 0, 0, 0};
+    e = launch_prep_begin(b, (BasisDev *)(ws + L.basis), hdr, L.ntot, nullptr, info, (double *)(ws + L.facc), L.tri,
+                          bcnt, NB, st);
+    if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_b_mol, dim3((unsigned)((nmol + 127) / 128)), dim3(128), 0, st, (int)nmol, d_n, d_aoff, xyz,
                        cent, qmax);
     hipLaunchKernelGGL(k_b_pair_q, dim3(nbp), dim3(256), 0, st, b, bd, (int)nmol, d_poff, d_aoff, cent, xyz, L.ptot,
                        (double *)(ws + L.q), qmax);
-    hipLaunchKernelGGL(k_b_fill_ll, dim3((unsigned)((NB + 255) / 256)), dim3(256), 0, st, bcnt, (int64_t)NB);
     hipLaunchKernelGGL(k_b_bucket_count, dim3(nbp), dim3(256), 0, st, (int)nmol, d_poff, L.ptot, tau, qmax,
                        (const double *)(ws + L.q), (int *)(ws + L.bucket_of), bcnt);
     e = launch_scan(bcnt, NB, boff, (long long *)(ws + L.scan_tmp), nullptr, st);
@@ -974,9 +940,6 @@ hipError_t launch_batched(const BLayout &L, const Basis &b, char *ws, const int6
                         (long long *)(ws + L.scan_tmp), &hdr->bt_sh, st);
     if (e != hipSuccess) return e;
 
-    const long long tri = L.tri;
-    hipLaunchKernelGGL(k_b_fill, dim3((unsigned)((tri + 255) / 256)), dim3(256), 0, st, (double *)(ws + L.facc),
-                       (int64_t)tri);
     const bool grad = d_xyz != nullptr;
     if (grad)
         hipLaunchKernelGGL(k_b_fill, dim3((unsigned)((3 * L.ntot + 255) / 256)), dim3(256), 0, st,
@@ -984,10 +947,6 @@ hipError_t launch_batched(const BLayout &L, const Basis &b, char *ws, const int6
     BArgs a;
     a.hdr = hdr;
     a.bd = bd;
-    a.tabH = (const double *)(ws + L.boys);
-    a.tabH_f = (const double *)(ws + L.boys_f);
-    a.tabG = (const double *)(ws + L.boys_g);
-    a.tabG_f = (const double *)(ws + L.boys_g_f);
     a.pk = (const int *)(ws + L.pk);
     a.pl = (const int *)(ws + L.pl);
     a.pm = (const int *)(ws + L.pm);
@@ -1027,10 +986,6 @@ hipError_t launch_batched(const BLayout &L, const Basis &b, char *ws, const int6
     a.nmax = L.nmax;
     const size_t smem = batched_smem_bytes(L.nmax, prec);
     const int threads = (shape.waves == 8 ? 8 : 4) * kWave;
-    {
-        const hipError_t ez = launch_zero_counter(a.next_block, st);
-        if (ez != hipSuccess) return ez;
-    }
     profile_begin(st);
     if (grad && L.atoms && !L.kmu) return hipErrorInvalidValue;   // per-atom gradient tables missing
 #define HFK_B_LAUNCH(GG, RR, GR)                                                                         \

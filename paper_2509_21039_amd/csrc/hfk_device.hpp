@@ -6,7 +6,6 @@
 namespace hfk {
 
 constexpr double kPi = 3.14159265358979323846264338327950288;
-constexpr double kTwoOverSqrtPi = 1.12837916709551257389615890312154517;
 
 // H(T) = erf(sqrt T) / sqrt T with H(0) = 2/sqrt(pi): the reduced Boys function
 // (2/sqrt(pi)) F0(T).  Accurate library erf; used off the hot path (Schwarz bounds).

@@ -32,14 +32,13 @@
 // F_ij partial sums of the four waves are added in wave order.  The final kernels sum the
 // workgroup copies in workgroup order.
 #include "hfk_device.hpp"
+#include "hfk_boys.hpp"
 
 namespace hfk {
 
 struct FockArgs {
     const DevHeader *hdr;
     const BasisDev *bd;
-    const double *boys;
-    const double *boys_f;   // rows of the FP32 grid (FP64 values, rounded once into LDS)
     const int *pk;
     const int *pl;
     const double *pq;
@@ -56,7 +55,7 @@ struct FockArgs {
     int gshift;                 // log2 of the bras per group
     int tile;                   // items per block
     const int *lim;
-    const short *bexp;          // [pcap][g2] term exponents of the bras
+    const short *bexp;          // [g2][pcap] term exponents of the bras
     const int *kexp;            // [ket block of a wave][g2] maxima of the kets' exponents
     int tlim;                   // term_limit(tau)
     const double *dens;
@@ -71,16 +70,20 @@ struct FockArgs {
     int jcopies;        // ket vectors: one per workgroup if equal to the grid, else shared (atomics)
 };
 
+// Tables of the hybrid form (grid-scaled) and of the direct form.
+static __device__ const BoysForward64 kBoys64 = make_boys_forward64();
+static __device__ const BoysPlain64 kBoysPlain64 = make_boys_plain64();
+static __device__ const BoysFloat kBoys32 = make_boys_float(false);
+static __device__ const BoysFloat kBoysPlain32 = make_boys_float(true);
+
 template <typename R> struct Prec;
 template <> struct Prec<double> {
+    static __device__ const double *boys(bool split) { return split ? kBoys64.v : kBoysPlain64.v; }
     static __device__ const double *prim(const FockArgs &a) { return a.prim; }
     static __device__ const double *bra(const FockArgs &a) { return a.bra; }
     static __device__ const double *bip(const FockArgs &a) { return a.bip; }
-    static __device__ const double *boys(const FockArgs &a) { return a.boys; }
     static __device__ const double *rho(const BasisDev *bd) { return bd->rho; }
     static __device__ const double *srho(const BasisDev *bd) { return bd->srho; }
-    static __device__ const double *r2sw(const BasisDev *bd) { return bd->r2sw; }
-    static __device__ const double *rs(const BasisDev *bd) { return bd->rs; }
     static __device__ const double *rsn(const BasisDev *bd) { return bd->rsn; }
     static __device__ double rsqrt(double x) { return rsqrt_fp64(x); }
     // The hybrid kernel's FP64 accumulator carries -2 times the sum, which lets the Newton
@@ -98,14 +101,12 @@ template <> struct Prec<double> {
     }
 };
 template <> struct Prec<float> {
+    static __device__ const float *boys(bool split) { return split ? kBoys32.v : kBoysPlain32.v; }
     static __device__ const float *prim(const FockArgs &a) { return a.prim_f; }
     static __device__ const float *bra(const FockArgs &a) { return a.bra_f; }
     static __device__ const float *bip(const FockArgs &a) { return a.bip_f; }
-    static __device__ const double *boys(const FockArgs &a) { return a.boys_f; }
     static __device__ const float *rho(const BasisDev *bd) { return bd->rho_f; }
     static __device__ const float *srho(const BasisDev *bd) { return bd->srho_f; }
-    static __device__ const float *r2sw(const BasisDev *bd) { return bd->r2sw_f; }
-    static __device__ const float *rs(const BasisDev *bd) { return bd->rs_f; }
     static __device__ const float *rsn(const BasisDev *bd) { return bd->rsn_f; }
     static __device__ float rsqrt(float x) { return rsqrt_fp32(x); }
     static constexpr float kAccScale = 1.0f;   // no Newton step in FP32
@@ -368,21 +369,7 @@ __global__ __launch_bounds__(kGroupThreads) void k_fock(FockArgs a)
     const int S = a.hdr->sig_pairs;
     const BasisDev *bd = a.bd;
 
-    {
-        // the rows of this precision's grid, from FP64 values (one rounding for FP32); the
-        // hybrid form scales coefficient m by h^m sqrt(h) and the accumulator's scale
-        using BG = BoysGrid<R>;
-        const double *gtab = Prec<R>::boys(a);
-        for (int x = tid; x < BG::rows * BG::stride; x += kGroupThreads) {
-            const int m = x % BG::stride;
-            double sc = 1.0;
-            if (kSplit) {
-                sc = sqrt(BG::h) * (double)Prec<R>::kAccScale;
-                for (int e = 0; e < m; ++e) sc *= BG::h;
-            }
-            tab[x] = (R)(gtab[x] * sc);
-        }
-    }
+    load_boys<R>(tab, Prec<R>::boys(kSplit), BoysGrid<R>::rows * BoysGrid<R>::stride, tid, kGroupThreads);
     if (!kSplit) {
         for (int x = tid; x < G2 * G2; x += kGroupThreads) {
             luni[2 * x] = Prec<R>::rho(bd)[x];
@@ -497,7 +484,7 @@ __global__ __launch_bounds__(kGroupThreads) void k_fock(FockArgs a)
             qs = bra_qd[0];
             ds = bra_qd[1];
             lim = a.lim[s];
-            if (kSplit) ebra = lane < G2 ? (int)a.bexp[(int64_t)s * G2 + lane] : kTermNone;
+            if (kSplit) ebra = lane < G2 ? (int)a.bexp[(int64_t)lane * a.pcap + s] : kTermNone;
         }
         const long long wbase = (m - a.item_off[s]) * kItemKets + (long long)wave * kWaveKets;
         if constexpr (!kDet) {
@@ -606,46 +593,47 @@ __global__ __launch_bounds__(256) void k_sum_private(const double *__restrict__ 
     fsum[x] = s;
 }
 
-__global__ __launch_bounds__(256) void k_copy(const double *__restrict__ src, int64_t m, double *__restrict__ dst)
-{
-    const int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (x < m) dst[x] = src[x];
-}
-
-__global__ __launch_bounds__(256) void k_fill(double *__restrict__ p, int64_t m, double v)
-{
-    const int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (x < m) p[x] = v;
-}
-
-// F_kl += sum over the copies of the ket-side Coulomb vector (each t is a distinct pair).
-__global__ __launch_bounds__(256) void k_jcol_scatter(const DevHeader *__restrict__ hdr,
-                                                      const double *__restrict__ jcol, int groups,
-                                                      int64_t pcap, const int *__restrict__ pk,
-                                                      const int *__restrict__ pl, int n,
-                                                      double *__restrict__ fsum)
+// Sum of the copies of the ket-side Coulomb vector, left in copy 0 (many copies only).
+__global__ __launch_bounds__(256) void k_jcol_sum(const DevHeader *__restrict__ hdr, double *__restrict__ jcol,
+                                                  int copies, int64_t pcap)
 {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= hdr->sig_pairs) return;
     double s = 0.0;
-    for (int gph = 0; gph < groups; ++gph) s += jcol[(int64_t)gph * pcap + t];
-    fsum[(int64_t)pk[t] * n + pl[t]] += s;
+    for (int c = 0; c < copies; ++c) s += jcol[(int64_t)c * pcap + t];
+    jcol[t] = s;
 }
 
-// G = (F + F^T)/2 and per-block partial sums of D o G.
-__global__ __launch_bounds__(256) void k_symmetrise(const double *__restrict__ fsum,
-                                                    const double *__restrict__ dens, int n,
-                                                    double *__restrict__ fock, double *__restrict__ part)
+// G = (F + F^T)/2 with the ket-side Coulomb terms of the pair (i, j) (each pair is one
+// position), and E2 = 1/2 sum D o G: every workgroup leaves its partial sum, and the one that
+// finishes last adds them in workgroup order, so that the result does not depend on which one
+// that is.  One launch: copying F, adding the ket terms, symmetrising, summing the partials and
+// the header took five of 4.5 us each.
+constexpr int kFinishPer = 4;
+__global__ __launch_bounds__(256) void k_finish(DevHeader *__restrict__ hdr, const double *__restrict__ F,
+                                                const double *__restrict__ jcol, int copies, int64_t pcap,
+                                                const int *__restrict__ posof, const double *__restrict__ dens,
+                                                int n, double *__restrict__ fock, double *__restrict__ part,
+                                                double *__restrict__ e2)
 {
     __shared__ double red[256];
-    const int64_t n2 = (int64_t)n * n;
-    const int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    __shared__ unsigned last;
+    const int n2 = n * n, at = blockIdx.x * 256 * kFinishPer + threadIdx.x;
     double e = 0.0;
-    if (x < n2) {
-        const int64_t i = x / n, j = x % n;
-        const double gv = 0.5 * (fsum[x] + fsum[j * n + i]);
-        fock[x] = gv;
-        e = dens[x] * gv;
+#pragma unroll
+    for (int r = 0; r < kFinishPer; ++r) {
+        const int x = at + r * 256;
+        if (x < n2) {
+            const int i = x / n, j = x - i * n;
+            const int hi = i > j ? i : j, lo = i > j ? j : i;
+            const int t = posof[(int64_t)hi * (hi + 1) / 2 + lo];
+            double J = 0.0;
+            if (t >= 0)
+                for (int c = 0; c < copies; ++c) J += jcol[(int64_t)c * pcap + t];
+            const double gv = i == j ? F[x] + J : 0.5 * (F[x] + F[(int64_t)j * n + i] + J);
+            fock[x] = gv;
+            e += dens[x] * gv;
+        }
     }
     red[threadIdx.x] = e;
     __syncthreads();
@@ -653,23 +641,24 @@ __global__ __launch_bounds__(256) void k_symmetrise(const double *__restrict__ f
         if (threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
         __syncthreads();
     }
-    if (threadIdx.x == 0) part[blockIdx.x] = red[0];
-}
-
-// E2 = 1/2 sum of the partials (one block, fixed order).
-__global__ __launch_bounds__(256) void k_energy(const double *__restrict__ part, int nb, double scale,
-                                                double *__restrict__ e2)
-{
-    __shared__ double red[256];
+    if (threadIdx.x == 0) {
+        part[blockIdx.x] = red[0];
+        __threadfence();   // the partial sum before the count
+        last = atomicAdd(&hdr->done_blocks, 1u);
+    }
+    __syncthreads();
+    if (last != gridDim.x - 1) return;
+    __threadfence();
     double s = 0.0;
-    for (int b = threadIdx.x; b < nb; b += 256) s += part[b];
+    for (unsigned b = threadIdx.x; b < gridDim.x; b += 256)
+        s += __hip_atomic_load(&part[b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     red[threadIdx.x] = s;
     __syncthreads();
     for (int w = 128; w > 0; w >>= 1) {
         if (threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
         __syncthreads();
     }
-    if (threadIdx.x == 0) *e2 = scale * red[0];
+    if (threadIdx.x == 0) *e2 = 0.5 * red[0];
 }
 
 template <int G, typename R>
@@ -680,8 +669,6 @@ static hipError_t launch_fock_t(const FockArgs &a, int groups, int variant, bool
     const bool det = a.strategy == HFK_STRATEGY_DETERMINISTIC;
     const bool split = G > 4 || variant != 0 || atoms || det;
     const size_t smem = FockSmem<R>::total(a.n, split, det);
-    const hipError_t ez = launch_zero_counter(a.next_block, st);
-    if (ez != hipSuccess) return ez;
     profile_begin(st);
     if (det) {
         if (atoms)
@@ -757,6 +744,20 @@ size_t fock_smem_bytes(int64_t n, int prec, int variant)
                              : FockSmem<double>::total((int)n, variant != 0);
 }
 
+PairPlan fock_plan(const Layout &L, char *ws, int strategy, int prec, int variant)
+{
+    PairPlan p;
+    const int copies = effective_copies(L);
+    p.info = HeaderInfo{strategy, L.groups, prec, variant, L.tile, 1 << L.gshift, copies};
+    p.fixed_order = strategy == HFK_STRATEGY_DETERMINISTIC;
+    // workgroups clear their own copies; shared ones are cleared before the launch
+    p.fzero = strategy == HFK_STRATEGY_ATOMIC ? (double *)(ws + L.fpriv) : nullptr;
+    p.nf = p.fzero ? L.n * L.n : 0;
+    p.jzero = copies < L.groups ? (double *)(ws + L.jcol) : nullptr;
+    p.jcopies = p.jzero ? copies : 0;
+    return p;
+}
+
 hipError_t launch_fock(const Layout &L, const Basis &b, char *ws, const double *dens, double tau, int prec,
                        int strategy, int variant, double *fock, double *e2, hipStream_t st)
 {
@@ -764,8 +765,6 @@ hipError_t launch_fock(const Layout &L, const Basis &b, char *ws, const double *
     FockArgs a;
     a.hdr = hdr;
     a.bd = (const BasisDev *)(ws + L.basis);
-    a.boys = (const double *)(ws + L.boys);
-    a.boys_f = (const double *)(ws + L.boys_f);
     a.pk = (const int *)(ws + L.pk);
     a.pl = (const int *)(ws + L.pl);
     a.pq = (const double *)(ws + L.pq);
@@ -779,7 +778,7 @@ hipError_t launch_fock(const Layout &L, const Basis &b, char *ws, const double *
     a.item_off = (const long long *)(ws + L.item_off);
     a.lim = (const int *)(ws + L.lim);
     a.bexp = (const short *)(ws + L.bexp);
-    a.kexp = (const int *)(ws + L.kexp);
+    a.kexp = (const int *)(ws + L.kexp256);
     a.tlim = term_limit(tau, prec);
     a.goff = (const long long *)(ws + L.goff);
     a.ngroups = L.ngroups;
@@ -795,15 +794,8 @@ hipError_t launch_fock(const Layout &L, const Basis &b, char *ws, const double *
     a.n = (int)L.n;
     a.strategy = strategy;
     a.jcopies = effective_copies(L);
-    if (a.jcopies < L.groups) {
-        // shared ket vectors are cleared before the launch (workgroups clear private ones)
-        const int64_t nj = (int64_t)a.jcopies * L.pcap;
-        hipLaunchKernelGGL(k_fill, dim3((unsigned)((nj + 255) / 256)), dim3(256), 0, st, a.jcol, nj, 0.0);
-    }
     const int64_t n2 = L.n * L.n;
     const unsigned nb2 = (unsigned)((n2 + 255) / 256);
-    if (strategy == HFK_STRATEGY_ATOMIC)
-        hipLaunchKernelGGL(k_fill, dim3(nb2), dim3(256), 0, st, a.fpriv, n2, 0.0);
     hipError_t err = hipSuccess;
     const int g = b.g;
     const bool at = L.atoms;
@@ -827,16 +819,22 @@ hipError_t launch_fock(const Layout &L, const Basis &b, char *ws, const double *
         }
     }
     if (err != hipSuccess) return err;
-    double *fsum = (double *)(ws + L.fsum);
-    if (strategy == HFK_STRATEGY_PRIVATE || strategy == HFK_STRATEGY_DETERMINISTIC)
+    const double *F = a.fpriv;
+    if (strategy == HFK_STRATEGY_PRIVATE || strategy == HFK_STRATEGY_DETERMINISTIC) {
+        double *fsum = (double *)(ws + L.fsum);
         hipLaunchKernelGGL(k_sum_private, dim3(nb2), dim3(256), 0, st, a.fpriv, L.groups, n2, fsum);
-    else
-        hipLaunchKernelGGL(k_copy, dim3(nb2), dim3(256), 0, st, a.fpriv, n2, fsum);
-    hipLaunchKernelGGL(k_jcol_scatter, dim3((unsigned)((L.pcap + 255) / 256)), dim3(256), 0, st, hdr, a.jcol,
-                       a.jcopies, L.pcap, a.pk, a.pl, a.n, fsum);
-    double *part = (double *)(ws + L.e2part);
-    hipLaunchKernelGGL(k_symmetrise, dim3(nb2), dim3(256), 0, st, fsum, dens, a.n, fock, part);
-    hipLaunchKernelGGL(k_energy, dim3(1), dim3(256), 0, st, part, (int)nb2, 0.5, e2);
+        F = fsum;
+    }
+    int copies = a.jcopies;
+    if (copies > 16) {
+        // both triangles of G would read every copy
+        hipLaunchKernelGGL(k_jcol_sum, dim3((unsigned)((L.pcap + 255) / 256)), dim3(256), 0, st, hdr, a.jcol, copies,
+                           L.pcap);
+        copies = 1;
+    }
+    hipLaunchKernelGGL(k_finish, dim3((unsigned)((n2 + 256 * kFinishPer - 1) / (256 * kFinishPer))), dim3(256), 0, st,
+                       hdr, F, (const double *)a.jcol, copies, L.pcap, (const int *)(ws + L.bucket_of), dens, a.n,
+                       fock, (double *)(ws + L.e2part), e2);
     return hipGetLastError();
 }
 

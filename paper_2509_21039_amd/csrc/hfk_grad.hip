@@ -31,16 +31,13 @@
 // registers and are reduced across the wave when the bra changes; ket-atom gradients go to
 // an LDS copy of the n x 3 gradient; each workgroup writes its copy out once.
 #include "hfk_device.hpp"
+#include "hfk_boys.hpp"
 
 namespace hfk {
 
 struct GradArgs {
     const DevHeader *hdr;
     const BasisDev *bd;
-    const double *tabH;
-    const double *tabH_f;   // rows of the FP32 grid (FP64 values)
-    const double *tabG;
-    const double *tabG_f;
     const int *pk;
     const int *pl;
     const double *pq;
@@ -61,7 +58,7 @@ struct GradArgs {
     int gshift;                 // log2 of the bras per group
     int tile;               // items per block
     const int *lim;
-    const short *bexp;          // [pcap][g2] term exponents of the bras
+    const short *bexp;          // [g2][pcap] term exponents of the bras
     const int *kexp;            // [ket block of a wave][g2] maxima of the kets' exponents
     int tlim;                   // term_limit(tau)
     const double *dens;
@@ -75,8 +72,12 @@ struct GradArgs {
     int n;
 };
 
+static __device__ const BoysGrad64 kBoysG64 = make_boys_grad64();
+static __device__ const BoysFloat kBoysG32 = make_boys_float(false);
+
 template <typename R> struct GPrec;
 template <> struct GPrec<double> {
+    static __device__ const double *boys() { return kBoysG64.v; }
     static __device__ const double *prim(const GradArgs &a) { return a.prim; }
     static __device__ const double *bra(const GradArgs &a) { return a.bra; }
     static __device__ const double *bip(const GradArgs &a) { return a.bip; }
@@ -85,6 +86,7 @@ template <> struct GPrec<double> {
     static __device__ double rsqrt(double x) { return rsqrt_fp64(x); }
 };
 template <> struct GPrec<float> {
+    static __device__ const float *boys() { return kBoysG32.v; }
     static __device__ const float *prim(const GradArgs &a) { return a.prim_f; }
     static __device__ const float *bra(const GradArgs &a) { return a.bra_f; }
     static __device__ const float *bip(const GradArgs &a) { return a.bip_f; }
@@ -119,37 +121,7 @@ void k_grad(GradArgs a)
     __shared__ int wperm[kWavesPerGroup][kWaveKets];
     __shared__ long long blk_at;
     for (int x = tid; x < 3 * n; x += kGroupThreads) lg[x] = 0.0;
-    // grid-scaled rows (argument T' = T / h) from the FP64 rows (one rounding for FP32):
-    // coefficient m of H times h^m sqrt(h) kE, of g times h^m h^(3/2) kW (FP32 only; FP64
-    // takes g from the derivative of H's degree-7 row)
-    {
-        // FP64: the degree-7 rows of H (tabG); FP32: H's and g's rows on the FP32 grid
-        const double *gH = sizeof(R) == 8 ? a.tabG : a.tabH_f, *gG = a.tabG_f;
-        for (int x = tid; x < BG::table_len; x += kGroupThreads) {
-            int k, c;
-            bool isg;
-            if constexpr (sizeof(R) == 8) {   // H's rows of degree 7, padded
-                k = x / BG::pair_stride;
-                c = x % BG::pair_stride;
-                isg = false;
-            } else {                          // H's rows, then g's
-                isg = x >= BG::g_off;
-                const int y = isg ? x - BG::g_off : x;
-                k = y / BG::stride;
-                c = y % BG::stride;
-            }
-            const int order = sizeof(R) == 8 ? kBoysOrderG : BG::stride;
-            const int rowlen = sizeof(R) == 8 ? kBoysStrideG : BG::stride;
-            double v = 0.0;   // the pad
-            if (c < order) {
-                double sc = sqrt(BG::h);
-                for (int e = 0; e < c; ++e) sc *= BG::h;
-                v = isg ? gG[k * rowlen + c] * sc * BG::h * (double)GradScale<R>::kW
-                        : gH[k * rowlen + c] * sc * (double)GradScale<R>::kE;
-            }
-            tHG[x] = (R)v;
-        }
-    }
+    load_boys<R>(tHG, GPrec<R>::boys(), BG::table_len, tid, kGroupThreads);
     __syncthreads();
 
     double eacc = 0.0;
@@ -215,7 +187,7 @@ void k_grad(GradArgs a)
                 qs = a.pq[s];
                 ds = a.pd[s];
                 lim = a.lim[s];
-                ebra = lane < G2 ? (int)a.bexp[(int64_t)s * G2 + lane] : kTermNone;
+                ebra = lane < G2 ? (int)a.bexp[(int64_t)lane * a.pcap + s] : kTermNone;
             }
             const long long wbase = (m - a.item_off[s]) * kItemKets + (long long)wave * kWaveKets;
             if (wbase >= lim) continue;
@@ -570,8 +542,6 @@ int grad_resident_groups(int g, int prec, int64_t n, bool atoms)
 template <int G, typename R>
 static hipError_t launch_grad_t(const GradArgs &a, int groups, size_t smem, bool atoms, hipStream_t st)
 {
-    const hipError_t ez = launch_zero_counter(a.next_block, st);
-    if (ez != hipSuccess) return ez;
     profile_begin(st);
     if (atoms)
         hipLaunchKernelGGL((k_grad<G, R, true>), dim3(groups), dim3(kGroupThreads), smem, st, a);
@@ -588,10 +558,6 @@ hipError_t launch_grad(const Layout &L, const Basis &b, char *ws, const double *
     GradArgs a;
     a.hdr = (const DevHeader *)(ws + L.hdr);
     a.bd = (const BasisDev *)(ws + L.basis);
-    a.tabH = (const double *)(ws + L.boys);
-    a.tabH_f = (const double *)(ws + L.boys_f);
-    a.tabG = (const double *)(ws + L.boys_g);
-    a.tabG_f = (const double *)(ws + L.boys_g_f);
     a.pk = (const int *)(ws + L.pk);
     a.pl = (const int *)(ws + L.pl);
     a.pq = (const double *)(ws + L.pq);
@@ -610,7 +576,7 @@ hipError_t launch_grad(const Layout &L, const Basis &b, char *ws, const double *
     a.item_off = (const long long *)(ws + L.item_off);
     a.lim = (const int *)(ws + L.lim);
     a.bexp = (const short *)(ws + L.bexp);
-    a.kexp = (const int *)(ws + L.kexp);
+    a.kexp = (const int *)(ws + L.kexp256);
     a.tlim = term_limit(tau, prec);
     a.goff = (const long long *)(ws + L.goff);
     a.ngroups = L.ngroups;

@@ -35,6 +35,8 @@ constexpr int kBoysOrder = 6;          // coefficients used (degree 5)
 constexpr int kBoysStride = 6;         // row length (48 bytes: 16-byte aligned rows)
 constexpr double kBoysH = 1.0 / 12.0;  // grid spacing
 constexpr double kBoysInvH = 12.0;
+constexpr double kSqrtBoysH = 0.28867513459481288;   // sqrt(1/12)
+constexpr double kTwoOverSqrtPi = 1.12837916709551257389615890312154517;
 constexpr double kTswitch = 32.0;      // above this H(T) = T^(-1/2) to < 1e-15 relative
 constexpr double kSqrtSwitchInvH = 19.595917942265423;   // sqrt(kTswitch / h) = sqrt(384)
 constexpr int kBoysGrid = 393;         // covers [0, 32.75): rows up to kTswitch / h and 8 more
@@ -127,7 +129,7 @@ struct DevHeader {
     int tile;                       // launch shape of the last build (for the stats)
     int group_bras;
     int ket_copies;
-    int pad1;
+    unsigned done_blocks;           // workgroups of the final kernel that have written their partial sums
     // batched block table: owned-molecule blocks, shared blocks, items per shared block
     long long bt_own;
     long long bt_sh;
@@ -163,16 +165,12 @@ struct BasisDev {
     double pi32[kMaxG2];        // (pi / p)^(3/2)
     double rho[kMaxG2 * kMaxG2];    // p q / (p + q), [ab * g2 + cd]
     double srho[kMaxG2 * kMaxG2];   // sqrt(rho)
-    double r2sw[kMaxG2 * kMaxG2];   // kTswitch / rho: |P-Q|^2 beyond which the far field is exact
-    double rs[3 * kMaxG2 * kMaxG2];     // (rho, sqrt(rho), kTswitch / rho) interleaved
-    float rs_f[3 * kMaxG2 * kMaxG2];
     double rsn[3 * kMaxG2 * kMaxG2];    // (kTswitch / rho, rho / h, sqrt(rho / h)): T on the table grid
     float rsn_f[3 * kMaxG2 * kMaxG2];   // the same on the FP32 grid (h = kBoysHF)
     double rsg[4 * kMaxG2 * kMaxG2];    // (kTswitch / rho, rho / h, sqrt(rho / h), (rho / h)^(3/2))
     float rsg_f[4 * kMaxG2 * kMaxG2];   // the same on the FP32 grid
     float rho_f[kMaxG2 * kMaxG2];
     float srho_f[kMaxG2 * kMaxG2];
-    float r2sw_f[kMaxG2 * kMaxG2];
 };
 
 // Workspace layout of the single-molecule path.  Every offset is 256-byte aligned.
@@ -183,7 +181,8 @@ struct Layout {
     int gshift;                 // log2 of the bras per group (tuned)
     int kcopies;                // ket-side Coulomb vectors requested (0: one per workgroup)
     bool private_ok;            // per-workgroup copies of F fit the memory budget
-    size_t hdr, basis, boys, boys_f;
+    int sub;                    // 64-ket chunks per wave of an item (items of 256 sub kets)
+    size_t hdr, basis;
     size_t q_unsorted, bucket_of, bucket_cnt, bucket_off, bucket_cur;
     size_t pk, pl, pq, pd;                 // sorted pair tables
     size_t prim;                           // [5][g2][pcap] doubles: Px, Py, Pz, S, |P|^2 (+ kTswitch/p per-atom)
@@ -194,9 +193,8 @@ struct Layout {
     size_t pmu, pfa;                       // per-atom gradient: [g2][pcap] mu and a/p of the ket pairs
     size_t bgw, bgw_f;                     // gradient: [pcap][g2][kGW] bra weights mu S, fa S, fb S, fa fb S, fb^2 S
     size_t bra, bra_f;                     // [pcap][g2][8] Px Py Pz S -2Px -2Py -2Pz |P|^2 (wave-uniform bra data)
-    size_t boys_g, boys_g_f;               // gradient tables: H of degree 7 (FP64), g(T) = -(4/sqrt(pi)) F1(T) (FP32 grid)
-    size_t bexp;                           // [pcap][g2] binary exponents bounding every primitive pair (term screen)
-    size_t kexp;                           // [pcap / kWaveKets, rounded up][g2] their maxima over the kets of a wave
+    size_t bexp;                           // [g2][pcap] binary exponents bounding every primitive pair (term screen)
+    size_t kexp64, kexp256;                // [blocks of 64 / 256 pairs][g2] their maxima
     size_t nitems, lim, item_off, scan_tmp;
     size_t gcnt, goff;                     // per bra group: blocks, and their exclusive prefix
     int64_t ngroups;                       // bra groups of 2^gshift bras
@@ -210,6 +208,7 @@ struct Layout {
     size_t e2tmp;                          // one double of scratch
     size_t grad;                           // [groups][n*3] gradient accumulators
     size_t total;
+    size_t static_bytes;                   // total less the term screen's tables (size rule of the allocation-free call)
 };
 
 // compact: the layout of the allocation-free call (one F for the atomics strategy, at most
@@ -234,7 +233,7 @@ struct BLayout {
     int64_t nmol, ptot, ntot, pcap;
     int64_t tri;                // sum of n (n + 1) / 2: entries of the packed triangles
     int g, g2, nmax;
-    size_t hdr, basis, boys, boys_f, boys_g, boys_g_f;
+    size_t hdr, basis;
     size_t mol_n, mol_aoff, mol_poff, mol_doff, mol_toff, cent, qmax;
     size_t q, bucket_of, bcnt, boff, bcur;
     size_t pk, pl, pm, pq, pd, prim, prim_f, bra, bra_f;
@@ -298,16 +297,32 @@ int device_cu_count();
 
 // ------------------------------------------------------------------ launchers
 // Each returns hipSuccess or the launch error; all enqueue on `st`.
-hipError_t launch_setup(const Basis &b, BasisDev *bd, double *boys, double *boys_f, double *boys_g,
-                        double *boys_g_f, DevHeader *hdr, int64_t n, const double *xyz, hipStream_t st);
-hipError_t launch_zero_counter(unsigned long long *p, hipStream_t st);
+// Launch configuration as hfk_read_stats reports it.
+struct HeaderInfo {
+    int strategy, groups, precision, variant, tile, group_bras, ket_copies;
+};
+hipError_t launch_prep_begin(const Basis &b, BasisDev *bd, DevHeader *hdr, int64_t n, const double *xyz,
+                             const HeaderInfo &info, double *fzero, int64_t nf, long long *cnt, int64_t ncnt,
+                             hipStream_t st);
 // fixed_order: pairs within a (band, cell) bucket by pair index (deterministic strategy)
 // instead of the order an atomic cursor hands out.  That mode waits for the stream once to
 // read the largest bucket and returns hipErrorNotSupported, before sorting, when it holds
 // more than kMaxFixedBucket pairs.
 constexpr int kMaxFixedBucket = 4096;
+struct PairPlan {
+    HeaderInfo info;
+    bool fixed_order;
+    double *fzero;              // accumulator of F to clear (nf values), or none
+    int64_t nf;
+    double *jzero;              // shared ket vectors to clear ([jcopies][pcap]), or none
+    int jcopies;
+};
 hipError_t launch_pairs(const Layout &L, const Basis &b, char *ws, const double *xyz, const double *dens,
-                        double tau, hipStream_t st, bool fixed_order = false);
+                        double tau, int prec, const PairPlan &plan, hipStream_t st);
+// The plan of a forward build with this strategy: its accumulators and its header entries.
+PairPlan fock_plan(const Layout &L, char *ws, int strategy, int prec, int variant);
+// Another density on the tables launch_pairs left (same geometry, basis, tau and shape).
+hipError_t launch_new_density(const Layout &L, char *ws, const double *dens, const PairPlan &plan, hipStream_t st);
 hipError_t launch_fock(const Layout &L, const Basis &b, char *ws, const double *dens, double tau,
                        int prec, int strategy, int variant, double *fock, double *e2, hipStream_t st);
 size_t fock_smem_bytes(int64_t n, int prec, int variant);

@@ -1,68 +1,69 @@
 // Setup and pair preparation for the Fock build: basis constants, Boys table, Schwarz
 // bounds, the Q-bucketed pair order and the work items of the quartet kernel.
+#include <string.h>
+
 #include "hfk_device.hpp"
 
 namespace hfk {
 
 // ------------------------------------------------------------------ setup
 
-// Basis constants per primitive pair and quartet; zeroes the header; centroid of xyz.
-__global__ __launch_bounds__(256) void k_setup(Basis b, BasisDev *__restrict__ bd,
-                                               DevHeader *__restrict__ hdr, int64_t n,
-                                               const double *__restrict__ xyz)
+// First launch of a build: basis constants per primitive pair and quartet, header, centroid and
+// bounding box of xyz if given (workgroup 0), and the clearing of F and of the bucket counters
+// (the others).
+// One launch in place of five: on small systems a launch costs more (4.5 us) than its work.
+__global__ __launch_bounds__(256) void k_prep_begin(Basis b, BasisDev *__restrict__ bd, DevHeader *__restrict__ hdr,
+                                                    int64_t n, const double *__restrict__ xyz, HeaderInfo info,
+                                                    double *__restrict__ fzero, int64_t nf,
+                                                    long long *__restrict__ cnt, int64_t ncnt)
 {
     const int t = threadIdx.x;
     const int g = b.g, g2 = b.g2;
-    for (int ab = t; ab < g2; ab += blockDim.x) {
-        const int a = ab / g, c = ab % g;
-        const double p = b.alpha[a] + b.alpha[c];
-        bd->p[ab] = p;
-        bd->mu[ab] = b.alpha[a] * b.alpha[c] / p;
-        bd->fa[ab] = b.alpha[a] / p;
-        bd->fb[ab] = b.alpha[c] / p;
-        bd->pi32[ab] = pow(kPi / p, 1.5);
-    }
-    for (int x = t; x < g2 * g2; x += blockDim.x) {
-        const int ab = x / g2, cd = x % g2;
-        const double p = b.alpha[ab / g] + b.alpha[ab % g];
-        const double q = b.alpha[cd / g] + b.alpha[cd % g];
-        const double rho = p * q / (p + q);
-        bd->rho[x] = rho;
-        bd->srho[x] = sqrt(rho);
-        bd->r2sw[x] = kTswitch / rho;
-        bd->rho_f[x] = (float)rho;
-        bd->rs[3 * x] = rho;
-        bd->rs[3 * x + 1] = sqrt(rho);
-        bd->rs[3 * x + 2] = kTswitch / rho;
-        bd->rs_f[3 * x] = (float)rho;
-        bd->rs_f[3 * x + 1] = (float)sqrt(rho);
-        bd->rs_f[3 * x + 2] = (float)(kTswitch / rho);
-        bd->rsn[3 * x] = kTswitch / rho;
-        bd->rsn[3 * x + 1] = rho * kBoysInvH;
-        bd->rsn[3 * x + 2] = sqrt(rho * kBoysInvH);
-        bd->rsn_f[3 * x] = (float)(kTswitch / rho);
-        bd->rsn_f[3 * x + 1] = (float)(rho * kBoysInvHF);
-        bd->rsn_f[3 * x + 2] = (float)sqrt(rho * kBoysInvHF);
-        {
-            const double r = rho * kBoysInvH, sr = sqrt(r);
+    if (blockIdx.x > 0 || gridDim.x == 1) {
+        const int64_t at = (int64_t)(gridDim.x == 1 ? 0 : blockIdx.x - 1) * blockDim.x + t;
+        const int64_t step = (int64_t)(gridDim.x == 1 ? 1 : gridDim.x - 1) * blockDim.x;
+        for (int64_t x = at; x < g2 * g2; x += step) {
+            const int ab = (int)x / g2, cd = (int)x % g2;
+            const double p = b.alpha[ab / g] + b.alpha[ab % g];
+            const double q = b.alpha[cd / g] + b.alpha[cd % g];
+            const double rho = p * q / (p + q);
+            if (cd == 0) {
+                const double mu = b.alpha[ab / g] * b.alpha[ab % g] / p;
+                bd->p[ab] = p;
+                bd->mu[ab] = mu;
+                bd->fa[ab] = b.alpha[ab / g] / p;
+                bd->fb[ab] = b.alpha[ab % g] / p;
+                bd->pi32[ab] = pow(kPi / p, 1.5);
+            }
+            bd->rho[x] = rho;
+            bd->srho[x] = sqrt(rho);
+            bd->rho_f[x] = (float)rho;
+            bd->srho_f[x] = (float)sqrt(rho);
+            const double r = rho * kBoysInvH, sr = sqrt(r), rf = rho * kBoysInvHF, srf = sqrt(rf);
+            bd->rsn[3 * x] = kTswitch / rho;
+            bd->rsn[3 * x + 1] = r;
+            bd->rsn[3 * x + 2] = sr;
+            bd->rsn_f[3 * x] = (float)(kTswitch / rho);
+            bd->rsn_f[3 * x + 1] = (float)rf;
+            bd->rsn_f[3 * x + 2] = (float)srf;
             bd->rsg[4 * x] = kTswitch / rho;
             bd->rsg[4 * x + 1] = r;
             bd->rsg[4 * x + 2] = sr;
             bd->rsg[4 * x + 3] = r * sr;
-            const double rf = rho * kBoysInvHF, srf = sqrt(rf);
             bd->rsg_f[4 * x] = (float)(kTswitch / rho);
             bd->rsg_f[4 * x + 1] = (float)rf;
             bd->rsg_f[4 * x + 2] = (float)srf;
             bd->rsg_f[4 * x + 3] = (float)(rf * srf);
         }
-        bd->srho_f[x] = (float)sqrt(rho);
-        bd->r2sw_f[x] = (float)(kTswitch / rho);
+        for (int64_t x = at; x < nf; x += step) fzero[x] = 0.0;
+        for (int64_t x = at; x < ncnt; x += step) cnt[x] = 0;
     }
-    // centroid and bounding box (block reductions, one block)
+    if (blockIdx.x > 0) return;
+    // centroid and bounding box (block reductions)
     __shared__ double red[3][256], rmin[3][256], rmax[3][256];
     double s0 = 0, s1 = 0, s2 = 0;
     double lo[3] = {1e300, 1e300, 1e300}, hi[3] = {-1e300, -1e300, -1e300};
-    for (int64_t i = t; i < n; i += blockDim.x) {
+    for (int64_t i = t; xyz && i < n; i += blockDim.x) {
         s0 += xyz[3 * i];
         s1 += xyz[3 * i + 1];
         s2 += xyz[3 * i + 2];
@@ -97,144 +98,120 @@ __global__ __launch_bounds__(256) void k_setup(Basis b, BasisDev *__restrict__ b
         hdr->items = 0;
         hdr->quartets = 0;
         hdr->max_bucket = 0;
+        hdr->next_block = 0;
+        hdr->done_blocks = 0;
         hdr->centroid[0] = red[0][0] / (double)n;
         hdr->centroid[1] = red[1][0] / (double)n;
         hdr->centroid[2] = red[2][0] / (double)n;
         hdr->natoms = (int)n;
+        hdr->strategy = info.strategy;
+        hdr->groups = info.groups;
+        hdr->precision = info.precision;
+        hdr->variant = info.variant;
+        hdr->tile = info.tile;
+        hdr->group_bras = info.group_bras;
+        hdr->ket_copies = info.ket_copies;
     }
 }
 
-// Boys tables.  Row k of `tg` holds (2/sqrt(pi)) (-1)^m F_m(k h) / m!, m = 0..7 (Taylor
-// coefficients of H(T) = erf(sqrt T)/sqrt T about T_k, rows of kBoysStrideG: the FP64 gradient
-// kernels take g(T) = -(4/sqrt(pi)) F1(T) = 2 H'(T) from its derivative); row k of `tab` is its
-// degree-5 Chebyshev economisation on [T_k - h/2, T_k + h/2] (the forward kernels' rows).  On
-// the FP32 grid (spacing kBoysHF, kBoysOrderF coefficients, still in FP64) `tab_f` holds H's
-// Taylor rows and `tg_f` g's, -(4/sqrt(pi)) (-1)^m F_{m+1}(k h) / m!.  The highest order
-// comes from its positive Kummer series (no cancellation), the lower ones from the downward
-// recursion F_m = (2T F_{m+1} + e^-T) / (2m + 1), which is stable in that direction (one
-// series per row instead of one per order: each term of a series is a division).
-__device__ inline void boys_rows(double T, int order, int stride, double *v, double *w)
+hipError_t launch_prep_begin(const Basis &b, BasisDev *bd, DevHeader *hdr, int64_t n, const double *xyz,
+                             const HeaderInfo &info, double *fzero, int64_t nf, long long *cnt, int64_t ncnt,
+                             hipStream_t st)
 {
-    double fm[kBoysOrderG + 1];
-    const double et = exp(-T);
-    {
-        const int m = order;
-        double term = 1.0 / (2.0 * m + 1.0), sum = term;
-        for (int i = 1; i < 400; ++i) {
-            term *= 2.0 * T / (2.0 * m + 2.0 * i + 1.0);
-            sum += term;
-            if (term < 1e-18 * sum) break;
-        }
-        fm[m] = et * sum;
-    }
-    for (int m = order - 1; m >= 0; --m) fm[m] = (2.0 * T * fm[m + 1] + et) / (2.0 * m + 1.0);
-    double fact = 1.0;
-    for (int m = 0; m < stride; ++m) {
-        v[m] = 0.0;
-        if (w) w[m] = 0.0;
-        if (m < order) {
-            if (m > 0) fact *= (double)m;
-            const double sgn = (m & 1) ? -1.0 : 1.0;
-            v[m] = kTwoOverSqrtPi * sgn * fm[m] / fact;
-            if (w) w[m] = -2.0 * kTwoOverSqrtPi * sgn * fm[m + 1] / fact;
-        }
-    }
-}
-
-__global__ void k_boys_table(double *__restrict__ tab, double *__restrict__ tab_f, double *__restrict__ tg,
-                             double *__restrict__ tg_f)
-{
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k < kBoysGrid) {
-        double *t7 = tg + k * kBoysStrideG;
-        boys_rows(k * kBoysH, kBoysOrderG, kBoysStrideG, t7, nullptr);
-        // economise to degree 5 in u = (T - T_k) / r, r = h/2 (b_m = c_m r^m): drop T7(u)/64
-        // and T6(u)/32 from the expansion, keeping the lower-degree parts of u^7 and u^6
-        //   u^7 = (T7 + 112 u^5 - 56 u^3 + 7 u) / 64,   u^6 = (T6 + 48 u^4 - 18 u^2 + 1) / 32
-        static_assert(kBoysOrder == 6 && kBoysOrderG == 8, "degree-7 rows economised to degree 5");
-        const double r = 0.5 * kBoysH;
-        double b[8], rm = 1.0;
-        for (int m = 0; m < 8; ++m) {
-            b[m] = t7[m] * rm;
-            rm *= r;
-        }
-        b[5] += b[7] * (112.0 / 64.0);
-        b[3] -= b[7] * (56.0 / 64.0);
-        b[1] += b[7] * (7.0 / 64.0);
-        b[4] += b[6] * (48.0 / 32.0);
-        b[2] -= b[6] * (18.0 / 32.0);
-        b[0] += b[6] * (1.0 / 32.0);
-        rm = 1.0;
-        for (int m = 0; m < kBoysStride; ++m) {
-            tab[k * kBoysStride + m] = b[m] / rm;
-            rm *= r;
-        }
-    }
-    if (k < kBoysGridF)
-        boys_rows(k * kBoysHF, kBoysOrderF, kBoysStrideF, tab_f + k * kBoysStrideF, tg_f + k * kBoysStrideF);
-}
-
-hipError_t launch_setup(const Basis &b, BasisDev *bd, double *boys, double *boys_f, double *boys_g,
-                        double *boys_g_f, DevHeader *hdr, int64_t n, const double *xyz, hipStream_t st)
-{
-    static_assert(kBoysGridF >= kBoysGrid, "one thread per row of the longer table");
-    hipLaunchKernelGGL(k_setup, dim3(1), dim3(256), 0, st, b, bd, hdr, n, xyz);
-    hipLaunchKernelGGL(k_boys_table, dim3((kBoysGridF + 63) / 64), dim3(64), 0, st, boys, boys_f, boys_g,
-                       boys_g_f);
+    // the constants of one basis take a workgroup or a few; the clearing 4 KB a thread at most
+    const int64_t work = (int64_t)b.g2 * b.g2 + (nf > ncnt ? nf : ncnt) / 4;
+    const int64_t nb = 1 + (work + 255) / 256;
+    hipLaunchKernelGGL(k_prep_begin, dim3((unsigned)(nb < 1024 ? nb : 1024)), dim3(256), 0, st, b, bd, hdr, n, xyz,
+                       info, fzero, nf, cnt, ncnt);
     return hipGetLastError();
 }
 
 // ------------------------------------------------------------------ pairs
 
-// Schwarz bound of every pair i >= j: Q_ij = sqrt((ij|ij)) in FP64, each primitive
-// quartet as S_ab S_cd sqrt(rho) H(rho |P-Q|^2) with H(T) = erf(sqrt T)/sqrt T.
-__global__ __launch_bounds__(256) void k_pair_q(Basis b, const BasisDev *__restrict__ bd,
-                                                DevHeader *__restrict__ hdr, int64_t n,
-                                                const double *__restrict__ xyz,
-                                                double *__restrict__ qout)
+// Schwarz bound of every pair i >= j: Q_ij = sqrt((ij|ij)) in FP64, TP lanes per pair.  All
+// primitive centres lie on the line A-B, P_ab - P_cd = (fb_ab - fb_cd) (B - A), and the matrix
+// (ab|cd) is symmetric, so the lanes share the g2 (g2 + 1) / 2 unordered primitive quartets,
+// each S_ab S_cd sqrt(rho) H(rho |P-Q|^2) with the library's erf.  One thread per pair summed
+// all g2^2 of them in a row: 43 us at 64 atoms and 627 us at 45 atoms with six primitives,
+// however few pairs there are.  With one basis on every atom a pair whose bound
+// U = sum |S_ab| p^(1/4) >= Q, times the largest U of any pair (the one at distance zero), is
+// below tau can never be significant: its Q is left at zero (most pairs of a sparse system).
+template <int TP>
+__global__ __launch_bounds__(256) void k_pair_q(Basis b, DevHeader *__restrict__ hdr, int64_t n, double tau,
+                                                const double *__restrict__ xyz, double *__restrict__ qout)
 {
+    constexpr int PB = 256 / TP;
+    extern __shared__ __attribute__((aligned(16))) double sm[];
+    __shared__ double red[256];
+    const int g = b.g, g2 = b.g2, l = threadIdx.x % TP, pb = threadIdx.x / TP;
+    double *S = sm + (size_t)pb * 3 * g2, *f = S + g2, *pp = f + g2;
     const int64_t npair = n * (n + 1) / 2;
-    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    double q = 0.0;
-    if (p < npair) {
+    const int64_t p = (int64_t)blockIdx.x * PB + pb;
+    const bool live = p < npair;
+    double r2 = 0.0, u = 0.0, u0 = 0.0;
+    if (live) {
         int64_t i, j;
         pair_of_index(p, i, j);
-        const double c0 = hdr->centroid[0], c1 = hdr->centroid[1], c2 = hdr->centroid[2];
-        double A[3] = {xyz[3 * i] - c0, xyz[3 * i + 1] - c1, xyz[3 * i + 2] - c2};
-        double B[3] = {xyz[3 * j] - c0, xyz[3 * j + 1] - c1, xyz[3 * j + 2] - c2};
-        double px[kMaxG2], py[kMaxG2], pz[kMaxG2], ps[kMaxG2], pp[kMaxG2];
-        double s = 0.0;
-        if (b.aexp) {
-            // per-atom bases: rho of every primitive quartet from the pair exponents
-            pair_prims_atoms(b, i, j, A, B, px, py, pz, ps, pp);
-            for (int ab = 0; ab < b.g2; ++ab)
-                for (int cd = 0; cd < b.g2; ++cd) {
-                    const double dx = px[ab] - px[cd], dy = py[ab] - py[cd], dz = pz[ab] - pz[cd];
-                    const double r2 = dx * dx + dy * dy + dz * dz;
-                    const double rho = pp[ab] * pp[cd] / (pp[ab] + pp[cd]);
-                    s += ps[ab] * ps[cd] * sqrt(rho) * erf_over_sqrt(rho * r2);
-                }
-        } else {
-            pair_prims(b, bd, A, B, px, py, pz, ps);
-            for (int ab = 0; ab < b.g2; ++ab)
-                for (int cd = 0; cd < b.g2; ++cd) {
-                    const double dx = px[ab] - px[cd], dy = py[ab] - py[cd], dz = pz[ab] - pz[cd];
-                    const double r2 = dx * dx + dy * dy + dz * dz;
-                    s += ps[ab] * ps[cd] * bd->srho[ab * b.g2 + cd] * erf_over_sqrt(bd->rho[ab * b.g2 + cd] * r2);
-                }
+        const double dx = xyz[3 * i] - xyz[3 * j], dy = xyz[3 * i + 1] - xyz[3 * j + 1],
+                     dz = xyz[3 * i + 2] - xyz[3 * j + 2];
+        r2 = dx * dx + dy * dy + dz * dz;
+        for (int ab = l; ab < g2; ab += TP) {
+            const int x = ab / g, y = ab % g;
+            const double ea = b.aexp ? b.aexp[i * g + x] : b.alpha[x], eb = b.aexp ? b.aexp[j * g + y] : b.alpha[y];
+            const double ww = b.aexp ? b.aw[i * g + x] * b.aw[j * g + y] : b.w[x] * b.w[y];
+            const double q = ea + eb, c = ww * pow(kPi / q, 1.5), s = c * exp(-(ea * eb / q) * r2);
+            const double q4 = sqrt(sqrt(q));
+            S[ab] = s;
+            f[ab] = eb / q;
+            pp[ab] = q;
+            u += fabs(s) * q4;
+            u0 += fabs(c) * q4;
         }
-        q = sqrt(s);
-        qout[p] = q;
     }
+#pragma unroll
+    for (int w = TP / 2; w > 0; w >>= 1) {
+        u += __shfl_xor(u, w, TP);
+        u0 += __shfl_xor(u0, w, TP);
+    }
+    __syncthreads();
+    double s = 0.0;
+    if (live && (b.aexp || !(u * u0 < tau))) {
+        const int nc = g2 * (g2 + 1) / 2;
+        for (int c = l; c < nc; c += TP) {
+            int ab = (int)((sqrtf(8.0f * (float)c + 1.0f) - 1.0f) * 0.5f);
+            while (ab * (ab + 1) / 2 > c) --ab;
+            while ((ab + 1) * (ab + 2) / 2 <= c) ++ab;
+            const int cd = c - ab * (ab + 1) / 2;
+            const double ss = S[ab] * S[cd];
+            if (ss == 0.0) continue;
+            const double df = f[ab] - f[cd], rho = pp[ab] * pp[cd] / (pp[ab] + pp[cd]);
+            const double v = ss * sqrt(rho) * erf_over_sqrt(rho * (df * df * r2));
+            s += ab == cd ? v : 2.0 * v;
+        }
+    }
+#pragma unroll
+    for (int w = TP / 2; w > 0; w >>= 1) s += __shfl_xor(s, w, TP);
+    const double q = sqrt(s);
+    if (live && l == 0) qout[p] = q;
     // block max, then one atomic per block (positive doubles order like their bit patterns)
-    __shared__ double red[256];
-    red[threadIdx.x] = q;
+    red[threadIdx.x] = live ? q : 0.0;
     __syncthreads();
     for (int w = 128; w > 0; w >>= 1) {
         if (threadIdx.x < w) red[threadIdx.x] = fmax(red[threadIdx.x], red[threadIdx.x + w]);
         __syncthreads();
     }
-    if (threadIdx.x == 0) atomicMax(&hdr->qmax_bits, (unsigned long long)__double_as_longlong(red[0]));
+    if (threadIdx.x == 0 && red[0] > 0.0)
+        atomicMax(&hdr->qmax_bits, (unsigned long long)__double_as_longlong(red[0]));
+}
+
+template <int TP>
+static void launch_pair_q(const Basis &b, DevHeader *hdr, int64_t n, double tau, const double *xyz, double *q,
+                          hipStream_t st)
+{
+    constexpr int PB = 256 / TP;
+    const int64_t np = n * (n + 1) / 2;
+    hipLaunchKernelGGL((k_pair_q<TP>), dim3((unsigned)((np + PB - 1) / PB)), dim3(256),
+                       sizeof(double) * 3 * (size_t)b.g2 * PB, st, b, hdr, n, tau, xyz, q);
 }
 
 // Morton index of the cell holding point c inside the bounding box.
@@ -282,119 +259,302 @@ __global__ __launch_bounds__(256) void k_bucket_cursors(const long long *__restr
     if (b == 0) hdr->sig_pairs = (int)off[kNumBuckets];
 }
 
-// Writes every significant pair at its bucketed position: atoms, Q, D_kl and the SoA
-// primitive-pair table {Px, Py, Pz, S} (FP64 and FP32), centred on the centroid.  With
-// per-atom bases (bip != NULL) the ket tables gain kTswitch / p as their last component
-// (FP64 component 5, FP32 component 4) and bip/bip_f receive it per bra primitive pair:
-// the two add up to kTswitch / rho of the quartet.
-__global__ __launch_bounds__(256) void k_pair_scatter(Basis b, const BasisDev *__restrict__ bd,
-                                                      const DevHeader *__restrict__ hdr, int64_t n,
-                                                      int64_t pcap, const double *__restrict__ xyz,
-                                                      const double *__restrict__ dens,
-                                                      const double *__restrict__ q,
-                                                      const int *__restrict__ bucket_of,
-                                                      int *__restrict__ cur, int *__restrict__ pk,
-                                                      int *__restrict__ pl, double *__restrict__ pq,
-                                                      double *__restrict__ pd, double *__restrict__ prim,
-                                                      float *__restrict__ prim_f, double *__restrict__ bra,
-                                                      float *__restrict__ bra_f, double *__restrict__ bip,
-                                                      float *__restrict__ bip_f, double *__restrict__ kmu,
-                                                      double *__restrict__ kfa, double *__restrict__ bgw,
-                                                      float *__restrict__ bgw_f, short *__restrict__ bexp,
-                                                      const int *__restrict__ slot)
+// Writes the tables of every significant pair at its position x, holding pair slot[x]: atoms, Q,
+// D_kl, the SoA primitive-pair table {Px, Py, Pz, S, |P|^2} centred on the centroid and the
+// bra rows, for the precision of the build.  One thread per (position, primitive pair): the
+// grid's y dimension is the primitive pair, so the table rows are written coalesced and the
+// exponentials of a pair run side by side (one thread per pair took 24 us at 64 atoms and
+// 81 us with six primitives).  With per-atom bases (bip != NULL) the ket tables gain
+// kTswitch / p as their last component (FP64 component 5, FP32 component 4) and bip receives
+// it per bra primitive pair: the two add up to kTswitch / rho of the quartet.  The 64
+// positions after the last pair are padded with harmless entries (atom 0, zero weight, centres
+// 1e6 bohr away), so that lanes past the last pair, or lanes pointed at the first pad entry,
+// read defined memory and land in the far branch with a zero integral.  A wave also leaves the
+// maximum of its 64 positions' term exponents, a workgroup that of its 256.
+struct PairTables {
+    const int *slot;
+    int *posof;         // [npair] position of every significant pair
+    int *pk, *pl;
+    double *pq, *pd;
+    double *prim;
+    float *prim_f;
+    double *bra;
+    float *bra_f;
+    double *bip;
+    float *bip_f;
+    double *kmu, *kfa;
+    double *bgw;
+    float *bgw_f;
+    short *bexp;        // [g2][pcap]
+    int *kexp64;        // [positions / 64][g2]
+    int *kexp256;       // [positions / 256][g2]
+    double *jzero;      // ket vectors to clear, [jcopies][pcap]
+    int jcopies;
+};
+template <typename R>
+__global__ __launch_bounds__(256) void k_pair_tables(Basis b, const BasisDev *__restrict__ bd,
+                                                     const DevHeader *__restrict__ hdr, int64_t pcap,
+                                                     const double *__restrict__ xyz, const double *__restrict__ dens,
+                                                     const double *__restrict__ q, int64_t n, PairTables T)
 {
-    const int64_t npair = n * (n + 1) / 2;
-    const int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    int64_t p;
-    int pos;
-    if (slot) {
-        // fixed order: thread x writes position x, holding pair slot[x]
-        if (x >= hdr->sig_pairs) return;
-        pos = (int)x;
-        p = slot[x];
-    } else {
-        // order within a bucket as the atomic cursor hands out places
-        p = x;
-        if (p >= npair) return;
-        const int bk = bucket_of[p];
-        if (bk < 0) return;
-        pos = atomicAdd(&cur[bk], 1);
-    }
-    int64_t i, j;
-    pair_of_index(p, i, j);
-    const double c0 = hdr->centroid[0], c1 = hdr->centroid[1], c2 = hdr->centroid[2];
-    double A[3] = {xyz[3 * i] - c0, xyz[3 * i + 1] - c1, xyz[3 * i + 2] - c2};
-    double B[3] = {xyz[3 * j] - c0, xyz[3 * j + 1] - c1, xyz[3 * j + 2] - c2};
-    double px[kMaxG2], py[kMaxG2], pz[kMaxG2], ps[kMaxG2], pp[kMaxG2], mu[kMaxG2], fa[kMaxG2];
-    if (b.aexp)
-        pair_prims_atoms(b, i, j, A, B, px, py, pz, ps, pp, mu, fa);
-    else
-        pair_prims(b, bd, A, B, px, py, pz, ps);
-    pk[pos] = (int)i;
-    pl[pos] = (int)j;
-    pq[pos] = q[p];
-    pd[pos] = dens[i * n + j];
-    const int g2 = b.g2;
-    for (int ab = 0; ab < g2; ++ab) {
-        prim[(0 * g2 + ab) * pcap + pos] = px[ab];
-        prim[(1 * g2 + ab) * pcap + pos] = py[ab];
-        prim[(2 * g2 + ab) * pcap + pos] = pz[ab];
-        prim[(3 * g2 + ab) * pcap + pos] = ps[ab];
-        prim[(4 * g2 + ab) * pcap + pos] = px[ab] * px[ab] + py[ab] * py[ab] + pz[ab] * pz[ab];
-        prim_f[(0 * g2 + ab) * pcap + pos] = (float)px[ab];
-        prim_f[(1 * g2 + ab) * pcap + pos] = (float)py[ab];
-        prim_f[(2 * g2 + ab) * pcap + pos] = (float)pz[ab];
-        prim_f[(3 * g2 + ab) * pcap + pos] = (float)ps[ab];
-        double *ba = bra + ((int64_t)pos * g2 + ab) * 8;
-        float *bf = bra_f + ((int64_t)pos * g2 + ab) * 8;
-        const double p2 = px[ab] * px[ab] + py[ab] * py[ab] + pz[ab] * pz[ab];
-        ba[0] = px[ab]; ba[1] = py[ab]; ba[2] = pz[ab]; ba[3] = ps[ab];
-        ba[4] = -2.0 * px[ab]; ba[5] = -2.0 * py[ab]; ba[6] = -2.0 * pz[ab]; ba[7] = p2;
-        bf[0] = (float)px[ab]; bf[1] = (float)py[ab]; bf[2] = (float)pz[ab]; bf[3] = (float)ps[ab];
-        bf[4] = (float)(-2.0 * px[ab]); bf[5] = (float)(-2.0 * py[ab]); bf[6] = (float)(-2.0 * pz[ab]);
-        bf[7] = (float)p2;
-    }
-    {
-        // exponents of the term screen
-        const double r = sqrt((A[0] - B[0]) * (A[0] - B[0]) + (A[1] - B[1]) * (A[1] - B[1]) +
-                              (A[2] - B[2]) * (A[2] - B[2]));
-        for (int ab = 0; ab < g2; ++ab) {
-            const double u = term_bound(ps[ab], b.aexp ? pp[ab] : bd->p[ab], b.aexp ? mu[ab] : bd->mu[ab], r,
-                                        bgw != nullptr);
-            bexp[(int64_t)pos * g2 + ab] = term_exponent(u);
+    constexpr bool kDouble = sizeof(R) == 8;
+    const int S = hdr->sig_pairs;
+    const int64_t at = (int64_t)blockIdx.x * 256;
+    if (at >= (int64_t)S + 64) return;
+    const int64_t pos = at + threadIdx.x;
+    const int g = b.g, g2 = b.g2, ab = blockIdx.y;
+    R *prim = kDouble ? (R *)T.prim : (R *)T.prim_f;
+    R *bra = kDouble ? (R *)T.bra : (R *)T.bra_f;
+    R *bip = kDouble ? (R *)T.bip : (R *)T.bip_f;
+    R *bgw = kDouble ? (R *)T.bgw : (R *)T.bgw_f;
+    int e = kTermNever;
+    if (pos < S) {
+        const int64_t p = T.slot[pos];
+        int64_t i, j;
+        pair_of_index(p, i, j);
+        const double c0 = hdr->centroid[0], c1 = hdr->centroid[1], c2 = hdr->centroid[2];
+        const double A[3] = {xyz[3 * i] - c0, xyz[3 * i + 1] - c1, xyz[3 * i + 2] - c2};
+        const double B[3] = {xyz[3 * j] - c0, xyz[3 * j + 1] - c1, xyz[3 * j + 2] - c2};
+        const double dx = A[0] - B[0], dy = A[1] - B[1], dz = A[2] - B[2];
+        const double ab2 = dx * dx + dy * dy + dz * dz;
+        double p_ab, mu, fa, fb, ps;
+        if (b.aexp) {
+            const double ea = b.aexp[i * g + ab / g], eb = b.aexp[j * g + ab % g];
+            p_ab = ea + eb;
+            mu = ea * eb / p_ab;
+            fa = ea / p_ab;
+            fb = eb / p_ab;
+            ps = b.aw[i * g + ab / g] * b.aw[j * g + ab % g] * exp(-mu * ab2) * pow(kPi / p_ab, 1.5);
+        } else {
+            p_ab = bd->p[ab];
+            mu = bd->mu[ab];
+            fa = bd->fa[ab];
+            fb = bd->fb[ab];
+            ps = b.w[ab / g] * b.w[ab % g] * exp(-mu * ab2) * bd->pi32[ab];
+        }
+        const double px = fa * A[0] + fb * B[0], py = fa * A[1] + fb * B[1], pz = fa * A[2] + fb * B[2];
+        const double p2 = px * px + py * py + pz * pz;
+        if (ab == 0) {
+            T.pk[pos] = (int)i;
+            T.pl[pos] = (int)j;
+            T.pq[pos] = q[p];
+            T.pd[pos] = dens[i * n + j];
+            T.posof[p] = (int)pos;
+            for (int c = 0; c < T.jcopies; ++c) T.jzero[(int64_t)c * pcap + pos] = 0.0;
+        }
+        prim[(0 * g2 + ab) * pcap + pos] = (R)px;
+        prim[(1 * g2 + ab) * pcap + pos] = (R)py;
+        prim[(2 * g2 + ab) * pcap + pos] = (R)pz;
+        prim[(3 * g2 + ab) * pcap + pos] = (R)ps;
+        if (kDouble) prim[(4 * g2 + ab) * pcap + pos] = (R)p2;
+        R *ba = bra + (pos * g2 + ab) * 8;
+        ba[0] = (R)px; ba[1] = (R)py; ba[2] = (R)pz; ba[3] = (R)ps;
+        ba[4] = (R)(-2.0 * px); ba[5] = (R)(-2.0 * py); ba[6] = (R)(-2.0 * pz); ba[7] = (R)p2;
+        if (bip) {
+            const R ip = (R)(kTswitch / p_ab);
+            prim[((kDouble ? 5 : 4) * g2 + ab) * pcap + pos] = ip;
+            bip[pos * g2 + ab] = ip;
+        }
+        if (T.kmu) {
+            // per-atom gradient: mu and a/p of every ket primitive pair
+            T.kmu[(int64_t)ab * pcap + pos] = mu;
+            T.kfa[(int64_t)ab * pcap + pos] = fa;
+        }
+        if (bgw) {
+            // gradient: the bra weights mu S, fa S, fb S, fa fb S, fb^2 S of every primitive pair
+            const double fbw = b.aexp ? 1.0 - fa : fb;
+            const double row[kGW] = {mu * ps, fa * ps, fbw * ps, fa * fbw * ps, fbw * fbw * ps, 0.0, 0.0, 0.0};
+            R *w = bgw + (pos * g2 + ab) * kGW;
+            for (int c = 0; c < kGW; ++c) w[c] = (R)row[c];
+        }
+        e = term_exponent(term_bound(ps, p_ab, mu, sqrt(ab2), bgw != nullptr));
+        T.bexp[(int64_t)ab * pcap + pos] = (short)e;
+    } else if (pos < (int64_t)S + 64) {
+        if (ab == 0) {
+            T.pk[pos] = 0;
+            T.pl[pos] = 0;
+            T.pq[pos] = 0.0;
+            T.pd[pos] = 0.0;
+        }
+        for (int c = 0; c < 4; ++c) prim[(c * g2 + ab) * pcap + pos] = c < 3 ? (R)1e6 : (R)0;
+        if (kDouble) prim[(4 * g2 + ab) * pcap + pos] = (R)3e12;
+        // kTswitch / p: the switch radius stays far below the pad distance
+        if (bip) prim[((kDouble ? 5 : 4) * g2 + ab) * pcap + pos] = (R)1;
+        if (T.kmu) {
+            T.kmu[(int64_t)ab * pcap + pos] = 0.0;
+            T.kfa[(int64_t)ab * pcap + pos] = 0.0;
         }
     }
-    if (bip) {
-        for (int ab = 0; ab < g2; ++ab) {
-            const double ip = kTswitch / pp[ab];
-            prim[(5 * g2 + ab) * pcap + pos] = ip;
-            prim_f[(4 * g2 + ab) * pcap + pos] = (float)ip;
-            bip[(int64_t)pos * g2 + ab] = ip;
-            bip_f[(int64_t)pos * g2 + ab] = (float)ip;
-        }
+    __shared__ int emax[4];
+#pragma unroll
+    for (int w = 32; w > 0; w >>= 1) {
+        const int o = __shfl_xor(e, w, 64);
+        e = o > e ? o : e;
     }
-    if (kmu) {
-        // per-atom gradient: mu and a/p of every ket primitive pair
-        for (int ab = 0; ab < g2; ++ab) {
-            kmu[(int64_t)ab * pcap + pos] = mu[ab];
-            kfa[(int64_t)ab * pcap + pos] = fa[ab];
-        }
+    if (threadIdx.x % 64 == 0) {
+        emax[threadIdx.x / 64] = e;
+        T.kexp64[(pos / 64) * g2 + ab] = e;
     }
-    if (bgw) {
-        // gradient: the bra weights mu S, fa S, fb S, fa fb S, fb^2 S of every primitive pair
-        for (int ab = 0; ab < g2; ++ab) {
-            const double m_ab = b.aexp ? mu[ab] : bd->mu[ab];
-            const double fa_ab = b.aexp ? fa[ab] : bd->fa[ab];
-            const double fb_ab = b.aexp ? 1.0 - fa[ab] : bd->fb[ab];
-            const double row[kGW] = {m_ab * ps[ab], fa_ab * ps[ab], fb_ab * ps[ab], fa_ab * fb_ab * ps[ab],
-                                     fb_ab * fb_ab * ps[ab], 0.0, 0.0, 0.0};
-            double *w = bgw + ((int64_t)pos * g2 + ab) * kGW;
-            float *wf = bgw_f + ((int64_t)pos * g2 + ab) * kGW;
-            for (int c = 0; c < kGW; ++c) {
-                w[c] = row[c];
-                wf[c] = (float)row[c];
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < 4; ++w) e = emax[w] > e ? emax[w] : e;
+        T.kexp256[(int64_t)blockIdx.x * g2 + ab] = e;
+    }
+}
+
+// New density on prepared tables: D_kl of every pair, and the accumulators of a build cleared.
+__global__ __launch_bounds__(256) void k_new_density(DevHeader *__restrict__ hdr, int64_t n, int64_t pcap,
+                                                     const double *__restrict__ dens, const int *__restrict__ pk,
+                                                     const int *__restrict__ pl, double *__restrict__ pd,
+                                                     double *__restrict__ fzero, int64_t nf,
+                                                     double *__restrict__ jzero, int jcopies)
+{
+    const int64_t at = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, step = (int64_t)gridDim.x * blockDim.x;
+    if (at == 0) {
+        hdr->next_block = 0;
+        hdr->done_blocks = 0;
+    }
+    const int S = hdr->sig_pairs;
+    for (int64_t x = at; x < nf; x += step) fzero[x] = 0.0;
+    for (int64_t t = at; t < S; t += step) {
+        pd[t] = dens[(int64_t)pk[t] * n + pl[t]];
+        for (int c = 0; c < jcopies; ++c) jzero[(int64_t)c * pcap + t] = 0.0;
+    }
+}
+
+// Order, ket ranges, items and blocks of a small system in one workgroup.  The general path
+// counts 2^19 buckets through global memory and scans three times (twelve launches, 4 to 5 us
+// each); here the buckets (kSmallBands bands, the last one open-ended, times kSmallCells cells:
+// the top bits of the Morton code) are counted in LDS, and everything up to the block offsets
+// follows from there.  Sixteen pairs a thread at most.
+constexpr int kSmallThreads = 1024, kSmallPer = 16;
+constexpr int64_t kSmallPairs = (int64_t)kSmallThreads * kSmallPer;
+constexpr int kSmallBands = 24, kSmallCells = 512, kSmallBuckets = kSmallBands * kSmallCells;
+static_assert(kSmallBuckets % kSmallThreads == 0, "whole bucket runs per thread");
+
+// Exclusive prefix over the workgroup of one value per thread; total to every thread.
+__device__ inline long long block_scan_1024(long long v, long long *__restrict__ wsum, long long &total)
+{
+    const int t = threadIdx.x, lane = t % kWave, wave = t / kWave;
+    long long x = v;
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+        const long long y = __shfl_up(x, o, kWave);
+        if (lane >= o) x += y;
+    }
+    if (lane == kWave - 1) wsum[wave] = x;
+    __syncthreads();
+    long long before = 0;
+    total = 0;
+    for (int w = 0; w < kSmallThreads / kWave; ++w) {
+        if (w < wave) before += wsum[w];
+        total += wsum[w];
+    }
+    __syncthreads();
+    return before + x - v;
+}
+
+__global__ __launch_bounds__(kSmallThreads) void k_order_small(
+    DevHeader *__restrict__ hdr, int64_t n, double tau, int64_t pcap, const double *__restrict__ xyz,
+    const double *__restrict__ q, int *__restrict__ posof, int *__restrict__ slot, int item_kets, int gshift, int tile,
+    int64_t ngroups, int *__restrict__ lims, long long *__restrict__ item_off, long long *__restrict__ goff)
+{
+    __shared__ int hist[kSmallBuckets];
+    __shared__ int band_at[kSmallBands + 1];
+    __shared__ long long wsum[kSmallThreads / kWave];
+    __shared__ int gmax[kSmallPairs / kMinGroupBras + 1];
+    const int t = threadIdx.x;
+    const int npair = (int)(n * (n + 1) / 2);
+    const double qmax = __longlong_as_double((long long)hdr->qmax_bits);
+    for (int x = t; x < kSmallBuckets; x += kSmallThreads) hist[x] = 0;
+    for (int64_t x = t; x < ngroups; x += kSmallThreads) gmax[x] = 0;
+    __syncthreads();
+    int bk[kSmallPer];
+#pragma unroll
+    for (int r = 0; r < kSmallPer; ++r) {
+        const int p = r * kSmallThreads + t;
+        bk[r] = -1;
+        if (p < npair) {
+            const double qp = q[p];
+            if (qp * qmax >= tau && qp > 0.0) {
+                int64_t i, j;
+                pair_of_index(p, i, j);
+                const double c[3] = {0.5 * (xyz[3 * i] + xyz[3 * j]), 0.5 * (xyz[3 * i + 1] + xyz[3 * j + 1]),
+                                     0.5 * (xyz[3 * i + 2] + xyz[3 * j + 2])};
+                const int band = q_band(qp), cell = morton_cell(c, hdr) / (kNumCells / kSmallCells);
+                bk[r] = (band < kSmallBands - 1 ? band : kSmallBands - 1) * kSmallCells + cell;
+                atomicAdd(&hist[bk[r]], 1);
+            } else {
+                posof[p] = -1;
             }
         }
+    }
+    __syncthreads();
+    // bucket offsets
+    constexpr int kPer = kSmallBuckets / kSmallThreads;
+    long long total;
+    {
+        int own[kPer], sum = 0;
+        for (int x = 0; x < kPer; ++x) {
+            own[x] = hist[t * kPer + x];
+            sum += own[x];
+        }
+        int run = (int)block_scan_1024(sum, wsum, total);
+        for (int x = 0; x < kPer; ++x) {
+            hist[t * kPer + x] = run;
+            if ((t * kPer + x) % kSmallCells == 0) band_at[(t * kPer + x) / kSmallCells] = run;
+            run += own[x];
+        }
+        if (t == 0) band_at[kSmallBands] = (int)total;
+    }
+    __syncthreads();
+    const int S = (int)total;
+    // positions (order within a bucket as the cursor hands out places)
+#pragma unroll
+    for (int r = 0; r < kSmallPer; ++r)
+        if (bk[r] >= 0) slot[atomicAdd(&hist[bk[r]], 1)] = r * kSmallThreads + t;
+    __threadfence_block();
+    __syncthreads();
+    // ket ranges: consecutive bras per thread, so that the item offsets are one more scan
+    const int per = (S + kSmallThreads - 1) / kSmallThreads;
+    long long mine = 0;
+    for (int x = 0; x < per; ++x) {
+        const int s = t * per + x;
+        if (s >= S) break;
+        const double thr = tau / q[slot[s]];
+        int bend = S;
+        if (thr > 0.0) {
+            // the band of the threshold finishes with the lane-level test; the first band and
+            // the last one are open-ended
+            const int bt = q_band(thr);
+            bend = bt >= kSmallBands - 1 ? S : band_at[bt + 1];
+        }
+        const int lim = bend < s + 1 ? bend : s + 1;
+        lims[s] = lim;
+        const int ni = (lim + item_kets - 1) / item_kets;
+        mine += ni;
+        atomicMax(&gmax[s >> gshift], (ni + tile - 1) / tile);
+    }
+    long long items;
+    long long run = block_scan_1024(mine, wsum, items);
+    for (int x = 0; x < per; ++x) {
+        const int s = t * per + x;
+        if (s >= S) break;
+        item_off[s] = run;
+        run += (lims[s] + item_kets - 1) / item_kets;
+    }
+    __syncthreads();
+    if (t == 0) {
+        item_off[S] = items;
+        long long nb = 0;
+        for (int64_t x = 0; x < ngroups; ++x) {
+            goff[x] = nb;
+            nb += (long long)gmax[x] << gshift;
+        }
+        goff[ngroups] = nb;
+        hdr->sig_pairs = S;
+        hdr->items = items;
+        hdr->blocks = nb;
     }
 }
 
@@ -485,20 +645,15 @@ hipError_t launch_pair_pad(const DevHeader *hdr, int64_t pcap, int g2, bool atom
 }
 
 // Ket range of every bra s (in bucketed order): kets t < lim_s with
-// lim_s = min(s + 1, end of the band holding tau / Q_s); items of kItemKets kets.  A workgroup
-// covers the kWaveKets kets that one wave of the quartet kernels takes, and leaves the maxima
-// of their term exponents in kexp.
-static_assert(kWaveKets == 256, "one workgroup of k_limits per wave's share of kets");
+// lim_s = min(s + 1, end of the band holding tau / Q_s); items of item_kets kets.
 __global__ __launch_bounds__(256) void k_limits(const DevHeader *__restrict__ hdr, double tau,
                                                 const double *__restrict__ pq,
                                                 const long long *__restrict__ boff,
                                                 long long *__restrict__ nitems, int *__restrict__ lims,
-                                                int64_t pcap, int g2, const short *__restrict__ bexp,
-                                                int *__restrict__ kexp)
+                                                int64_t pcap, int item_kets)
 {
     const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t S = hdr->sig_pairs;
-    block_term_maxima<kWaveKets, 256>(S, g2, bexp, kexp);
     if (s >= pcap) return;
     long long ni = 0;
     if (s < S) {
@@ -513,7 +668,7 @@ __global__ __launch_bounds__(256) void k_limits(const DevHeader *__restrict__ hd
             bend = bt + 1 >= kNumBands ? S : boff[(bt + 1) * kNumCells];
         }
         const int64_t lim = bend < s + 1 ? bend : s + 1;
-        ni = (lim + kItemKets - 1) / kItemKets;
+        ni = (lim + item_kets - 1) / item_kets;
         lims[s] = (int)lim;
     } else {
         lims[s] = 0;
@@ -750,24 +905,6 @@ hipError_t launch_dens_check_batched(DevHeader *hdr, int64_t nmol, const long lo
     return hipGetLastError();
 }
 
-__global__ void k_zero_u64(unsigned long long *__restrict__ p)
-{
-    if (threadIdx.x == 0) *p = 0ULL;
-}
-
-// Zeroes a work counter with a kernel (stream-ordered, no memset node).
-hipError_t launch_zero_counter(unsigned long long *p, hipStream_t st)
-{
-    hipLaunchKernelGGL(k_zero_u64, dim3(1), dim3(64), 0, st, p);
-    return hipGetLastError();
-}
-
-__global__ void k_fill_i64(long long *__restrict__ p, int64_t m)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < m) p[i] = 0;
-}
-
 // Blocks of every bra group: 2^gshift x the largest block count of its bras (bras with
 // fewer blocks leave empty slots, skipped by the kernels).
 // One workgroup per group of bras: the largest block count of its bras (a block-wide max).
@@ -795,52 +932,95 @@ __global__ __launch_bounds__(256) void k_group_blocks(const DevHeader *__restric
 }
 
 hipError_t launch_pairs(const Layout &L, const Basis &b, char *ws, const double *xyz, const double *dens,
-                        double tau, hipStream_t st, bool fixed_order)
+                        double tau, int prec, const PairPlan &plan, hipStream_t st)
 {
     DevHeader *hdr = (DevHeader *)(ws + L.hdr);
-    const BasisDev *bd = (const BasisDev *)(ws + L.basis);
+    BasisDev *bd = (BasisDev *)(ws + L.basis);
     const int64_t np = L.npair;
     const int bs = 256;
     const unsigned nbp = (unsigned)((np + bs - 1) / bs);
     long long *cnt = (long long *)(ws + L.bucket_cnt);
     long long *off = (long long *)(ws + L.bucket_off);
     int *cur = (int *)(ws + L.bucket_cur);
-    hipLaunchKernelGGL(k_fill_i64, dim3((kNumBuckets + 255) / 256), dim3(256), 0, st, cnt, (int64_t)kNumBuckets);
-    hipLaunchKernelGGL(k_pair_q, dim3(nbp), dim3(bs), 0, st, b, bd, hdr, L.n, xyz, (double *)(ws + L.q_unsorted));
-    hipLaunchKernelGGL(k_bucket_count, dim3(nbp), dim3(bs), 0, st, L.n, tau, hdr, xyz,
-                       (const double *)(ws + L.q_unsorted), (int *)(ws + L.bucket_of), cnt);
-    hipError_t e = launch_scan(cnt, kNumBuckets, off, (long long *)(ws + L.scan_tmp), nullptr, st);
+    double *q = (double *)(ws + L.q_unsorted);
+    int *posof = (int *)(ws + L.bucket_of);
+    const bool small = np <= kSmallPairs && !plan.fixed_order;
+    const int item_kets = kWavesPerGroup * kWave * L.sub;
+    hipError_t e = launch_prep_begin(b, bd, hdr, L.n, xyz, plan.info, plan.fzero, plan.nf, cnt,
+                                     small ? 0 : (int64_t)kNumBuckets, st);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_bucket_cursors, dim3((kNumBuckets + 255) / 256), dim3(256), 0, st, off, cur, hdr);
-    // fixed order: the pair of every position first (the item counts' storage is free until
-    // the limits are computed below)
-    int *slot = fixed_order ? (int *)(ws + L.nitems) : nullptr;
-    if (fixed_order) {
-        hipLaunchKernelGGL(k_bucket_max, dim3((kNumBuckets + 255) / 256), dim3(256), 0, st, off, hdr);
-        int hmax = 0;
-        e = hipMemcpyAsync(&hmax, &hdr->max_bucket, sizeof(int), hipMemcpyDeviceToHost, st);
-        if (e == hipSuccess) e = hipStreamSynchronize(st);
-        if (e != hipSuccess) return e;
-        if (hmax > kMaxFixedBucket) return hipErrorNotSupported;
-        hipLaunchKernelGGL(k_slot_fill, dim3(nbp), dim3(bs), 0, st, np, (const int *)(ws + L.bucket_of), cur, slot);
-        hipLaunchKernelGGL(k_slot_sort, dim3((kNumBuckets + 255) / 256), dim3(256), 0, st, off, slot);
+    // lanes per pair: about three primitive quartets each
+    switch (b.g) {
+    case 1: launch_pair_q<1>(b, hdr, L.n, tau, xyz, q, st); break;
+    case 2: launch_pair_q<4>(b, hdr, L.n, tau, xyz, q, st); break;
+    case 3: launch_pair_q<16>(b, hdr, L.n, tau, xyz, q, st); break;
+    default: launch_pair_q<64>(b, hdr, L.n, tau, xyz, q, st); break;
     }
-    hipLaunchKernelGGL(k_pair_scatter, dim3(nbp), dim3(bs), 0, st, b, bd, hdr, L.n, L.pcap, xyz, dens,
-                       (const double *)(ws + L.q_unsorted), (const int *)(ws + L.bucket_of), cur,
-                       (int *)(ws + L.pk), (int *)(ws + L.pl), (double *)(ws + L.pq), (double *)(ws + L.pd),
-                       (double *)(ws + L.prim), (float *)(ws + L.prim_f), (double *)(ws + L.bra),
-                       (float *)(ws + L.bra_f), L.atoms ? (double *)(ws + L.bip) : nullptr,
-                       L.atoms ? (float *)(ws + L.bip_f) : nullptr, L.pmu ? (double *)(ws + L.pmu) : nullptr,
-                       L.pmu ? (double *)(ws + L.pfa) : nullptr, L.bgw ? (double *)(ws + L.bgw) : nullptr,
-                       L.bgw ? (float *)(ws + L.bgw_f) : nullptr, (short *)(ws + L.bexp), slot);
-    hipLaunchKernelGGL(k_pair_pad, dim3((unsigned)((L.pcap + 255) / 256)), dim3(256), 0, st, hdr, L.pcap, L.g2,
-                       true, L.atoms ? 5 : -1, L.atoms ? 4 : -1,
-                       (int *)(ws + L.pk), (int *)(ws + L.pl), (double *)(ws + L.pq), (double *)(ws + L.pd),
-                       (double *)(ws + L.prim), (float *)(ws + L.prim_f), L.pmu ? (double *)(ws + L.pmu) : nullptr,
-                       L.pmu ? (double *)(ws + L.pfa) : nullptr);
+    // the pair of every position (the item counts' storage is free until the limits are computed)
+    int *slot = (int *)(ws + L.nitems);
+    if (small) {
+        hipLaunchKernelGGL(k_order_small, dim3(1), dim3(kSmallThreads), 0, st, hdr, L.n, tau, L.pcap, xyz,
+                           (const double *)q, posof, slot, item_kets, L.gshift, L.tile, L.ngroups,
+                           (int *)(ws + L.lim), (long long *)(ws + L.item_off), (long long *)(ws + L.goff));
+    } else {
+        hipLaunchKernelGGL(k_bucket_count, dim3(nbp), dim3(bs), 0, st, L.n, tau, hdr, xyz, (const double *)q, posof,
+                           cnt);
+        e = launch_scan(cnt, kNumBuckets, off, (long long *)(ws + L.scan_tmp), nullptr, st);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(k_bucket_cursors, dim3((kNumBuckets + 255) / 256), dim3(256), 0, st, off, cur, hdr);
+        if (plan.fixed_order) {
+            hipLaunchKernelGGL(k_bucket_max, dim3((kNumBuckets + 255) / 256), dim3(256), 0, st, off, hdr);
+            int hmax = 0;
+            e = hipMemcpyAsync(&hmax, &hdr->max_bucket, sizeof(int), hipMemcpyDeviceToHost, st);
+            if (e == hipSuccess) e = hipStreamSynchronize(st);
+            if (e != hipSuccess) return e;
+            if (hmax > kMaxFixedBucket) return hipErrorNotSupported;
+        }
+        hipLaunchKernelGGL(k_slot_fill, dim3(nbp), dim3(bs), 0, st, np, (const int *)posof, cur, slot);
+        if (plan.fixed_order)
+            hipLaunchKernelGGL(k_slot_sort, dim3((kNumBuckets + 255) / 256), dim3(256), 0, st, off, slot);
+    }
+    PairTables T;
+    memset(&T, 0, sizeof(T));
+    T.slot = slot;
+    T.posof = posof;
+    T.pk = (int *)(ws + L.pk);
+    T.pl = (int *)(ws + L.pl);
+    T.pq = (double *)(ws + L.pq);
+    T.pd = (double *)(ws + L.pd);
+    T.prim = (double *)(ws + L.prim);
+    T.prim_f = (float *)(ws + L.prim_f);
+    T.bra = (double *)(ws + L.bra);
+    T.bra_f = (float *)(ws + L.bra_f);
+    if (L.atoms) {
+        T.bip = (double *)(ws + L.bip);
+        T.bip_f = (float *)(ws + L.bip_f);
+    }
+    if (L.pmu) {
+        T.kmu = (double *)(ws + L.pmu);
+        T.kfa = (double *)(ws + L.pfa);
+    }
+    if (L.bgw) {
+        T.bgw = (double *)(ws + L.bgw);
+        T.bgw_f = (float *)(ws + L.bgw_f);
+    }
+    T.bexp = (short *)(ws + L.bexp);
+    T.kexp64 = (int *)(ws + L.kexp64);
+    T.kexp256 = (int *)(ws + L.kexp256);
+    T.jzero = plan.jzero;
+    T.jcopies = plan.jcopies;
+    // np + 64 positions at most (64 pads after the last pair)
+    const dim3 grid((unsigned)((np + 64 + 255) / 256), (unsigned)L.g2);
+    if (prec == HFK_MIXED)
+        hipLaunchKernelGGL((k_pair_tables<float>), grid, dim3(256), 0, st, b, (const BasisDev *)bd, hdr, L.pcap, xyz,
+                           dens, (const double *)q, L.n, T);
+    else
+        hipLaunchKernelGGL((k_pair_tables<double>), grid, dim3(256), 0, st, b, (const BasisDev *)bd, hdr, L.pcap, xyz,
+                           dens, (const double *)q, L.n, T);
+    if (small) return hipGetLastError();
     hipLaunchKernelGGL(k_limits, dim3((unsigned)((L.pcap + 255) / 256)), dim3(256), 0, st, hdr, tau,
                        (const double *)(ws + L.pq), off, (long long *)(ws + L.nitems), (int *)(ws + L.lim),
-                       L.pcap, L.g2, (const short *)(ws + L.bexp), (int *)(ws + L.kexp));
+                       L.pcap, item_kets);
     e = launch_scan((const long long *)(ws + L.nitems), L.pcap, (long long *)(ws + L.item_off),
                     (long long *)(ws + L.scan_tmp), &hdr->items, st);
     if (e != hipSuccess) return e;
@@ -848,6 +1028,16 @@ hipError_t launch_pairs(const Layout &L, const Basis &b, char *ws, const double 
                        (const long long *)(ws + L.nitems), L.ngroups, L.gshift, L.tile, (long long *)(ws + L.gcnt));
     return launch_scan((const long long *)(ws + L.gcnt), L.ngroups, (long long *)(ws + L.goff),
                        (long long *)(ws + L.scan_tmp), &hdr->blocks, st);
+}
+
+hipError_t launch_new_density(const Layout &L, char *ws, const double *dens, const PairPlan &plan, hipStream_t st)
+{
+    const int64_t work = plan.nf > L.npair ? plan.nf : L.npair;
+    const int64_t nb = (work + 255) / 256;
+    hipLaunchKernelGGL(k_new_density, dim3((unsigned)(nb < 2048 ? nb : 2048)), dim3(256), 0, st,
+                       (DevHeader *)(ws + L.hdr), L.n, L.pcap, dens, (const int *)(ws + L.pk),
+                       (const int *)(ws + L.pl), (double *)(ws + L.pd), plan.fzero, plan.nf, plan.jzero, plan.jcopies);
+    return hipGetLastError();
 }
 
 }  // namespace hfk

@@ -395,9 +395,13 @@ hfk_status run_scf(const Layout &L, const Basis &b, char *ws, const ScfLayout &S
     bool have_old = false, conv = false;
     int it = 0;
     double *e2tmp = scal + 1;
+    const PairPlan plan = fock_plan(L, ws, strat, prec, 1);
     for (it = 1; it <= max_iter; ++it) {
         // G(D), F = H + G
-        hipError_t ef = launch_pairs(L, b, ws, xyz, dens, tau, st, strat == HFK_STRATEGY_DETERMINISTIC);
+        // the pairs, their order and tables depend on the geometry only: later builds take the
+        // new density on the tables of the first
+        hipError_t ef = it == 1 ? launch_pairs(L, b, ws, xyz, dens, tau, prec, plan, st)
+                                : launch_new_density(L, ws, dens, plan, st);
         if (ef == hipSuccess) ef = launch_fock(L, b, ws, dens, tau, prec, strat, 1, G, e2tmp, st);
         if (ef != hipSuccess) return say(c, HFK_EHIP, "Fock build failed");
         hipLaunchKernelGGL(k_add, dim3(blocks(n2)), dim3(256), 0, st, n2, H, G, F);
