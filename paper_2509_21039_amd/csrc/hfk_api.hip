@@ -69,6 +69,7 @@ Layout make_layout(int64_t n, int g, int prec, int with_grad, int groups, bool a
     L.tile = prec == HFK_MIXED ? 2 * kTileItems : kTileItems;
     L.gshift = 10;   // kGroupBras
     L.sub = kSubChunks;
+    L.nsplit = 1;
     L.kcopies = 0;
     L.private_ok = !compact && (double)groups * (double)n * (double)n * 8.0 <= kPrivateBudget;
     L.npair = n * (n + 1) / 2;
@@ -312,16 +313,18 @@ static thread_local const BatchedConfig *g_force_b = nullptr;
 // The configuration before any tuning.  Timed over whole calls (side kernels included) on
 // MI355X for He 64 to 1024 and H/He 128, FP64 and mixed: ATOMIC was the faster strategy at
 // every size (the per-workgroup copies of F and their summation cost more than the atomics
-// they save), and small systems ran fastest with fewer workgroups per CU (2 at 64 atoms,
-// 4 at 128, the most that fit above).  Blocks of four items of 1024 kets (eight with the
-// FP32 ket table, half the size), groups of 1024 bras, one ket vector per workgroup.
-static TunedConfig default_config(int64_t n, int precision)
+// they save), with as many workgroups per CU as fit (four up to 64 atoms: mixed 198 against
+// 204 us).  Blocks of eight items (fewer row flushes) up to 256 atoms and with the FP32 ket
+// table; four with the larger FP64 one, which then stays in L2; one where the waves of a
+// workgroup share long chunks (20 atoms with six primitives: 99 against 124 us with two).
+// Groups of 1024 bras.  Eight shared ket-side Coulomb vectors: they stay cached where one per
+// workgroup does not (he512 FP64 68.0 against 69.2 ms, he1024 mixed 210.0 against 221.2 ms,
+// he128 2.12 against 2.19 ms).
+static TunedConfig default_config(int64_t n, int precision, int ngauss)
 {
-    // eight shared ket-side Coulomb vectors: they stay cached where one per workgroup does
-    // not (he512 FP64 68.0 against 69.2 ms, he1024 mixed 210.0 against 221.2 ms, he128 2.12
-    // against 2.19 ms)
-    return TunedConfig{HFK_STRATEGY_ATOMIC, 1, n <= 64 ? 2 : (n <= 128 ? 4 : 6),
-                       precision == HFK_MIXED ? 2 * kTileItems : kTileItems, kGroupBras, kDefaultKetCopies};
+    int tile = n <= 256 || precision == HFK_MIXED ? 2 * kTileItems : kTileItems;
+    if (ngauss >= 5 && n * (n + 1) / 2 <= 400) tile = 1;
+    return TunedConfig{HFK_STRATEGY_ATOMIC, 1, n <= 64 ? 4 : 6, tile, kGroupBras, kDefaultKetCopies};
 }
 
 // Before tuning: eight-wave workgroups, two per CU (the LDS holds two molecules' triangles
@@ -341,7 +344,7 @@ static bool lookup_tuned(const std::string &arch, int precision, int bucket, Tun
 
 static TunedConfig pick_config(int32_t strategy, int32_t precision, int64_t n, int32_t ngauss)
 {
-    TunedConfig c = default_config(n, precision);
+    TunedConfig c = default_config(n, precision, ngauss);
     if (g_force) {
         c = *g_force;
     } else {
@@ -361,6 +364,36 @@ static TunedConfig pick_config(int32_t strategy, int32_t precision, int64_t n, i
                         precision == HFK_MIXED ? 2 * kTileItems : kTileItems, kGroupBras, 0};
     }
     return c;
+}
+
+// No more workgroups than there can be blocks: a workgroup that only finds the counter
+// exhausted still loads its table, and on the smallest systems there are more of them than bras.
+static int forward_groups(const Layout &L, int groups)
+{
+    const int64_t per = (int64_t)item_kets(L) * L.tile;
+    const int64_t blocks = L.npair * ((L.npair + per - 1) / per);
+    return blocks < groups ? (int)blocks : groups;
+}
+
+// Items of the forward build (the deterministic strategy keeps its own).  Large systems give a
+// wave four chunks of 64 kets of an item: the screened kets are packed across them and a bra's
+// rows are cleared and flushed once per 4096 or 8192 kets.  Small ones have too few such items
+// to go round, and a bra with 500 kets leaves two of its four waves idle: one chunk per wave
+// there.  The line is where the two cross, in pairs (us, four chunks against one): 32 atoms
+// 90 / 77, 64 atoms 245 / 239 (mixed 201 / 198), 128 atoms 1087 / 1106; per-atom bases 100
+// atoms 948 / 903; with five or six primitives a chunk is ten times as long and the line lies
+// higher: 45 atoms 926 / 559, 90 atoms 4964 / 4121.  The smallest FP64 systems have fewer
+// chunks than SIMDs: their waves share one chunk, each with every fourth bra primitive pair
+// (8 atoms 49 / 40; 20 atoms with six primitives 184 / 99, with three 53 / 55).  Mixed builds
+// don't split: partial FP32 sums would round differently.
+static void set_items(Layout &L, int strat, int variant, int precision)
+{
+    if (strat == HFK_STRATEGY_DETERMINISTIC) return;
+    const int64_t one_chunk = L.g >= 5 ? 8192 : (L.atoms ? 6000 : 2500);
+    if (L.npair > one_chunk) return;
+    L.sub = 1;
+    const int64_t shared = L.g >= 5 ? 400 : 64;
+    if (precision == HFK_FP64 && variant != 0 && L.npair <= shared) L.nsplit = kWavesPerGroup;
 }
 
 static BatchedConfig pick_batched_config(int32_t precision)
@@ -594,11 +627,12 @@ static hfk_status fock_one_basis(int64_t natoms, const double *xyz, int32_t ngau
     int strat = cfg.strategy;
     if (strat == HFK_STRATEGY_PRIVATE && !L.private_ok) strat = HFK_STRATEGY_ATOMIC;
     set_shape(L, cfg.tile, cfg.gbras, cfg.kcopies);
+    set_items(L, strat, cfg.variant, precision);
     {
         // no more persistent workgroups than fit on a CU at once
         const bool det = strat == HFK_STRATEGY_DETERMINISTIC;
         const int fit = fock_resident_groups(ngauss, precision, cfg.variant, natoms, false, det);
-        L.groups = cus * (fit > 0 && cfg.gpc > fit ? fit : cfg.gpc);
+        L.groups = forward_groups(L, cus * (fit > 0 && cfg.gpc > fit ? fit : cfg.gpc));
         if (det) {
             hfk_status sd = det_groups(L);
             if (sd != HFK_OK) return sd;
@@ -714,10 +748,11 @@ hfk_status hfk_fock_atoms(int64_t natoms, const double *xyz, int32_t ngauss, con
     int strat = cfg.strategy;
     if (strat == HFK_STRATEGY_PRIVATE && !L.private_ok) strat = HFK_STRATEGY_ATOMIC;
     set_shape(L, cfg.tile, cfg.gbras, cfg.kcopies);
+    set_items(L, strat, 1, precision);
     {
         const bool det = strat == HFK_STRATEGY_DETERMINISTIC;
         const int fit = fock_resident_groups(ngauss, precision, 1, natoms, true, det);
-        L.groups = cus * (fit > 0 && cfg.gpc > fit ? fit : cfg.gpc);
+        L.groups = forward_groups(L, cus * (fit > 0 && cfg.gpc > fit ? fit : cfg.gpc));
         if (det) {
             hfk_status sd = det_groups(L);
             if (sd != HFK_OK) return sd;
@@ -797,10 +832,11 @@ hfk_status hfk_scf(int64_t natoms, const double *xyz, const double *charges_host
     int strat = cfg.strategy;
     if (strat == HFK_STRATEGY_PRIVATE && !L.private_ok) strat = HFK_STRATEGY_ATOMIC;
     set_shape(L, cfg.tile, cfg.gbras, cfg.kcopies);
+    set_items(L, strat, 1, precision);
     {
         const bool det = strat == HFK_STRATEGY_DETERMINISTIC;
         const int fit = fock_resident_groups(ngauss, precision, 1, natoms, true, det);
-        L.groups = cus * (fit > 0 && cfg.gpc > fit ? fit : cfg.gpc);
+        L.groups = forward_groups(L, cus * (fit > 0 && cfg.gpc > fit ? fit : cfg.gpc));
         if (det) {
             hfk_status sd = det_groups(L);
             if (sd != HFK_OK) return sd;
@@ -940,9 +976,10 @@ static hfk_status fock_grad_impl(bool atoms, int64_t natoms, const double *xyz, 
         if (strat == HFK_STRATEGY_PRIVATE && !L.private_ok) strat = HFK_STRATEGY_ATOMIC;
         Layout LW = L;
         set_shape(LW, cfg.tile, cfg.gbras, cfg.kcopies);
+        set_items(LW, strat, cfg.variant, precision);
         Layout LF = LW;
         const int fit = fock_resident_groups(ngauss, precision, cfg.variant, natoms, atoms);
-        LF.groups = cus * (fit > 0 && cfg.gpc > fit ? fit : cfg.gpc);
+        LF.groups = forward_groups(LF, cus * (fit > 0 && cfg.gpc > fit ? fit : cfg.gpc));
         PairPlan wplan = fock_plan(LF, ws, strat, precision, cfg.variant);
         wplan.info = plan.info;
         e = launch_pairs(LF, b, ws, xyz, xw, tau, precision, wplan, st);
@@ -1218,7 +1255,7 @@ hfk_status hfk_tune(int64_t natoms, const double *xyz, int32_t ngauss, const dou
     if (cus <= 0) return fail(HFK_EHIP, "no HIP device");
     const Layout L0 = make_layout(natoms, ngauss, precision, 0, groups_cap(cus));
     hfk_status err = HFK_OK;
-    TunedConfig best = default_config(natoms, precision);
+    TunedConfig best = default_config(natoms, precision, ngauss);
     if (ngauss > 4) best.variant = 1;
     TunedConfig cand;
     auto run = [&]() {

@@ -218,6 +218,31 @@ __device__ inline double boys_eval_d(const double *__restrict__ tab, unsigned of
 // loads (they are never written while a kernel runs).
 template <typename T> using cptr = const __attribute__((address_space(4))) T *;
 
+// A value known to be the same in every lane, moved to scalar registers, so that what is
+// derived from it (addresses, loop bounds, loads through cptr) stays out of the vector ones.
+__device__ inline int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ inline long long uniform(long long v)
+{
+    const int lo = __builtin_amdgcn_readfirstlane((int)v), hi = __builtin_amdgcn_readfirstlane((int)(v >> 32));
+    return ((long long)hi << 32) | (unsigned)lo;
+}
+
+// Block `at` of the numbering of bra groups: the last group g with goff[g] <= at, and within it
+// ket-block-major over the group's bras (the last group holds what is left of the S bras).
+__device__ inline void block_bra(cptr<long long> goff, int64_t ngroups, int gshift, int S, long long at, int &s,
+                                 int &kblock)
+{
+    int64_t lo = 0, hi = ngroups - 1;
+    while (lo < hi) {
+        const int64_t mid = (lo + hi + 1) >> 1;
+        if (goff[mid] <= at) lo = mid; else hi = mid - 1;
+    }
+    const int first = (int)(lo << gshift), left = S - first;
+    const unsigned nb = left < (1 << gshift) ? left : 1 << gshift, local = (unsigned)(at - goff[lo]);
+    kblock = (int)(local / nb);
+    s = first + (int)(local % nb);
+}
+
 // Term masks of the quartet kernels.  Lane ab < G^2 holds the bra's exponent e_ab (kTermNone
 // in the other lanes); kexp points at the maxima over the wave's kets of the G ket primitive
 // pairs of one row cb.  need[d] has bit ab set if some ket primitive pair d' <= d of the row
@@ -364,15 +389,16 @@ __device__ inline double wave_sum(double v)
 
 __device__ inline int lane_id() { return (int)__lane_id(); }
 
-// Packs this wave's kets t = base + r * 64 + lane (r < kSubChunks) for which keep(t) holds
+// Packs this wave's kets t = base + r * 64 + lane (r < sub <= kSubChunks) for which keep(t) holds
 // into perm[0 .. count), in ascending order (ballot + lane count, no atomics), and returns
 // the wave-uniform count.
 template <typename Keep>
-__device__ inline int pack_kets(long long base, int lane, int *__restrict__ perm, Keep keep)
+__device__ inline int pack_kets(long long base, int lane, int *__restrict__ perm, Keep keep, int sub = kSubChunks)
 {
     int count = 0;
 #pragma unroll
     for (int r = 0; r < kSubChunks; ++r) {
+        if (r >= sub) break;
         const long long t = base + r * kWave + lane;
         const bool ok = keep(t);
         const unsigned long long mk = __builtin_amdgcn_ballot_w64(ok);

@@ -57,6 +57,9 @@ struct FockArgs {
     const int *lim;
     const short *bexp;          // [g2][pcap] term exponents of the bras
     const int *kexp;            // [ket block of a wave][g2] maxima of the kets' exponents
+    int sub;                    // 64-ket chunks per wave of an item
+    int nsplit;                 // waves that share a chunk's bra primitive pairs
+    int last_first;             // blocks from the end of the numbering
     int tlim;                   // term_limit(tau)
     const double *dens;
     double *fpriv;
@@ -336,8 +339,16 @@ template <typename R> struct FockSmem {
     }
 };
 
+// Waves per SIMD the compiler has to leave room for where it ends just above the register
+// count of one more by itself: FP64 per-atom bases with three primitives (97 VGPRs; 96 for five
+// waves) and five or six primitives (130; 128 for four).
+template <int G, typename R, bool kAtoms> constexpr int fock_waves()
+{
+    return sizeof(R) == 8 ? (G == 3 && kAtoms ? 5 : (G >= 5 && !kAtoms ? 4 : 1)) : 1;
+}
 template <int G, typename R, bool kSplit, bool kAtoms = false, bool kDet = false>
-__global__ __launch_bounds__(kGroupThreads) void k_fock(FockArgs a)
+__global__ __launch_bounds__(kGroupThreads) __attribute__((amdgpu_waves_per_eu(kDet ? 1 : fock_waves<G, R, kAtoms>())))
+void k_fock(FockArgs a)
 {
     constexpr int G2 = G * G;
     extern __shared__ __attribute__((aligned(16))) double smem[];
@@ -357,16 +368,13 @@ __global__ __launch_bounds__(kGroupThreads) void k_fock(FockArgs a)
     int *stk = (int *)(stv + kWavesPerGroup * kWaveKets);         // [waves][kWaveKets] k
     int *stl = stk + kWavesPerGroup * kWaveKets;                  // [waves][kWaveKets] l
     __shared__ double jbs[kWavesPerGroup];
-    __shared__ int bra_at[2];
-    __shared__ double bra_qd[2];
     __shared__ int wperm[kWavesPerGroup][kWaveKets];
 
     const int tid = threadIdx.x;
-    const int wave = tid / kWave;
+    const int wave = uniform(tid / kWave);
     const int lane = tid % kWave;
     const int gid = blockIdx.x, ng = gridDim.x;
-    const long long M = a.hdr->items;
-    const int S = a.hdr->sig_pairs;
+    const int S = ((cptr<DevHeader>)a.hdr)->sig_pairs;
     const BasisDev *bd = a.bd;
 
     load_boys<R>(tab, Prec<R>::boys(kSplit), BoysGrid<R>::rows * BoysGrid<R>::stride, tid, kGroupThreads);
@@ -377,44 +385,43 @@ __global__ __launch_bounds__(kGroupThreads) void k_fock(FockArgs a)
         }
     }
     const cptr<R> crs = (cptr<R>)Prec<R>::rsn(bd);
-    const bool jshared = a.jcopies < ng;
+    // a ket vector of the workgroup's own is cleared here, and added to without atomics unless
+    // its waves meet on a ket
+    const bool jown = a.jcopies >= ng, jshared = !jown || a.nsplit > 1;
+    // waves that share a chunk each take every kWavesPerGroup-th bra primitive pair
+    const bool myterms = lane < G2 && (a.nsplit == 1 || lane % kWavesPerGroup == wave);
+    const int wkets = kWave * a.sub, ikets = (a.nsplit > 1 ? 1 : kWavesPerGroup) * wkets;
     double *jcol = a.jcol + (int64_t)(gid % a.jcopies) * a.pcap;
     const bool priv = kDet || a.strategy == HFK_STRATEGY_PRIVATE;
     double *fp = priv ? a.fpriv + (int64_t)gid * n * n : a.fpriv;
     if (priv) {
         for (int64_t x = tid; x < (int64_t)n * n; x += kGroupThreads) fp[x] = 0.0;
     }
-    if (!jshared) {
+    if (jown) {
         for (int64_t x = tid; x < S; x += kGroupThreads) jcol[x] = 0.0;
     }
     __syncthreads();
     const R *prim = Prec<R>::prim(a);
     unsigned long long kept = 0;
     __shared__ long long blk_at;
-    const long long NB = a.hdr->blocks;
-    (void)M;
+    const long long NB = ((cptr<DevHeader>)a.hdr)->blocks;
+    const cptr<long long> goff = (cptr<long long>)a.goff, item_off = (cptr<long long>)a.item_off;
     // blocks (bra group, ket block K, bra) fetched from a global counter until exhausted, or
     // dealt out by a static grid stride (deterministic strategy)
     for (long long it = 0;; ++it) {
     if (!kDet && tid == 0) blk_at = (long long)atomicAdd(a.next_block, 1ULL);
     __syncthreads();
-    const long long blk = kDet ? (long long)gid + it * ng : blk_at;
+    const long long blk = kDet ? (long long)gid + it * ng : uniform(blk_at);
     __syncthreads();
     if (blk >= NB) break;
     int s;
     long long m0, m1;
     {
-        // group: the last g with goff[g] <= blk; within it K-major over the group's bras
-        int64_t lo = 0, hi = a.ngroups - 1;
-        while (lo < hi) {
-            const int64_t mid = (lo + hi + 1) >> 1;
-            if (a.goff[mid] <= blk) lo = mid; else hi = mid - 1;
-        }
-        const long long local = blk - a.goff[lo];
-        s = (int)((lo << a.gshift) + (local & ((1LL << a.gshift) - 1)));
-        if (s >= S) continue;
-        const long long i1 = a.item_off[s + 1];
-        m0 = a.item_off[s] + (local >> a.gshift) * a.tile;
+        const long long at = a.last_first ? NB - 1 - blk : blk;
+        int kb;
+        block_bra(goff, a.ngroups, a.gshift, S, at, s, kb);
+        const long long i1 = item_off[s + 1];
+        m0 = item_off[s] + (long long)kb * a.tile;
         if (m0 >= i1) continue;   // this bra has fewer blocks than the group's longest
         m1 = m0 + a.tile < i1 ? m0 + a.tile : i1;
     }
@@ -424,7 +431,7 @@ __global__ __launch_bounds__(kGroupThreads) void k_fock(FockArgs a)
 
     for (long long m = m0; m <= m1; ++m) {
         if (m < m1) {
-            while (a.item_off[s + 1] <= m) ++s;
+            while (item_off[s + 1] <= m) ++s;
         }
         if (m == m1 || s != cur) {
             if (cur >= 0) {
@@ -467,30 +474,25 @@ __global__ __launch_bounds__(kGroupThreads) void k_fock(FockArgs a)
             if (m == m1) break;
             const R *br = Prec<R>::bra(a) + (int64_t)s * 8 * G2;
             if (!kSplit && tid < 4 * G2) lbra[tid] = br[8 * (tid / 4) + tid % 4];
-            if (tid == 0) {
-                bra_at[0] = a.pk[s];
-                bra_at[1] = a.pl[s];
-                bra_qd[0] = a.pq[s];
-                bra_qd[1] = a.pd[s];
-            }
             for (int c = tid; c < n; c += kGroupThreads) {
                 rowi[c] = 0.0;
                 rowj[c] = 0.0;
             }
             __syncthreads();
             cur = s;
-            bi = bra_at[0];
-            bj = bra_at[1];
-            qs = bra_qd[0];
-            ds = bra_qd[1];
-            lim = a.lim[s];
-            if (kSplit) ebra = lane < G2 ? (int)a.bexp[(int64_t)lane * a.pcap + s] : kTermNone;
+            // scalar loads: the bra's data stays in scalar registers
+            bi = ((cptr<int>)a.pk)[s];
+            bj = ((cptr<int>)a.pl)[s];
+            qs = ((cptr<double>)a.pq)[s];
+            ds = ((cptr<double>)a.pd)[s];
+            lim = ((cptr<int>)a.lim)[s];
+            if (kSplit) ebra = myterms ? (int)a.bexp[(int64_t)lane * a.pcap + s] : kTermNone;
         }
-        const long long wbase = (m - a.item_off[s]) * kItemKets + (long long)wave * kWaveKets;
+        const long long wbase = (m - item_off[s]) * ikets + (a.nsplit > 1 ? 0 : wave * wkets);
         if constexpr (!kDet) {
             if (wbase >= lim) continue;
         }
-        const cptr<int> kexp = (cptr<int>)(a.kexp + __builtin_amdgcn_readfirstlane((int)(wbase / kWaveKets)) * G2);
+        const cptr<int> kexp = (cptr<int>)(a.kexp + (int)(wbase / wkets) * G2);
         // one 64-lane chunk: ket t per lane (valid: kept by the screen), scatter of v
         // (deterministic strategy: the exchange updates are staged at position `slot`)
         auto chunk = [&](int t, bool valid, int slot) {
@@ -509,7 +511,7 @@ __global__ __launch_bounds__(kGroupThreads) void k_fock(FockArgs a)
             const double v = valid ? (double)eri * deg : 0.0;
             jb = fma(a.pd[t], v, jb);
             if (valid) {
-                ++kept;
+                if (a.nsplit == 1 || wave == 0) ++kept;
                 if (jshared)
                     atomicAdd(&jcol[t], 4.0 * ds * v);
                 else
@@ -559,7 +561,7 @@ __global__ __launch_bounds__(kGroupThreads) void k_fock(FockArgs a)
             // keep the screened kets of this wave's 256, in order, packed into full chunks
             int *perm = wperm[wave];
             const int nvalid = pack_kets(wbase, lane, perm,
-                                         [&](long long t) { return t < lim && qs * a.pq[t] >= a.tau; });
+                                         [&](long long t) { return t < lim && qs * a.pq[t] >= a.tau; }, a.sub);
             if (nvalid == 0) continue;
             for (int c0 = 0; c0 < nvalid; c0 += kWave) {
                 const bool valid = c0 + lane < nvalid;
@@ -567,7 +569,7 @@ __global__ __launch_bounds__(kGroupThreads) void k_fock(FockArgs a)
             }
             __builtin_amdgcn_wave_barrier();
         } else {
-            for (int c = 0; c < kSubChunks; ++c) {
+            for (int c = 0; c < a.sub; ++c) {
                 const long long t0 = wbase + c * kWave;
                 if (t0 >= lim) break;
                 const long long t = t0 + lane;   // < S + 64 <= pcap: padded tables
@@ -605,31 +607,33 @@ __global__ __launch_bounds__(256) void k_jcol_sum(const DevHeader *__restrict__ 
 }
 
 // G = (F + F^T)/2 with the ket-side Coulomb terms of the pair (i, j) (each pair is one
-// position), and E2 = 1/2 sum D o G: every workgroup leaves its partial sum, and the one that
-// finishes last adds them in workgroup order, so that the result does not depend on which one
-// that is.  One launch: copying F, adding the ket terms, symmetrising, summing the partials and
-// the header took five of 4.5 us each.
+// position), and the workgroups' partial sums of D o G; a single workgroup writes E2 itself.
+// One or two launches: copying F, adding the ket terms, symmetrising and summing took four of
+// 4.5 us.  (Summing the partials in the workgroup that ends last needs a device-wide fence in
+// every workgroup, which made the kernel 16 us at 64 atoms.)
 constexpr int kFinishPer = 4;
-__global__ __launch_bounds__(256) void k_finish(DevHeader *__restrict__ hdr, const double *__restrict__ F,
-                                                const double *__restrict__ jcol, int copies, int64_t pcap,
-                                                const int *__restrict__ posof, const double *__restrict__ dens,
-                                                int n, double *__restrict__ fock, double *__restrict__ part,
-                                                double *__restrict__ e2)
+template <int kThreads>
+__global__ __launch_bounds__(kThreads) void k_finish(const double *__restrict__ F, const double *__restrict__ jcol,
+                                                     int copies, int64_t pcap, const int *__restrict__ posof,
+                                                     const double *__restrict__ dens, int n,
+                                                     double *__restrict__ fock, double *__restrict__ part,
+                                                     double *__restrict__ e2)
 {
-    __shared__ double red[256];
-    __shared__ unsigned last;
-    const int n2 = n * n, at = blockIdx.x * 256 * kFinishPer + threadIdx.x;
+    __shared__ double red[kThreads];
+    const int n2 = n * n, at = blockIdx.x * kThreads * kFinishPer + threadIdx.x;
     double e = 0.0;
 #pragma unroll
     for (int r = 0; r < kFinishPer; ++r) {
-        const int x = at + r * 256;
+        const int x = at + r * kThreads;
         if (x < n2) {
             const int i = x / n, j = x - i * n;
             const int hi = i > j ? i : j, lo = i > j ? j : i;
             const int t = posof[(int64_t)hi * (hi + 1) / 2 + lo];
             double J = 0.0;
-            if (t >= 0)
+            if (t >= 0) {
+#pragma unroll 8
                 for (int c = 0; c < copies; ++c) J += jcol[(int64_t)c * pcap + t];
+            }
             const double gv = i == j ? F[x] + J : 0.5 * (F[x] + F[(int64_t)j * n + i] + J);
             fock[x] = gv;
             e += dens[x] * gv;
@@ -637,21 +641,24 @@ __global__ __launch_bounds__(256) void k_finish(DevHeader *__restrict__ hdr, con
     }
     red[threadIdx.x] = e;
     __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
+    for (int w = kThreads / 2; w > 0; w >>= 1) {
         if (threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
         __syncthreads();
     }
     if (threadIdx.x == 0) {
-        part[blockIdx.x] = red[0];
-        __threadfence();   // the partial sum before the count
-        last = atomicAdd(&hdr->done_blocks, 1u);
+        if (gridDim.x == 1)
+            *e2 = 0.5 * red[0];
+        else
+            part[blockIdx.x] = red[0];
     }
-    __syncthreads();
-    if (last != gridDim.x - 1) return;
-    __threadfence();
+}
+
+// E2 = 1/2 sum of the partials (one block, fixed order).
+__global__ __launch_bounds__(256) void k_energy(const double *__restrict__ part, int nb, double *__restrict__ e2)
+{
+    __shared__ double red[256];
     double s = 0.0;
-    for (unsigned b = threadIdx.x; b < gridDim.x; b += 256)
-        s += __hip_atomic_load(&part[b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    for (int b = threadIdx.x; b < nb; b += 256) s += part[b];
     red[threadIdx.x] = s;
     __syncthreads();
     for (int w = 128; w > 0; w >>= 1) {
@@ -778,7 +785,10 @@ hipError_t launch_fock(const Layout &L, const Basis &b, char *ws, const double *
     a.item_off = (const long long *)(ws + L.item_off);
     a.lim = (const int *)(ws + L.lim);
     a.bexp = (const short *)(ws + L.bexp);
-    a.kexp = (const int *)(ws + L.kexp256);
+    a.kexp = (const int *)(ws + (L.sub == kSubChunks ? L.kexp256 : L.kexp64));
+    a.sub = L.sub;
+    a.nsplit = L.nsplit;
+    a.last_first = L.sub == kSubChunks ? 0 : 1;
     a.tlim = term_limit(tau, prec);
     a.goff = (const long long *)(ws + L.goff);
     a.ngroups = L.ngroups;
@@ -832,9 +842,17 @@ hipError_t launch_fock(const Layout &L, const Basis &b, char *ws, const double *
                            L.pcap);
         copies = 1;
     }
-    hipLaunchKernelGGL(k_finish, dim3((unsigned)((n2 + 256 * kFinishPer - 1) / (256 * kFinishPer))), dim3(256), 0, st,
-                       hdr, F, (const double *)a.jcol, copies, L.pcap, (const int *)(ws + L.bucket_of), dens, a.n,
-                       fock, (double *)(ws + L.e2part), e2);
+    double *part = (double *)(ws + L.e2part);
+    const int *posof = (const int *)(ws + L.bucket_of);
+    if (n2 <= 1024 * kFinishPer) {
+        hipLaunchKernelGGL((k_finish<1024>), dim3(1), dim3(1024), 0, st, F, (const double *)a.jcol, copies, L.pcap, posof,
+                           dens, a.n, fock, part, e2);
+    } else {
+        const unsigned nb = (unsigned)((n2 + 256 * kFinishPer - 1) / (256 * kFinishPer));
+        hipLaunchKernelGGL((k_finish<256>), dim3(nb), dim3(256), 0, st, F, (const double *)a.jcol, copies, L.pcap, posof,
+                           dens, a.n, fock, part, e2);
+        hipLaunchKernelGGL(k_energy, dim3(1), dim3(256), 0, st, (const double *)part, (int)nb, e2);
+    }
     return hipGetLastError();
 }
 

@@ -113,10 +113,9 @@ void k_grad(GradArgs a)
     // the Boys table first (16-byte aligned rows), then the gradient partials
     R *tHG = (R *)smem;
     double *lg = (double *)(tHG + BG::table_len);   // [n*3]
-    const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
+    const int tid = threadIdx.x, wave = uniform(tid / kWave), lane = tid % kWave;
     const int gid = blockIdx.x;
-    const long long M = a.hdr->items;
-    const int S = a.hdr->sig_pairs;
+    const int S = ((cptr<DevHeader>)a.hdr)->sig_pairs;
     const BasisDev *bd = a.bd;
     __shared__ int wperm[kWavesPerGroup][kWaveKets];
     __shared__ long long blk_at;
@@ -126,33 +125,27 @@ void k_grad(GradArgs a)
 
     double eacc = 0.0;
     // blocks (bra group, ket block K, bra) fetched from a global counter until exhausted
-    const long long NB = a.hdr->blocks;
-    (void)M;
+    const long long NB = ((cptr<DevHeader>)a.hdr)->blocks;
+    const cptr<long long> goff = (cptr<long long>)a.goff, item_off = (cptr<long long>)a.item_off;
     for (;;) {
     __syncthreads();
     if (tid == 0) blk_at = (long long)atomicAdd(a.next_block, 1ULL);
     __syncthreads();
-    if (blk_at >= NB) break;
+    const long long got = uniform(blk_at);
+    if (got >= NB) break;
     // taken from the end of the numbering: the bras are in Q-bucket order with kets t <= s,
     // so the last blocks hold the most kets; starting with them leaves the small ones for
     // the tail (he128: -1.2% FP64 and -3.3% mixed kernel time; the forward kernel keeps the
     // forward order, where the reverse measured 0.2% slower at 512 atoms)
-    const long long blk = NB - 1 - blk_at;
+    const long long blk = NB - 1 - got;
     {
         int s;
         long long m0, m1;
         {
-            // group: the last g with goff[g] <= blk; within it K-major over the group's bras
-            int64_t lo = 0, hi = a.ngroups - 1;
-            while (lo < hi) {
-                const int64_t mid = (lo + hi + 1) >> 1;
-                if (a.goff[mid] <= blk) lo = mid; else hi = mid - 1;
-            }
-            const long long local = blk - a.goff[lo];
-            s = (int)((lo << a.gshift) + (local & ((1LL << a.gshift) - 1)));
-            if (s >= S) continue;
-            const long long i1 = a.item_off[s + 1];
-            m0 = a.item_off[s] + (local >> a.gshift) * a.tile;
+            int kb;
+            block_bra(goff, a.ngroups, a.gshift, S, blk, s, kb);
+            const long long i1 = item_off[s + 1];
+            m0 = item_off[s] + (long long)kb * a.tile;
             if (m0 >= i1) continue;
             m1 = m0 + a.tile < i1 ? m0 + a.tile : i1;
         }
@@ -166,7 +159,7 @@ void k_grad(GradArgs a)
         double gA[3] = {0, 0, 0}, gB[3] = {0, 0, 0};
         for (long long m = m0; m <= m1; ++m) {
             if (m < m1) {
-                while (a.item_off[s + 1] <= m) ++s;
+                while (item_off[s + 1] <= m) ++s;
             }
             if (m == m1 || s != cur) {
                 if (cur >= 0) {
@@ -182,16 +175,17 @@ void k_grad(GradArgs a)
                 }
                 if (m == m1) break;
                 cur = s;
-                bi = a.pk[s];
-                bj = a.pl[s];
-                qs = a.pq[s];
-                ds = a.pd[s];
-                lim = a.lim[s];
+                // scalar loads: the bra's data stays in scalar registers
+                bi = ((cptr<int>)a.pk)[s];
+                bj = ((cptr<int>)a.pl)[s];
+                qs = ((cptr<double>)a.pq)[s];
+                ds = ((cptr<double>)a.pd)[s];
+                lim = ((cptr<int>)a.lim)[s];
                 ebra = lane < G2 ? (int)a.bexp[(int64_t)lane * a.pcap + s] : kTermNone;
             }
-            const long long wbase = (m - a.item_off[s]) * kItemKets + (long long)wave * kWaveKets;
+            const long long wbase = (m - item_off[s]) * kItemKets + (long long)wave * kWaveKets;
             if (wbase >= lim) continue;
-            const cptr<int> kexp = (cptr<int>)(a.kexp + __builtin_amdgcn_readfirstlane((int)(wbase / kWaveKets)) * G2);
+            const cptr<int> kexp = (cptr<int>)(a.kexp + (int)(wbase / kWaveKets) * G2);
             int *perm = wperm[wave];
             const int nvalid = pack_kets(wbase, lane, perm,
                                          [&](long long t) { return t < lim && qs * a.pq[t] >= a.tau; });
@@ -377,7 +371,7 @@ void k_grad(GradArgs a)
                         gam = deg * (4.0 * (xs * dt + ds * xt) - (Xi[k] * Dj[l] + Di[k] * Xj[l]) -
                                      (Xi[l] * Dj[k] + Di[l] * Xj[k]));
                     }
-                    const double *xa = a.xyz + 3 * bi, *xb = a.xyz + 3 * bj;
+                    const cptr<double> xa = (cptr<double>)a.xyz + 3 * bi, xb = (cptr<double>)a.xyz + 3 * bj;
                     const double *xc = a.xyz + 3 * k, *xd = a.xyz + 3 * l;
 #pragma unroll
                     for (int c = 0; c < 3; ++c) {

@@ -129,7 +129,7 @@ struct DevHeader {
     int tile;                       // launch shape of the last build (for the stats)
     int group_bras;
     int ket_copies;
-    unsigned done_blocks;           // workgroups of the final kernel that have written their partial sums
+    int pad1;
     // batched block table: owned-molecule blocks, shared blocks, items per shared block
     long long bt_own;
     long long bt_sh;
@@ -181,7 +181,8 @@ struct Layout {
     int gshift;                 // log2 of the bras per group (tuned)
     int kcopies;                // ket-side Coulomb vectors requested (0: one per workgroup)
     bool private_ok;            // per-workgroup copies of F fit the memory budget
-    int sub;                    // 64-ket chunks per wave of an item (items of 256 sub kets)
+    int sub;                    // 64-ket chunks per wave of an item (1 or kSubChunks)
+    int nsplit;                 // forward: waves that share a chunk's bra primitive pairs (1 or kWavesPerGroup)
     size_t hdr, basis;
     size_t q_unsorted, bucket_of, bucket_cnt, bucket_off, bucket_cur;
     size_t pk, pl, pq, pd;                 // sorted pair tables
@@ -210,6 +211,9 @@ struct Layout {
     size_t total;
     size_t static_bytes;                   // total less the term screen's tables (size rule of the allocation-free call)
 };
+
+// Kets of an item: every wave's chunks, or one wave's if all share them.
+inline int item_kets(const Layout &L) { return (L.nsplit > 1 ? 1 : kWavesPerGroup) * kWave * L.sub; }
 
 // compact: the layout of the allocation-free call (one F for the atomics strategy, at most
 // kCompactKetCopies shared ket vectors).

@@ -99,7 +99,6 @@ __global__ __launch_bounds__(256) void k_prep_begin(Basis b, BasisDev *__restric
         hdr->quartets = 0;
         hdr->max_bucket = 0;
         hdr->next_block = 0;
-        hdr->done_blocks = 0;
         hdr->centroid[0] = red[0][0] / (double)n;
         hdr->centroid[1] = red[1][0] / (double)n;
         hdr->centroid[2] = red[2][0] / (double)n;
@@ -128,6 +127,20 @@ hipError_t launch_prep_begin(const Basis &b, BasisDev *bd, DevHeader *hdr, int64
 
 // ------------------------------------------------------------------ pairs
 
+// Morton index of the cell holding point c inside the bounding box.
+__device__ inline int morton_cell(const double *c, const DevHeader *__restrict__ hdr)
+{
+    constexpr int side = 1 << kCellBits;
+    int code = 0;
+    for (int d = 0; d < 3; ++d) {
+        const double ext = hdr->bmax[d] - hdr->bmin[d];
+        int u = ext > 0.0 ? (int)((c[d] - hdr->bmin[d]) / ext * side) : 0;
+        u = u < 0 ? 0 : (u >= side ? side - 1 : u);
+        for (int b = 0; b < kCellBits; ++b) code |= ((u >> b) & 1) << (3 * b + d);
+    }
+    return code;
+}
+
 // Schwarz bound of every pair i >= j: Q_ij = sqrt((ij|ij)) in FP64, TP lanes per pair.  All
 // primitive centres lie on the line A-B, P_ab - P_cd = (fb_ab - fb_cd) (B - A), and the matrix
 // (ab|cd) is symmetric, so the lanes share the g2 (g2 + 1) / 2 unordered primitive quartets,
@@ -136,9 +149,11 @@ hipError_t launch_prep_begin(const Basis &b, BasisDev *bd, DevHeader *hdr, int64
 // however few pairs there are.  With one basis on every atom a pair whose bound
 // U = sum |S_ab| p^(1/4) >= Q, times the largest U of any pair (the one at distance zero), is
 // below tau can never be significant: its Q is left at zero (most pairs of a sparse system).
+// Also the pair's bucket (Q band, spatial cell of its centre).
 template <int TP>
 __global__ __launch_bounds__(256) void k_pair_q(Basis b, DevHeader *__restrict__ hdr, int64_t n, double tau,
-                                                const double *__restrict__ xyz, double *__restrict__ qout)
+                                                const double *__restrict__ xyz, double *__restrict__ qout,
+                                                int *__restrict__ bucket)
 {
     constexpr int PB = 256 / TP;
     extern __shared__ __attribute__((aligned(16))) double sm[];
@@ -149,8 +164,8 @@ __global__ __launch_bounds__(256) void k_pair_q(Basis b, DevHeader *__restrict__
     const int64_t p = (int64_t)blockIdx.x * PB + pb;
     const bool live = p < npair;
     double r2 = 0.0, u = 0.0, u0 = 0.0;
+    int64_t i = 0, j = 0;
     if (live) {
-        int64_t i, j;
         pair_of_index(p, i, j);
         const double dx = xyz[3 * i] - xyz[3 * j], dy = xyz[3 * i + 1] - xyz[3 * j + 1],
                      dz = xyz[3 * i + 2] - xyz[3 * j + 2];
@@ -192,7 +207,12 @@ __global__ __launch_bounds__(256) void k_pair_q(Basis b, DevHeader *__restrict__
 #pragma unroll
     for (int w = TP / 2; w > 0; w >>= 1) s += __shfl_xor(s, w, TP);
     const double q = sqrt(s);
-    if (live && l == 0) qout[p] = q;
+    if (live && l == 0) {
+        qout[p] = q;
+        const double c[3] = {0.5 * (xyz[3 * i] + xyz[3 * j]), 0.5 * (xyz[3 * i + 1] + xyz[3 * j + 1]),
+                             0.5 * (xyz[3 * i + 2] + xyz[3 * j + 2])};
+        bucket[p] = q_band(q) * kNumCells + morton_cell(c, hdr);
+    }
     // block max, then one atomic per block (positive doubles order like their bit patterns)
     red[threadIdx.x] = live ? q : 0.0;
     __syncthreads();
@@ -206,48 +226,27 @@ __global__ __launch_bounds__(256) void k_pair_q(Basis b, DevHeader *__restrict__
 
 template <int TP>
 static void launch_pair_q(const Basis &b, DevHeader *hdr, int64_t n, double tau, const double *xyz, double *q,
-                          hipStream_t st)
+                          int *bucket, hipStream_t st)
 {
     constexpr int PB = 256 / TP;
     const int64_t np = n * (n + 1) / 2;
     hipLaunchKernelGGL((k_pair_q<TP>), dim3((unsigned)((np + PB - 1) / PB)), dim3(256),
-                       sizeof(double) * 3 * (size_t)b.g2 * PB, st, b, hdr, n, tau, xyz, q);
+                       sizeof(double) * 3 * (size_t)b.g2 * PB, st, b, hdr, n, tau, xyz, q, bucket);
 }
 
-// Morton index of the cell holding point c inside the bounding box.
-__device__ inline int morton_cell(const double *c, const DevHeader *__restrict__ hdr)
-{
-    constexpr int side = 1 << kCellBits;
-    int code = 0;
-    for (int d = 0; d < 3; ++d) {
-        const double ext = hdr->bmax[d] - hdr->bmin[d];
-        int u = ext > 0.0 ? (int)((c[d] - hdr->bmin[d]) / ext * side) : 0;
-        u = u < 0 ? 0 : (u >= side ? side - 1 : u);
-        for (int b = 0; b < kCellBits; ++b) code |= ((u >> b) & 1) << (3 * b + d);
-    }
-    return code;
-}
-
-__global__ __launch_bounds__(256) void k_bucket_count(int64_t n, double tau, const DevHeader *__restrict__ hdr,
-                                                      const double *__restrict__ xyz,
+// Counts the significant pairs of every bucket; the others' bucket becomes -1.
+__global__ __launch_bounds__(256) void k_bucket_count(int64_t npair, double tau, const DevHeader *__restrict__ hdr,
                                                       const double *__restrict__ q, int *__restrict__ bucket_of,
                                                       long long *__restrict__ cnt)
 {
-    const int64_t npair = n * (n + 1) / 2;
     const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= npair) return;
     const double qmax = __longlong_as_double((long long)hdr->qmax_bits);
     const double qp = q[p];
-    int b = -1;
-    if (qp * qmax >= tau && qp > 0.0) {
-        int64_t i, j;
-        pair_of_index(p, i, j);
-        const double c[3] = {0.5 * (xyz[3 * i] + xyz[3 * j]), 0.5 * (xyz[3 * i + 1] + xyz[3 * j + 1]),
-                             0.5 * (xyz[3 * i + 2] + xyz[3 * j + 2])};
-        b = q_band(qp) * kNumCells + morton_cell(c, hdr);
-        atomicAdd((unsigned long long *)&cnt[b], 1ULL);
-    }
-    bucket_of[p] = b;
+    if (qp * qmax >= tau && qp > 0.0)
+        atomicAdd((unsigned long long *)&cnt[bucket_of[p]], 1ULL);
+    else
+        bucket_of[p] = -1;
 }
 
 // Bucket offsets -> cursors (int) and the significant-pair total.
@@ -412,7 +411,6 @@ __global__ __launch_bounds__(256) void k_new_density(DevHeader *__restrict__ hdr
     const int64_t at = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, step = (int64_t)gridDim.x * blockDim.x;
     if (at == 0) {
         hdr->next_block = 0;
-        hdr->done_blocks = 0;
     }
     const int S = hdr->sig_pairs;
     for (int64_t x = at; x < nf; x += step) fzero[x] = 0.0;
@@ -455,8 +453,7 @@ __device__ inline long long block_scan_1024(long long v, long long *__restrict__
 }
 
 __global__ __launch_bounds__(kSmallThreads) void k_order_small(
-    DevHeader *__restrict__ hdr, int64_t n, double tau, int64_t pcap, const double *__restrict__ xyz,
-    const double *__restrict__ q, int *__restrict__ posof, int *__restrict__ slot, int item_kets, int gshift, int tile,
+    DevHeader *__restrict__ hdr, int64_t n, double tau, const double *__restrict__ q, int *__restrict__ posof, int *__restrict__ slot, int item_kets, int gshift, int tile,
     int64_t ngroups, int *__restrict__ lims, long long *__restrict__ item_off, long long *__restrict__ goff)
 {
     __shared__ int hist[kSmallBuckets];
@@ -476,12 +473,8 @@ __global__ __launch_bounds__(kSmallThreads) void k_order_small(
         bk[r] = -1;
         if (p < npair) {
             const double qp = q[p];
+            const int b = posof[p], band = b / kNumCells, cell = b % kNumCells / (kNumCells / kSmallCells);
             if (qp * qmax >= tau && qp > 0.0) {
-                int64_t i, j;
-                pair_of_index(p, i, j);
-                const double c[3] = {0.5 * (xyz[3 * i] + xyz[3 * j]), 0.5 * (xyz[3 * i + 1] + xyz[3 * j + 1]),
-                                     0.5 * (xyz[3 * i + 2] + xyz[3 * j + 2])};
-                const int band = q_band(qp), cell = morton_cell(c, hdr) / (kNumCells / kSmallCells);
                 bk[r] = (band < kSmallBands - 1 ? band : kSmallBands - 1) * kSmallCells + cell;
                 atomicAdd(&hist[bk[r]], 1);
             } else {
@@ -549,7 +542,8 @@ __global__ __launch_bounds__(kSmallThreads) void k_order_small(
         long long nb = 0;
         for (int64_t x = 0; x < ngroups; ++x) {
             goff[x] = nb;
-            nb += (long long)gmax[x] << gshift;
+            const long long left = S - (x << gshift), gb = 1LL << gshift;
+            nb += gmax[x] * (left < 0 ? 0 : (left < gb ? left : gb));
         }
         goff[ngroups] = nb;
         hdr->sig_pairs = S;
@@ -905,8 +899,9 @@ hipError_t launch_dens_check_batched(DevHeader *hdr, int64_t nmol, const long lo
     return hipGetLastError();
 }
 
-// Blocks of every bra group: 2^gshift x the largest block count of its bras (bras with
-// fewer blocks leave empty slots, skipped by the kernels).
+// Blocks of every bra group: its bras (2^gshift, or what is left in the last one) times the
+// largest block count among them (bras with fewer blocks leave empty slots, skipped by the
+// kernels).
 // One workgroup per group of bras: the largest block count of its bras (a block-wide max).
 __global__ __launch_bounds__(256) void k_group_blocks(const DevHeader *__restrict__ hdr,
                                                       const long long *__restrict__ nitems, int64_t ngroups,
@@ -928,7 +923,7 @@ __global__ __launch_bounds__(256) void k_group_blocks(const DevHeader *__restric
         if (tid < w) red[tid] = red[tid + w] > red[tid] ? red[tid + w] : red[tid];
         __syncthreads();
     }
-    if (tid == 0) gcnt[g] = red[0] * gb;
+    if (tid == 0) gcnt[g] = red[0] * (S - g * gb < gb ? S - g * gb : gb);
 }
 
 hipError_t launch_pairs(const Layout &L, const Basis &b, char *ws, const double *xyz, const double *dens,
@@ -945,26 +940,24 @@ hipError_t launch_pairs(const Layout &L, const Basis &b, char *ws, const double 
     double *q = (double *)(ws + L.q_unsorted);
     int *posof = (int *)(ws + L.bucket_of);
     const bool small = np <= kSmallPairs && !plan.fixed_order;
-    const int item_kets = kWavesPerGroup * kWave * L.sub;
+    const int ikets = item_kets(L);
     hipError_t e = launch_prep_begin(b, bd, hdr, L.n, xyz, plan.info, plan.fzero, plan.nf, cnt,
                                      small ? 0 : (int64_t)kNumBuckets, st);
     if (e != hipSuccess) return e;
     // lanes per pair: about three primitive quartets each
     switch (b.g) {
-    case 1: launch_pair_q<1>(b, hdr, L.n, tau, xyz, q, st); break;
-    case 2: launch_pair_q<4>(b, hdr, L.n, tau, xyz, q, st); break;
-    case 3: launch_pair_q<16>(b, hdr, L.n, tau, xyz, q, st); break;
-    default: launch_pair_q<64>(b, hdr, L.n, tau, xyz, q, st); break;
+    case 1: launch_pair_q<1>(b, hdr, L.n, tau, xyz, q, posof, st); break;
+    case 2: launch_pair_q<4>(b, hdr, L.n, tau, xyz, q, posof, st); break;
+    case 3: launch_pair_q<16>(b, hdr, L.n, tau, xyz, q, posof, st); break;
+    default: launch_pair_q<64>(b, hdr, L.n, tau, xyz, q, posof, st); break;
     }
     // the pair of every position (the item counts' storage is free until the limits are computed)
     int *slot = (int *)(ws + L.nitems);
     if (small) {
-        hipLaunchKernelGGL(k_order_small, dim3(1), dim3(kSmallThreads), 0, st, hdr, L.n, tau, L.pcap, xyz,
-                           (const double *)q, posof, slot, item_kets, L.gshift, L.tile, L.ngroups,
+        hipLaunchKernelGGL(k_order_small, dim3(1), dim3(kSmallThreads), 0, st, hdr, L.n, tau, (const double *)q, posof, slot, ikets, L.gshift, L.tile, L.ngroups,
                            (int *)(ws + L.lim), (long long *)(ws + L.item_off), (long long *)(ws + L.goff));
     } else {
-        hipLaunchKernelGGL(k_bucket_count, dim3(nbp), dim3(bs), 0, st, L.n, tau, hdr, xyz, (const double *)q, posof,
-                           cnt);
+        hipLaunchKernelGGL(k_bucket_count, dim3(nbp), dim3(bs), 0, st, np, tau, hdr, (const double *)q, posof, cnt);
         e = launch_scan(cnt, kNumBuckets, off, (long long *)(ws + L.scan_tmp), nullptr, st);
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL(k_bucket_cursors, dim3((kNumBuckets + 255) / 256), dim3(256), 0, st, off, cur, hdr);
@@ -1020,7 +1013,7 @@ hipError_t launch_pairs(const Layout &L, const Basis &b, char *ws, const double 
     if (small) return hipGetLastError();
     hipLaunchKernelGGL(k_limits, dim3((unsigned)((L.pcap + 255) / 256)), dim3(256), 0, st, hdr, tau,
                        (const double *)(ws + L.pq), off, (long long *)(ws + L.nitems), (int *)(ws + L.lim),
-                       L.pcap, item_kets);
+                       L.pcap, ikets);
     e = launch_scan((const long long *)(ws + L.nitems), L.pcap, (long long *)(ws + L.item_off),
                     (long long *)(ws + L.scan_tmp), &hdr->items, st);
     if (e != hipSuccess) return e;
