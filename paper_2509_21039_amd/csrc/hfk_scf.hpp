@@ -11,7 +11,7 @@ constexpr int kDiisMax = 8;   // Fock matrices kept for the DIIS extrapolation
 struct ScfLayout {
     size_t S, H, X, F, G, Fx, A, C, T1, T2;   // n x n FP64 (column-major where it matters)
     size_t eps, evw;                          // [n] eigenvalues, [n] eigensolver scratch
-    size_t info, scal;                        // eigensolver status; device scalars (E_nn, E2, |err|max)
+    size_t info, scal;                        // eigensolver status; device scalars (E_nn, E2, |err|max, DIIS row)
     size_t Z;                                 // [n] nuclear charges
     size_t diisF, diisE;                      // [kDiisMax][n*n]
     size_t rocws;                             // linear-algebra library scratch
