@@ -259,6 +259,7 @@ struct BatchedConfig {
     int block_items;        // 0 = automatic
     long long owned_bound;  // -1 = no owned molecules
     int waves;              // waves per workgroup: 4 or 8
+    bool automatic = false; // neither tuned nor set: waves and gpc follow the kernel's occupancy
 };
 
 // Size bucket of the tuning table: ceil(log2 n).
@@ -399,6 +400,7 @@ static void set_items(Layout &L, int strat, int variant, int precision)
 static BatchedConfig pick_batched_config(int32_t precision)
 {
     BatchedConfig c = default_batched_config();
+    c.automatic = g_cfg_b.gpc <= 0 && g_cfg_b.waves <= 0;
     if (g_force_b) return *g_force_b;
     {
         const std::string arch = device_arch();
@@ -1117,7 +1119,19 @@ static hfk_status fock_batched_impl(bool atoms, int64_t nmol, const int64_t *ato
                         "the molecules outside the tolerance: %.3e, tolerance %.3e)",
                         h.dchk_mol, bits_to_double(h.dchk_ratio), g_debug_tol);
     }
-    const BatchedConfig bc = pick_batched_config(precision);
+    BatchedConfig bc = pick_batched_config(precision);
+    if (bc.automatic) {
+        // four-wave workgroups where more waves fit on a CU that way: the FP64 gradient's register
+        // count allows three waves per SIMD, one eight-wave workgroup (300 clusters of up to 40
+        // atoms: 4.4 ms against 5.7)
+        const bool gr = d_xyz != nullptr;
+        const int f4 = batched_resident_groups(ngauss, precision, gr, atoms, L.nmax, 4);
+        const int f8 = batched_resident_groups(ngauss, precision, gr, atoms, L.nmax, 8);
+        if (4 * (f4 < kMaxBatchGroupsPerCU ? f4 : kMaxBatchGroupsPerCU) > 8 * (f8 < bc.gpc ? f8 : bc.gpc)) {
+            bc.waves = 4;
+            bc.gpc = kMaxBatchGroupsPerCU;
+        }
+    }
     int gpc = bc.gpc;
     {
         const int fit = batched_resident_groups(ngauss, precision, d_xyz != nullptr, atoms, L.nmax, bc.waves);
@@ -1127,8 +1141,6 @@ static hfk_status fock_batched_impl(bool atoms, int64_t nmol, const int64_t *ato
     e = launch_batched(L, b, ws, atom_off_host, xyz, dens_packed, tau, precision, fock_packed, e2, d_xyz, cus * gpc,
                        shape, st);
     if (e != hipSuccess) return hip_fail(e, "batched launch");
-    e = launch_header_info(ws + L.hdr, 0, cus * gpc, precision, -1, st, -1, 0, 0);
-    if (e != hipSuccess) return hip_fail(e, "header launch");
     note_last(workspace, stream);
     return HFK_OK;
 }

@@ -45,7 +45,7 @@ struct BArgs {
     const double *kfa;
     const long long *item_off;
     const int *lim;
-    const short *bexp;      // [pcap][g2] term exponents of the bras
+    const short *bexp;      // [g2][pcap] term exponents of the bras
     const int *kexp;        // [64 kets][g2] maxima of the kets' exponents
     int tlim;               // term_limit(tau)
     const int *klo;
@@ -104,66 +104,83 @@ __device__ inline int mol_of(const long long *__restrict__ off, int nmol, long l
 
 // ------------------------------------------------------------------ pair preparation
 
-__global__ void k_b_mol(int nmol, const int *__restrict__ nm, const long long *__restrict__ aoff,
-                        const double *__restrict__ xyz, double *__restrict__ cent, unsigned long long *__restrict__ qmax)
+// Centroid of every molecule, one wave each.
+__global__ __launch_bounds__(256) void k_b_mol(int nmol, const int *__restrict__ nm, const long long *__restrict__ aoff,
+                                               const double *__restrict__ xyz, double *__restrict__ cent,
+                                               unsigned long long *__restrict__ qmax)
 {
-    const int m = blockIdx.x * blockDim.x + threadIdx.x;
-    if (m >= nmol) return;
+    const int m = (int)((blockIdx.x * blockDim.x + threadIdx.x) / kWave), lane = threadIdx.x % kWave;
+    if (m >= nmol) return;   // a whole wave
     double c[3] = {0, 0, 0};
-    for (int i = 0; i < nm[m]; ++i)
+    for (int i = lane; i < nm[m]; i += kWave)
         for (int d = 0; d < 3; ++d) c[d] += xyz[3 * (aoff[m] + i) + d];
-    for (int d = 0; d < 3; ++d) cent[3 * m + d] = c[d] / nm[m];
-    qmax[m] = 0;
+    for (int d = 0; d < 3; ++d) {
+        const double s = wave_sum(c[d]);
+        if (lane == 0) cent[3 * m + d] = s / nm[m];
+    }
+    if (lane == 0) qmax[m] = 0;
 }
 
-__global__ __launch_bounds__(256) void k_b_pair_q(Basis b, const BasisDev *__restrict__ bd, int nmol,
-                                                  const long long *__restrict__ poff,
-                                                  const long long *__restrict__ aoff,
-                                                  const double *__restrict__ cent, const double *__restrict__ xyz,
-                                                  long long ptot, double *__restrict__ qout,
+// Schwarz bounds, TP lanes per pair, as in the single-molecule preparation: the primitive
+// centres of a pair lie on the line A-B, and the lanes share its unordered primitive quartets.
+// (One thread per pair took 56 us for 64 small molecules and 1.1 ms for 500 clusters.)
+template <int TP>
+__global__ __launch_bounds__(256) void k_b_pair_q(Basis b, int nmol, const long long *__restrict__ poff,
+                                                  const long long *__restrict__ aoff, const double *__restrict__ xyz,
+                                                  long long ptot, double *__restrict__ qout, int *__restrict__ mol,
                                                   unsigned long long *__restrict__ qmax)
 {
-    const long long p = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= ptot) return;
-    const int m = mol_of(poff, nmol, p);
-    int64_t i, j;
-    pair_of_index(p - poff[m], i, j);
-    const double *c = cent + 3 * m;
-    const double *xa = xyz + 3 * (aoff[m] + i), *xb = xyz + 3 * (aoff[m] + j);
-    double A[3] = {xa[0] - c[0], xa[1] - c[1], xa[2] - c[2]};
-    double B[3] = {xb[0] - c[0], xb[1] - c[1], xb[2] - c[2]};
-    double px[kMaxG2], py[kMaxG2], pz[kMaxG2], ps[kMaxG2], pp[kMaxG2];
-    double s = 0.0;
-    if (b.aexp) {
-        pair_prims_atoms(b, aoff[m] + i, aoff[m] + j, A, B, px, py, pz, ps, pp);
-        for (int ab = 0; ab < b.g2; ++ab)
-            for (int cd = 0; cd < b.g2; ++cd) {
-                const double dx = px[ab] - px[cd], dy = py[ab] - py[cd], dz = pz[ab] - pz[cd];
-                const double rho = pp[ab] * pp[cd] / (pp[ab] + pp[cd]);
-                s += ps[ab] * ps[cd] * sqrt(rho) * erf_over_sqrt(rho * (dx * dx + dy * dy + dz * dz));
-            }
-    } else {
-        pair_prims(b, bd, A, B, px, py, pz, ps);
-        for (int ab = 0; ab < b.g2; ++ab)
-            for (int cd = 0; cd < b.g2; ++cd) {
-                const double dx = px[ab] - px[cd], dy = py[ab] - py[cd], dz = pz[ab] - pz[cd];
-                s += ps[ab] * ps[cd] * bd->srho[ab * b.g2 + cd] *
-                     erf_over_sqrt(bd->rho[ab * b.g2 + cd] * (dx * dx + dy * dy + dz * dz));
-            }
+    constexpr int PB = 256 / TP;
+    extern __shared__ __attribute__((aligned(16))) double sm[];
+    const int l = threadIdx.x % TP, pb = threadIdx.x / TP;
+    double *tab = sm + (size_t)pb * 3 * b.g2;
+    const long long p = (long long)blockIdx.x * PB + pb;
+    const bool live = p < ptot;
+    int m = 0;
+    double r2 = 0.0;
+    if (live) {
+        m = mol_of(poff, nmol, p);
+        int64_t i, j;
+        pair_of_index(p - poff[m], i, j);
+        i += aoff[m];
+        j += aoff[m];
+        const double dx = xyz[3 * i] - xyz[3 * j], dy = xyz[3 * i + 1] - xyz[3 * j + 1],
+                     dz = xyz[3 * i + 2] - xyz[3 * j + 2];
+        r2 = dx * dx + dy * dy + dz * dz;
+        for (int ab = l; ab < b.g2; ab += TP) pair_q_entry(b, i, j, ab, r2, tab);
     }
-    const double q = sqrt(s);
-    qout[p] = q;
-    atomicMax(&qmax[m], (unsigned long long)__double_as_longlong(q));
+    __syncthreads();
+    double s = live ? pair_q_sum(b.g2, r2, l, TP, tab) : 0.0;
+#pragma unroll
+    for (int w = TP / 2; w > 0; w >>= 1) s += __shfl_xor(s, w, TP);
+    if (live && l == 0) {
+        const double q = sqrt(s);
+        qout[p] = q;
+        mol[p] = m;
+        // most pairs are below the largest one met so far
+        const unsigned long long bits = (unsigned long long)__double_as_longlong(q);
+        if (bits > __hip_atomic_load(&qmax[m], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(&qmax[m], bits);
+    }
 }
 
-__global__ __launch_bounds__(256) void k_b_bucket_count(int nmol, const long long *__restrict__ poff, long long ptot,
-                                                        double tau, const unsigned long long *__restrict__ qmax,
+template <int TP>
+static void launch_b_pair_q(const Basis &b, int nmol, const long long *poff, const long long *aoff, const double *xyz,
+                            long long ptot, double *q, int *mol, unsigned long long *qmax, hipStream_t st)
+{
+    constexpr int PB = 256 / TP;
+    hipLaunchKernelGGL((k_b_pair_q<TP>), dim3((unsigned)((ptot + PB - 1) / PB)), dim3(256),
+                       sizeof(double) * 3 * (size_t)b.g2 * PB, st, b, nmol, poff, aoff, xyz, ptot, q, mol, qmax);
+}
+
+// bucket_of holds the pair's molecule; it becomes its (molecule, band) bucket, or -1.
+__global__ __launch_bounds__(256) void k_b_bucket_count(long long ptot, double tau,
+                                                        const unsigned long long *__restrict__ qmax,
                                                         const double *__restrict__ q, int *__restrict__ bucket_of,
                                                         long long *__restrict__ cnt)
 {
     const long long p = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= ptot) return;
-    const int m = mol_of(poff, nmol, p);
+    const int m = bucket_of[p];
     const double qm = __longlong_as_double((long long)qmax[m]);
     const double qp = q[p];
     int bk = -1;
@@ -185,104 +202,115 @@ __global__ __launch_bounds__(256) void k_b_cursors(const long long *__restrict__
     }
 }
 
-__global__ __launch_bounds__(256) void k_b_pair_scatter(
-    Basis b, const BasisDev *__restrict__ bd, int nmol, const long long *__restrict__ poff,
-    const long long *__restrict__ aoff, const long long *__restrict__ doff, const int *__restrict__ nm,
-    const double *__restrict__ cent, const double *__restrict__ xyz, const double *__restrict__ dens, long long ptot,
-    int64_t pcap, const double *__restrict__ q, const int *__restrict__ bucket_of, int *__restrict__ cur,
-    int *__restrict__ pk, int *__restrict__ pl, int *__restrict__ pm, double *__restrict__ pq, double *__restrict__ pd,
-    double *__restrict__ prim, float *__restrict__ prim_f, double *__restrict__ bra, float *__restrict__ bra_f,
-    double *__restrict__ bip, float *__restrict__ bip_f, double *__restrict__ kmu, double *__restrict__ kfa,
-    short *__restrict__ bexp, bool grad)
+// Position of every significant pair (order within a bucket as the cursor hands out places).
+__global__ __launch_bounds__(256) void k_b_slot(long long ptot, const int *__restrict__ bucket_of,
+                                                int *__restrict__ cur, int *__restrict__ slot, int *__restrict__ pm)
 {
     const long long p = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= ptot) return;
     const int bk = bucket_of[p];
     if (bk < 0) return;
     const int pos = atomicAdd(&cur[bk], 1);
-    const int m = bk / kNumBands;
-    int64_t i, j;
-    pair_of_index(p - poff[m], i, j);
-    const double *c = cent + 3 * m;
-    const double *xa = xyz + 3 * (aoff[m] + i), *xb = xyz + 3 * (aoff[m] + j);
-    double A[3] = {xa[0] - c[0], xa[1] - c[1], xa[2] - c[2]};
-    double B[3] = {xb[0] - c[0], xb[1] - c[1], xb[2] - c[2]};
-    double px[kMaxG2], py[kMaxG2], pz[kMaxG2], ps[kMaxG2], pp[kMaxG2], mu[kMaxG2], fa[kMaxG2];
-    if (b.aexp)
-        pair_prims_atoms(b, aoff[m] + i, aoff[m] + j, A, B, px, py, pz, ps, pp, mu, fa);
-    else
-        pair_prims(b, bd, A, B, px, py, pz, ps);
-    pk[pos] = (int)i;
-    pl[pos] = (int)j;
-    pm[pos] = m;
-    pq[pos] = q[p];
-    pd[pos] = dens[doff[m] + i * nm[m] + j];
-    const int g2 = b.g2;
-    for (int ab = 0; ab < g2; ++ab) {
-        prim[(0 * g2 + ab) * pcap + pos] = px[ab];
-        prim[(1 * g2 + ab) * pcap + pos] = py[ab];
-        prim[(2 * g2 + ab) * pcap + pos] = pz[ab];
-        prim[(3 * g2 + ab) * pcap + pos] = ps[ab];
-        prim_f[(0 * g2 + ab) * pcap + pos] = (float)px[ab];
-        prim_f[(1 * g2 + ab) * pcap + pos] = (float)py[ab];
-        prim_f[(2 * g2 + ab) * pcap + pos] = (float)pz[ab];
-        prim_f[(3 * g2 + ab) * pcap + pos] = (float)ps[ab];
-        // bra row: centre, charge and the charge weighted by mu and by the fractions
-        // fa = a/p, fb = b/p of the primitive pair (the gradient's bra weights)
-        double *ba = bra + ((int64_t)pos * g2 + ab) * kBBra;
-        float *bf = bra_f + ((int64_t)pos * g2 + ab) * kBBra;
-        const double m_ab = b.aexp ? mu[ab] : bd->mu[ab];
-        const double fa_ab = b.aexp ? fa[ab] : bd->fa[ab];
-        const double fb_ab = b.aexp ? 1.0 - fa[ab] : bd->fb[ab];
-        const double row[kBBra] = {px[ab], py[ab], pz[ab], ps[ab], m_ab * ps[ab], fa_ab * ps[ab], fb_ab * ps[ab],
-                                   fa_ab * fb_ab * ps[ab], fb_ab * fb_ab * ps[ab], 0.0, 0.0, 0.0};
-        for (int c = 0; c < kBBra; ++c) {
-            ba[c] = row[c];
-            bf[c] = (float)row[c];
-        }
-    }
-    {
-        // exponents of the term screen
-        const double r = sqrt((A[0] - B[0]) * (A[0] - B[0]) + (A[1] - B[1]) * (A[1] - B[1]) +
-                              (A[2] - B[2]) * (A[2] - B[2]));
-        for (int ab = 0; ab < g2; ++ab)
-            bexp[(int64_t)pos * g2 + ab] =
-                term_exponent(term_bound(ps[ab], b.aexp ? pp[ab] : bd->p[ab], b.aexp ? mu[ab] : bd->mu[ab], r, grad));
-    }
-    if (bip) {
-        for (int ab = 0; ab < g2; ++ab) {
-            const double sw = kTswitch / pp[ab];
-            prim[(4 * g2 + ab) * pcap + pos] = sw;
-            prim_f[(4 * g2 + ab) * pcap + pos] = (float)sw;
-            bip[(int64_t)pos * g2 + ab] = sw;
-            bip_f[(int64_t)pos * g2 + ab] = (float)sw;
-        }
-    }
-    if (kmu) {
-        for (int ab = 0; ab < g2; ++ab) {
-            kmu[(int64_t)ab * pcap + pos] = mu[ab];
-            kfa[(int64_t)ab * pcap + pos] = fa[ab];
-        }
-    }
+    slot[pos] = (int)p;
+    pm[pos] = bk / kNumBands;
 }
 
-__global__ void k_b_pad(const DevHeader *__restrict__ hdr, int64_t pcap, int *__restrict__ pm)
+// Tables of every significant pair at its position, for the precision of the build: one thread
+// per (position, primitive pair), as in the single-molecule preparation, with 64 pad entries
+// after the last pair and the maxima of the term exponents over every 64 positions.  (One
+// thread per pair took 53 us for 64 small molecules and 1.0 ms for 500 clusters.)
+struct BTables {
+    const int *slot, *pm;
+    int *pk, *pl;
+    double *pq, *pd;
+    void *prim, *bra, *bip;   // of the build's precision
+    double *kmu, *kfa;
+    short *bexp;              // [g2][pcap]
+    int *kexp;                // [positions / 64][g2]
+    bool grad;
+};
+template <typename R>
+__global__ __launch_bounds__(256) void k_b_tables(Basis b, const BasisDev *__restrict__ bd,
+                                                  const DevHeader *__restrict__ hdr,
+                                                  const long long *__restrict__ poff,
+                                                  const long long *__restrict__ aoff,
+                                                  const long long *__restrict__ doff, const int *__restrict__ nm,
+                                                  const double *__restrict__ cent, const double *__restrict__ xyz,
+                                                  const double *__restrict__ dens, const double *__restrict__ q,
+                                                  int64_t pcap, BTables T)
 {
-    const int64_t pos = hdr->sig_pairs + (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (pos < pcap) pm[pos] = 0;
+    const int S = hdr->sig_pairs;
+    const int64_t at = (int64_t)blockIdx.x * 256;
+    if (at >= (int64_t)S + 64) return;
+    const int64_t pos = at + threadIdx.x;
+    const int g = b.g, g2 = b.g2, ab = blockIdx.y;
+    R *prim = (R *)T.prim, *bra = (R *)T.bra, *bip = (R *)T.bip;
+    int e = kTermNever;
+    if (pos < S) {
+        const long long p = T.slot[pos];
+        const int m = T.pm[pos];
+        int64_t i, j;
+        pair_of_index(p - poff[m], i, j);
+        const double *c = cent + 3 * m;
+        const int64_t gi = aoff[m] + i, gj = aoff[m] + j;
+        const double A[3] = {xyz[3 * gi] - c[0], xyz[3 * gi + 1] - c[1], xyz[3 * gi + 2] - c[2]};
+        const double B[3] = {xyz[3 * gj] - c[0], xyz[3 * gj + 1] - c[1], xyz[3 * gj + 2] - c[2]};
+        const PrimPair w = prim_pair(b, bd, gi, gj, ab, A, B);
+        if (ab == 0) {
+            T.pk[pos] = (int)i;
+            T.pl[pos] = (int)j;
+            T.pq[pos] = q[p];
+            T.pd[pos] = dens[doff[m] + i * nm[m] + j];
+        }
+        prim[(0 * g2 + ab) * pcap + pos] = (R)w.x;
+        prim[(1 * g2 + ab) * pcap + pos] = (R)w.y;
+        prim[(2 * g2 + ab) * pcap + pos] = (R)w.z;
+        prim[(3 * g2 + ab) * pcap + pos] = (R)w.S;
+        // bra row: centre, charge and the charge weighted by mu and by the fractions
+        // fa = a/p, fb = b/p of the primitive pair (the gradient's bra weights)
+        const double fb = b.aexp ? 1.0 - w.fa : w.fb;
+        const double row[kBBra] = {w.x, w.y, w.z, w.S, w.mu * w.S, w.fa * w.S, fb * w.S,
+                                   w.fa * fb * w.S, fb * fb * w.S, 0.0, 0.0, 0.0};
+        R *ba = bra + (pos * g2 + ab) * kBBra;
+        for (int x = 0; x < kBBra; ++x) ba[x] = (R)row[x];
+        if (bip) {
+            const R sw = (R)(kTswitch / w.p);
+            prim[(4 * g2 + ab) * pcap + pos] = sw;
+            bip[pos * g2 + ab] = sw;
+        }
+        if (T.kmu) {
+            T.kmu[(int64_t)ab * pcap + pos] = w.mu;
+            T.kfa[(int64_t)ab * pcap + pos] = w.fa;
+        }
+        e = term_exponent(term_bound(w.S, w.p, w.mu, sqrt(w.ab2), T.grad));
+        T.bexp[(int64_t)ab * pcap + pos] = (short)e;
+        (void)g;
+    } else if (pos < (int64_t)S + 64) {
+        if (ab == 0) {
+            T.pk[pos] = 0;
+            T.pl[pos] = 0;
+            T.pq[pos] = 0.0;
+            T.pd[pos] = 0.0;
+        }
+        for (int x = 0; x < 4; ++x) prim[(x * g2 + ab) * pcap + pos] = x < 3 ? (R)1e6 : (R)0;
+        if (bip) prim[(4 * g2 + ab) * pcap + pos] = (R)1;
+        if (T.kmu) {
+            T.kmu[(int64_t)ab * pcap + pos] = 0.0;
+            T.kfa[(int64_t)ab * pcap + pos] = 0.0;
+        }
+    }
+    e = wave_max(e);
+    if (threadIdx.x % kWave == 0) T.kexp[(pos / kWave) * g2 + ab] = e;
 }
 
 // Ket range of every bra s: kets t in [klo_s, lim_s), klo_s the first pair of its molecule,
-// lim_s = min(s + 1, end of the molecule's band holding tau / Q_s).  A workgroup also leaves
-// the maxima of its pairs' term exponents over every 64 consecutive pairs in kexp.
+// lim_s = min(s + 1, end of the molecule's band holding tau / Q_s).
 __global__ __launch_bounds__(256) void k_b_limits(const DevHeader *__restrict__ hdr, double tau,
                                                   const double *__restrict__ pq, const int *__restrict__ pm,
                                                   const long long *__restrict__ boff, long long *__restrict__ nitems,
-                                                  int *__restrict__ lims, int *__restrict__ klo, int64_t pcap,
-                                                  int g2, const short *__restrict__ bexp, int *__restrict__ kexp)
+                                                  int *__restrict__ lims, int *__restrict__ klo, int64_t pcap)
 {
     const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    block_term_maxima<kWave, 256>(hdr->sig_pairs, g2, bexp, kexp);
     if (s >= pcap) return;
     long long ni = 0;
     if (s < hdr->sig_pairs) {
@@ -312,31 +340,79 @@ __global__ __launch_bounds__(256) void k_b_limits(const DevHeader *__restrict__ 
 // Block table of the quartet kernel.  Per molecule: its item range, and either one owned
 // block (all its items; molecules with at most owned_bound unique quartets before the
 // screen, P (P + 1) / 2 with P = n (n + 1) / 2) or ceil(items / bsz) shared blocks.
-// bsz = block_items, or (0: automatic) total items / (8 x workgroups) clamped to
-// [kBlockItems, 4 kBlockItems]: big batches get fewer fetches and molecule switches, small
-// ones keep enough blocks to spread.
-__global__ __launch_bounds__(256) void k_b_blocks(DevHeader *__restrict__ hdr, int64_t nmol,
+// bsz = block_items, or (0: automatic) total items / (8 x workgroups) clamped: at most
+// 4 kBlockItems (big batches get fewer fetches and molecule switches), and at least
+// kBlockItems for molecules of up to 32 items on average, which then are about a block each
+// (200 molecules of up to 10 atoms: 261 us with 16, 278 with 4), a quarter of that for larger
+// ones, whose blocks otherwise leave workgroups idle (64 molecules of up to 24 atoms: 503 us
+// with 16, 370 with 4; 8 of up to 48: 522 and 429).  One workgroup, which also forms the
+// blocks' prefix sums (a launch for each and three per prefix sum took 30 us).
+constexpr int kBlockThreads = 1024;
+__global__ __launch_bounds__(kBlockThreads) void k_b_blocks(DevHeader *__restrict__ hdr, int64_t nmol,
                                                   const int *__restrict__ nm, const long long *__restrict__ boff,
                                                   const long long *__restrict__ item_off, int block_items,
                                                   long long owned_bound, int groups, long long *__restrict__ mi0,
-                                                  long long *__restrict__ mi1, long long *__restrict__ cnt_own,
-                                                  long long *__restrict__ cnt_sh)
+                                                  long long *__restrict__ mi1, long long *__restrict__ off_own,
+                                                  long long *__restrict__ off_sh)
 {
-    const int64_t m = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    __shared__ long long wsum[2][kBlockThreads / kWave];
+    const int t = threadIdx.x, lane = t % kWave, wave = t / kWave;
     long long bsz = block_items;
     if (bsz <= 0) {
+        const long long least = hdr->items <= 32 * nmol ? kBlockItems : kBlockItems / 4;
         bsz = hdr->items / (8LL * (long long)groups);
-        bsz = bsz < kBlockItems ? kBlockItems : (bsz > 4 * kBlockItems ? 4 * kBlockItems : bsz);
+        bsz = bsz < least ? least : (bsz > 4 * kBlockItems ? 4 * kBlockItems : bsz);
     }
-    if (m == 0) hdr->bsz = bsz;
-    if (m >= nmol) return;
-    const long long i0 = item_off[boff[m * kNumBands]], i1 = item_off[boff[(m + 1) * kNumBands]];
-    mi0[m] = i0;
-    mi1[m] = i1;
-    const long long n = nm[m], P = n * (n + 1) / 2;
-    const bool own = owned_bound > 0 && P * (P + 1) / 2 <= owned_bound;
-    cnt_own[m] = own && i1 > i0 ? 1 : 0;
-    cnt_sh[m] = own ? 0 : (i1 - i0 + bsz - 1) / bsz;
+    long long base_own = 0, base_sh = 0;
+    for (int64_t m0 = 0; m0 < nmol; m0 += kBlockThreads) {
+        const int64_t m = m0 + t;
+        long long own = 0, sh = 0;
+        if (m < nmol) {
+            const long long i0 = item_off[boff[m * kNumBands]], i1 = item_off[boff[(m + 1) * kNumBands]];
+            mi0[m] = i0;
+            mi1[m] = i1;
+            const long long n = nm[m], P = n * (n + 1) / 2;
+            const bool whole = owned_bound > 0 && P * (P + 1) / 2 <= owned_bound;
+            own = whole && i1 > i0 ? 1 : 0;
+            sh = whole ? 0 : (i1 - i0 + bsz - 1) / bsz;
+        }
+        long long x = own, y = sh;
+#pragma unroll
+        for (int o = 1; o < kWave; o <<= 1) {
+            const long long u = __shfl_up(x, o, kWave), v = __shfl_up(y, o, kWave);
+            if (lane >= o) {
+                x += u;
+                y += v;
+            }
+        }
+        __syncthreads();
+        if (lane == kWave - 1) {
+            wsum[0][wave] = x;
+            wsum[1][wave] = y;
+        }
+        __syncthreads();
+        long long before_own = base_own, before_sh = base_sh;
+        for (int w = 0; w < kBlockThreads / kWave; ++w) {
+            if (w < wave) {
+                before_own += wsum[0][w];
+                before_sh += wsum[1][w];
+            }
+            base_own += wsum[0][w];
+            base_sh += wsum[1][w];
+        }
+        if (m < nmol) {
+            off_own[m] = before_own + x - own;
+            off_sh[m] = before_sh + y - sh;
+        }
+    }
+    if (t == 0) {
+        off_own[nmol] = base_own;
+        off_sh[nmol] = base_sh;
+        hdr->bt_own = base_own;
+        hdr->bt_sh = base_sh;
+        hdr->bsz = bsz;
+        hdr->tile = (int)bsz;
+    }
 }
 
 // ------------------------------------------------------------------ fused quartet kernel
@@ -460,7 +536,7 @@ __global__ __launch_bounds__(kBatchMaxThreads) void k_batched(BArgs a)
             ds = ((cptr<double>)a.pd)[s];
             lim = ((cptr<int>)a.lim)[s];
             klo = ((cptr<int>)a.klo)[s];
-            ebra = lane < G2 ? (int)a.bexp[(int64_t)s * G2 + lane] : kTermNone;
+            ebra = lane < G2 ? (int)a.bexp[(int64_t)lane * a.pcap + s] : kTermNone;
         }
         const long long t0 = klo + (m - a.item_off[s]) * kKetsPerItem + (u % kUnitsPerItem) * kWave;
         if (t0 >= lim) continue;
@@ -683,15 +759,18 @@ __global__ __launch_bounds__(kBatchMaxThreads) void k_batched(BArgs a)
     if (lane == 0 && kept) atomicAdd(a.quartets, kept);
 }
 
-// G from the folded lower triangle and E2 = 1/2 sum D o G, one block per molecule.
+// G from the folded lower triangle, E2 = 1/2 sum D o G and the gradient, one block per molecule.
 __global__ __launch_bounds__(256) void k_b_final(const int *__restrict__ mol_n, const long long *__restrict__ doff,
                                                  const long long *__restrict__ toff, const double *__restrict__ facc,
                                                  const double *__restrict__ dens, double *__restrict__ fock,
-                                                 double *__restrict__ e2)
+                                                 double *__restrict__ e2, const long long *__restrict__ aoff,
+                                                 const double *__restrict__ gacc, double *__restrict__ d_xyz)
 {
     __shared__ double red[256];
     const int m = blockIdx.x;
     const int n = mol_n[m];
+    if (d_xyz)
+        for (int x = threadIdx.x; x < 3 * n; x += 256) d_xyz[3 * aoff[m] + x] = gacc[3 * aoff[m] + x];
     const double *L = facc + toff[m];
     double e = 0.0;
     for (int x = threadIdx.x; x < n * n; x += 256) {
@@ -707,18 +786,6 @@ __global__ __launch_bounds__(256) void k_b_final(const int *__restrict__ mol_n, 
         __syncthreads();
     }
     if (threadIdx.x == 0) e2[m] = 0.5 * red[0];
-}
-
-__global__ void k_b_fill(double *__restrict__ p, int64_t m)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < m) p[i] = 0.0;
-}
-
-__global__ void k_b_copy(const double *__restrict__ s, int64_t m, double *__restrict__ d)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < m) d[i] = s[i];
 }
 
 // ------------------------------------------------------------------ host side
@@ -829,7 +896,7 @@ BLayout make_blayout(int64_t nmol, const int64_t *atom_off, int g, int with_grad
     L.bra_f = take(sizeof(float) * kBBra * g2 * PC);
     L.nitems = take(sizeof(long long) * PC);
     L.bexp = take(sizeof(short) * (size_t)L.g2 * (size_t)L.pcap);
-    L.kexp = take(sizeof(int) * (size_t)L.g2 * (size_t)(L.pcap / kWave + 1));
+    L.kexp = take(sizeof(int) * (size_t)L.g2 * (size_t)(L.pcap / kWave + 4));
     L.lim = take(sizeof(int) * PC);
     L.klo = take(sizeof(int) * PC);
     L.item_off = take(sizeof(long long) * (PC + 1));
@@ -839,8 +906,6 @@ BLayout make_blayout(int64_t nmol, const int64_t *atom_off, int g, int with_grad
     L.gacc = with_grad ? take(sizeof(double) * 3 * (size_t)ntot) : 0;
     L.mol_i0 = take(sizeof(long long) * NM);
     L.mol_i1 = take(sizeof(long long) * NM);
-    L.cnt_own = take(sizeof(long long) * NM);
-    L.cnt_sh = take(sizeof(long long) * NM);
     L.off_own = take(sizeof(long long) * (NM + 1));
     L.off_sh = take(sizeof(long long) * (NM + 1));
     L.total = o;
@@ -849,9 +914,12 @@ BLayout make_blayout(int64_t nmol, const int64_t *atom_off, int g, int with_grad
 
 hipError_t upload_batch_tables(const BLayout &L, char *ws, const int64_t *atom_off_host, hipStream_t st)
 {
+    // the five tables lie one after another in the workspace: one copy of their staged image
     const int64_t nmol = L.nmol;
-    std::vector<int> nm(nmol);
-    std::vector<long long> aoff(nmol + 1), poff(nmol + 1), doff(nmol + 1), toff(nmol + 1);
+    std::vector<char> image(L.cent - L.mol_n);
+    int *nm = (int *)image.data();
+    auto table = [&](size_t at) { return (long long *)(image.data() + (at - L.mol_n)); };
+    long long *aoff = table(L.mol_aoff), *poff = table(L.mol_poff), *doff = table(L.mol_doff), *toff = table(L.mol_toff);
     aoff[0] = poff[0] = doff[0] = toff[0] = 0;
     for (int64_t m = 0; m < nmol; ++m) {
         const long long n = atom_off_host[m + 1] - atom_off_host[m];
@@ -861,16 +929,8 @@ hipError_t upload_batch_tables(const BLayout &L, char *ws, const int64_t *atom_o
         doff[m + 1] = doff[m] + n * n;
         toff[m + 1] = toff[m] + n * (n + 1) / 2;
     }
-    hipError_t e = hipMemcpyAsync(ws + L.mol_n, nm.data(), sizeof(int) * nmol, hipMemcpyHostToDevice, st);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(ws + L.mol_aoff, aoff.data(), sizeof(long long) * (nmol + 1), hipMemcpyHostToDevice, st);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(ws + L.mol_poff, poff.data(), sizeof(long long) * (nmol + 1), hipMemcpyHostToDevice, st);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(ws + L.mol_doff, doff.data(), sizeof(long long) * (nmol + 1), hipMemcpyHostToDevice, st);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(ws + L.mol_toff, toff.data(), sizeof(long long) * (nmol + 1), hipMemcpyHostToDevice, st);
-    // the host vectors end with this call: wait until the copies have consumed them
+    hipError_t e = hipMemcpyAsync(ws + L.mol_n, image.data(), image.size(), hipMemcpyHostToDevice, st);
+    // the host image ends with this call: wait until the copy has consumed it
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     return e;
 }
@@ -898,52 +958,65 @@ hipError_t launch_batched(const BLayout &L, const Basis &b, char *ws, const int6
     int *bcur = (int *)(ws + L.bcur);
     // header and basis constants, F's accumulators and the bucket counters cleared
     const HeaderInfo info{0, groups, prec, -1, 0, 0, 0};
-    e = launch_prep_begin(b, (BasisDev *)(ws + L.basis), hdr, L.ntot, nullptr, info, (double *)(ws + L.facc), L.tri,
+    const bool grad = d_xyz != nullptr;
+    // the gradient's accumulators follow F's
+    const int64_t nacc = grad ? (int64_t)(L.gacc - L.facc) / 8 + 3 * L.ntot : L.tri;
+    e = launch_prep_begin(b, (BasisDev *)(ws + L.basis), hdr, L.ntot, nullptr, info, (double *)(ws + L.facc), nacc,
                           bcnt, NB, st);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_b_mol, dim3((unsigned)((nmol + 127) / 128)), dim3(128), 0, st, (int)nmol, d_n, d_aoff, xyz,
-                       cent, qmax);
-    hipLaunchKernelGGL(k_b_pair_q, dim3(nbp), dim3(256), 0, st, b, bd, (int)nmol, d_poff, d_aoff, cent, xyz, L.ptot,
-                       (double *)(ws + L.q), qmax);
-    hipLaunchKernelGGL(k_b_bucket_count, dim3(nbp), dim3(256), 0, st, (int)nmol, d_poff, L.ptot, tau, qmax,
-                       (const double *)(ws + L.q), (int *)(ws + L.bucket_of), bcnt);
+    hipLaunchKernelGGL(k_b_mol, dim3((unsigned)((nmol + 3) / 4)), dim3(256), 0, st, (int)nmol, d_n, d_aoff, xyz, cent,
+                       qmax);
+    double *q = (double *)(ws + L.q);
+    int *bucket = (int *)(ws + L.bucket_of);
+    switch (b.g) {
+    case 1: launch_b_pair_q<1>(b, (int)nmol, d_poff, d_aoff, xyz, L.ptot, q, bucket, qmax, st); break;
+    case 2: launch_b_pair_q<4>(b, (int)nmol, d_poff, d_aoff, xyz, L.ptot, q, bucket, qmax, st); break;
+    case 3: launch_b_pair_q<16>(b, (int)nmol, d_poff, d_aoff, xyz, L.ptot, q, bucket, qmax, st); break;
+    default: launch_b_pair_q<64>(b, (int)nmol, d_poff, d_aoff, xyz, L.ptot, q, bucket, qmax, st); break;
+    }
+    hipLaunchKernelGGL(k_b_bucket_count, dim3(nbp), dim3(256), 0, st, L.ptot, tau, qmax, (const double *)q, bucket,
+                       bcnt);
     e = launch_scan(bcnt, NB, boff, (long long *)(ws + L.scan_tmp), nullptr, st);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_b_cursors, dim3((unsigned)((NB + 255) / 256)), dim3(256), 0, st, boff, NB, bcur, hdr);
-    hipLaunchKernelGGL(k_b_pair_scatter, dim3(nbp), dim3(256), 0, st, b, bd, (int)nmol, d_poff, d_aoff, d_doff, d_n,
-                       cent, xyz, dens, L.ptot, L.pcap, (const double *)(ws + L.q), (const int *)(ws + L.bucket_of), bcur,
-                       (int *)(ws + L.pk), (int *)(ws + L.pl), (int *)(ws + L.pm), (double *)(ws + L.pq),
-                       (double *)(ws + L.pd), (double *)(ws + L.prim), (float *)(ws + L.prim_f), (double *)(ws + L.bra),
-                       (float *)(ws + L.bra_f), L.atoms ? (double *)(ws + L.bip) : nullptr,
-                       L.atoms ? (float *)(ws + L.bip_f) : nullptr, L.kmu ? (double *)(ws + L.kmu) : nullptr,
-                       L.kmu ? (double *)(ws + L.kfa) : nullptr, (short *)(ws + L.bexp), d_xyz != nullptr);
+    // the pair of every position (the item counts' storage is free until the limits are computed)
+    int *slot = (int *)(ws + L.nitems);
+    hipLaunchKernelGGL(k_b_slot, dim3(nbp), dim3(256), 0, st, L.ptot, (const int *)bucket, bcur, slot,
+                       (int *)(ws + L.pm));
+    BTables T;
+    T.slot = slot;
+    T.pm = (const int *)(ws + L.pm);
+    T.pk = (int *)(ws + L.pk);
+    T.pl = (int *)(ws + L.pl);
+    T.pq = (double *)(ws + L.pq);
+    T.pd = (double *)(ws + L.pd);
+    const bool mixed = prec == HFK_MIXED;
+    T.prim = ws + (mixed ? L.prim_f : L.prim);
+    T.bra = ws + (mixed ? L.bra_f : L.bra);
+    T.bip = L.atoms ? ws + (mixed ? L.bip_f : L.bip) : nullptr;
+    T.kmu = L.kmu ? (double *)(ws + L.kmu) : nullptr;
+    T.kfa = L.kmu ? (double *)(ws + L.kfa) : nullptr;
+    T.bexp = (short *)(ws + L.bexp);
+    T.kexp = (int *)(ws + L.kexp);
+    T.grad = grad;
+    const dim3 tgrid((unsigned)((L.ptot + 64 + 255) / 256), (unsigned)L.g2);
+    if (mixed)
+        hipLaunchKernelGGL((k_b_tables<float>), tgrid, dim3(256), 0, st, b, bd, hdr, d_poff, d_aoff, d_doff, d_n, cent,
+                           xyz, dens, (const double *)q, L.pcap, T);
+    else
+        hipLaunchKernelGGL((k_b_tables<double>), tgrid, dim3(256), 0, st, b, bd, hdr, d_poff, d_aoff, d_doff, d_n, cent,
+                           xyz, dens, (const double *)q, L.pcap, T);
     const unsigned nbc = (unsigned)((L.pcap + 255) / 256);
-    e = launch_pair_pad(hdr, L.pcap, L.g2, L.atoms, (int *)(ws + L.pk), (int *)(ws + L.pl), (double *)(ws + L.pq),
-                        (double *)(ws + L.pd), (double *)(ws + L.prim), (float *)(ws + L.prim_f),
-                        L.kmu ? (double *)(ws + L.kmu) : nullptr, L.kmu ? (double *)(ws + L.kfa) : nullptr, st);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_b_pad, dim3(nbc), dim3(256), 0, st, hdr, L.pcap, (int *)(ws + L.pm));
     hipLaunchKernelGGL(k_b_limits, dim3(nbc), dim3(256), 0, st, hdr, tau, (const double *)(ws + L.pq),
                        (const int *)(ws + L.pm), boff, (long long *)(ws + L.nitems), (int *)(ws + L.lim),
-                       (int *)(ws + L.klo), L.pcap, L.g2, (const short *)(ws + L.bexp), (int *)(ws + L.kexp));
+                       (int *)(ws + L.klo), L.pcap);
     e = launch_scan((const long long *)(ws + L.nitems), L.pcap, (long long *)(ws + L.item_off),
                     (long long *)(ws + L.scan_tmp), &hdr->items, st);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_b_blocks, dim3((unsigned)((nmol + 255) / 256)), dim3(256), 0, st, hdr, (int64_t)nmol, d_n,
+    hipLaunchKernelGGL(k_b_blocks, dim3(1), dim3(kBlockThreads), 0, st, hdr, (int64_t)nmol, d_n,
                        (const long long *)boff, (const long long *)(ws + L.item_off), shape.block_items,
                        shape.owned_bound, groups, (long long *)(ws + L.mol_i0), (long long *)(ws + L.mol_i1),
-                       (long long *)(ws + L.cnt_own), (long long *)(ws + L.cnt_sh));
-    e = launch_scan((const long long *)(ws + L.cnt_own), nmol, (long long *)(ws + L.off_own),
-                    (long long *)(ws + L.scan_tmp), &hdr->bt_own, st);
-    if (e == hipSuccess)
-        e = launch_scan((const long long *)(ws + L.cnt_sh), nmol, (long long *)(ws + L.off_sh),
-                        (long long *)(ws + L.scan_tmp), &hdr->bt_sh, st);
-    if (e != hipSuccess) return e;
-
-    const bool grad = d_xyz != nullptr;
-    if (grad)
-        hipLaunchKernelGGL(k_b_fill, dim3((unsigned)((3 * L.ntot + 255) / 256)), dim3(256), 0, st,
-                           (double *)(ws + L.gacc), (int64_t)(3 * L.ntot));
+                       (long long *)(ws + L.off_own), (long long *)(ws + L.off_sh));
     BArgs a;
     a.hdr = hdr;
     a.bd = bd;
@@ -1041,10 +1114,7 @@ hipError_t launch_batched(const BLayout &L, const Basis &b, char *ws, const int6
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_b_final, dim3((unsigned)nmol), dim3(256), 0, st, d_n, d_doff, d_toff,
-                       (const double *)(ws + L.facc), dens, fock, e2);
-    if (grad)
-        hipLaunchKernelGGL(k_b_copy, dim3((unsigned)((3 * L.ntot + 255) / 256)), dim3(256), 0, st,
-                           (const double *)(ws + L.gacc), (int64_t)(3 * L.ntot), d_xyz);
+                       (const double *)(ws + L.facc), dens, fock, e2, d_aoff, (const double *)a.gacc, d_xyz);
     return hipGetLastError();
 }
 

@@ -16,48 +16,87 @@ __device__ inline double erf_over_sqrt(double T)
     return erf(s) / s;
 }
 
-// Gaussian product of the primitives of atoms A and B (coordinates already centred):
-// P_ab = (a A + b B)/p and S_ab = w_a w_b exp(-mu |A-B|^2) (pi/p)^(3/2), the charge of
-// the product distribution, for every primitive pair ab = a*g + b.
-__device__ inline void pair_prims(const Basis &b, const BasisDev *__restrict__ bd, const double *A,
-                                  const double *B, double *px, double *py, double *pz, double *ps)
+// Gaussian product of primitive pair ab = a*g + b of atoms i (at A) and j (at B, coordinates
+// already centred): P = (a A + b B)/p, charge S = w_a w_b exp(-mu |A-B|^2) (pi/p)^(3/2), and
+// p, mu, fa = a/p, fb = b/p.  With per-atom bases the exponents and weights come from the rows
+// of atoms i and j.
+struct PrimPair {
+    double x, y, z, S, p, mu, fa, fb, ab2;
+};
+__device__ inline PrimPair prim_pair(const Basis &b, const BasisDev *__restrict__ bd, int64_t i, int64_t j, int ab,
+                                     const double *A, const double *B)
 {
+    PrimPair w;
     const double dx = A[0] - B[0], dy = A[1] - B[1], dz = A[2] - B[2];
-    const double ab2 = dx * dx + dy * dy + dz * dz;
-    for (int ab = 0; ab < b.g2; ++ab) {
-        const int a = ab / b.g, c = ab % b.g;
-        const double fa = bd->fa[ab], fb = bd->fb[ab];
-        px[ab] = fa * A[0] + fb * B[0];
-        py[ab] = fa * A[1] + fb * B[1];
-        pz[ab] = fa * A[2] + fb * B[2];
-        ps[ab] = b.w[a] * b.w[c] * exp(-bd->mu[ab] * ab2) * bd->pi32[ab];
+    w.ab2 = dx * dx + dy * dy + dz * dz;
+    if (b.aexp) {
+        const double ea = b.aexp[i * b.g + ab / b.g], eb = b.aexp[j * b.g + ab % b.g];
+        w.p = ea + eb;
+        w.mu = ea * eb / w.p;
+        w.fa = ea / w.p;
+        w.fb = eb / w.p;
+        w.S = b.aw[i * b.g + ab / b.g] * b.aw[j * b.g + ab % b.g] * exp(-w.mu * w.ab2) * pow(kPi / w.p, 1.5);
+    } else {
+        w.p = bd->p[ab];
+        w.mu = bd->mu[ab];
+        w.fa = bd->fa[ab];
+        w.fb = bd->fb[ab];
+        w.S = b.w[ab / b.g] * b.w[ab % b.g] * exp(-w.mu * w.ab2) * bd->pi32[ab];
     }
+    w.x = w.fa * A[0] + w.fb * B[0];
+    w.y = w.fa * A[1] + w.fb * B[1];
+    w.z = w.fa * A[2] + w.fb * B[2];
+    return w;
 }
 
-// Per-atom bases: the same for atoms i (at A) and j (at B) with exponents and weights from
-// the atom rows, plus p = alpha_a + alpha_b of every primitive pair (a on i, b on j).
-__device__ inline void pair_prims_atoms(const Basis &b, int64_t i, int64_t j, const double *A, const double *B,
-                                        double *px, double *py, double *pz, double *ps, double *pp,
-                                        double *pmu = nullptr, double *pfa = nullptr)
+// Schwarz bound of a pair: (ij|ij) = sum over the unordered primitive quartets, from a table of
+// S, fb and p per primitive pair (tab[0 .. 3 g2)).  All primitive centres lie on the line A-B,
+// P_ab - P_cd = (fb_ab - fb_cd) (B - A).
+__device__ inline void pair_q_entry(const Basis &b, int64_t i, int64_t j, int ab, double r2, double *__restrict__ tab,
+                                    double *bound = nullptr, double *bound0 = nullptr)
 {
-    const double dx = A[0] - B[0], dy = A[1] - B[1], dz = A[2] - B[2];
-    const double ab2 = dx * dx + dy * dy + dz * dz;
-    const double *ei = b.aexp + i * b.g, *ej = b.aexp + j * b.g;
-    const double *wi = b.aw + i * b.g, *wj = b.aw + j * b.g;
-    for (int ab = 0; ab < b.g2; ++ab) {
-        const int a = ab / b.g, c = ab % b.g;
-        const double p = ei[a] + ej[c];
-        const double fa = ei[a] / p, fb = ej[c] / p;
-        px[ab] = fa * A[0] + fb * B[0];
-        py[ab] = fa * A[1] + fb * B[1];
-        pz[ab] = fa * A[2] + fb * B[2];
-        ps[ab] = wi[a] * wj[c] * exp(-(ei[a] * ej[c] / p) * ab2) * pow(kPi / p, 1.5);
-        pp[ab] = p;
-        if (pmu) {
-            pmu[ab] = ei[a] * ej[c] / p;
-            pfa[ab] = fa;
-        }
+    const int x = ab / b.g, y = ab % b.g;
+    const double ea = b.aexp ? b.aexp[i * b.g + x] : b.alpha[x], eb = b.aexp ? b.aexp[j * b.g + y] : b.alpha[y];
+    const double ww = b.aexp ? b.aw[i * b.g + x] * b.aw[j * b.g + y] : b.w[x] * b.w[y];
+    const double p = ea + eb, c = ww * pow(kPi / p, 1.5), s = c * exp(-(ea * eb / p) * r2);
+    tab[ab] = s;
+    tab[b.g2 + ab] = eb / p;
+    tab[2 * b.g2 + ab] = p;
+    if (bound) {
+        // |S| p^(1/4), here and at distance zero
+        const double p4 = sqrt(sqrt(p));
+        *bound += fabs(s) * p4;
+        *bound0 += fabs(c) * p4;
     }
+}
+// Lane l of `lanes`: its share of the sum.
+__device__ inline double pair_q_sum(int g2, double r2, int l, int lanes, const double *__restrict__ tab)
+{
+    const double *S = tab, *f = tab + g2, *pp = f + g2;
+    double s = 0.0;
+    const int nc = g2 * (g2 + 1) / 2;
+    for (int c = l; c < nc; c += lanes) {
+        int ab = (int)((sqrtf(8.0f * (float)c + 1.0f) - 1.0f) * 0.5f);
+        while (ab * (ab + 1) / 2 > c) --ab;
+        while ((ab + 1) * (ab + 2) / 2 <= c) ++ab;
+        const int cd = c - ab * (ab + 1) / 2;
+        const double ss = S[ab] * S[cd];
+        if (ss == 0.0) continue;
+        const double df = f[ab] - f[cd], rho = pp[ab] * pp[cd] / (pp[ab] + pp[cd]);
+        const double v = ss * sqrt(rho) * erf_over_sqrt(rho * (df * df * r2));
+        s += ab == cd ? v : 2.0 * v;
+    }
+    return s;
+}
+
+__device__ inline int wave_max(int v)
+{
+#pragma unroll
+    for (int w = 32; w > 0; w >>= 1) {
+        const int o = __shfl_xor(v, w, 64);
+        v = o > v ? o : v;
+    }
+    return v;
 }
 
 // Binary exponent e with u < 2^e of a primitive pair's bound (see term_limit).
@@ -76,28 +115,6 @@ __device__ inline double term_bound(double S, double p, double mu, double r, boo
 {
     const double sp = sqrt(p), u = fabs(S) * sqrt(sp);
     return grad ? u * fmax(1.0, fmax(sp, 2.0 * r * mu)) : u;
-}
-
-// Called by a whole workgroup of kThreads threads, for kThreads consecutive pairs: the maxima
-// of the term exponents of every kBlock of them, into kexp[block][g2].
-template <int kBlock, int kThreads>
-__device__ inline void block_term_maxima(int64_t pairs, int g2, const short *__restrict__ bexp,
-                                         int *__restrict__ kexp)
-{
-    constexpr int kSub = kThreads / kBlock;
-    const int64_t at = (int64_t)blockIdx.x * kThreads;
-    if (at >= pairs) return;   // the same for the whole workgroup
-    __shared__ int emax[kSub * kMaxG2];
-    for (int x = threadIdx.x; x < kSub * g2; x += kThreads) emax[x] = kTermNever;
-    __syncthreads();
-    // consecutive lanes read consecutive exponents
-    const int cnt = (int)(pairs - at < kThreads ? pairs - at : kThreads) * g2;
-    for (int x = threadIdx.x; x < cnt; x += kThreads)
-        atomicMax(&emax[x / (kBlock * g2) * g2 + x % g2], (int)bexp[at * g2 + x]);
-    __syncthreads();
-    for (int x = threadIdx.x; x < kSub * g2; x += kThreads) {
-        if (at + (int64_t)(x / g2) * kBlock < pairs) kexp[(int64_t)blockIdx.x * kSub * g2 + x] = emax[x];
-    }
 }
 
 // Reciprocal square root in FP64: the hardware estimate (relative error ~5e-8) refined by

@@ -245,7 +245,7 @@ struct BLayout {
     size_t nitems, lim, klo, item_off, scan_tmp;
     size_t facc, gacc;
     size_t mol_i0, mol_i1;              // per molecule: first and end item
-    size_t cnt_own, cnt_sh, off_own, off_sh;   // per molecule: blocks of each kind and their prefix
+    size_t off_own, off_sh;             // per molecule: prefix of its blocks of each kind
     bool atoms;                 // per-atom bases: ket component 4 is kTswitch/p, tables below
     size_t arow;                // [2][sum n][g] exponents and weights of every atom
     size_t bip, bip_f;          // [pcap][g2] kTswitch/p of the bra pairs
@@ -277,11 +277,6 @@ int batched_resident_groups(int g, int prec, bool grad, bool atoms, int nmax, in
 hipError_t launch_dens_check(DevHeader *hdr, int64_t n, const double *dens, hipStream_t st);
 hipError_t launch_dens_check_batched(DevHeader *hdr, int64_t nmol, const long long *mol_doff, const int *mol_n,
                                      const double *dens, double tol, hipStream_t st);
-// Pads the batched pair tables (four-component ket table, plus kTswitch/p with per-atom
-// bases; kmu/kfa: per-atom gradient tables or NULL) past the last pair.
-hipError_t launch_pair_pad(const DevHeader *hdr, int64_t pcap, int g2, bool atoms, int *pk, int *pl, double *pq,
-                           double *pd, double *prim, float *prim_f, double *kmu, double *kfa, hipStream_t st);
-
 // Screen of primitive terms.  A primitive pair is bounded by u = |S_ab| p^(1/4) (times
 // max(1, 2 mu R, sqrt p) in the gradient's tables, for the derivative terms), so that a
 // primitive quartet is at most u_ab u_cd: S_ab S_cd E(r) with E <= (2/sqrt(pi)) sqrt(rho) and
@@ -335,8 +330,6 @@ int fock_resident_groups(int g, int prec, int variant, int64_t n, bool atoms = f
 void profile_begin(hipStream_t st);
 void profile_end(hipStream_t st);
 
-hipError_t launch_header_info(char *hdr, int strategy, int groups, int precision, int variant,
-                              hipStream_t st, int tile = 0, int group_bras = 0, int ket_copies = 0);
 hipError_t launch_scan(const long long *in, int64_t m, long long *out, long long *tmp, long long *total,
                        hipStream_t st);
 // Gradient kernel and its reductions.  xdens: X of the two-density contraction (see

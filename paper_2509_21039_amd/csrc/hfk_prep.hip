@@ -158,8 +158,8 @@ __global__ __launch_bounds__(256) void k_pair_q(Basis b, DevHeader *__restrict__
     constexpr int PB = 256 / TP;
     extern __shared__ __attribute__((aligned(16))) double sm[];
     __shared__ double red[256];
-    const int g = b.g, g2 = b.g2, l = threadIdx.x % TP, pb = threadIdx.x / TP;
-    double *S = sm + (size_t)pb * 3 * g2, *f = S + g2, *pp = f + g2;
+    const int l = threadIdx.x % TP, pb = threadIdx.x / TP;
+    double *tab = sm + (size_t)pb * 3 * b.g2;
     const int64_t npair = n * (n + 1) / 2;
     const int64_t p = (int64_t)blockIdx.x * PB + pb;
     const bool live = p < npair;
@@ -170,18 +170,7 @@ __global__ __launch_bounds__(256) void k_pair_q(Basis b, DevHeader *__restrict__
         const double dx = xyz[3 * i] - xyz[3 * j], dy = xyz[3 * i + 1] - xyz[3 * j + 1],
                      dz = xyz[3 * i + 2] - xyz[3 * j + 2];
         r2 = dx * dx + dy * dy + dz * dz;
-        for (int ab = l; ab < g2; ab += TP) {
-            const int x = ab / g, y = ab % g;
-            const double ea = b.aexp ? b.aexp[i * g + x] : b.alpha[x], eb = b.aexp ? b.aexp[j * g + y] : b.alpha[y];
-            const double ww = b.aexp ? b.aw[i * g + x] * b.aw[j * g + y] : b.w[x] * b.w[y];
-            const double q = ea + eb, c = ww * pow(kPi / q, 1.5), s = c * exp(-(ea * eb / q) * r2);
-            const double q4 = sqrt(sqrt(q));
-            S[ab] = s;
-            f[ab] = eb / q;
-            pp[ab] = q;
-            u += fabs(s) * q4;
-            u0 += fabs(c) * q4;
-        }
+        for (int ab = l; ab < b.g2; ab += TP) pair_q_entry(b, i, j, ab, r2, tab, &u, &u0);
     }
 #pragma unroll
     for (int w = TP / 2; w > 0; w >>= 1) {
@@ -189,21 +178,7 @@ __global__ __launch_bounds__(256) void k_pair_q(Basis b, DevHeader *__restrict__
         u0 += __shfl_xor(u0, w, TP);
     }
     __syncthreads();
-    double s = 0.0;
-    if (live && (b.aexp || !(u * u0 < tau))) {
-        const int nc = g2 * (g2 + 1) / 2;
-        for (int c = l; c < nc; c += TP) {
-            int ab = (int)((sqrtf(8.0f * (float)c + 1.0f) - 1.0f) * 0.5f);
-            while (ab * (ab + 1) / 2 > c) --ab;
-            while ((ab + 1) * (ab + 2) / 2 <= c) ++ab;
-            const int cd = c - ab * (ab + 1) / 2;
-            const double ss = S[ab] * S[cd];
-            if (ss == 0.0) continue;
-            const double df = f[ab] - f[cd], rho = pp[ab] * pp[cd] / (pp[ab] + pp[cd]);
-            const double v = ss * sqrt(rho) * erf_over_sqrt(rho * (df * df * r2));
-            s += ab == cd ? v : 2.0 * v;
-        }
-    }
+    double s = live && (b.aexp || !(u * u0 < tau)) ? pair_q_sum(b.g2, r2, l, TP, tab) : 0.0;
 #pragma unroll
     for (int w = TP / 2; w > 0; w >>= 1) s += __shfl_xor(s, w, TP);
     const double q = sqrt(s);
@@ -301,7 +276,7 @@ __global__ __launch_bounds__(256) void k_pair_tables(Basis b, const BasisDev *__
     const int64_t at = (int64_t)blockIdx.x * 256;
     if (at >= (int64_t)S + 64) return;
     const int64_t pos = at + threadIdx.x;
-    const int g = b.g, g2 = b.g2, ab = blockIdx.y;
+    const int g2 = b.g2, ab = blockIdx.y;
     R *prim = kDouble ? (R *)T.prim : (R *)T.prim_f;
     R *bra = kDouble ? (R *)T.bra : (R *)T.bra_f;
     R *bip = kDouble ? (R *)T.bip : (R *)T.bip_f;
@@ -314,24 +289,8 @@ __global__ __launch_bounds__(256) void k_pair_tables(Basis b, const BasisDev *__
         const double c0 = hdr->centroid[0], c1 = hdr->centroid[1], c2 = hdr->centroid[2];
         const double A[3] = {xyz[3 * i] - c0, xyz[3 * i + 1] - c1, xyz[3 * i + 2] - c2};
         const double B[3] = {xyz[3 * j] - c0, xyz[3 * j + 1] - c1, xyz[3 * j + 2] - c2};
-        const double dx = A[0] - B[0], dy = A[1] - B[1], dz = A[2] - B[2];
-        const double ab2 = dx * dx + dy * dy + dz * dz;
-        double p_ab, mu, fa, fb, ps;
-        if (b.aexp) {
-            const double ea = b.aexp[i * g + ab / g], eb = b.aexp[j * g + ab % g];
-            p_ab = ea + eb;
-            mu = ea * eb / p_ab;
-            fa = ea / p_ab;
-            fb = eb / p_ab;
-            ps = b.aw[i * g + ab / g] * b.aw[j * g + ab % g] * exp(-mu * ab2) * pow(kPi / p_ab, 1.5);
-        } else {
-            p_ab = bd->p[ab];
-            mu = bd->mu[ab];
-            fa = bd->fa[ab];
-            fb = bd->fb[ab];
-            ps = b.w[ab / g] * b.w[ab % g] * exp(-mu * ab2) * bd->pi32[ab];
-        }
-        const double px = fa * A[0] + fb * B[0], py = fa * A[1] + fb * B[1], pz = fa * A[2] + fb * B[2];
+        const PrimPair w = prim_pair(b, bd, i, j, ab, A, B);
+        const double px = w.x, py = w.y, pz = w.z, ps = w.S, mu = w.mu, fa = w.fa, p_ab = w.p, ab2 = w.ab2;
         const double p2 = px * px + py * py + pz * pz;
         if (ab == 0) {
             T.pk[pos] = (int)i;
@@ -361,10 +320,10 @@ __global__ __launch_bounds__(256) void k_pair_tables(Basis b, const BasisDev *__
         }
         if (bgw) {
             // gradient: the bra weights mu S, fa S, fb S, fa fb S, fb^2 S of every primitive pair
-            const double fbw = b.aexp ? 1.0 - fa : fb;
+            const double fbw = b.aexp ? 1.0 - fa : w.fb;
             const double row[kGW] = {mu * ps, fa * ps, fbw * ps, fa * fbw * ps, fbw * fbw * ps, 0.0, 0.0, 0.0};
-            R *w = bgw + (pos * g2 + ab) * kGW;
-            for (int c = 0; c < kGW; ++c) w[c] = (R)row[c];
+            R *bw = bgw + (pos * g2 + ab) * kGW;
+            for (int c = 0; c < kGW; ++c) bw[c] = (R)row[c];
         }
         e = term_exponent(term_bound(ps, p_ab, mu, sqrt(ab2), bgw != nullptr));
         T.bexp[(int64_t)ab * pcap + pos] = (short)e;
@@ -385,11 +344,7 @@ __global__ __launch_bounds__(256) void k_pair_tables(Basis b, const BasisDev *__
         }
     }
     __shared__ int emax[4];
-#pragma unroll
-    for (int w = 32; w > 0; w >>= 1) {
-        const int o = __shfl_xor(e, w, 64);
-        e = o > e ? o : e;
-    }
+    e = wave_max(e);
     if (threadIdx.x % 64 == 0) {
         emax[threadIdx.x / 64] = e;
         T.kexp64[(pos / 64) * g2 + ab] = e;
@@ -594,50 +549,6 @@ __global__ __launch_bounds__(256) void k_slot_sort(const long long *__restrict__
     }
 }
 
-// Pads the tail chunk of the sorted tables with harmless entries (atom 0, zero weight,
-// centres 1e6 bohr away) so that lanes past the last pair, or lanes pointed at the first
-// pad entry, read defined memory and land in the far branch with a zero integral.
-// Ket table components: Px Py Pz S always; p2: FP64 component 4 holds |P|^2; swc / swc_f:
-// the FP64 / FP32 component holding kTswitch/p of per-atom bases (-1: none), padded with
-// 1 so that the switch radius stays far below the pad distance.  kmu/kfa (per-atom
-// gradient tables, or NULL) are zeroed there too.
-__global__ void k_pair_pad(const DevHeader *__restrict__ hdr, int64_t pcap, int g2, bool p2, int swc, int swc_f,
-                           int *__restrict__ pk, int *__restrict__ pl, double *__restrict__ pq,
-                           double *__restrict__ pd, double *__restrict__ prim, float *__restrict__ prim_f,
-                           double *__restrict__ kmu, double *__restrict__ kfa)
-{
-    const int64_t s = hdr->sig_pairs;
-    const int64_t pos = s + (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (pos >= pcap) return;
-    pk[pos] = 0;
-    pl[pos] = 0;
-    pq[pos] = 0.0;
-    pd[pos] = 0.0;
-    for (int ab = 0; ab < g2; ++ab) {
-        for (int c = 0; c < 4; ++c) {
-            prim[(c * g2 + ab) * pcap + pos] = c < 3 ? 1e6 : 0.0;
-            prim_f[(c * g2 + ab) * pcap + pos] = c < 3 ? 1e6f : 0.0f;
-        }
-        if (p2) prim[(4 * g2 + ab) * pcap + pos] = 3e12;
-        if (swc >= 0) prim[((int64_t)swc * g2 + ab) * pcap + pos] = 1.0;
-        if (swc_f >= 0) prim_f[((int64_t)swc_f * g2 + ab) * pcap + pos] = 1.0f;
-        if (kmu) {
-            kmu[(int64_t)ab * pcap + pos] = 0.0;
-            kfa[(int64_t)ab * pcap + pos] = 0.0;
-        }
-    }
-}
-
-hipError_t launch_pair_pad(const DevHeader *hdr, int64_t pcap, int g2, bool atoms, int *pk, int *pl, double *pq,
-                           double *pd, double *prim, float *prim_f, double *kmu, double *kfa, hipStream_t st)
-{
-    // the batched tables hold the four-component ket table, plus kTswitch/p as component 4
-    // (FP64 and FP32) with per-atom bases
-    hipLaunchKernelGGL(k_pair_pad, dim3((unsigned)((pcap + 255) / 256)), dim3(256), 0, st, hdr, pcap, g2, false,
-                       atoms ? 4 : -1, atoms ? 4 : -1, pk, pl, pq, pd, prim, prim_f, kmu, kfa);
-    return hipGetLastError();
-}
-
 // Ket range of every bra s (in bucketed order): kets t < lim_s with
 // lim_s = min(s + 1, end of the band holding tau / Q_s); items of item_kets kets.
 __global__ __launch_bounds__(256) void k_limits(const DevHeader *__restrict__ hdr, double tau,
@@ -750,26 +661,6 @@ hipError_t launch_scan(const long long *in, int64_t m, long long *out, long long
     hipLaunchKernelGGL(k_scan_reduce, dim3(nb), dim3(kScanBlock), 0, st, in, m, tmp);
     hipLaunchKernelGGL(k_scan_blocks, dim3(1), dim3(kScanBlock), 0, st, tmp, nb);
     hipLaunchKernelGGL(k_scan_final, dim3(nb), dim3(kScanBlock), 0, st, in, m, tmp, out, total);
-    return hipGetLastError();
-}
-
-__global__ void k_header_info(DevHeader *hdr, int strategy, int groups, int precision, int variant, int tile,
-                              int group_bras, int ket_copies)
-{
-    hdr->strategy = strategy;
-    hdr->groups = groups;
-    hdr->precision = precision;
-    hdr->variant = variant;
-    hdr->tile = tile >= 0 ? tile : (int)hdr->bsz;   // batched: the block size its table used
-    hdr->group_bras = group_bras;
-    hdr->ket_copies = ket_copies;
-}
-
-hipError_t launch_header_info(char *hdr, int strategy, int groups, int precision, int variant, hipStream_t st,
-                              int tile, int group_bras, int ket_copies)
-{
-    hipLaunchKernelGGL(k_header_info, dim3(1), dim3(1), 0, st, (DevHeader *)hdr, strategy, groups, precision,
-                       variant, tile, group_bras, ket_copies);
     return hipGetLastError();
 }
 
