@@ -217,7 +217,7 @@ static Basis make_basis(int32_t ngauss, const double *exps, const double *coefs)
 constexpr int64_t kMaxAtoms = 6144;
 // n above which the gradient kernel's LDS copy of dE2/dR (n x 3) and its Boys tables no longer fit
 constexpr int64_t kMaxGradAtoms = 4096;
-constexpr int kGradGroupsPerCU = 4;
+constexpr int kGradGroupsPerCU = 6;   // as many as fit: four in FP64, five in FP32 (He 200 4.46 -> 4.00 ms)
 constexpr int kDefaultKetCopies = 8;   // untuned default: shared ket-side Coulomb vectors
 // Items per block of the gradient kernel: eight (he512 FP64 184 ms against 191 with four;
 // its per-item work is about 2.4 times the forward's, so fewer row flushes matter more
@@ -369,7 +369,7 @@ static TunedConfig pick_config(int32_t strategy, int32_t precision, int64_t n, i
 
 // No more workgroups than there can be blocks: a workgroup that only finds the counter
 // exhausted still loads its table, and on the smallest systems there are more of them than bras.
-static int forward_groups(const Layout &L, int groups)
+static int block_groups(const Layout &L, int groups)
 {
     const int64_t per = (int64_t)item_kets(L) * L.tile;
     const int64_t blocks = L.npair * ((L.npair + per - 1) / per);
@@ -634,7 +634,7 @@ static hfk_status fock_one_basis(int64_t natoms, const double *xyz, int32_t ngau
         // no more persistent workgroups than fit on a CU at once
         const bool det = strat == HFK_STRATEGY_DETERMINISTIC;
         const int fit = fock_resident_groups(ngauss, precision, cfg.variant, natoms, false, det);
-        L.groups = forward_groups(L, cus * (fit > 0 && cfg.gpc > fit ? fit : cfg.gpc));
+        L.groups = block_groups(L, cus * (fit > 0 && cfg.gpc > fit ? fit : cfg.gpc));
         if (det) {
             hfk_status sd = det_groups(L);
             if (sd != HFK_OK) return sd;
@@ -754,7 +754,7 @@ hfk_status hfk_fock_atoms(int64_t natoms, const double *xyz, int32_t ngauss, con
     {
         const bool det = strat == HFK_STRATEGY_DETERMINISTIC;
         const int fit = fock_resident_groups(ngauss, precision, 1, natoms, true, det);
-        L.groups = forward_groups(L, cus * (fit > 0 && cfg.gpc > fit ? fit : cfg.gpc));
+        L.groups = block_groups(L, cus * (fit > 0 && cfg.gpc > fit ? fit : cfg.gpc));
         if (det) {
             hfk_status sd = det_groups(L);
             if (sd != HFK_OK) return sd;
@@ -838,7 +838,7 @@ hfk_status hfk_scf(int64_t natoms, const double *xyz, const double *charges_host
     {
         const bool det = strat == HFK_STRATEGY_DETERMINISTIC;
         const int fit = fock_resident_groups(ngauss, precision, 1, natoms, true, det);
-        L.groups = forward_groups(L, cus * (fit > 0 && cfg.gpc > fit ? fit : cfg.gpc));
+        L.groups = block_groups(L, cus * (fit > 0 && cfg.gpc > fit ? fit : cfg.gpc));
         if (det) {
             hfk_status sd = det_groups(L);
             if (sd != HFK_OK) return sd;
@@ -934,16 +934,22 @@ static hfk_status fock_grad_impl(bool atoms, int64_t natoms, const double *xyz, 
     Layout L = make_layout(natoms, ngauss, precision, 1, groups_cap(cus), atoms);
     if (workspace_bytes < L.total)
         return fail(HFK_ENOMEM, "workspace holds %zu bytes, %zu needed", workspace_bytes, L.total);
+    // items of one chunk per wave on small systems, for the forward build's reasons (us, four
+    // chunks against one: 20 atoms 132 / 82, 64 atoms 437 / 378, 128 atoms 2341 / 2309, mixed
+    // 1102 / 1113; 50 atoms with six primitives 2694 / 1813; 200 atoms 8729 / 8929)
+    L.sub = L.npair <= (ngauss >= 5 ? 20000 : (precision == HFK_MIXED ? 6000 : 8256)) ? 1 : kSubChunks;
+    // the gradient kernel's blocks: eight items (sixteen small ones), groups of 1024 bras, unless
+    // hfk_set_shape asks for another shape (the pull-back build below takes the forward's shape)
+    set_shape(L, g_cfg_tile > 0 ? g_cfg_tile : (L.sub == 1 ? 2 * kGradTileItems : kGradTileItems),
+              g_cfg_gbras > 0 ? g_cfg_gbras : kGroupBras, 0);
     {
         // as many persistent workgroups as fit on a CU, up to kGradGroupsPerCU (or the count
-        // hfk_set_config asks for)
+        // hfk_set_config asks for); fewer on the smallest systems, whose copies of the gradient
+        // would take longer to sum than they save (20 atoms: 82 us with two per CU, 100 with six)
         const int fit = grad_resident_groups(ngauss, precision, natoms, atoms);
-        const int want = g_cfg_gpc > 0 ? g_cfg_gpc : kGradGroupsPerCU;
-        L.groups = cus * (fit > 0 && fit < want ? fit : want);
+        const int want = g_cfg_gpc > 0 ? g_cfg_gpc : (natoms <= 24 ? 2 : (natoms <= 48 ? 3 : kGradGroupsPerCU));
+        L.groups = block_groups(L, cus * (fit > 0 && fit < want ? fit : want));
     }
-    // the gradient kernel's blocks: eight items, groups of 1024 bras, unless hfk_set_shape
-    // asks for another shape (the pull-back build below takes the forward's shape)
-    set_shape(L, g_cfg_tile > 0 ? g_cfg_tile : kGradTileItems, g_cfg_gbras > 0 ? g_cfg_gbras : kGroupBras, 0);
     char *ws = (char *)workspace;
     hipStream_t st = (hipStream_t)stream;
     s = debug_check(ws + L.hdr, natoms, dens, st, "dens");
@@ -977,11 +983,12 @@ static hfk_status fock_grad_impl(bool atoms, int64_t natoms, const double *xyz, 
         int strat = cfg.strategy;
         if (strat == HFK_STRATEGY_PRIVATE && !L.private_ok) strat = HFK_STRATEGY_ATOMIC;
         Layout LW = L;
+        LW.sub = kSubChunks;
         set_shape(LW, cfg.tile, cfg.gbras, cfg.kcopies);
         set_items(LW, strat, cfg.variant, precision);
         Layout LF = LW;
         const int fit = fock_resident_groups(ngauss, precision, cfg.variant, natoms, atoms);
-        LF.groups = forward_groups(LF, cus * (fit > 0 && cfg.gpc > fit ? fit : cfg.gpc));
+        LF.groups = block_groups(LF, cus * (fit > 0 && cfg.gpc > fit ? fit : cfg.gpc));
         PairPlan wplan = fock_plan(LF, ws, strat, precision, cfg.variant);
         wplan.info = plan.info;
         e = launch_pairs(LF, b, ws, xyz, xw, tau, precision, wplan, st);

@@ -61,6 +61,7 @@ struct GradArgs {
     const short *bexp;          // [g2][pcap] term exponents of the bras
     const int *kexp;            // [ket block of a wave][g2] maxima of the kets' exponents
     int tlim;                   // term_limit(tau)
+    int sub;                    // 64-ket chunks per wave of an item
     const double *dens;
     const double *xdens;    // X of the two-density contraction, or NULL (Gamma from D alone)
     const double *xyz;
@@ -124,6 +125,7 @@ void k_grad(GradArgs a)
     __syncthreads();
 
     double eacc = 0.0;
+    const int wkets = kWave * a.sub;
     // blocks (bra group, ket block K, bra) fetched from a global counter until exhausted
     const long long NB = ((cptr<DevHeader>)a.hdr)->blocks;
     const cptr<long long> goff = (cptr<long long>)a.goff, item_off = (cptr<long long>)a.item_off;
@@ -183,12 +185,12 @@ void k_grad(GradArgs a)
                 lim = ((cptr<int>)a.lim)[s];
                 ebra = lane < G2 ? (int)a.bexp[(int64_t)lane * a.pcap + s] : kTermNone;
             }
-            const long long wbase = (m - item_off[s]) * kItemKets + (long long)wave * kWaveKets;
+            const long long wbase = (m - item_off[s]) * (kWavesPerGroup * wkets) + wave * wkets;
             if (wbase >= lim) continue;
-            const cptr<int> kexp = (cptr<int>)(a.kexp + (int)(wbase / kWaveKets) * G2);
+            const cptr<int> kexp = (cptr<int>)(a.kexp + (int)(wbase / wkets) * G2);
             int *perm = wperm[wave];
             const int nvalid = pack_kets(wbase, lane, perm,
-                                         [&](long long t) { return t < lim && qs * a.pq[t] >= a.tau; });
+                                         [&](long long t) { return t < lim && qs * a.pq[t] >= a.tau; }, a.sub);
             if (nvalid == 0) continue;
             for (int c0 = 0; c0 < nvalid; c0 += kWave) {
                 const bool valid = c0 + lane < nvalid;
@@ -409,31 +411,60 @@ void k_grad(GradArgs a)
     }
 }
 
-// d_xyz = g_e2 * sum over workgroups; E2 = sum of partials (fixed order); d_dens = g_e2 * G.
-// d_xyz = scale * sum of the workgroup partials; scale = g_e2[0], or 1 when g_e2 is NULL
-// (the two-density contraction already carries it).
-// Sum of the workgroups' gradient copies: a workgroup takes kRedOut consecutive outputs, each
-// in kRedSlices interleaved slices of the copies (coalesced rows, many loads in flight), and
-// adds the slices in a fixed order.
-constexpr int kRedOut = 16, kRedSlices = 16;
-static_assert(kRedOut * kRedSlices == 256, "one 256-thread workgroup");
-__global__ __launch_bounds__(256) void k_grad_reduce(const double *__restrict__ gpriv, int groups, int64_t m,
-                                                     const double *__restrict__ g_e2, double *__restrict__ d_xyz)
+// The sums after the gradient kernel, in one launch:
+//   d_xyz = scale * sum of the workgroups' gradient copies, scale = g_e2[0], or 1 without g_e2
+//   (the two-density contraction already carries it): a workgroup takes kRedOut consecutive
+//   outputs, each in kRedSlices interleaved slices of the copies (coalesced rows, many loads in
+//   flight), and adds the slices in a fixed order;
+//   E2 = sum of the workgroups' partial energies (one workgroup, fixed order), if asked for;
+//   d_dens = g_e2 * G, if asked for.
+// (Sixteen slices in a launch of their own took 21 us at 128 atoms, the other two 4.5 us each.)
+constexpr int kRedOut = 16, kRedSlices = 64, kRedThreads = kRedOut * kRedSlices;
+__global__ __launch_bounds__(kRedThreads) void k_grad_finish(const double *__restrict__ gpriv, int groups, int m,
+                                                             const double *__restrict__ gscale,
+                                                             double *__restrict__ d_xyz,
+                                                             const double *__restrict__ epart,
+                                                             double *__restrict__ e2,
+                                                             const double *__restrict__ fock_in,
+                                                             const double *__restrict__ g_e2,
+                                                             double *__restrict__ d_dens, int64_t n2)
 {
-    __shared__ double part[kRedSlices][kRedOut];
-    const int o = threadIdx.x % kRedOut, sl = threadIdx.x / kRedOut;
-    const int64_t x = (int64_t)blockIdx.x * kRedOut + o;
-    double s = 0.0;
-    if (x < m) {
-        for (int gph = sl; gph < groups; gph += kRedSlices) s += gpriv[(int64_t)gph * m + x];
+    __shared__ double part[kRedThreads];
+    const int t = threadIdx.x, nred = (m + kRedOut - 1) / kRedOut;
+    if ((int)blockIdx.x < nred) {
+        const int o = t % kRedOut, sl = t / kRedOut, x = (int)blockIdx.x * kRedOut + o;
+        double s = 0.0;
+        if (x < m) {
+#pragma unroll 4
+            for (int c = sl; c < groups; c += kRedSlices) s += gpriv[(int64_t)c * m + x];
+        }
+        part[t] = s;
+        __syncthreads();
+        for (int w = kRedSlices / 2; w > 0; w >>= 1) {
+            if (sl < w) part[t] += part[t + w * kRedOut];
+            __syncthreads();
+        }
+        if (sl == 0 && x < m) d_xyz[x] = gscale ? gscale[0] * part[t] : part[t];
+        return;
     }
-    part[sl][o] = s;
-    __syncthreads();
-    if (sl == 0 && x < m) {
-        double t = part[0][o];
-        for (int k = 1; k < kRedSlices; ++k) t += part[k][o];
-        d_xyz[x] = g_e2 ? g_e2[0] * t : t;
+    int b = (int)blockIdx.x - nred;
+    if (e2) {
+        if (b == 0) {
+            double s = 0.0;
+            for (int c = t; c < groups; c += kRedThreads) s += epart[c];
+            part[t] = s;
+            __syncthreads();
+            for (int w = kRedThreads / 2; w > 0; w >>= 1) {
+                if (t < w) part[t] += part[t + w];
+                __syncthreads();
+            }
+            if (t == 0) *e2 = part[0];
+            return;
+        }
+        --b;
     }
+    const int64_t x = (int64_t)b * kRedThreads + t;
+    if (d_dens && x < n2) d_dens[x] = g_e2[0] * fock_in[x];
 }
 
 __global__ __launch_bounds__(256) void k_make_xw(int64_t n, const double *__restrict__ dens,
@@ -468,28 +499,6 @@ hipError_t launch_axpy_dev(int64_t m, const double *g_e2, const double *x, doubl
 {
     hipLaunchKernelGGL(k_axpy_dev, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, st, m, g_e2, x, y);
     return hipGetLastError();
-}
-
-__global__ __launch_bounds__(256) void k_grad_energy(const double *__restrict__ epart, int groups,
-                                                     double *__restrict__ e2)
-{
-    __shared__ double red[256];
-    double s = 0.0;
-    for (int b = threadIdx.x; b < groups; b += 256) s += epart[b];
-    red[threadIdx.x] = s;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if (threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) *e2 = red[0];
-}
-
-__global__ __launch_bounds__(256) void k_scale_copy(const double *__restrict__ src, int64_t m,
-                                                    const double *__restrict__ g_e2, double *__restrict__ dst)
-{
-    const int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (x < m) dst[x] = g_e2[0] * src[x];
 }
 
 size_t grad_smem_bytes(int64_t n, int prec)
@@ -570,7 +579,8 @@ hipError_t launch_grad(const Layout &L, const Basis &b, char *ws, const double *
     a.item_off = (const long long *)(ws + L.item_off);
     a.lim = (const int *)(ws + L.lim);
     a.bexp = (const short *)(ws + L.bexp);
-    a.kexp = (const int *)(ws + L.kexp256);
+    a.kexp = (const int *)(ws + (L.sub == kSubChunks ? L.kexp256 : L.kexp64));
+    a.sub = L.sub;
     a.tlim = term_limit(tau, prec);
     a.goff = (const long long *)(ws + L.goff);
     a.ngroups = L.ngroups;
@@ -607,15 +617,12 @@ hipError_t launch_grad(const Layout &L, const Basis &b, char *ws, const double *
         }
     }
     if (err != hipSuccess) return err;
-    const int64_t m = 3 * L.n;
-    hipLaunchKernelGGL(k_grad_reduce, dim3((unsigned)((m + kRedOut - 1) / kRedOut)), dim3(256), 0, st, a.gpriv,
-                       L.groups, m, xdens ? nullptr : g_e2, d_xyz);
-    if (e2_out) hipLaunchKernelGGL(k_grad_energy, dim3(1), dim3(256), 0, st, a.epart, L.groups, e2_out);
-    if (d_dens) {
-        const int64_t n2 = L.n * L.n;
-        hipLaunchKernelGGL(k_scale_copy, dim3((unsigned)((n2 + 255) / 256)), dim3(256), 0, st, fock_in, n2, g_e2,
-                           d_dens);
-    }
+    const int m = (int)(3 * L.n);
+    const int64_t n2 = L.n * L.n;
+    const unsigned nb = (unsigned)((m + kRedOut - 1) / kRedOut + (e2_out ? 1 : 0) +
+                                   (d_dens ? (n2 + kRedThreads - 1) / kRedThreads : 0));
+    hipLaunchKernelGGL(k_grad_finish, dim3(nb), dim3(kRedThreads), 0, st, (const double *)a.gpriv, L.groups, m,
+                       xdens ? nullptr : g_e2, d_xyz, (const double *)a.epart, e2_out, fock_in, g_e2, d_dens, n2);
     return hipGetLastError();
 }
 
