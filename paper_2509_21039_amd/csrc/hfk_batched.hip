@@ -243,7 +243,7 @@ __global__ __launch_bounds__(256) void k_b_tables(Basis b, const BasisDev *__res
     const int64_t at = (int64_t)blockIdx.x * 256;
     if (at >= (int64_t)S + 64) return;
     const int64_t pos = at + threadIdx.x;
-    const int g = b.g, g2 = b.g2, ab = blockIdx.y;
+    const int g2 = b.g2, ab = blockIdx.y;
     R *prim = (R *)T.prim, *bra = (R *)T.bra, *bip = (R *)T.bip;
     int e = kTermNever;
     if (pos < S) {
@@ -262,10 +262,10 @@ __global__ __launch_bounds__(256) void k_b_tables(Basis b, const BasisDev *__res
             T.pq[pos] = q[p];
             T.pd[pos] = dens[doff[m] + i * nm[m] + j];
         }
-        prim[(0 * g2 + ab) * pcap + pos] = (R)w.x;
-        prim[(1 * g2 + ab) * pcap + pos] = (R)w.y;
-        prim[(2 * g2 + ab) * pcap + pos] = (R)w.z;
-        prim[(3 * g2 + ab) * pcap + pos] = (R)w.S;
+        if (bip)
+            KetTable<R, false, true>::store(prim, pcap, ab, pos, (R)w.x, (R)w.y, (R)w.z, (R)w.S, (R)0, (R)(kTswitch / w.p));
+        else
+            KetTable<R, false, false>::store(prim, pcap, ab, pos, (R)w.x, (R)w.y, (R)w.z, (R)w.S, (R)0, (R)0);
         // bra row: centre, charge and the charge weighted by mu and by the fractions
         // fa = a/p, fb = b/p of the primitive pair (the gradient's bra weights)
         const double fb = b.aexp ? 1.0 - w.fa : w.fb;
@@ -273,18 +273,13 @@ __global__ __launch_bounds__(256) void k_b_tables(Basis b, const BasisDev *__res
                                    w.fa * fb * w.S, fb * fb * w.S, 0.0, 0.0, 0.0};
         R *ba = bra + (pos * g2 + ab) * kBBra;
         for (int x = 0; x < kBBra; ++x) ba[x] = (R)row[x];
-        if (bip) {
-            const R sw = (R)(kTswitch / w.p);
-            prim[(4 * g2 + ab) * pcap + pos] = sw;
-            bip[pos * g2 + ab] = sw;
-        }
+        if (bip) bip[pos * g2 + ab] = (R)(kTswitch / w.p);
         if (T.kmu) {
             T.kmu[(int64_t)ab * pcap + pos] = w.mu;
             T.kfa[(int64_t)ab * pcap + pos] = w.fa;
         }
         e = term_exponent(term_bound(w.S, w.p, w.mu, sqrt(w.ab2), T.grad));
         T.bexp[(int64_t)ab * pcap + pos] = (short)e;
-        (void)g;
     } else if (pos < (int64_t)S + 64) {
         if (ab == 0) {
             T.pk[pos] = 0;
@@ -292,8 +287,10 @@ __global__ __launch_bounds__(256) void k_b_tables(Basis b, const BasisDev *__res
             T.pq[pos] = 0.0;
             T.pd[pos] = 0.0;
         }
-        for (int x = 0; x < 4; ++x) prim[(x * g2 + ab) * pcap + pos] = x < 3 ? (R)1e6 : (R)0;
-        if (bip) prim[(4 * g2 + ab) * pcap + pos] = (R)1;
+        if (bip)
+            KetTable<R, false, true>::store(prim, pcap, ab, pos, (R)1e6, (R)1e6, (R)1e6, (R)0, (R)0, (R)1);
+        else
+            KetTable<R, false, false>::store(prim, pcap, ab, pos, (R)1e6, (R)1e6, (R)1e6, (R)0, (R)0, (R)1);
         if (T.kmu) {
             T.kmu[(int64_t)ab * pcap + pos] = 0.0;
             T.kfa[(int64_t)ab * pcap + pos] = 0.0;
@@ -562,21 +559,11 @@ __global__ __launch_bounds__(kBatchMaxThreads) void k_batched(BArgs a)
             if (!need[G - 1]) continue;
             R kx[G], ky[G], kz[G], ks[G], kp[G];
             R kms[G], kds[G], kcs[G], kcds[G];   // S_cd times mu_cd, fd, fc, fc fd
-            // buffer loads of the ket table: component and this cb's rows in the resource,
-            // the row as a scalar offset, the ket as a 32-bit lane offset
-            const unsigned tb = (unsigned)t * (unsigned)sizeof(R);
-            auto ld = [&](int c, int d) {
-                return ket_load<R>(ket_rows(prim, (int64_t)c * G2 + cb * G, a.pcap, G), tb,
-                                  (int)((int64_t)d * a.pcap * (int64_t)sizeof(R)));
-            };
 #pragma unroll
             for (int d = 0; d < G; ++d) {
                 if (G <= 4 && !need[d]) continue;   // no bra primitive pair reads it
-                kx[d] = ld(0, d);
-                ky[d] = ld(1, d);
-                kz[d] = ld(2, d);
-                ks[d] = ld(3, d);
-                kp[d] = kAtoms ? ld(4, d) : R(0);
+                R q;
+                KetTable<R, false, kAtoms>::load(prim, a.pcap, cb * G + d, (unsigned)t, kx[d], ky[d], kz[d], ks[d], q, kp[d]);
             }
             if (kGrad) {
 #pragma unroll
@@ -602,7 +589,7 @@ __global__ __launch_bounds__(kBatchMaxThreads) void k_batched(BArgs a)
                 constexpr int D0 = G - decltype(nd)::value;   // first term of the row
                 // every scalar of this bra primitive in one batch of scalar loads:
                 // Px Py Pz S mu*S fa*S fb*S fa*fb*S fb^2*S, and the switch data
-                const cptr<R> bp = bra + kBBra * ab;
+                const cptr<R> bp = at_bytes<R>(bra, (unsigned)ab * (kBBra * sizeof(R)));
                 R b[kGrad ? 9 : 4], u[4 * G], bsw = R(0);
 #pragma unroll
                 for (int c = 0; c < (kGrad ? 9 : 4); ++c) b[c] = bp[c];
@@ -610,7 +597,8 @@ __global__ __launch_bounds__(kBatchMaxThreads) void k_batched(BArgs a)
                     bsw = bipp[ab];
                     asm volatile("" ::"s"(bsw));
                 } else {
-                    const cptr<R> up = rsg + 4 * (ab * G2 + cb * G);
+                    const cptr<R> up =
+                        at_bytes<R>(rsg, ((unsigned)ab * G2 + (unsigned)cb * G) * (unsigned)(4 * sizeof(R)));
 #pragma unroll
                     for (int c = 4 * D0; c < 4 * G; ++c) u[c] = up[c];
 #pragma unroll

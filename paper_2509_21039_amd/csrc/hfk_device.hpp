@@ -312,51 +312,87 @@ template <int ND> struct TermCount {
     static constexpr int value = ND;
 };
 template <int G, int ND, typename T, typename Body>
-__device__ __attribute__((always_inline)) inline void term_dispatch(const T *need, T bit, int ab, Body &&body)
+__device__ __attribute__((always_inline)) inline void term_dispatch(const T *need, int ab, Body &&body)
 {
     constexpr int kStep = G <= 4 ? 1 : 2;
     if constexpr (ND - kStep < 1) {
         body(TermCount<ND>{}, ab);
     } else {
         // terms before the last ND - kStep: d < G - ND + kStep
-        if (need[G - ND + kStep - 1] & bit)
+        if ((need[G - ND + kStep - 1] >> ab) & 1)
             body(TermCount<ND>{}, ab);
         else
-            term_dispatch<G, ND - kStep>(need, bit, ab, body);
+            term_dispatch<G, ND - kStep>(need, ab, body);
     }
 }
 template <int G, typename T, typename Body>
 __device__ __attribute__((always_inline)) inline void for_terms(const T *need, Body &&body)
 {
-    for (T m = need[G - 1]; m;) {
-        const int ab = term_first(m);
-        const T bit = m & (~m + 1);
-        m ^= bit;
-        term_dispatch<G, G>(need, bit, ab, body);
+    for (T m = need[G - 1]; m; m &= m - 1) term_dispatch<G, G>(need, term_first(m), body);
+}
+
+// A uniform table at a 32-bit byte offset: the scalar load takes base and offset as they are.
+// (The offset is hidden from the optimiser, which otherwise forms the 64-bit sum of its parts.)
+template <typename R> __device__ inline cptr<R> at_bytes(cptr<R> base, unsigned bytes)
+{
+    asm("" : "+s"(bytes));
+    return (cptr<R>)((cptr<char>)base + bytes);
+}
+
+// Ket table: one row per primitive pair cd, and within a row the values of a pair in 16-byte
+// pieces, pair after pair: FP64 (Px, Py), (Pz, S) and a tail of |P|^2 (kQ) and kTswitch / p
+// (kAtoms); FP32 (Px, Py, Pz, S) and a tail of kTswitch / p (kAtoms).  A lane's ket is two or three
+// loads (FP32: one or two) of one buffer resource with the 64-bit part of the address in its
+// base; an 8-byte load takes the texture addresser as long as a 16-byte one (16 cycles per
+// wave), and a resource per value cost three scalar instructions each.  Offsets within a row
+// stay below 2^31 for up to 2^31 / 48 pairs.
+template <typename R, bool kQ, bool kAtoms> struct KetTable {
+    static constexpr bool kDouble = sizeof(R) == 8;
+    static constexpr int kTail = (kQ ? 1 : 0) + (kAtoms ? 1 : 0);
+    static constexpr int kRow = (4 + kTail) * (int)sizeof(R);          // bytes of a row per pair
+    static constexpr int kTailAt = 4 * (int)sizeof(R);                 // times pcap: where the tail starts
+
+    static __device__ void store(R *tab, int64_t pcap, int cd, int64_t t, R x, R y, R z, R S, R q, R sw)
+    {
+        char *row = (char *)tab + (int64_t)cd * kRow * pcap;
+        if constexpr (kDouble) {
+            ((double2 *)row)[t] = make_double2(x, y);
+            ((double2 *)(row + 16 * pcap))[t] = make_double2(z, S);
+        } else {
+            ((float4 *)row)[t] = make_float4(x, y, z, S);
+        }
+        R *tail = (R *)(row + (int64_t)kTailAt * pcap) + t * kTail;
+        if constexpr (kQ) tail[0] = q;
+        if constexpr (kAtoms) tail[kQ ? 1 : 0] = sw;
     }
-}
-
-// Buffer loads from an SoA table [C][g2][pcap] with the ket t as a 32-bit lane offset.  A
-// resource covers `rows` consecutive primitive-pair rows of one component starting at row
-// first_row (the 64-bit part of the address lives in the resource base), and the row within
-// it is the scalar offset d * pcap * sizeof(R): every offset and the record count stay below
-// 2^31 for tables of up to 2^31 / (rows * sizeof(R)) pairs, whatever the number of
-// components and primitive pairs in front.
-template <typename R>
-__device__ inline __amdgpu_buffer_rsrc_t ket_rows(const R *tab, int64_t first_row, int64_t pcap, int rows)
-{
-    return __builtin_amdgcn_make_buffer_rsrc((void *)(tab + first_row * pcap), (short)0,
-                                             (int)((int64_t)rows * pcap * (int64_t)sizeof(R)), 0x00020000);
-}
-
-template <typename R>
-__device__ inline R ket_load(__amdgpu_buffer_rsrc_t rc, unsigned voff, int soff)
-{
-    if constexpr (sizeof(R) == 8)
-        return __builtin_bit_cast(R, __builtin_amdgcn_raw_buffer_load_b64(rc, (int)voff, soff, 0));
-    else
-        return __builtin_bit_cast(R, __builtin_amdgcn_raw_buffer_load_b32(rc, (int)voff, soff, 0));
-}
+    static __device__ void load(const R *tab, int64_t pcap, int cd, unsigned t, R &x, R &y, R &z, R &S, R &q, R &sw)
+    {
+        const __amdgpu_buffer_rsrc_t rc = __builtin_amdgcn_make_buffer_rsrc(
+            (void *)((char *)const_cast<R *>(tab) + (int64_t)cd * kRow * pcap), (short)0, (int)(kRow * pcap), 0x00020000);
+        const auto v = __builtin_amdgcn_raw_buffer_load_b128(rc, (int)(t * 16u), 0, 0);
+        if constexpr (kDouble) {
+            const double2 xy = __builtin_bit_cast(double2, v);
+            const double2 zs = __builtin_bit_cast(
+                double2, __builtin_amdgcn_raw_buffer_load_b128(rc, (int)(t * 16u), (int)(16 * pcap), 0));
+            x = xy.x; y = xy.y; z = zs.x; S = zs.y;
+            if constexpr (kTail == 2) {
+                const double2 w = __builtin_bit_cast(
+                    double2, __builtin_amdgcn_raw_buffer_load_b128(rc, (int)(t * 16u), (int)(32 * pcap), 0));
+                q = w.x; sw = w.y;
+            } else if constexpr (kTail == 1) {
+                const double w = __builtin_bit_cast(
+                    double, __builtin_amdgcn_raw_buffer_load_b64(rc, (int)(t * 8u), (int)(32 * pcap), 0));
+                if constexpr (kQ) q = w; else sw = w;
+            }
+        } else {
+            const float4 w = __builtin_bit_cast(float4, v);
+            x = w.x; y = w.y; z = w.z; S = w.w;
+            if constexpr (kAtoms)
+                sw = __builtin_bit_cast(float,
+                                        __builtin_amdgcn_raw_buffer_load_b32(rc, (int)(t * 4u), (int)(16 * pcap), 0));
+        }
+    }
+};
 
 // Pair index p = i(i+1)/2 + j (i >= j) back to (i, j).
 __device__ inline void pair_of_index(int64_t p, int64_t &i, int64_t &j)

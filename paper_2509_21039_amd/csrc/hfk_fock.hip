@@ -157,11 +157,9 @@ __device__ inline R quartet_eri_direct(const R *__restrict__ lbra, const R *__re
         R kx[G], ky[G], kz[G], ks[G];
 #pragma unroll
         for (int d = 0; d < G; ++d) {
-            const int cd = cb * G + d;
-            kx[d] = prim[(int64_t)(0 * G2 + cd) * pcap + t];
-            ky[d] = prim[(int64_t)(1 * G2 + cd) * pcap + t];
-            kz[d] = prim[(int64_t)(2 * G2 + cd) * pcap + t];
-            ks[d] = prim[(int64_t)(3 * G2 + cd) * pcap + t];
+            R q, sw;
+            KetTable<R, sizeof(R) == 8, false>::load(prim, pcap, cb * G + d, (unsigned)t, kx[d], ky[d], kz[d], ks[d], q,
+                                                     sw);
         }
 #pragma unroll 1
         for (int ab = 0; ab < G2; ++ab) {
@@ -226,7 +224,6 @@ __device__ inline R quartet_eri_hybrid(cptr<R> bra, const R *__restrict__ prim, 
 {
     constexpr int G2 = G * G;
     constexpr bool kExpand = sizeof(R) == 8;
-    constexpr int kPComp = kExpand ? 5 : 4;   // ket component holding kTswitch / p (per-atom bases)
     using TM = typename TermMask<G>::T;
     // FP32 with up to three primitives loads the next cb's ket data while it works on this one
     // (the kernel has registers to spare: he1024 mixed 209.6 -> 203.2 ms); FP64 would drop from
@@ -237,26 +234,15 @@ __device__ inline R quartet_eri_hybrid(cptr<R> bra, const R *__restrict__ prim, 
     R eri = R(0);
     R kx[kSlots][G], ky[kSlots][G], kz[kSlots][G], ks[kSlots][G], kq[kSlots][G], kp[kSlots][G];
     TM need[kSlots][G];
-    // buffer loads: one resource per component over the G rows of a cb, the row as a scalar
-    // offset and the ket as a 32-bit lane offset (no 64-bit address math per lane)
-    const unsigned tb = t * (unsigned)sizeof(R);
     auto load_cb = [&](int cbl, int slot) {
         term_masks<G>(ebra, kexp + cbl * G, tlim, need[slot]);
-        auto ld = [&](int c, int d) {
-            return ket_load<R>(ket_rows(prim, (int64_t)c * G2 + cbl * G, pcap, G), tb,
-                               (int)((int64_t)d * pcap * (int64_t)sizeof(R)));
-        };
 #pragma unroll
         for (int d = 0; d < G; ++d) {
             // no bra primitive pair reads it (prefetched rows are loaded whole: with a known
             // number of loads in flight the wait for one row leaves the next one's running)
             if (!kPrefetch && G <= 4 && !need[slot][d]) continue;
-            kx[slot][d] = ld(0, d);
-            ky[slot][d] = ld(1, d);
-            kz[slot][d] = ld(2, d);
-            ks[slot][d] = ld(3, d);
-            kq[slot][d] = kExpand ? ld(4, d) : R(0);
-            kp[slot][d] = kAtoms ? ld(kPComp, d) : R(0);
+            KetTable<R, kExpand, kAtoms>::load(prim, pcap, cbl * G + d, t, kx[slot][d], ky[slot][d], kz[slot][d],
+                                               ks[slot][d], kq[slot][d], kp[slot][d]);
         }
     };
     constexpr int kCbUnroll = kPrefetch ? G : 1;   // the slots must be compile-time indices
@@ -271,7 +257,7 @@ __device__ inline R quartet_eri_hybrid(cptr<R> bra, const R *__restrict__ prim, 
         }
         for_terms<G>(need[cur], [&](auto nd, int ab) __attribute__((always_inline)) {
             constexpr int D0 = G - decltype(nd)::value;   // first term of the row
-            const cptr<R> bp = bra + 8 * ab;
+            const cptr<R> bp = at_bytes<R>(bra, (unsigned)ab * (8 * sizeof(R)));
             R b[8];
 #pragma unroll
             for (int c = 0; c < 8; ++c) b[c] = bp[c];
@@ -301,7 +287,7 @@ __device__ inline R quartet_eri_hybrid(cptr<R> bra, const R *__restrict__ prim, 
                     }
                 }
             } else {
-                const cptr<R> up = rsn + 3 * (ab * G2 + cb * G);
+                const cptr<R> up = at_bytes<R>(rsn, ((unsigned)ab * G2 + (unsigned)cb * G) * (unsigned)(3 * sizeof(R)));
                 R u[3 * G];
 #pragma unroll
                 for (int c = 3 * D0; c < 3 * G; ++c) u[c] = up[c];
@@ -384,7 +370,8 @@ void k_fock(FockArgs a)
             luni[2 * x + 1] = Prec<R>::srho(bd)[x];
         }
     }
-    const cptr<R> crs = (cptr<R>)Prec<R>::rsn(bd);
+    cptr<R> crs = (cptr<R>)Prec<R>::rsn(bd);
+    asm("" : "+s"(crs));   // a base of its own, not the table's place in the basis constants
     // a ket vector of the workgroup's own is cleared here, and added to without atomics unless
     // its waves meet on a ket
     const bool jown = a.jcopies >= ng, jshared = !jown || a.nsplit > 1;

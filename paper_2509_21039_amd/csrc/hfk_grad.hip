@@ -104,7 +104,6 @@ __global__ __launch_bounds__(kGroupThreads) __attribute__((amdgpu_waves_per_eu((
 void k_grad(GradArgs a)
 {
     constexpr int G2 = G * G;
-    constexpr int kPComp = sizeof(R) == 8 ? 5 : 4;   // ket component holding kTswitch / p
     // FP64 forms |P-Q|^2 from the expanded table entries (4 operations, centroid-centred
     // coordinates keep the cancellation near 1e-13 bohr^2); FP32 subtracts the centres
     constexpr bool kExpand = sizeof(R) == 8;
@@ -212,22 +211,11 @@ void k_grad(GradArgs a)
                     typename TermMask<G>::T need[G];
                     term_masks<G>(ebra, kexp + cb * G, a.tlim, need);
                     if (!need[G - 1]) continue;
-                    // buffer loads of the ket table: component and this cb's rows in the
-                    // resource, the row as a scalar offset, the ket as a 32-bit lane offset
-                    const unsigned tb = (unsigned)t * (unsigned)sizeof(R);
-                    auto ld = [&](int c, int d) {
-                        return ket_load<R>(ket_rows(prim, (int64_t)c * G2 + cb * G, a.pcap, G), tb,
-                                          (int)((int64_t)d * a.pcap * (int64_t)sizeof(R)));
-                    };
 #pragma unroll
                     for (int d = 0; d < G; ++d) {
                         if (G <= 4 && !need[d]) continue;   // no bra primitive pair reads it
-                        kx[d] = ld(0, d);
-                        ky[d] = ld(1, d);
-                        kz[d] = ld(2, d);
-                        ks[d] = ld(3, d);
-                        kp[d] = kAtoms ? ld(kPComp, d) : R(0);
-                        kq[d] = kExpand ? ld(4, d) : R(0);
+                        KetTable<R, kExpand, kAtoms>::load(prim, a.pcap, cb * G + d, (unsigned)t, kx[d], ky[d], kz[d], ks[d],
+                                                           kq[d], kp[d]);
                     }
                     // ket weights (mu_cd, fd, fc, fc fd): per lane for per-atom bases, else
                     // uniform scalars
@@ -257,8 +245,8 @@ void k_grad(GradArgs a)
                         // every scalar of this bra primitive in one batch of scalar loads: the
                         // centre and charge, the weights mu S, fa S, fb S, fa fb S, fb^2 S, and
                         // the switch data
-                        const cptr<R> bp = bra + 8 * ab;
-                        const cptr<R> wp = bwp + kGW * ab;
+                        const cptr<R> bp = at_bytes<R>(bra, (unsigned)ab * (8 * sizeof(R)));
+                        const cptr<R> wp = at_bytes<R>(bwp, (unsigned)ab * (kGW * sizeof(R)));
                         R b[8], bw[5], u[4 * G], bsw = R(0);
 #pragma unroll
                         for (int c = 0; c < (kExpand ? 8 : 4); ++c) b[c] = bp[c];
@@ -268,7 +256,8 @@ void k_grad(GradArgs a)
                             bsw = bipp[ab];
                             asm volatile("" ::"s"(bsw));
                         } else {
-                            const cptr<R> up = rsg + 4 * (ab * G2 + cb * G);
+                            const cptr<R> up =
+                                at_bytes<R>(rsg, ((unsigned)ab * G2 + (unsigned)cb * G) * (unsigned)(4 * sizeof(R)));
 #pragma unroll
                             for (int c = 4 * D0; c < 4 * G; ++c) u[c] = up[c];
 #pragma unroll

@@ -234,13 +234,12 @@ __global__ __launch_bounds__(256) void k_bucket_cursors(const long long *__restr
 }
 
 // Writes the tables of every significant pair at its position x, holding pair slot[x]: atoms, Q,
-// D_kl, the SoA primitive-pair table {Px, Py, Pz, S, |P|^2} centred on the centroid and the
+// D_kl, the ket table {Px, Py, Pz, S, |P|^2} centred on the centroid (see KetTable) and the
 // bra rows, for the precision of the build.  One thread per (position, primitive pair): the
 // grid's y dimension is the primitive pair, so the table rows are written coalesced and the
 // exponentials of a pair run side by side (one thread per pair took 24 us at 64 atoms and
-// 81 us with six primitives).  With per-atom bases (bip != NULL) the ket tables gain
-// kTswitch / p as their last component (FP64 component 5, FP32 component 4) and bip receives
-// it per bra primitive pair: the two add up to kTswitch / rho of the quartet.  The 64
+// 81 us with six primitives).  With per-atom bases (bip != NULL) the ket table gains
+// kTswitch / p as its last value and bip receives it per bra primitive pair: the two add up to kTswitch / rho of the quartet.  The 64
 // positions after the last pair are padded with harmless entries (atom 0, zero weight, centres
 // 1e6 bohr away), so that lanes past the last pair, or lanes pointed at the first pad entry,
 // read defined memory and land in the far branch with a zero integral.  A wave also leaves the
@@ -300,19 +299,15 @@ __global__ __launch_bounds__(256) void k_pair_tables(Basis b, const BasisDev *__
             T.posof[p] = (int)pos;
             for (int c = 0; c < T.jcopies; ++c) T.jzero[(int64_t)c * pcap + pos] = 0.0;
         }
-        prim[(0 * g2 + ab) * pcap + pos] = (R)px;
-        prim[(1 * g2 + ab) * pcap + pos] = (R)py;
-        prim[(2 * g2 + ab) * pcap + pos] = (R)pz;
-        prim[(3 * g2 + ab) * pcap + pos] = (R)ps;
-        if (kDouble) prim[(4 * g2 + ab) * pcap + pos] = (R)p2;
+        if (bip)
+            KetTable<R, kDouble, true>::store(prim, pcap, ab, pos, (R)px, (R)py, (R)pz, (R)ps, (R)p2,
+                                              (R)(kTswitch / p_ab));
+        else
+            KetTable<R, kDouble, false>::store(prim, pcap, ab, pos, (R)px, (R)py, (R)pz, (R)ps, (R)p2, (R)0);
         R *ba = bra + (pos * g2 + ab) * 8;
         ba[0] = (R)px; ba[1] = (R)py; ba[2] = (R)pz; ba[3] = (R)ps;
         ba[4] = (R)(-2.0 * px); ba[5] = (R)(-2.0 * py); ba[6] = (R)(-2.0 * pz); ba[7] = (R)p2;
-        if (bip) {
-            const R ip = (R)(kTswitch / p_ab);
-            prim[((kDouble ? 5 : 4) * g2 + ab) * pcap + pos] = ip;
-            bip[pos * g2 + ab] = ip;
-        }
+        if (bip) bip[pos * g2 + ab] = (R)(kTswitch / p_ab);
         if (T.kmu) {
             // per-atom gradient: mu and a/p of every ket primitive pair
             T.kmu[(int64_t)ab * pcap + pos] = mu;
@@ -334,10 +329,11 @@ __global__ __launch_bounds__(256) void k_pair_tables(Basis b, const BasisDev *__
             T.pq[pos] = 0.0;
             T.pd[pos] = 0.0;
         }
-        for (int c = 0; c < 4; ++c) prim[(c * g2 + ab) * pcap + pos] = c < 3 ? (R)1e6 : (R)0;
-        if (kDouble) prim[(4 * g2 + ab) * pcap + pos] = (R)3e12;
-        // kTswitch / p: the switch radius stays far below the pad distance
-        if (bip) prim[((kDouble ? 5 : 4) * g2 + ab) * pcap + pos] = (R)1;
+        // kTswitch / p = 1: the switch radius stays far below the pad distance
+        if (bip)
+            KetTable<R, kDouble, true>::store(prim, pcap, ab, pos, (R)1e6, (R)1e6, (R)1e6, (R)0, (R)3e12, (R)1);
+        else
+            KetTable<R, kDouble, false>::store(prim, pcap, ab, pos, (R)1e6, (R)1e6, (R)1e6, (R)0, (R)3e12, (R)1);
         if (T.kmu) {
             T.kmu[(int64_t)ab * pcap + pos] = 0.0;
             T.kfa[(int64_t)ab * pcap + pos] = 0.0;
