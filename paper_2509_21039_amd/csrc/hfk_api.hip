@@ -69,6 +69,7 @@ Layout make_layout(int64_t n, int g, int prec, int with_grad, int groups, bool a
     L.tile = prec == HFK_MIXED ? 2 * kTileItems : kTileItems;
     L.gshift = 10;   // kGroupBras
     L.sub = kSubChunks;
+    L.nw = kWavesPerGroup;
     L.nsplit = 1;
     L.kcopies = 0;
     L.private_ok = !compact && (double)groups * (double)n * (double)n * 8.0 <= kPrivateBudget;
@@ -315,15 +316,16 @@ static thread_local const BatchedConfig *g_force_b = nullptr;
 // MI355X for He 64 to 1024 and H/He 128, FP64 and mixed: ATOMIC was the faster strategy at
 // every size (the per-workgroup copies of F and their summation cost more than the atomics
 // they save), with as many workgroups per CU as fit (four up to 64 atoms: mixed 198 against
-// 204 us).  Blocks of eight items (fewer row flushes) up to 256 atoms and with the FP32 ket
-// table; four with the larger FP64 one, which then stays in L2; one where the waves of a
+// 204 us).  Blocks of eight items (he512 FP64 the same with four, 300 atoms 10.5 with four and
+// 10.4 ms, 1024 at 3 bohr 28.6 and 28.2, he1024 mixed 119 and 115); one where the waves of a
 // workgroup share long chunks (20 atoms with six primitives: 99 against 124 us with two).
 // Groups of 1024 bras.  Eight shared ket-side Coulomb vectors: they stay cached where one per
 // workgroup does not (he512 FP64 68.0 against 69.2 ms, he1024 mixed 210.0 against 221.2 ms,
 // he128 2.12 against 2.19 ms).
 static TunedConfig default_config(int64_t n, int precision, int ngauss)
 {
-    int tile = n <= 256 || precision == HFK_MIXED ? 2 * kTileItems : kTileItems;
+    (void)precision;
+    int tile = 2 * kTileItems;
     if (ngauss >= 5 && n * (n + 1) / 2 <= 400) tile = 1;
     return TunedConfig{HFK_STRATEGY_ATOMIC, 1, n <= 64 ? 4 : 6, tile, kGroupBras, kDefaultKetCopies};
 }
@@ -390,6 +392,7 @@ static int block_groups(const Layout &L, int groups)
 static void set_items(Layout &L, int strat, int variant, int precision)
 {
     if (strat == HFK_STRATEGY_DETERMINISTIC) return;
+    L.nw = fock_waves_per_group(L.g, precision, variant, L.n, L.atoms, false);
     const int64_t one_chunk = L.g >= 5 ? 8192 : (L.atoms ? 6000 : 2500);
     if (L.npair > one_chunk) return;
     L.sub = 1;
@@ -633,7 +636,7 @@ static hfk_status fock_one_basis(int64_t natoms, const double *xyz, int32_t ngau
     {
         // no more persistent workgroups than fit on a CU at once
         const bool det = strat == HFK_STRATEGY_DETERMINISTIC;
-        const int fit = fock_resident_groups(ngauss, precision, cfg.variant, natoms, false, det);
+        const int fit = fock_resident_groups(ngauss, precision, cfg.variant, natoms, false, det, L.nw);
         L.groups = block_groups(L, cus * (fit > 0 && cfg.gpc > fit ? fit : cfg.gpc));
         if (det) {
             hfk_status sd = det_groups(L);
@@ -753,7 +756,7 @@ hfk_status hfk_fock_atoms(int64_t natoms, const double *xyz, int32_t ngauss, con
     set_items(L, strat, 1, precision);
     {
         const bool det = strat == HFK_STRATEGY_DETERMINISTIC;
-        const int fit = fock_resident_groups(ngauss, precision, 1, natoms, true, det);
+        const int fit = fock_resident_groups(ngauss, precision, 1, natoms, true, det, L.nw);
         L.groups = block_groups(L, cus * (fit > 0 && cfg.gpc > fit ? fit : cfg.gpc));
         if (det) {
             hfk_status sd = det_groups(L);
@@ -837,7 +840,7 @@ hfk_status hfk_scf(int64_t natoms, const double *xyz, const double *charges_host
     set_items(L, strat, 1, precision);
     {
         const bool det = strat == HFK_STRATEGY_DETERMINISTIC;
-        const int fit = fock_resident_groups(ngauss, precision, 1, natoms, true, det);
+        const int fit = fock_resident_groups(ngauss, precision, 1, natoms, true, det, L.nw);
         L.groups = block_groups(L, cus * (fit > 0 && cfg.gpc > fit ? fit : cfg.gpc));
         if (det) {
             hfk_status sd = det_groups(L);
@@ -984,10 +987,11 @@ static hfk_status fock_grad_impl(bool atoms, int64_t natoms, const double *xyz, 
         if (strat == HFK_STRATEGY_PRIVATE && !L.private_ok) strat = HFK_STRATEGY_ATOMIC;
         Layout LW = L;
         LW.sub = kSubChunks;
+        LW.nw = kWavesPerGroup;
         set_shape(LW, cfg.tile, cfg.gbras, cfg.kcopies);
         set_items(LW, strat, cfg.variant, precision);
         Layout LF = LW;
-        const int fit = fock_resident_groups(ngauss, precision, cfg.variant, natoms, atoms);
+        const int fit = fock_resident_groups(ngauss, precision, cfg.variant, natoms, atoms, false, LW.nw);
         LF.groups = block_groups(LF, cus * (fit > 0 && cfg.gpc > fit ? fit : cfg.gpc));
         PairPlan wplan = fock_plan(LF, ws, strat, precision, cfg.variant);
         wplan.info = plan.info;

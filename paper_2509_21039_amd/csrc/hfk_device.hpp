@@ -443,10 +443,12 @@ __device__ inline double wave_sum(double v)
 __device__ inline int lane_id() { return (int)__lane_id(); }
 
 // Packs this wave's kets t = base + r * 64 + lane (r < sub <= kSubChunks) for which keep(t) holds
-// into perm[0 .. count), in ascending order (ballot + lane count, no atomics), and returns
-// the wave-uniform count.
+// into perm[0 .. count), as their distance from base (below 256), in ascending order (ballot +
+// lane count, no atomics), and returns the wave-uniform count.
+static_assert(kWave * kSubChunks <= 256, "distances fit a byte");
 template <typename Keep>
-__device__ inline int pack_kets(long long base, int lane, int *__restrict__ perm, Keep keep, int sub = kSubChunks)
+__device__ inline int pack_kets(long long base, int lane, unsigned char *__restrict__ perm, Keep keep,
+                                int sub = kSubChunks)
 {
     int count = 0;
 #pragma unroll
@@ -457,7 +459,7 @@ __device__ inline int pack_kets(long long base, int lane, int *__restrict__ perm
         const unsigned long long mk = __builtin_amdgcn_ballot_w64(ok);
         if (ok)
             perm[count + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(mk >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mk, 0u))] =
-                (int)t;
+                (unsigned char)(r * kWave + lane);
         count += (int)__popcll(mk);
     }
     __builtin_amdgcn_wave_barrier();

@@ -319,11 +319,34 @@ template <typename R> struct FockSmem {
     static constexpr size_t uni_bytes = 4 * sizeof(R) * 16 + 2 * sizeof(R) * kCombos;   // bra, (rho, srho)
     // deterministic strategy: per wave, kWaveKets staged updates (v, then k and l)
     static constexpr size_t stage_bytes = kWavesPerGroup * kWaveKets * (sizeof(double) + 2 * sizeof(int));
-    static size_t total(int n, bool split, bool det = false)
+    // rows i and j of F, and (drows) of D; per wave, the packed kets of the hybrid form
+    static size_t total(int n, bool split, bool det, bool drows, int nw)
     {
-        return sizeof(double) * 2 * (size_t)n + tab_bytes + (split ? 0 : uni_bytes) + (det ? stage_bytes : 0);
+        return sizeof(double) * (drows ? 4 : 2) * (size_t)n + tab_bytes + (split ? (size_t)nw * kWaveKets : uni_bytes) +
+               (det ? stage_bytes : 0);
     }
 };
+constexpr size_t kCuLds = (size_t)160 << 10, kStaticLds = 256;   // a CU's LDS; what the kernel declares itself
+
+// Workgroups of nw waves that the LDS and the waves the registers allow (five per SIMD in FP64,
+// six in FP32) leave a CU.
+static int fock_groups(int64_t n, int prec, bool drows, int nw)
+{
+    const size_t need = (prec == HFK_MIXED ? FockSmem<float>::total((int)n, true, false, drows, nw)
+                                           : FockSmem<double>::total((int)n, true, false, drows, nw)) + kStaticLds;
+    const int by_lds = (int)(kCuLds / need), by_waves = (prec == HFK_MIXED ? 24 : 20) / nw;
+    return by_lds < by_waves ? by_lds : by_waves;
+}
+
+// Rows i and j of D in LDS too, for the hybrid form with up to three primitives outside the
+// deterministic strategy, where no workgroup is lost for it: reading D_ik, D_il, D_jk and D_jl
+// from memory takes 256 of the 600 texture-addresser cycles of 64 quartets (64 lanes, as many
+// lines each).  300 atoms FP64 10.7 -> 10.4 ms, 512 mixed 23.1 -> 22.3; where the rows cost a
+// workgroup (512 FP64: four per CU for five) 40.2 -> 42.5.
+static bool fock_drows(int g, int64_t n, int prec, bool split, bool det, int nw)
+{
+    return g <= 3 && split && !det && fock_groups(n, prec, true, nw) >= fock_groups(n, prec, false, nw);
+}
 
 // Waves per SIMD the compiler has to leave room for where it ends just above the register
 // count of one more by itself: FP64 per-atom bases with three primitives (97 VGPRs; 96 for five
@@ -332,9 +355,14 @@ template <int G, typename R, bool kAtoms> constexpr int fock_waves()
 {
     return sizeof(R) == 8 ? (G == 3 && kAtoms ? 5 : (G >= 5 && !kAtoms ? 4 : 1)) : 1;
 }
-template <int G, typename R, bool kSplit, bool kAtoms = false, bool kDet = false>
-__global__ __launch_bounds__(kGroupThreads) __attribute__((amdgpu_waves_per_eu(kDet ? 1 : fock_waves<G, R, kAtoms>())))
-void k_fock(FockArgs a)
+// Widest workgroup: the hybrid form with up to three primitives (below 128 VGPRs).
+template <int G, bool kSplit, bool kDet> constexpr int fock_max_threads()
+{
+    return kSplit && !kDet && G <= 3 ? 1024 : kGroupThreads;
+}
+template <int G, typename R, bool kSplit, bool kAtoms = false, bool kDet = false, bool kDRows = false>
+__global__ __launch_bounds__((fock_max_threads<G, kSplit, kDet>()))
+__attribute__((amdgpu_waves_per_eu(kDet ? 1 : fock_waves<G, R, kAtoms>()))) void k_fock(FockArgs a)
 {
     constexpr int G2 = G * G;
     extern __shared__ __attribute__((aligned(16))) double smem[];
@@ -346,6 +374,8 @@ void k_fock(FockArgs a)
     double *rowi = (double *)sp;
     double *rowj = rowi + n;
     sp += sizeof(double) * 2 * (size_t)n;
+    double2 *dij = (double2 *)sp;           // kDRows: (D_ic, D_jc)
+    if (kDRows) sp += sizeof(double2) * (size_t)n;
     R *lbra = (R *)sp;                      // direct form: [G2][4] Px, Py, Pz, S of the current bra
     R *luni = lbra + 4 * 16;                // direct form: (rho, sqrt rho) per primitive quartet
     // deterministic strategy: staged exchange updates of each wave (the hybrid form has no
@@ -354,18 +384,18 @@ void k_fock(FockArgs a)
     int *stk = (int *)(stv + kWavesPerGroup * kWaveKets);         // [waves][kWaveKets] k
     int *stl = stk + kWavesPerGroup * kWaveKets;                  // [waves][kWaveKets] l
     __shared__ double jbs[kWavesPerGroup];
-    __shared__ int wperm[kWavesPerGroup][kWaveKets];
-
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, nthr = (int)blockDim.x, nw = nthr / kWave;
     const int wave = uniform(tid / kWave);
     const int lane = tid % kWave;
+    // hybrid form: the packed kets of each wave, after the staged updates if there are any
+    unsigned char *perm = (unsigned char *)(kDet ? (char *)(stl + kWavesPerGroup * kWaveKets) : sp) + wave * kWaveKets;
     const int gid = blockIdx.x, ng = gridDim.x;
     const int S = ((cptr<DevHeader>)a.hdr)->sig_pairs;
     const BasisDev *bd = a.bd;
 
-    load_boys<R>(tab, Prec<R>::boys(kSplit), BoysGrid<R>::rows * BoysGrid<R>::stride, tid, kGroupThreads);
+    load_boys<R>(tab, Prec<R>::boys(kSplit), BoysGrid<R>::rows * BoysGrid<R>::stride, tid, nthr);
     if (!kSplit) {
-        for (int x = tid; x < G2 * G2; x += kGroupThreads) {
+        for (int x = tid; x < G2 * G2; x += nthr) {
             luni[2 * x] = Prec<R>::rho(bd)[x];
             luni[2 * x + 1] = Prec<R>::srho(bd)[x];
         }
@@ -377,15 +407,15 @@ void k_fock(FockArgs a)
     const bool jown = a.jcopies >= ng, jshared = !jown || a.nsplit > 1;
     // waves that share a chunk each take every kWavesPerGroup-th bra primitive pair
     const bool myterms = lane < G2 && (a.nsplit == 1 || lane % kWavesPerGroup == wave);
-    const int wkets = kWave * a.sub, ikets = (a.nsplit > 1 ? 1 : kWavesPerGroup) * wkets;
+    const int wkets = kWave * a.sub, ikets = (a.nsplit > 1 ? 1 : nw) * wkets;
     double *jcol = a.jcol + (int64_t)(gid % a.jcopies) * a.pcap;
     const bool priv = kDet || a.strategy == HFK_STRATEGY_PRIVATE;
     double *fp = priv ? a.fpriv + (int64_t)gid * n * n : a.fpriv;
     if (priv) {
-        for (int64_t x = tid; x < (int64_t)n * n; x += kGroupThreads) fp[x] = 0.0;
+        for (int64_t x = tid; x < (int64_t)n * n; x += nthr) fp[x] = 0.0;
     }
     if (jown) {
-        for (int64_t x = tid; x < S; x += kGroupThreads) jcol[x] = 0.0;
+        for (int64_t x = tid; x < S; x += nthr) jcol[x] = 0.0;
     }
     __syncthreads();
     const R *prim = Prec<R>::prim(a);
@@ -442,15 +472,15 @@ void k_fock(FockArgs a)
                 double *fi = fp + (int64_t)bi * n, *fj = fp + (int64_t)bj * n;
                 if (priv) {
                     if (bi == bj) {
-                        for (int c = tid; c < n; c += kGroupThreads) fi[c] += rowi[c] + rowj[c];
+                        for (int c = tid; c < n; c += nthr) fi[c] += rowi[c] + rowj[c];
                     } else {
-                        for (int c = tid; c < n; c += kGroupThreads) {
+                        for (int c = tid; c < n; c += nthr) {
                             fi[c] += rowi[c];
                             fj[c] += rowj[c];
                         }
                     }
                 } else {
-                    for (int c = tid; c < n; c += kGroupThreads) {
+                    for (int c = tid; c < n; c += nthr) {
                         const double vi = rowi[c], vj = rowj[c];
                         if (vi != 0.0) atomicAdd(&fi[c], vi);
                         if (vj != 0.0) atomicAdd(&fj[c], vj);
@@ -461,15 +491,17 @@ void k_fock(FockArgs a)
             if (m == m1) break;
             const R *br = Prec<R>::bra(a) + (int64_t)s * 8 * G2;
             if (!kSplit && tid < 4 * G2) lbra[tid] = br[8 * (tid / 4) + tid % 4];
-            for (int c = tid; c < n; c += kGroupThreads) {
-                rowi[c] = 0.0;
-                rowj[c] = 0.0;
-            }
-            __syncthreads();
-            cur = s;
             // scalar loads: the bra's data stays in scalar registers
             bi = ((cptr<int>)a.pk)[s];
             bj = ((cptr<int>)a.pl)[s];
+            for (int c = tid; c < n; c += nthr) {
+                rowi[c] = 0.0;
+                rowj[c] = 0.0;
+                if constexpr (kDRows)
+                    dij[c] = make_double2(a.dens[(int64_t)bi * n + c], a.dens[(int64_t)bj * n + c]);
+            }
+            __syncthreads();
+            cur = s;
             qs = ((cptr<double>)a.pq)[s];
             ds = ((cptr<double>)a.pd)[s];
             lim = ((cptr<int>)a.lim)[s];
@@ -508,23 +540,30 @@ void k_fock(FockArgs a)
                     stk[wave * kWaveKets + slot] = k;
                     stl[wave * kWaveKets + slot] = l;
                 } else {
-                    const double *Di = a.dens + (int64_t)bi * n;
-                    const double *Dj = a.dens + (int64_t)bj * n;
-                    atomicAdd(&rowi[k], -Dj[l] * v);
-                    atomicAdd(&rowi[l], -Dj[k] * v);
-                    atomicAdd(&rowj[k], -Di[l] * v);
-                    atomicAdd(&rowj[l], -Di[k] * v);
+                    double2 Dk, Dl;
+                    if constexpr (kDRows) {
+                        Dk = dij[k];
+                        Dl = dij[l];
+                    } else {
+                        const double *Di = a.dens + (int64_t)bi * n;
+                        const double *Dj = a.dens + (int64_t)bj * n;
+                        Dk = make_double2(Di[k], Dj[k]);
+                        Dl = make_double2(Di[l], Dj[l]);
+                    }
+                    atomicAdd(&rowi[k], -Dl.y * v);
+                    atomicAdd(&rowi[l], -Dk.y * v);
+                    atomicAdd(&rowj[k], -Dl.x * v);
+                    atomicAdd(&rowj[l], -Dk.x * v);
                 }
             }
         };
         if constexpr (kDet) {
             int nvalid = 0;
             if (wbase < lim) {
-                int *perm = wperm[wave];
                 nvalid = pack_kets(wbase, lane, perm, [&](long long t) { return t < lim && qs * a.pq[t] >= a.tau; });
                 for (int c0 = 0; c0 < nvalid; c0 += kWave) {
                     const bool valid = c0 + lane < nvalid;
-                    chunk(valid ? perm[c0 + lane] : S, valid, c0 + lane);
+                    chunk(valid ? (int)wbase + perm[c0 + lane] : S, valid, c0 + lane);
                 }
             }
             // every wave's updates are staged; apply them wave after wave
@@ -546,13 +585,12 @@ void k_fock(FockArgs a)
             }
         } else if (kSplit) {
             // keep the screened kets of this wave's 256, in order, packed into full chunks
-            int *perm = wperm[wave];
             const int nvalid = pack_kets(wbase, lane, perm,
                                          [&](long long t) { return t < lim && qs * a.pq[t] >= a.tau; }, a.sub);
             if (nvalid == 0) continue;
             for (int c0 = 0; c0 < nvalid; c0 += kWave) {
                 const bool valid = c0 + lane < nvalid;
-                chunk(valid ? perm[c0 + lane] : S, valid, 0);   // S: first pad entry
+                chunk(valid ? (int)wbase + perm[c0 + lane] : S, valid, 0);   // S: first pad entry
             }
             __builtin_amdgcn_wave_barrier();
         } else {
@@ -655,87 +693,89 @@ __global__ __launch_bounds__(256) void k_energy(const double *__restrict__ part,
     if (threadIdx.x == 0) *e2 = 0.5 * red[0];
 }
 
+template <int G, typename R> using FockKernel = void (*)(FockArgs);
+
+// The kernel of a build: the direct form keeps a bra's primitive data in LDS slots sized for
+// g <= 4; per-atom bases and the deterministic strategy run the hybrid form only.
 template <int G, typename R>
-static hipError_t launch_fock_t(const FockArgs &a, int groups, int variant, bool atoms, hipStream_t st)
+static FockKernel<G, R> fock_kernel(bool split, bool atoms, bool det, bool drows)
 {
-    // the direct form keeps a bra's primitive data in LDS slots sized for g <= 4; per-atom
-    // bases and the deterministic strategy run the hybrid form only
+    (void)drows;
+    (void)split;
+    if (det) return atoms ? k_fock<G, R, true, true, true> : k_fock<G, R, true, false, true>;
+    if constexpr (G <= 3) {
+        if (drows) return atoms ? k_fock<G, R, true, true, false, true> : k_fock<G, R, true, false, false, true>;
+    }
+    if (atoms) return k_fock<G, R, true, true>;
+    if constexpr (G <= 4) {
+        if (!split) return k_fock<G, R, false>;
+    }
+    return k_fock<G, R, true>;
+}
+
+template <int G, typename R>
+static hipError_t launch_fock_t(const FockArgs &a, int groups, int nw, int variant, bool atoms, hipStream_t st)
+{
     const bool det = a.strategy == HFK_STRATEGY_DETERMINISTIC;
     const bool split = G > 4 || variant != 0 || atoms || det;
-    const size_t smem = FockSmem<R>::total(a.n, split, det);
+    const bool drows = fock_drows(G, a.n, sizeof(R) == 8 ? HFK_FP64 : HFK_MIXED, split, det, nw);
+    const size_t smem = FockSmem<R>::total(a.n, split, det, drows, nw);
     profile_begin(st);
-    if (det) {
-        if (atoms)
-            hipLaunchKernelGGL((k_fock<G, R, true, true, true>), dim3(groups), dim3(kGroupThreads), smem, st, a);
-        else
-            hipLaunchKernelGGL((k_fock<G, R, true, false, true>), dim3(groups), dim3(kGroupThreads), smem, st, a);
-    } else if (atoms) {
-        hipLaunchKernelGGL((k_fock<G, R, true, true>), dim3(groups), dim3(kGroupThreads), smem, st, a);
-    } else if constexpr (G > 4) {
-        hipLaunchKernelGGL((k_fock<G, R, true>), dim3(groups), dim3(kGroupThreads), smem, st, a);
-    } else {
-        if (split)
-            hipLaunchKernelGGL((k_fock<G, R, true>), dim3(groups), dim3(kGroupThreads), smem, st, a);
-        else
-            hipLaunchKernelGGL((k_fock<G, R, false>), dim3(groups), dim3(kGroupThreads), smem, st, a);
-    }
+    hipLaunchKernelGGL((fock_kernel<G, R>(split, atoms, det, drows)), dim3(groups), dim3(nw * kWave), smem, st, a);
     profile_end(st);
     return hipGetLastError();
 }
 
 template <int G, typename R>
-static int resident_t(bool split, size_t smem, bool atoms, bool det)
+static int resident_t(bool split, bool atoms, bool det, int64_t n, int nw)
 {
+    split = split || G > 4;
+    const bool drows = fock_drows(G, n, sizeof(R) == 8 ? HFK_FP64 : HFK_MIXED, split, det, nw);
+    const size_t smem = FockSmem<R>::total((int)n, split, det, drows, nw);
     int nb = 0;
-    hipError_t e;
-    if (det) {
-        e = atoms ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_fock<G, R, true, true, true>, kGroupThreads,
-                                                                 smem)
-                  : hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_fock<G, R, true, false, true>, kGroupThreads,
-                                                                 smem);
-    } else if (atoms) {
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_fock<G, R, true, true>, kGroupThreads, smem);
-    } else if constexpr (G > 4) {
-        (void)split;
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_fock<G, R, true>, kGroupThreads, smem);
-    } else {
-        e = split ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_fock<G, R, true>, kGroupThreads, smem)
-                  : hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_fock<G, R, false>, kGroupThreads, smem);
-    }
+    const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
+        &nb, reinterpret_cast<const void *>(fock_kernel<G, R>(split, atoms, det, drows)), nw * kWave, smem);
     return e == hipSuccess ? nb : 0;
 }
 
 // Workgroups of the quartet kernel that fit on one CU at once (registers and LDS); 0 if
 // the runtime cannot tell.  Persistent workgroups beyond this would only queue.
-int fock_resident_groups(int g, int prec, int variant, int64_t n, bool atoms, bool det)
+int fock_resident_groups(int g, int prec, int variant, int64_t n, bool atoms, bool det, int nw)
 {
     const bool split = variant != 0 || atoms || det;
-    const size_t smem = prec == HFK_MIXED ? FockSmem<float>::total((int)n, split, det)
-                                          : FockSmem<double>::total((int)n, split, det);
     if (prec == HFK_MIXED) {
         switch (g) {
-        case 1: return resident_t<1, float>(split, smem, atoms, det);
-        case 2: return resident_t<2, float>(split, smem, atoms, det);
-        case 3: return resident_t<3, float>(split, smem, atoms, det);
-        case 4: return resident_t<4, float>(split, smem, atoms, det);
-        case 5: return resident_t<5, float>(true, smem, atoms, det);
-        default: return resident_t<6, float>(true, smem, atoms, det);
+        case 1: return resident_t<1, float>(split, atoms, det, n, nw);
+        case 2: return resident_t<2, float>(split, atoms, det, n, nw);
+        case 3: return resident_t<3, float>(split, atoms, det, n, nw);
+        case 4: return resident_t<4, float>(split, atoms, det, n, nw);
+        case 5: return resident_t<5, float>(split, atoms, det, n, nw);
+        default: return resident_t<6, float>(split, atoms, det, n, nw);
         }
     }
     switch (g) {
-    case 1: return resident_t<1, double>(split, smem, atoms, det);
-    case 2: return resident_t<2, double>(split, smem, atoms, det);
-    case 3: return resident_t<3, double>(split, smem, atoms, det);
-    case 4: return resident_t<4, double>(split, smem, atoms, det);
-    case 5: return resident_t<5, double>(true, smem, atoms, det);
-    default: return resident_t<6, double>(true, smem, atoms, det);
+    case 1: return resident_t<1, double>(split, atoms, det, n, nw);
+    case 2: return resident_t<2, double>(split, atoms, det, n, nw);
+    case 3: return resident_t<3, double>(split, atoms, det, n, nw);
+    case 4: return resident_t<4, double>(split, atoms, det, n, nw);
+    case 5: return resident_t<5, double>(split, atoms, det, n, nw);
+    default: return resident_t<6, double>(split, atoms, det, n, nw);
     }
 }
 
-size_t fock_smem_bytes(int64_t n, int prec, int variant)
+// The LDS rows of F grow with the atoms, and with four waves sharing them fewer and fewer waves
+// fit on a CU (12 at 2016 atoms): wider workgroups share a pair of rows among more waves, and are
+// taken where more waves then fit (2016 atoms at 4 bohr: FP64 33.8 ms with four, 30.0 with eight,
+// mixed 25.0 and 16.4).  Where the count is the same four waves lose less at the end of a block
+// (1024 atoms at 3 bohr 28.2 against 29.0 ms), and widths that the four SIMDs don't share evenly
+// lose on both sides (five waves 31.1, six 37.8).
+int fock_waves_per_group(int g, int prec, int variant, int64_t n, bool atoms, bool det)
 {
-    return prec == HFK_MIXED ? FockSmem<float>::total((int)n, variant != 0)
-                             : FockSmem<double>::total((int)n, variant != 0);
+    if (g > 3 || det || (variant == 0 && !atoms)) return kWavesPerGroup;
+    int best = kWavesPerGroup;
+    for (const int nw : {8, 16})
+        if (nw * fock_groups(n, prec, false, nw) > best * fock_groups(n, prec, false, best)) best = nw;
+    return best;
 }
 
 PairPlan fock_plan(const Layout &L, char *ws, int strategy, int prec, int variant)
@@ -798,21 +838,21 @@ hipError_t launch_fock(const Layout &L, const Basis &b, char *ws, const double *
     const bool at = L.atoms;
     if (prec == HFK_MIXED) {
         switch (g) {
-        case 1: err = launch_fock_t<1, float>(a, L.groups, variant, at, st); break;
-        case 2: err = launch_fock_t<2, float>(a, L.groups, variant, at, st); break;
-        case 3: err = launch_fock_t<3, float>(a, L.groups, variant, at, st); break;
-        case 4: err = launch_fock_t<4, float>(a, L.groups, variant, at, st); break;
-        case 5: err = launch_fock_t<5, float>(a, L.groups, 1, at, st); break;
-        default: err = launch_fock_t<6, float>(a, L.groups, 1, at, st); break;
+        case 1: err = launch_fock_t<1, float>(a, L.groups, L.nw, variant, at, st); break;
+        case 2: err = launch_fock_t<2, float>(a, L.groups, L.nw, variant, at, st); break;
+        case 3: err = launch_fock_t<3, float>(a, L.groups, L.nw, variant, at, st); break;
+        case 4: err = launch_fock_t<4, float>(a, L.groups, L.nw, variant, at, st); break;
+        case 5: err = launch_fock_t<5, float>(a, L.groups, L.nw, 1, at, st); break;
+        default: err = launch_fock_t<6, float>(a, L.groups, L.nw, 1, at, st); break;
         }
     } else {
         switch (g) {
-        case 1: err = launch_fock_t<1, double>(a, L.groups, variant, at, st); break;
-        case 2: err = launch_fock_t<2, double>(a, L.groups, variant, at, st); break;
-        case 3: err = launch_fock_t<3, double>(a, L.groups, variant, at, st); break;
-        case 4: err = launch_fock_t<4, double>(a, L.groups, variant, at, st); break;
-        case 5: err = launch_fock_t<5, double>(a, L.groups, 1, at, st); break;
-        default: err = launch_fock_t<6, double>(a, L.groups, 1, at, st); break;
+        case 1: err = launch_fock_t<1, double>(a, L.groups, L.nw, variant, at, st); break;
+        case 2: err = launch_fock_t<2, double>(a, L.groups, L.nw, variant, at, st); break;
+        case 3: err = launch_fock_t<3, double>(a, L.groups, L.nw, variant, at, st); break;
+        case 4: err = launch_fock_t<4, double>(a, L.groups, L.nw, variant, at, st); break;
+        case 5: err = launch_fock_t<5, double>(a, L.groups, L.nw, 1, at, st); break;
+        default: err = launch_fock_t<6, double>(a, L.groups, L.nw, 1, at, st); break;
         }
     }
     if (err != hipSuccess) return err;

@@ -117,7 +117,7 @@ void k_grad(GradArgs a)
     const int gid = blockIdx.x;
     const int S = ((cptr<DevHeader>)a.hdr)->sig_pairs;
     const BasisDev *bd = a.bd;
-    __shared__ int wperm[kWavesPerGroup][kWaveKets];
+    __shared__ unsigned char wperm[kWavesPerGroup][kWaveKets];
     __shared__ long long blk_at;
     for (int x = tid; x < 3 * n; x += kGroupThreads) lg[x] = 0.0;
     load_boys<R>(tHG, GPrec<R>::boys(), BG::table_len, tid, kGroupThreads);
@@ -187,13 +187,13 @@ void k_grad(GradArgs a)
             const long long wbase = (m - item_off[s]) * (kWavesPerGroup * wkets) + wave * wkets;
             if (wbase >= lim) continue;
             const cptr<int> kexp = (cptr<int>)(a.kexp + (int)(wbase / wkets) * G2);
-            int *perm = wperm[wave];
+            unsigned char *perm = wperm[wave];
             const int nvalid = pack_kets(wbase, lane, perm,
                                          [&](long long t) { return t < lim && qs * a.pq[t] >= a.tau; }, a.sub);
             if (nvalid == 0) continue;
             for (int c0 = 0; c0 < nvalid; c0 += kWave) {
                 const bool valid = c0 + lane < nvalid;
-                const long long t = valid ? perm[c0 + lane] : S;   // S: first pad entry
+                const long long t = valid ? wbase + perm[c0 + lane] : S;   // S: first pad entry
                 const cptr<R> bra = (cptr<R>)(GPrec<R>::bra(a) + (int64_t)s * 8 * G2);
                 const cptr<R> bipp = kAtoms ? (cptr<R>)(GPrec<R>::bip(a) + (int64_t)s * G2) : nullptr;
                 const cptr<R> bwp = (cptr<R>)(GPrec<R>::bgw(a) + (int64_t)s * kGW * G2);

@@ -100,7 +100,7 @@ constexpr int kGW = 8;
 // eight items and 220 GB with sixteen; two or three items cut reads further but flush rows
 // more often and run slower.  The FP32 ket table is half the size, and eight items are the
 // faster choice there.
-constexpr int kTileItems = 4;
+constexpr int kTileItems = 4;   // the deterministic strategy's (eight with the FP32 ket table)
 constexpr int kGroupBras = 1024;
 // Bras per group are a power of two in [kMinGroupBras, kMaxGroupBras] (tuned); the group
 // tables are sized for the smallest.
@@ -182,6 +182,7 @@ struct Layout {
     int kcopies;                // ket-side Coulomb vectors requested (0: one per workgroup)
     bool private_ok;            // per-workgroup copies of F fit the memory budget
     int sub;                    // 64-ket chunks per wave of an item (1 or kSubChunks)
+    int nw;                     // waves of a workgroup of the quartet kernel
     int nsplit;                 // forward: waves that share a chunk's bra primitive pairs (1 or kWavesPerGroup)
     size_t hdr, basis;
     size_t q_unsorted, bucket_of, bucket_cnt, bucket_off, bucket_cur;
@@ -213,8 +214,7 @@ struct Layout {
 };
 
 // Kets of an item: every wave's chunks, or one wave's if all share them.
-inline int item_kets(const Layout &L) { return (L.nsplit > 1 ? 1 : kWavesPerGroup) * kWave * L.sub; }
-
+inline int item_kets(const Layout &L) { return (L.nsplit > 1 ? 1 : L.nw) * kWave * L.sub; }
 // compact: the layout of the allocation-free call (one F for the atomics strategy, at most
 // kCompactKetCopies shared ket vectors).
 constexpr int kCompactKetCopies = 8;
@@ -324,8 +324,9 @@ PairPlan fock_plan(const Layout &L, char *ws, int strategy, int prec, int varian
 hipError_t launch_new_density(const Layout &L, char *ws, const double *dens, const PairPlan &plan, hipStream_t st);
 hipError_t launch_fock(const Layout &L, const Basis &b, char *ws, const double *dens, double tau,
                        int prec, int strategy, int variant, double *fock, double *e2, hipStream_t st);
-size_t fock_smem_bytes(int64_t n, int prec, int variant);
-int fock_resident_groups(int g, int prec, int variant, int64_t n, bool atoms = false, bool det = false);
+int fock_resident_groups(int g, int prec, int variant, int64_t n, bool atoms, bool det, int nw = kWavesPerGroup);
+// Waves per workgroup of a forward build.
+int fock_waves_per_group(int g, int prec, int variant, int64_t n, bool atoms, bool det);
 // Events around the quartet kernel when profiling is enabled (no-ops otherwise).
 void profile_begin(hipStream_t st);
 void profile_end(hipStream_t st);
