@@ -85,7 +85,8 @@ typedef struct hfk_stats {
     int32_t groups;          /* persistent workgroups launched */
     int32_t precision;       /* hfk_precision used */
     int32_t variant;         /* quartet-kernel variant used (hfk_set_config) */
-    int32_t tile_items;      /* items (1024 kets each) per block of the single-molecule
+    int32_t tile_items;      /* items (1024 kets each, fewer on small systems and
+                              * more in the wide workgroups of large ones) per block of the single-molecule
                                 kernels, or items (256 kets) per block of the batched one */
     int32_t group_bras;      /* bras per group whose blocks are numbered ket-block-major */
     int32_t ket_copies;      /* copies of the ket-side Coulomb vector (= groups: one per
@@ -128,7 +129,7 @@ hfk_status hfk_fock(int64_t natoms, const double *xyz, int32_t ngauss,
 
 /* hfk_fock for callers that cannot allocate device memory (code under HIP graph capture,
  * tight serving loops, harnesses that forbid hipMalloc): the same build with the atomics
- * strategy, whose scratch is a static device array of 64 MiB inside the library instead
+ * strategy, whose scratch is a static device array of 66 MiB inside the library instead
  * of a caller workspace.  The call allocates nothing (no hipMalloc, no library routine that
  * allocates).  Every GPU the library runs on holds its own copy of that array until the
  * process ends; every call on a GPU shares that GPU's copy, so calls that overlap in time on
@@ -228,7 +229,7 @@ hfk_status hfk_scf_workspace_bytes(int64_t natoms, int32_t ngauss, int32_t preci
  *                    both tolerances were met)
  *   workspace        hfk_scf_workspace_bytes(...) bytes, 256-byte aligned
  * The call waits for `stream` whenever the loop needs a number on the host and returns when
- * the loop has ended.  Dense products and eigenproblems run in rocBLAS and rocSOLVER with
+ * the loop has ended.  Above 64 atoms dense products and eigenproblems run in rocBLAS and rocSOLVER with
  * their scratch taken from the workspace (HFK_ENOMEM if their own query asks for more).
  * Errors as hfk_fock_atoms; HFK_EUNSUPPORTED for a (nearly) singular overlap matrix; HFK_EHIP
  * also when an eigensolve does not converge (a Fock matrix or guess density with NaN or Inf). */
@@ -355,7 +356,7 @@ hfk_status hfk_set_config(int32_t variant, int32_t groups_per_cu);
 /* Process-wide override of the quartet-tile shape of hfk_fock and hfk_fock_atoms (and of
  * the gradient kernel and pull-back build of hfk_fock_grad; not of the deterministic
  * strategy), for tuning and tests:
- *   tile_items     items of 1024 kets per block of one bra, 1..16 (0: library choice)
+ *   tile_items     items (of 1024 kets; see hfk_stats) per block of one bra, 1..16 (0: library choice)
  *   group_bras     bras per group whose blocks are numbered ket-block-major: 256, 512,
  *                  1024, 2048 or 4096 (0: library choice)
  *   ket_copies     copies of the ket-side Coulomb vector: 1..1024 shared copies updated

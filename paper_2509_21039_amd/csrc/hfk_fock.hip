@@ -5,14 +5,14 @@
 // Work decomposition.  Significant pairs are stored in Q-bucketed order (t = 0 .. S-1),
 // so the kets kept by the screen for a bra s form a prefix t < lim_s (t <= s keeps each
 // unordered quartet once; a lane-level test Q_s Q_t >= tau handles the partial bucket).
-// An item is (bra s, 1024 consecutive kets).  Persistent workgroups fetch blocks of up to
-// kTileItems items of one bra from a global counter (the cost per item varies with the
-// bra's surroundings, and static ranges left a long tail of slow workgroups).  Blocks are
-// numbered ket-block-major within groups of bras (1024 unless tuned), so the workgroups running
-// together read the same kets, which then come from L2.  Each of a workgroup's four waves
-// takes 256 kets of an item and runs them as 64-lane chunks, one ket per lane; the bra's
-// primitive data are wave-uniform.  In the hybrid form the wave first packs the kets that
-// pass the screen (ballot + lane count, order kept so loads stay coalesced) into full
+// An item is (bra s, up to four 64-lane chunks of consecutive kets per wave: 1024 kets with four
+// waves; one chunk per wave on small systems, and on the smallest one chunk for all four).
+// Persistent workgroups fetch blocks of items of one bra from a global counter (the cost per
+// item varies with the bra's surroundings, and static ranges left a long tail of slow
+// workgroups).  Blocks are numbered ket-block-major within groups of bras (1024 unless tuned),
+// so the workgroups running together read the same kets, which then come from L2.  One ket per
+// lane; the bra's primitive data are wave-uniform.  In the hybrid form the wave first packs the
+// kets that pass the screen (ballot + lane count, order kept so loads stay coalesced) into full
 // chunks.
 //
 // Accumulation (replacing one global FP64 atomic per update):

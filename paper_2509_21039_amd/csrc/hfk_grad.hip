@@ -24,9 +24,9 @@
 // one reciprocal square root; the bra's (mu, a/p) come through scalar loads and the ket's
 // from two SoA tables read once per ket primitive pair.
 //
-// Work decomposition as in the forward kernel (items of 1024 kets of one bra, blocks of
+// Work decomposition as in the forward kernel (items of one bra, blocks of
 // items fetched from a global counter in the same bra-group numbering, taken from its end
-// so that the largest blocks start first, 256 kets per wave packed
+// so that the largest blocks start first, a wave's kets packed
 // into full 64-lane chunks after the screen).  Bra-atom gradients accumulate in
 // registers and are reduced across the wave when the bra changes; ket-atom gradients go to
 // an LDS copy of the n x 3 gradient; each workgroup writes its copy out once.

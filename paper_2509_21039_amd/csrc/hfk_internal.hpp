@@ -77,11 +77,10 @@ constexpr int kWave = 64;
 constexpr int kWavesPerGroup = 4;
 constexpr int kGroupThreads = kWave * kWavesPerGroup;
 constexpr int kKetsPerItem = kGroupThreads;   // one 64-ket chunk per wave per item
-// Single-molecule items: (bra, kItemKets kets); each wave takes kWaveKets of them and runs
+// Single-molecule items: each wave takes up to kWaveKets consecutive kets of a bra and runs
 // them as kSubChunks 64-lane chunks.
 constexpr int kSubChunks = 4;
 constexpr int kWaveKets = kWave * kSubChunks;
-constexpr int kItemKets = kWavesPerGroup * kWaveKets;
 constexpr int kBlockItems = 16;  // items per dynamically fetched block of the quartet kernels
 // Batched kernel: items of kKetsPerItem kets are cut into units of one wave's 64 kets; the
 // workgroup has 4 or 8 waves (set at launch, at most kBatchMaxThreads threads); the bra table
@@ -91,16 +90,11 @@ constexpr int kBatchMaxThreads = 512;
 constexpr int kBBra = 12;
 // Gradient bra weights per primitive pair of the single-molecule tables.
 constexpr int kGW = 8;
-// Single-molecule blocks: kTileItems items of one bra (twice as many with FP32 ket data).
-// Bras are taken kGroupBras at a time and their blocks are numbered ket-block-major (block
-// K of every bra of the group, then block K+1), so the workgroups running at the same
-// moment read the same few thousand kets and the ket table is served from L2 instead of
-// streaming past it.  Four FP64 items (4096 kets, 1.5 MB of ket data) fit next to the rest
-// in an XCD's 4 MB L2: fabric reads per launch at 512 atoms are 30 GB against 105 GB with
-// eight items and 220 GB with sixteen; two or three items cut reads further but flush rows
-// more often and run slower.  The FP32 ket table is half the size, and eight items are the
-// faster choice there.
-constexpr int kTileItems = 4;   // the deterministic strategy's (eight with the FP32 ket table)
+// Single-molecule blocks: a few items of one bra.  Bras are taken kGroupBras at a time and
+// their blocks are numbered ket-block-major (block K of every bra of the group, then block
+// K+1), so the workgroups running at the same moment read the same few thousand kets and the
+// ket table is served from L2 instead of streaming past it.
+constexpr int kTileItems = 4;   // the deterministic strategy's (eight with the FP32 ket table); twice that by default
 constexpr int kGroupBras = 1024;
 // Bras per group are a power of two in [kMinGroupBras, kMaxGroupBras] (tuned); the group
 // tables are sized for the smallest.
