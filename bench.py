@@ -503,6 +503,8 @@ def main():
         "roofline": {"bound": "alu", "achieved": achieved, "peak": FP64_VALU_PEAK_TFLOPS, "unit": "TFLOP/s",
                      "frac": achieved / FP64_VALU_PEAK_TFLOPS, "traffic": measured_traffic(r["stats"]),
                      "kernel": "k_fock<3,double>", "kernel_ms": r["kernel_ms"],
+                     "note": "achieved and frac are nominal: every primitive term counted, also the negligible "
+                             "ones that the kernel leaves out, so frac is not a utilisation",
                      "flop_per_quartet": flop_per_quartet(g)},
         "e2": r["e2"],
     }
