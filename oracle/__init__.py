@@ -18,6 +18,7 @@ Parity status of each function (what pins it, in ``tests/test_oracle.py``):
   eri4                          pinned (per-centre contractions): two-centre Gaussian-charge closed
                                 form with unequal exponents, coincident-centre value, scaling law
                                 (exponents x l^2, lengths / l gives x l), 8-fold symmetry
+  eri_tensor_atoms              pinned: its contraction equals the brute-force plain definition
   one_electron_atoms            pinned: 1-D quadrature of overlap and kinetic energy (the latter as
                                 1/2 <g_a'|g_b'>), nucleus-on-centre closed form 2 sqrt(2a/pi), each
                                 Gaussian product as a charge cloud erf(sqrt(p) R)/R away from a nucleus
@@ -104,6 +105,9 @@ def _load():
         lib.hfo_grad_pair_atoms.argtypes = lib.hfo_grad_pair.argtypes
         lib.hfo_grad_atoms.restype = ctypes.c_int
         lib.hfo_grad_atoms.argtypes = lib.hfo_grad.argtypes
+        lib.hfo_eri_tensor_atoms.restype = ctypes.c_int
+        lib.hfo_eri_tensor_atoms.argtypes = [ctypes.c_int64, _dp, ctypes.c_int, _dp, _dp, ctypes.c_double,
+                                             ctypes.c_int, _dp]
         lib.hfo_one_electron_atoms.restype = ctypes.c_int
         lib.hfo_one_electron_atoms.argtypes = [ctypes.c_int64, _dp, _dp, ctypes.c_int, _dp, _dp, _dp, _dp, _dp]
         lib.hfo_num_threads.restype = ctypes.c_int
@@ -328,6 +332,15 @@ def grad_pair_atoms(xyz, dens, xdens, exps, coefs, tau, Q=None, nthreads: int = 
     if rc != 0:
         raise MemoryError("oracle grad_pair_atoms: out of memory")
     return gr
+
+
+def eri_tensor_atoms(xyz, exps, coefs, tau, nthreads: int = 0) -> np.ndarray:
+    """V[i, j, k, l] = (ij|kl) where the screen keeps the quartet, 0 elsewhere (n^4 values)."""
+    xyz, px, e, pe, c, pc, n, g = _atoms(xyz, exps, coefs)
+    V = np.empty((n, n, n, n))
+    if _load().hfo_eri_tensor_atoms(n, px, g, pe, pc, float(tau), int(nthreads), V.ctypes.data_as(_dp)) != 0:
+        raise MemoryError("oracle eri_tensor_atoms: out of memory")
+    return V
 
 
 def one_electron_atoms(xyz, charges, exps, coefs):

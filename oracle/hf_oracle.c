@@ -28,7 +28,9 @@
  *   F_ij += 4 D_kl v,  F_kl += 4 D_ij v,
  *   F_ik -= D_jl v,    F_il -= D_jk v,   F_jk -= D_il v,   F_jl -= D_ik v,
  * followed by G = (F + F^T) / 2.  hfo_fock_bruteforce and hfo_fock_element evaluate the
- * plain definition directly and pin the scatter.
+ * plain definition directly and pin the scatter: they form every integral from the four
+ * centres (eri_core), while the builds and gradients form the primitive products of a pair
+ * once (products) and take integrals of two such lists (eri_products).
  *
  * The nuclear gradient (hfo_grad) differentiates E2 = sum_unique Gamma_ijkl (ij|kl),
  * Gamma = deg (4 D_ij D_kl - D_ik D_jl - D_il D_jk), with the screening decisions held
@@ -56,6 +58,7 @@
 #endif
 
 #define HFO_PI 3.14159265358979323846264338327950288
+#define HFO_MAXG 16     /* primitives per atom */
 
 /* ---------------------------------------------------------------- Boys function */
 
@@ -90,11 +93,13 @@ double hfo_boys0(double t)
 
 /* F1(t): series below t = 1, closed form (F0 - exp(-t)) / (2t) at and above (the two terms
  * differ by at least half of F0 there, so the subtraction loses under one digit). */
-double hfo_boys1(double t)
+static double boys1_of(double t, double f0)
 {
     if (t < 1.0) return hfo_boys_series(1, t);
-    return (hfo_boys0(t) - exp(-t)) / (2.0 * t);
+    return (f0 - exp(-t)) / (2.0 * t);
 }
+
+double hfo_boys1(double t) { return boys1_of(t, hfo_boys0(t)); }
 
 /* ---------------------------------------------------------------- basis */
 
@@ -192,53 +197,84 @@ double hfo_eri4(const double *A, const double *B, const double *C, const double 
     return eri_core(A, B, C, D, g, eA, wA, eB, wB, eC, wC, eD, wD);
 }
 
+/* Primitive product (a, b) of a pair of atoms at A and B. */
+typedef struct {
+    double p, mu, fa, fb, K, P[3];     /* p = a + b, mu = a b / p, fa = a / p, fb = b / p */
+} product;
+
+static void products(const double *A, const double *B, int g, const double *eA, const double *wA, const double *eB,
+                     const double *wB, product *t)
+{
+    double ab2 = 0.0;
+    for (int x = 0; x < 3; ++x) ab2 += (A[x] - B[x]) * (A[x] - B[x]);
+    for (int a = 0; a < g; ++a)
+        for (int b = 0; b < g; ++b, ++t) {
+            t->p = eA[a] + eB[b];
+            t->mu = eA[a] * eB[b] / t->p;
+            t->fa = eA[a] / t->p;
+            t->fb = eB[b] / t->p;
+            t->K = wA[a] * wB[b] * exp(-t->mu * ab2);
+            for (int x = 0; x < 3; ++x) t->P[x] = (eA[a] * A[x] + eB[b] * B[x]) / t->p;
+        }
+}
+
+/* Contracted (AB|CD) of two lists of g2 products.  A term whose K_ab K_cd is zero (the
+ * exponentials underflow for atoms far apart) adds nothing and is passed over. */
+static double eri_products(const product *s, const product *t, int g2)
+{
+    const double two_pi52 = 2.0 * pow(HFO_PI, 2.5);
+    double eri = 0.0;
+    for (int ab = 0; ab < g2; ++ab)
+        for (int cd = 0; cd < g2; ++cd) {
+            const double p = s[ab].p, q = t[cd].p, K = s[ab].K * t[cd].K;
+            if (K == 0.0) continue;
+            double pq2 = 0.0;
+            for (int x = 0; x < 3; ++x) pq2 += (s[ab].P[x] - t[cd].P[x]) * (s[ab].P[x] - t[cd].P[x]);
+            eri += two_pi52 / (p * q * sqrt(p + q)) * K * hfo_boys0(p * q / (p + q) * pq2);
+        }
+    return eri;
+}
+
 /* Gradient of one contracted (AB|CD) with respect to the four centres, each scaled by
- * gamma and added into gA, gB, gC, gD (3 components each).  Per primitive quartet, with
- * E = pref K_ab K_cd:
+ * gamma and added into gA, gB, gC, gD (3 components each), from the products s of (A, B) and t
+ * of (C, D).  Per primitive quartet, with E = pref K_ab K_cd:
  *   d/dA = E [ -2 mu_ab (A-B) F0 - 2 rho (a/p) (P-Q) F1 ]
  *   d/dB = E [ +2 mu_ab (A-B) F0 - 2 rho (b/p) (P-Q) F1 ]
  *   d/dC = E [ -2 mu_cd (C-D) F0 + 2 rho (c/q) (P-Q) F1 ]
- *   d/dD = E [ +2 mu_cd (C-D) F0 + 2 rho (d/q) (P-Q) F1 ]                                 */
-static void eri_grad(const double *A, const double *B, const double *C, const double *D, int g,
-                     const double *eA, const double *wA, const double *eB, const double *wB,
-                     const double *eC, const double *wC, const double *eD, const double *wD, double gamma,
-                     double *gA, double *gB, double *gC, double *gD)
+ *   d/dD = E [ +2 mu_cd (C-D) F0 + 2 rho (d/q) (P-Q) F1 ]
+ * Returns gamma (AB|CD), the sum of E F0. */
+static double eri_grad(const double *A, const double *B, const double *C, const double *D, const product *s,
+                       const product *t, int g2, double gamma, double *gA, double *gB, double *gC, double *gD)
 {
-    double ab2 = 0.0, cd2 = 0.0;
-    for (int x = 0; x < 3; ++x) {
-        ab2 += (A[x] - B[x]) * (A[x] - B[x]);
-        cd2 += (C[x] - D[x]) * (C[x] - D[x]);
-    }
-    for (int a = 0; a < g; ++a)
-        for (int b = 0; b < g; ++b) {
-            double p = eA[a] + eB[b];
-            double muab = eA[a] * eB[b] / p;
-            double Kab = wA[a] * wB[b] * exp(-muab * ab2);
-            double P[3];
-            for (int x = 0; x < 3; ++x) P[x] = (eA[a] * A[x] + eB[b] * B[x]) / p;
-            for (int c = 0; c < g; ++c)
-                for (int d = 0; d < g; ++d) {
-                    double q = eC[c] + eD[d];
-                    double mucd = eC[c] * eD[d] / q;
-                    double Kcd = wC[c] * wD[d] * exp(-mucd * cd2);
-                    double Q[3], pq2 = 0.0;
-                    for (int x = 0; x < 3; ++x) {
-                        Q[x] = (eC[c] * C[x] + eD[d] * D[x]) / q;
-                        pq2 += (P[x] - Q[x]) * (P[x] - Q[x]);
-                    }
-                    double rho = p * q / (p + q);
-                    double E = gamma * 2.0 * pow(HFO_PI, 2.5) / (p * q * sqrt(p + q)) * Kab * Kcd;
-                    double T = rho * pq2;
-                    double f0 = hfo_boys0(T), f1 = hfo_boys1(T);
-                    for (int x = 0; x < 3; ++x) {
-                        double pqx = P[x] - Q[x];
-                        gA[x] += E * (-2.0 * muab * (A[x] - B[x]) * f0 - 2.0 * rho * (eA[a] / p) * pqx * f1);
-                        gB[x] += E * (+2.0 * muab * (A[x] - B[x]) * f0 - 2.0 * rho * (eB[b] / p) * pqx * f1);
-                        gC[x] += E * (-2.0 * mucd * (C[x] - D[x]) * f0 + 2.0 * rho * (eC[c] / q) * pqx * f1);
-                        gD[x] += E * (+2.0 * mucd * (C[x] - D[x]) * f0 + 2.0 * rho * (eD[d] / q) * pqx * f1);
-                    }
-                }
+    const double two_pi52 = 2.0 * pow(HFO_PI, 2.5);
+    double value = 0.0, a[3] = {0, 0, 0}, b[3] = {0, 0, 0}, c[3] = {0, 0, 0}, d[3] = {0, 0, 0}, sab = 0.0, scd = 0.0;
+    for (int ab = 0; ab < g2; ++ab)
+        for (int cd = 0; cd < g2; ++cd) {
+            const product *u = s + ab, *v = t + cd;
+            const double p = u->p, q = v->p, rho = p * q / (p + q);
+            const double E = gamma * two_pi52 / (p * q * sqrt(p + q)) * u->K * v->K;
+            if (E == 0.0) continue;
+            double pq2 = 0.0;
+            for (int x = 0; x < 3; ++x) pq2 += (u->P[x] - v->P[x]) * (u->P[x] - v->P[x]);
+            const double T = rho * pq2, f0 = hfo_boys0(T), f1 = 2.0 * rho * E * boys1_of(T, f0);
+            value += E * f0;
+            sab += 2.0 * u->mu * (E * f0);
+            scd += 2.0 * v->mu * (E * f0);
+            for (int x = 0; x < 3; ++x) {
+                const double w = (u->P[x] - v->P[x]) * f1;
+                a[x] -= u->fa * w;
+                b[x] -= u->fb * w;
+                c[x] += v->fa * w;
+                d[x] += v->fb * w;
+            }
         }
+    for (int x = 0; x < 3; ++x) {
+        gA[x] += a[x] - sab * (A[x] - B[x]);
+        gB[x] += b[x] + sab * (A[x] - B[x]);
+        gC[x] += c[x] - scd * (C[x] - D[x]);
+        gD[x] += d[x] + scd * (C[x] - D[x]);
+    }
+    return value;
 }
 
 /* (ij|kl) of atoms i, j, k, l under a basis description with weights W (atom_weights). */
@@ -251,14 +287,12 @@ static double eri_atoms(const double *xyz, int g, const double *exps, const doub
                     exps + k * s, W + k * sw, exps + l * s, W + l * sw);
 }
 
-static void eri_grad_atoms(const double *xyz, int g, const double *exps, const double *W, int64_t astride,
-                           int64_t i, int64_t j, int64_t k, int64_t l, double gamma, double *grad)
+/* Products of atoms i and j under a basis description. */
+static void products_atoms(const double *xyz, int g, const double *exps, const double *W, int64_t astride, int64_t i,
+                           int64_t j, product *t)
 {
     const int64_t s = astride, sw = astride ? g : 0;
-    eri_grad(xyz + 3 * i, xyz + 3 * j, xyz + 3 * k, xyz + 3 * l, g,
-             exps + i * s, W + i * sw, exps + j * s, W + j * sw,
-             exps + k * s, W + k * sw, exps + l * s, W + l * sw, gamma,
-             grad + 3 * i, grad + 3 * j, grad + 3 * k, grad + 3 * l);
+    products(xyz + 3 * i, xyz + 3 * j, g, exps + i * s, W + i * sw, exps + j * s, W + j * sw, t);
 }
 
 /* ---------------------------------------------------------------- Schwarz */
@@ -280,7 +314,11 @@ static int schwarz_s(int64_t n, const double *xyz, int g, const double *exps, co
 #pragma omp parallel for schedule(dynamic, 16)
 #endif
     for (int64_t i = 0; i < n; ++i)
-        for (int64_t j = 0; j <= i; ++j) Q[pidx(i, j)] = sqrt(eri_atoms(xyz, g, exps, W, astride, i, j, i, j));
+        for (int64_t j = 0; j <= i; ++j) {
+            product t[HFO_MAXG * HFO_MAXG];
+            products_atoms(xyz, g, exps, W, astride, i, j, t);
+            Q[pidx(i, j)] = sqrt(eri_products(t, t, g * g));
+        }
     free(W);
     return 0;
 }
@@ -320,15 +358,55 @@ static double *schwarz_or(const double *Qin, int64_t n, const double *xyz, int g
     return Q;
 }
 
-/* (i, j) of every canonical pair index i(i+1)/2 + j. */
-static int64_t *pair_list(int64_t n)
+/* The pairs that any quartet can be kept with, in canonical order, and their products.  A pair
+ * with Q Qmax < tau has Q Q_kl < tau for every kl (rounding keeps the order of products), so
+ * the quartets kept are the same as over all pairs. */
+typedef struct {
+    int64_t count;
+    int64_t *ij;        /* canonical index i(i+1)/2 + j */
+    int64_t *i, *j;
+    product *prod;      /* [count][g2] */
+} pairs;
+
+static void pairs_free(pairs *s)
 {
-    const int64_t npair = n * (n + 1) / 2;
-    int64_t *pi = (int64_t *)malloc(sizeof(int64_t) * (size_t)npair * 2);
-    if (!pi) return NULL;
-    for (int64_t i = 0, p = 0; i < n; ++i)
-        for (int64_t j = 0; j <= i; ++j, ++p) { pi[2 * p] = i; pi[2 * p + 1] = j; }
-    return pi;
+    free(s->ij);
+    free(s->i);
+    free(s->j);
+    free(s->prod);
+}
+
+static int pairs_make(int64_t n, const double *xyz, int g, const double *exps, const double *coefs, int64_t astride,
+                      const double *Q, double tau, pairs *s)
+{
+    const int64_t npair = n * (n + 1) / 2, g2 = (int64_t)g * g;
+    double qmax = 0.0;
+    int64_t m = 0;
+    memset(s, 0, sizeof(*s));
+    for (int64_t x = 0; x < npair; ++x)
+        if (Q[x] > qmax) qmax = Q[x];
+    for (int64_t x = 0; x < npair; ++x) m += !(Q[x] * qmax < tau);
+    s->ij = (int64_t *)malloc(sizeof(int64_t) * (size_t)(m + 1));
+    s->i = (int64_t *)malloc(sizeof(int64_t) * (size_t)(m + 1));
+    s->j = (int64_t *)malloc(sizeof(int64_t) * (size_t)(m + 1));
+    s->prod = (product *)malloc(sizeof(product) * (size_t)((m + 1) * g2));
+    double *W = atom_weights(n, g, exps, coefs, astride);
+    if (!s->ij || !s->i || !s->j || !s->prod || !W) {
+        pairs_free(s);
+        free(W);
+        return -1;
+    }
+    for (int64_t i = 0, x = 0; i < n; ++i)
+        for (int64_t j = 0; j <= i; ++j, ++x) {
+            if (Q[x] * qmax < tau) continue;
+            s->ij[s->count] = x;
+            s->i[s->count] = i;
+            s->j[s->count] = j;
+            products_atoms(xyz, g, exps, W, astride, i, j, s->prod + s->count * g2);
+            ++s->count;
+        }
+    free(W);
+    return 0;
 }
 
 /* ---------------------------------------------------------------- Fock build */
@@ -345,9 +423,8 @@ static int fock_s(int64_t n, const double *xyz, int g, const double *exps, const
     int ownQ = 0;
     double *Q = schwarz_or(Qin, n, xyz, g, exps, coefs, astride, nthreads, &ownQ);
     if (!Q) return -1;
-    int64_t *pi = pair_list(n);
-    double *W = atom_weights(n, g, exps, coefs, astride);
-    if (!pi || !W) { free(pi); free(W); if (ownQ) free(Q); return -1; }
+    pairs pr;
+    if (pairs_make(n, xyz, g, exps, coefs, astride, Q, tau, &pr) != 0) { if (ownQ) free(Q); return -1; }
     if (bra_begin < 0) bra_begin = 0;
     if (bra_end > npair) bra_end = npair;
 
@@ -369,12 +446,13 @@ static int fock_s(int64_t n, const double *xyz, int g, const double *exps, const
 #ifdef _OPENMP
 #pragma omp for schedule(dynamic, 1)
 #endif
-            for (int64_t ij = bra_begin; ij < bra_end; ++ij) {
-                const int64_t i = pi[2 * ij], j = pi[2 * ij + 1];
-                for (int64_t kl = 0; kl <= ij; ++kl) {
+            for (int64_t x = 0; x < pr.count; ++x) {
+                const int64_t ij = pr.ij[x], i = pr.i[x], j = pr.j[x];
+                if (ij < bra_begin || ij >= bra_end) continue;
+                for (int64_t y = 0; y <= x; ++y) {
+                    const int64_t kl = pr.ij[y], k = pr.i[y], l = pr.j[y];
                     if (Q[ij] * Q[kl] < tau) continue;
-                    const int64_t k = pi[2 * kl], l = pi[2 * kl + 1];
-                    double eri = eri_atoms(xyz, g, exps, W, astride, i, j, k, l);
+                    double eri = eri_products(pr.prod + x * g * g, pr.prod + y * g * g, g * g);
                     double v = eri * quartet_deg(i, j, k, l, ij, kl);
                     Fp[i * n + j] += 4.0 * dens[k * n + l] * v;
                     Fp[k * n + l] += 4.0 * dens[i * n + j] * v;
@@ -392,8 +470,7 @@ static int fock_s(int64_t n, const double *xyz, int g, const double *exps, const
             free(Fp);
         }
     }
-    free(pi);
-    free(W);
+    pairs_free(&pr);
     if (ownQ) free(Q);
     if (failed) return -1;
     /* G = (F + F^T) / 2 and E2 = 1/2 sum D o G */
@@ -500,13 +577,11 @@ static int grad_s(int64_t n, const double *xyz, int g, const double *exps, const
                   const double *dens, double tau, const double *Qin, int nthreads,
                   double *grad, double *e2, int64_t *nsurv)
 {
-    const int64_t npair = n * (n + 1) / 2;
     int ownQ = 0;
     double *Q = schwarz_or(Qin, n, xyz, g, exps, coefs, astride, nthreads, &ownQ);
     if (!Q) return -1;
-    int64_t *pi = pair_list(n);
-    double *W = atom_weights(n, g, exps, coefs, astride);
-    if (!pi || !W) { free(pi); free(W); if (ownQ) free(Q); return -1; }
+    pairs pr;
+    if (pairs_make(n, xyz, g, exps, coefs, astride, Q, tau, &pr) != 0) { if (ownQ) free(Q); return -1; }
     memset(grad, 0, sizeof(double) * (size_t)(3 * n));
     double energy = 0.0;
     int64_t count = 0;
@@ -526,16 +601,17 @@ static int grad_s(int64_t n, const double *xyz, int g, const double *exps, const
 #ifdef _OPENMP
 #pragma omp for schedule(dynamic, 1)
 #endif
-            for (int64_t ij = 0; ij < npair; ++ij) {
-                const int64_t i = pi[2 * ij], j = pi[2 * ij + 1];
-                for (int64_t kl = 0; kl <= ij; ++kl) {
+            for (int64_t x = 0; x < pr.count; ++x) {
+                const int64_t ij = pr.ij[x], i = pr.i[x], j = pr.j[x];
+                for (int64_t y = 0; y <= x; ++y) {
+                    const int64_t kl = pr.ij[y], k = pr.i[y], l = pr.j[y];
                     if (Q[ij] * Q[kl] < tau) continue;
-                    const int64_t k = pi[2 * kl], l = pi[2 * kl + 1];
                     double gam = quartet_deg(i, j, k, l, ij, kl) *
                                  (4.0 * dens[i * n + j] * dens[k * n + l] - dens[i * n + k] * dens[j * n + l] -
                                   dens[i * n + l] * dens[j * n + k]);
-                    energy += gam * eri_atoms(xyz, g, exps, W, astride, i, j, k, l);
-                    eri_grad_atoms(xyz, g, exps, W, astride, i, j, k, l, gam, gp);
+                    energy += eri_grad(xyz + 3 * i, xyz + 3 * j, xyz + 3 * k, xyz + 3 * l, pr.prod + x * g * g,
+                                       pr.prod + y * g * g, g * g, gam, gp + 3 * i, gp + 3 * j, gp + 3 * k,
+                                       gp + 3 * l);
                     ++count;
                 }
             }
@@ -546,8 +622,7 @@ static int grad_s(int64_t n, const double *xyz, int g, const double *exps, const
             free(gp);
         }
     }
-    free(pi);
-    free(W);
+    pairs_free(&pr);
     if (ownQ) free(Q);
     if (failed) return -1;
     if (e2) *e2 = energy;
@@ -579,13 +654,11 @@ static int grad_pair_s(int64_t n, const double *xyz, int g, const double *exps, 
                        int64_t astride, const double *dens, const double *xdens, double tau, const double *Qin,
                        int nthreads, double *grad)
 {
-    const int64_t npair = n * (n + 1) / 2;
     int ownQ = 0;
     double *Q = schwarz_or(Qin, n, xyz, g, exps, coefs, astride, nthreads, &ownQ);
     if (!Q) return -1;
-    int64_t *pi = pair_list(n);
-    double *W = atom_weights(n, g, exps, coefs, astride);
-    if (!pi || !W) { free(pi); free(W); if (ownQ) free(Q); return -1; }
+    pairs pr;
+    if (pairs_make(n, xyz, g, exps, coefs, astride, Q, tau, &pr) != 0) { if (ownQ) free(Q); return -1; }
     memset(grad, 0, sizeof(double) * (size_t)(3 * n));
     int failed = 0;
 #ifdef _OPENMP
@@ -603,17 +676,19 @@ static int grad_pair_s(int64_t n, const double *xyz, int g, const double *exps, 
 #ifdef _OPENMP
 #pragma omp for schedule(dynamic, 1)
 #endif
-            for (int64_t ij = 0; ij < npair; ++ij) {
-                const int64_t i = pi[2 * ij], j = pi[2 * ij + 1];
-                for (int64_t kl = 0; kl <= ij; ++kl) {
+            for (int64_t x = 0; x < pr.count; ++x) {
+                const int64_t ij = pr.ij[x], i = pr.i[x], j = pr.j[x];
+                for (int64_t y = 0; y <= x; ++y) {
+                    const int64_t kl = pr.ij[y], k = pr.i[y], l = pr.j[y];
                     if (Q[ij] * Q[kl] < tau) continue;
-                    const int64_t k = pi[2 * kl], l = pi[2 * kl + 1];
                     const double *X = xdens, *D = dens;
                     const double b = quartet_deg(i, j, k, l, ij, kl) *
                                      (4.0 * (X[i * n + j] * D[k * n + l] + D[i * n + j] * X[k * n + l]) -
                                       (X[i * n + k] * D[j * n + l] + D[i * n + k] * X[j * n + l]) -
                                       (X[i * n + l] * D[j * n + k] + D[i * n + l] * X[j * n + k]));
-                    eri_grad_atoms(xyz, g, exps, W, astride, i, j, k, l, b, gp);
+                    (void)eri_grad(xyz + 3 * i, xyz + 3 * j, xyz + 3 * k, xyz + 3 * l, pr.prod + x * g * g,
+                                   pr.prod + y * g * g, g * g, b, gp + 3 * i, gp + 3 * j, gp + 3 * k,
+                                   gp + 3 * l);
                 }
             }
 #ifdef _OPENMP
@@ -623,8 +698,7 @@ static int grad_pair_s(int64_t n, const double *xyz, int g, const double *exps, 
             free(gp);
         }
     }
-    free(pi);
-    free(W);
+    pairs_free(&pr);
     if (ownQ) free(Q);
     return failed ? -1 : 0;
 }
@@ -641,6 +715,40 @@ int hfo_grad_pair_atoms(int64_t n, const double *xyz, int g, const double *exps,
                         double *grad)
 {
     return grad_pair_s(n, xyz, g, exps, coefs, g, dens, xdens, tau, Qin, nthreads, grad);
+}
+
+/* Every (ij|kl) that the screen keeps, in all its eight places of V (n^4 values, zero where the
+ * quartet is screened away), with per-atom bases.  With M_ijkl = V_ijkl - V_ikjl / 2 the plain
+ * definition is G_ij = sum_kl M_ijkl D_kl, so a self-consistent field forms the integrals
+ * once.  Returns 0, or -1 when memory runs out. */
+int hfo_eri_tensor_atoms(int64_t n, const double *xyz, int g, const double *exps, const double *coefs, double tau,
+                         int nthreads, double *V)
+{
+    int ownQ = 0;
+    double *Q = schwarz_or(NULL, n, xyz, g, exps, coefs, g, nthreads, &ownQ);
+    if (!Q) return -1;
+    pairs pr;
+    if (pairs_make(n, xyz, g, exps, coefs, g, Q, tau, &pr) != 0) { free(Q); return -1; }
+    memset(V, 0, sizeof(double) * (size_t)(n * n * n * n));
+#ifdef _OPENMP
+    if (nthreads > 0) omp_set_num_threads(nthreads);
+#pragma omp parallel for schedule(dynamic, 1)
+#endif
+    for (int64_t x = 0; x < pr.count; ++x)
+        for (int64_t y = 0; y <= x; ++y) {
+            if (Q[pr.ij[x]] * Q[pr.ij[y]] < tau) continue;
+            const double v = eri_products(pr.prod + x * g * g, pr.prod + y * g * g, g * g);
+            const int64_t b[2] = {pr.i[x] * n + pr.j[x], pr.j[x] * n + pr.i[x]};
+            const int64_t k[2] = {pr.i[y] * n + pr.j[y], pr.j[y] * n + pr.i[y]};
+            for (int e = 0; e < 2; ++e)
+                for (int f = 0; f < 2; ++f) {
+                    V[b[e] * n * n + k[f]] = v;
+                    V[k[f] * n * n + b[e]] = v;
+                }
+        }
+    pairs_free(&pr);
+    free(Q);
+    return 0;
 }
 
 /* ---------------------------------------------------------------- one-electron integrals */

@@ -12,7 +12,10 @@ from __future__ import annotations
 
 import numpy as np
 
-from . import fock_atoms, one_electron_atoms
+from . import eri_tensor_atoms, fock_atoms, one_electron_atoms
+
+# Up to this many atoms the integrals are formed once and kept (n^4 values, 330 MB).
+MAX_KEPT_ATOMS = 80
 
 
 def nuclear_repulsion(xyz, charges) -> float:
@@ -35,6 +38,17 @@ def density_from(F, X, nocc):
     C = X @ Cp
     Co = C[:, :nocc]
     return 2.0 * Co @ Co.T, eps, C
+
+
+def two_electron(xyz, exps, coefs, tau):
+    """D -> G(D): G_ij = sum_kl D_kl [(ij|kl) - (ik|jl) / 2] over the kept integrals, formed once,
+    or a build per density above MAX_KEPT_ATOMS."""
+    n = len(xyz)
+    if n > MAX_KEPT_ATOMS:
+        return lambda D: fock_atoms(xyz, D, exps, coefs, tau)[0]
+    V = eri_tensor_atoms(xyz, exps, coefs, tau)
+    M = (V - 0.5 * V.transpose(0, 2, 1, 3)).reshape(n * n, n * n)
+    return lambda D: (M @ D.reshape(-1)).reshape(n, n)
 
 
 def diis_extrapolate(Fs, errs):
@@ -64,8 +78,9 @@ def scf(xyz, charges, exps, coefs, nocc, tau, max_iter=100, e_tol=1e-10, d_tol=1
     e_old = None
     converged = False
     it = 0
+    build = two_electron(xyz, exps, coefs, tau)
     for it in range(1, max_iter + 1):
-        G = fock_atoms(xyz, D, exps, coefs, tau)[0]
+        G = build(D)
         F = H + G
         E = 0.5 * float(np.sum(D * (H + F))) + enn
         err = X.T @ (F @ D @ S - S @ D @ F) @ X
