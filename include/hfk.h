@@ -320,13 +320,13 @@ hfk_status hfk_tune(int64_t natoms, const double *xyz, int32_t ngauss,
                     double *fock, double *e2, void *workspace, size_t workspace_bytes,
                     void *stream, const char *cache_path, int32_t *best_out);
 
-/* Autotuner of the batched path: times hfk_fock_batched on the given batch, one dimension
- * at a time from the untuned default: waves per workgroup {8, 4}, persistent workgroups per
- * compute unit 1..4, items (256 kets) per block {auto, 8, 16, 32, 64, 128}, and the
+/* Autotuner of the batched path: times hfk_fock_batched on the given batch, from what an
+ * untuned call runs: waves per workgroup {8, 4} with persistent workgroups per compute unit
+ * 1..4 (up to what fits on a CU), items (256 kets) per block {auto, 8, 16, 32, 64, 128}, and the
  * accumulation strategy {shared: blocks of a molecule added to G with atomics; owned:
  * molecules up to a work bound run whole in one workgroup and are stored without atomics,
  * bound {2^14, 2^16, 2^18} quartets}.  Keeps the fastest for the rest of the process under (device
- * architecture, precision), writes the table to cache_path when it is not NULL, and
+ * architecture, precision, ngauss, with or without d_xyz) for calls of one basis, writes the table to cache_path when it is not NULL, and
  * returns the chosen workgroups per CU in best_gpc_out (may be NULL).  Arguments as
  * hfk_fock_batched (outputs overwritten). */
 hfk_status hfk_tune_batched(int64_t nmol, const int64_t *atom_off_host, const double *xyz,
@@ -337,7 +337,8 @@ hfk_status hfk_tune_batched(int64_t nmol, const int64_t *atom_off_host, const do
                             const char *cache_path, int32_t *best_gpc_out);
 
 /* Loads a table written by hfk_tune / hfk_tune_batched (JSON); entries for another device
- * architecture are kept but not used on this one.  Errors: HFK_EINVAL (NULL, unreadable,
+ * architecture are kept but not used on this one, and a batched entry without ngauss, grad and
+ * atoms (older tables) applies to every batch of its precision.  Errors: HFK_EINVAL (NULL, unreadable,
  * not such a table, or an entry out of range). */
 hfk_status hfk_load_tuning(const char *cache_path);
 

@@ -4,6 +4,7 @@
 #include <stdio.h>
 #include <string.h>
 
+#include <algorithm>
 #include <mutex>
 #include <string>
 #include <utility>
@@ -262,6 +263,22 @@ struct BatchedConfig {
     int waves;              // waves per workgroup: 4 or 8
     bool automatic = false; // neither tuned nor set: waves and gpc follow the kernel's occupancy
 };
+static bool same(const BatchedConfig &a, const BatchedConfig &b)
+{
+    return a.gpc == b.gpc && a.block_items == b.block_items && a.owned_bound == b.owned_bound && a.waves == b.waves;
+}
+
+// What the batched kernel is compiled for besides the precision.  Its registers, and with them
+// the waves that fit on a CU, differ between kinds, so a tuned entry is of one kind (-1: of any,
+// as in tables written without it).
+struct BatchedKind {
+    int ngauss, grad, atoms;
+};
+static bool same(const BatchedKind &a, const BatchedKind &b)
+{
+    return a.ngauss == b.ngauss && a.grad == b.grad && a.atoms == b.atoms;
+}
+constexpr BatchedKind kAnyKind{-1, -1, -1};
 
 // Size bucket of the tuning table: ceil(log2 n).
 static int size_bucket(int64_t n)
@@ -299,6 +316,7 @@ struct TuneEntry {
 struct BatchedEntry {
     std::string arch;
     int precision;
+    BatchedKind kind;
     BatchedConfig cfg;
 };
 static std::mutex g_tune_mu;
@@ -400,22 +418,40 @@ static void set_items(Layout &L, int strat, int variant, int precision)
     if (precision == HFK_FP64 && variant != 0 && L.npair <= shared) L.nsplit = kWavesPerGroup;
 }
 
-static BatchedConfig pick_batched_config(int32_t precision)
+// A tuned entry of this kind of call, else one of any kind, else the default with its waves and
+// workgroups left to the kernel's occupancy; then the overrides.
+static BatchedConfig pick_batched_config(int32_t precision, const BatchedKind &kind)
 {
+    if (g_force_b) return *g_force_b;
     BatchedConfig c = default_batched_config();
     c.automatic = g_cfg_b.gpc <= 0 && g_cfg_b.waves <= 0;
-    if (g_force_b) return *g_force_b;
     {
         const std::string arch = device_arch();
         std::lock_guard<std::mutex> lk(g_tune_mu);
-        for (const BatchedEntry &e : g_tuned_b)
-            if (e.arch == arch && e.precision == precision) c = e.cfg;
+        for (const BatchedKind &k : {kAnyKind, kind})
+            for (const BatchedEntry &e : g_tuned_b)
+                if (e.arch == arch && e.precision == precision && same(e.kind, k)) c = e.cfg;
     }
     if (g_cfg_b.gpc > 0) c.gpc = g_cfg_b.gpc;
     if (g_cfg_b.block_items > 0) c.block_items = g_cfg_b.block_items;
     if (g_cfg_b.owned_bound != 0) c.owned_bound = g_cfg_b.owned_bound;
     if (g_cfg_b.waves > 0) c.waves = g_cfg_b.waves;
     return c;
+}
+
+// Waves and workgroups per CU of an automatic configuration: four-wave workgroups where more
+// waves fit on a CU that way.  The FP64 gradient's register count allows three waves per SIMD,
+// one eight-wave workgroup (300 clusters of up to 40 atoms: 4.4 ms against 5.7).
+static void settle_batched(BatchedConfig &c, int32_t precision, const BatchedKind &kind, int nmax)
+{
+    if (!c.automatic) return;
+    c.automatic = false;
+    const int f4 = batched_resident_groups(kind.ngauss, precision, kind.grad, kind.atoms, nmax, 4);
+    const int f8 = batched_resident_groups(kind.ngauss, precision, kind.grad, kind.atoms, nmax, 8);
+    if (4 * (f4 < kMaxBatchGroupsPerCU ? f4 : kMaxBatchGroupsPerCU) > 8 * (f8 < c.gpc ? f8 : c.gpc)) {
+        c.waves = 4;
+        c.gpc = kMaxBatchGroupsPerCU;
+    }
 }
 
 // ------------------------------------------------------------------ debug mode
@@ -1130,19 +1166,9 @@ static hfk_status fock_batched_impl(bool atoms, int64_t nmol, const int64_t *ato
                         "the molecules outside the tolerance: %.3e, tolerance %.3e)",
                         h.dchk_mol, bits_to_double(h.dchk_ratio), g_debug_tol);
     }
-    BatchedConfig bc = pick_batched_config(precision);
-    if (bc.automatic) {
-        // four-wave workgroups where more waves fit on a CU that way: the FP64 gradient's register
-        // count allows three waves per SIMD, one eight-wave workgroup (300 clusters of up to 40
-        // atoms: 4.4 ms against 5.7)
-        const bool gr = d_xyz != nullptr;
-        const int f4 = batched_resident_groups(ngauss, precision, gr, atoms, L.nmax, 4);
-        const int f8 = batched_resident_groups(ngauss, precision, gr, atoms, L.nmax, 8);
-        if (4 * (f4 < kMaxBatchGroupsPerCU ? f4 : kMaxBatchGroupsPerCU) > 8 * (f8 < bc.gpc ? f8 : bc.gpc)) {
-            bc.waves = 4;
-            bc.gpc = kMaxBatchGroupsPerCU;
-        }
-    }
+    const BatchedKind kind{ngauss, d_xyz != nullptr, atoms};
+    BatchedConfig bc = pick_batched_config(precision, kind);
+    settle_batched(bc, precision, kind, L.nmax);
     int gpc = bc.gpc;
     {
         const int fit = batched_resident_groups(ngauss, precision, d_xyz != nullptr, atoms, L.nmax, bc.waves);
@@ -1229,11 +1255,11 @@ static hfk_status write_tuning(const char *path)
     fprintf(f, "  ],\n  \"batched\": [\n");
     for (size_t x = 0; x < g_tuned_b.size(); ++x) {
         const BatchedEntry &t = g_tuned_b[x];
-        fprintf(f,
-                "    {\"arch\": \"%s\", \"precision\": %d, \"gpc\": %d, \"block_items\": %d, \"owned_bound\": %lld, "
-                "\"waves\": %d}%s\n",
-                t.arch.c_str(), t.precision, t.cfg.gpc, t.cfg.block_items, t.cfg.owned_bound, t.cfg.waves,
-                x + 1 < g_tuned_b.size() ? "," : "");
+        fprintf(f, "    {\"arch\": \"%s\", \"precision\": %d, ", t.arch.c_str(), t.precision);
+        if (t.kind.ngauss > 0)
+            fprintf(f, "\"ngauss\": %d, \"grad\": %d, \"atoms\": %d, ", t.kind.ngauss, t.kind.grad, t.kind.atoms);
+        fprintf(f, "\"gpc\": %d, \"block_items\": %d, \"owned_bound\": %lld, \"waves\": %d}%s\n", t.cfg.gpc,
+                t.cfg.block_items, t.cfg.owned_bound, t.cfg.waves, x + 1 < g_tuned_b.size() ? "," : "");
     }
     fprintf(f, "  ]\n}\n");
     fclose(f);
@@ -1251,15 +1277,17 @@ static void store_tuned(const std::string &arch, int precision, int bucket, cons
     g_tuned.push_back(TuneEntry{arch, precision, bucket, c});
 }
 
-static void store_tuned_b(const std::string &arch, int precision, const BatchedConfig &c)
+// An entry of any kind replaces every entry of its precision.
+static void store_tuned_b(const std::string &arch, int precision, const BatchedKind &kind, const BatchedConfig &c)
 {
     std::lock_guard<std::mutex> lk(g_tune_mu);
-    for (BatchedEntry &e : g_tuned_b)
-        if (e.arch == arch && e.precision == precision) {
-            e.cfg = c;
-            return;
-        }
-    g_tuned_b.push_back(BatchedEntry{arch, precision, c});
+    const bool any = same(kind, kAnyKind);
+    g_tuned_b.erase(std::remove_if(g_tuned_b.begin(), g_tuned_b.end(),
+                                   [&](const BatchedEntry &e) {
+                                       return e.arch == arch && e.precision == precision && (any || same(e.kind, kind));
+                                   }),
+                    g_tuned_b.end());
+    g_tuned_b.push_back(BatchedEntry{arch, precision, kind, c});
 }
 
 extern "C" {
@@ -1342,7 +1370,9 @@ hfk_status hfk_tune_batched(int64_t nmol, const int64_t *atom_off_host, const do
         return fail(HFK_EINVAL, "precision must be HFK_FP64 or HFK_MIXED (got %d)", (int)precision);
     hipStream_t st = (hipStream_t)stream;
     hfk_status err = HFK_OK;
+    // what an untuned call runs
     BatchedConfig best = default_batched_config();
+    best.automatic = true;
     BatchedConfig cand;
     auto run = [&]() {
         return hfk_fock_batched(nmol, atom_off_host, xyz, ngauss, exps_host, coefs_host, dens_packed, tau, precision,
@@ -1356,29 +1386,44 @@ hfk_status hfk_tune_batched(int64_t nmol, const int64_t *atom_off_host, const do
         return ms;
     };
     double best_ms = timed(best);
-    auto try_dim = [&](auto set, const long long *vals, int nv) {
-        for (int x = 0; x < nv && err == HFK_OK; ++x) {
-            BatchedConfig c = best;
-            set(c, vals[x]);
-            if (memcmp(&c, &best, sizeof(c)) == 0) continue;
-            const double ms = timed(c);
-            if (err == HFK_OK && ms < best_ms * (1.0 - kTuneMargin)) {
-                best_ms = ms;
-                best = c;
-            }
+    if (err != HFK_OK) return err;
+    const BatchedKind kind{ngauss, d_xyz != nullptr, 0};
+    const int nmax = make_blayout(nmol, atom_off_host, ngauss, kind.grad, false).nmax;
+    settle_batched(best, precision, kind, nmax);
+    auto try_config = [&](const BatchedConfig &c) {
+        if (err != HFK_OK || same(c, best)) return;
+        const double ms = timed(c);
+        if (err == HFK_OK && ms < best_ms * (1.0 - kTuneMargin)) {
+            best_ms = ms;
+            best = c;
         }
     };
-    const long long gpcs[4] = {1, 2, 3, 4};
-    const long long items[6] = {0, 8, 16, 32, 64, 128};
-    const long long owned[4] = {-1, 1LL << 14, 1LL << 16, 1LL << 18};
-    const long long waves[2] = {8, 4};
-    try_dim([](BatchedConfig &c, long long v) { c.waves = (int)v; }, waves, 2);
-    try_dim([](BatchedConfig &c, long long v) { c.gpc = (int)v; }, gpcs, 4);
-    try_dim([](BatchedConfig &c, long long v) { c.block_items = (int)v; }, items, 6);
-    try_dim([](BatchedConfig &c, long long v) { c.owned_bound = v; }, owned, 4);
-    try_dim([](BatchedConfig &c, long long v) { c.gpc = (int)v; }, gpcs, 4);
+    // waves and workgroups per CU together: one without the other may not fit the registers
+    auto try_waves = [&]() {
+        for (const int waves : {8, 4})
+            for (int gpc = 1; gpc <= kMaxBatchGroupsPerCU; ++gpc) {
+                const int fit = batched_resident_groups(ngauss, precision, kind.grad, false, nmax, waves);
+                if (fit > 0 && gpc > fit) break;   // more would only queue
+                BatchedConfig c = best;
+                c.waves = waves;
+                c.gpc = gpc;
+                try_config(c);
+            }
+    };
+    try_waves();
+    for (const int items : {0, 8, 16, 32, 64, 128}) {
+        BatchedConfig c = best;
+        c.block_items = items;
+        try_config(c);
+    }
+    for (const long long owned : {-1LL, 1LL << 14, 1LL << 16, 1LL << 18}) {
+        BatchedConfig c = best;
+        c.owned_bound = owned;
+        try_config(c);
+    }
+    try_waves();
     if (err != HFK_OK) return err;
-    store_tuned_b(device_arch(), precision, best);
+    store_tuned_b(device_arch(), precision, kind, best);
     if (best_gpc_out) *best_gpc_out = best.gpc;
     if (cache_path) return write_tuning(cache_path);
     return HFK_OK;
@@ -1452,7 +1497,15 @@ hfk_status hfk_load_tuning(const char *cache_path)
                 !json_ll(o, "waves", &v[3]) || v[0] < 1 || v[0] > kMaxBatchGroupsPerCU || v[1] < 0 || v[1] > 1024 ||
                 v[2] == 0 || v[2] < -1 || (v[3] != 4 && v[3] != 8))
                 return fail(HFK_EINVAL, "bad batched entry in %s", cache_path);
-            batched.push_back(BatchedEntry{arch, (int)prec, BatchedConfig{(int)v[0], (int)v[1], v[2], (int)v[3]}});
+            // tables written before entries had a kind apply to every call
+            long long k[3];
+            BatchedKind kind = kAnyKind;
+            if (json_ll(o, "ngauss", &k[0]) && json_ll(o, "grad", &k[1]) && json_ll(o, "atoms", &k[2])) {
+                if (k[0] < 1 || k[0] > HFK_MAX_NGAUSS || k[1] < 0 || k[1] > 1 || k[2] < 0 || k[2] > 1)
+                    return fail(HFK_EINVAL, "bad batched entry in %s", cache_path);
+                kind = BatchedKind{(int)k[0], (int)k[1], (int)k[2]};
+            }
+            batched.push_back(BatchedEntry{arch, (int)prec, kind, BatchedConfig{(int)v[0], (int)v[1], v[2], (int)v[3]}});
         } else {
             long long bucket;
             if (!json_ll(o, "size_bucket", &bucket) || !json_ll(o, "strategy", &v[0]) || !json_ll(o, "variant", &v[1]) ||
@@ -1466,7 +1519,7 @@ hfk_status hfk_load_tuning(const char *cache_path)
         }
     }
     for (const TuneEntry &e : single) store_tuned(e.arch, e.precision, e.bucket, e.cfg);
-    for (const BatchedEntry &e : batched) store_tuned_b(e.arch, e.precision, e.cfg);
+    for (const BatchedEntry &e : batched) store_tuned_b(e.arch, e.precision, e.kind, e.cfg);
     return HFK_OK;
 }
 
