@@ -310,7 +310,8 @@ hfk_status hfk_set_debug(int32_t on, double sym_tol);
  *   ket-side Coulomb vectors {one per workgroup, 8 shared, 32 shared},
  *   accumulation strategy {ATOMIC, PRIVATE}, quartet-kernel variant {hybrid, direct}.
  * The result is kept for the rest of the process under (device architecture, precision,
- * size bucket ceil(log2 natoms)) and written to cache_path as JSON when cache_path is not
+ * size bucket ceil(log2 natoms), ngauss; builds of another ngauss without an entry of their
+ * own take it too where the untuned default is the same, 1 to 4 or 5 and more) and written to cache_path as JSON when cache_path is not
  * NULL (with every other tuned entry of the process).  best_out (may be NULL) receives the
  * chosen hfk_strategy.  Inputs and workspace as hfk_fock (fock and e2 are overwritten).
  * Waits for `stream`.  Errors as hfk_fock. */
@@ -337,8 +338,9 @@ hfk_status hfk_tune_batched(int64_t nmol, const int64_t *atom_off_host, const do
                             const char *cache_path, int32_t *best_gpc_out);
 
 /* Loads a table written by hfk_tune / hfk_tune_batched (JSON); entries for another device
- * architecture are kept but not used on this one, and a batched entry without ngauss, grad and
- * atoms (older tables) applies to every batch of its precision.  Errors: HFK_EINVAL (NULL, unreadable,
+ * architecture are kept but not used on this one, and an entry without ngauss (a batched one
+ * without ngauss, grad and atoms), as in older tables, applies to every call of its precision
+ * and size.  Errors: HFK_EINVAL (NULL, unreadable,
  * not such a table, or an entry out of range). */
 hfk_status hfk_load_tuning(const char *cache_path);
 

@@ -311,6 +311,7 @@ struct TuneEntry {
     std::string arch;
     int precision;
     int bucket;
+    int ngauss;             // of the system it was timed on (0: not said, as in older tables)
     TunedConfig cfg;
 };
 struct BatchedEntry {
@@ -330,6 +331,9 @@ static BatchedConfig g_cfg_b{0, 0, 0, 0};
 static thread_local const TunedConfig *g_force = nullptr;
 static thread_local const BatchedConfig *g_force_b = nullptr;
 
+// From here on a chunk of 64 kets is so long (g^4 terms) that small systems are split finer.
+constexpr int kManyPrimitives = 5;
+
 // The configuration before any tuning.  Timed over whole calls (side kernels included) on
 // MI355X for He 64 to 1024 and H/He 128, FP64 and mixed: ATOMIC was the faster strategy at
 // every size (the per-workgroup copies of F and their summation cost more than the atomics
@@ -344,7 +348,7 @@ static TunedConfig default_config(int64_t n, int precision, int ngauss)
 {
     (void)precision;
     int tile = 2 * kTileItems;
-    if (ngauss >= 5 && n * (n + 1) / 2 <= 400) tile = 1;
+    if (ngauss >= kManyPrimitives && n * (n + 1) / 2 <= 400) tile = 1;
     return TunedConfig{HFK_STRATEGY_ATOMIC, 1, n <= 64 ? 4 : 6, tile, kGroupBras, kDefaultKetCopies};
 }
 
@@ -352,15 +356,23 @@ static TunedConfig default_config(int64_t n, int precision, int ngauss)
 // up to 96 atoms), automatic block size, every molecule in shared blocks.
 static BatchedConfig default_batched_config() { return BatchedConfig{2, 0, -1, 8}; }
 
-static bool lookup_tuned(const std::string &arch, int precision, int bucket, TunedConfig *out)
+// The entry of this many primitives, else one that does not say, else one on the same side of
+// kManyPrimitives, whose default is the same.
+static bool lookup_tuned(const std::string &arch, int precision, int bucket, int ngauss, TunedConfig *out)
 {
     std::lock_guard<std::mutex> lk(g_tune_mu);
-    for (const TuneEntry &e : g_tuned)
-        if (e.arch == arch && e.precision == precision && e.bucket == bucket) {
+    int best = 0;
+    for (const TuneEntry &e : g_tuned) {
+        if (e.arch != arch || e.precision != precision || e.bucket != bucket) continue;
+        const int rank = e.ngauss == ngauss ? 3
+                         : e.ngauss == 0    ? 2
+                                            : (e.ngauss >= kManyPrimitives) == (ngauss >= kManyPrimitives);
+        if (rank > best) {
+            best = rank;
             *out = e.cfg;
-            return true;
         }
-    return false;
+    }
+    return best > 0;
 }
 
 static TunedConfig pick_config(int32_t strategy, int32_t precision, int64_t n, int32_t ngauss)
@@ -370,7 +382,7 @@ static TunedConfig pick_config(int32_t strategy, int32_t precision, int64_t n, i
         c = *g_force;
     } else {
         TunedConfig t;
-        if (lookup_tuned(device_arch(), precision, size_bucket(n), &t)) c = t;
+        if (lookup_tuned(device_arch(), precision, size_bucket(n), ngauss, &t)) c = t;
         if (strategy == HFK_STRATEGY_PRIVATE || strategy == HFK_STRATEGY_ATOMIC) c.strategy = strategy;
         if (g_cfg_variant >= 0) c.variant = g_cfg_variant;
         if (g_cfg_gpc > 0) c.gpc = g_cfg_gpc;
@@ -1246,11 +1258,14 @@ static hfk_status write_tuning(const char *path)
     fprintf(f, "{\n  \"format\": \"hfk-tuning-2\",\n  \"entries\": [\n");
     for (size_t x = 0; x < g_tuned.size(); ++x) {
         const TuneEntry &t = g_tuned[x];
+        fprintf(f, "    {\"arch\": \"%s\", \"precision\": %d, \"size_bucket\": %d, ", t.arch.c_str(), t.precision,
+                t.bucket);
+        if (t.ngauss > 0) fprintf(f, "\"ngauss\": %d, ", t.ngauss);
         fprintf(f,
-                "    {\"arch\": \"%s\", \"precision\": %d, \"size_bucket\": %d, \"strategy\": %d, \"variant\": %d, "
-                "\"gpc\": %d, \"tile_items\": %d, \"group_bras\": %d, \"ket_copies\": %d}%s\n",
-                t.arch.c_str(), t.precision, t.bucket, t.cfg.strategy, t.cfg.variant, t.cfg.gpc, t.cfg.tile,
-                t.cfg.gbras, t.cfg.kcopies, x + 1 < g_tuned.size() ? "," : "");
+                "\"strategy\": %d, \"variant\": %d, \"gpc\": %d, \"tile_items\": %d, \"group_bras\": %d, "
+                "\"ket_copies\": %d}%s\n",
+                t.cfg.strategy, t.cfg.variant, t.cfg.gpc, t.cfg.tile, t.cfg.gbras, t.cfg.kcopies,
+                x + 1 < g_tuned.size() ? "," : "");
     }
     fprintf(f, "  ],\n  \"batched\": [\n");
     for (size_t x = 0; x < g_tuned_b.size(); ++x) {
@@ -1266,15 +1281,17 @@ static hfk_status write_tuning(const char *path)
     return HFK_OK;
 }
 
-static void store_tuned(const std::string &arch, int precision, int bucket, const TunedConfig &c)
+// An entry that does not say its ngauss replaces every entry of its precision and size.
+static void store_tuned(const std::string &arch, int precision, int bucket, int ngauss, const TunedConfig &c)
 {
     std::lock_guard<std::mutex> lk(g_tune_mu);
-    for (TuneEntry &e : g_tuned)
-        if (e.arch == arch && e.precision == precision && e.bucket == bucket) {
-            e.cfg = c;
-            return;
-        }
-    g_tuned.push_back(TuneEntry{arch, precision, bucket, c});
+    g_tuned.erase(std::remove_if(g_tuned.begin(), g_tuned.end(),
+                                 [&](const TuneEntry &e) {
+                                     return e.arch == arch && e.precision == precision && e.bucket == bucket &&
+                                            (ngauss == 0 || e.ngauss == ngauss);
+                                 }),
+                  g_tuned.end());
+    g_tuned.push_back(TuneEntry{arch, precision, bucket, ngauss, c});
 }
 
 // An entry of any kind replaces every entry of its precision.
@@ -1354,7 +1371,7 @@ hfk_status hfk_tune(int64_t natoms, const double *xyz, int32_t ngauss, const dou
     try_dim([](TunedConfig &c, int v) { c.gpc = v; }, gpcs, 6);
     try_dim([](TunedConfig &c, int v) { c.tile = v; }, tiles, 5);
     if (err != HFK_OK) return err;
-    store_tuned(device_arch(), precision, size_bucket(natoms), best);
+    store_tuned(device_arch(), precision, size_bucket(natoms), ngauss, best);
     if (best_out) *best_out = best.strategy;
     if (cache_path) return write_tuning(cache_path);
     return HFK_OK;
@@ -1514,11 +1531,14 @@ hfk_status hfk_load_tuning(const char *cache_path)
                 v[1] > 1 || v[2] < 1 || v[2] > kMaxGroupsPerCU || v[3] < 1 || v[3] > kMaxTileItems ||
                 !is_pow2_in(v[4], kMinGroupBras, kMaxGroupBras) || v[5] < 0 || v[5] > 1024)
                 return fail(HFK_EINVAL, "bad entry in %s", cache_path);
-            single.push_back(TuneEntry{arch, (int)prec, (int)bucket,
+            long long ng = 0;
+            if (json_ll(o, "ngauss", &ng) && (ng < 1 || ng > HFK_MAX_NGAUSS))
+                return fail(HFK_EINVAL, "bad entry in %s", cache_path);
+            single.push_back(TuneEntry{arch, (int)prec, (int)bucket, (int)ng,
                                        TunedConfig{(int)v[0], (int)v[1], (int)v[2], (int)v[3], (int)v[4], (int)v[5]}});
         }
     }
-    for (const TuneEntry &e : single) store_tuned(e.arch, e.precision, e.bucket, e.cfg);
+    for (const TuneEntry &e : single) store_tuned(e.arch, e.precision, e.bucket, e.ngauss, e.cfg);
     for (const BatchedEntry &e : batched) store_tuned_b(e.arch, e.precision, e.kind, e.cfg);
     return HFK_OK;
 }

@@ -87,3 +87,40 @@ def test_tuning_one_kind_of_batch_does_not_slow_another(hfk_dev, tmp_path):
     assert all(timed(grad) <= 1.05 * untuned[grad] for grad in (False, True))
     entries = json.load(open(path))["batched"]
     assert sorted((x["ngauss"], x["grad"], x["atoms"]) for x in entries) == [(3, 0, 0), (3, 1, 0)]
+
+
+def _tile(hfk, torch, dev, n, g):
+    s = random_cluster(n, 40 + g, box=6.0)
+    e, c = 0.2 * 3.0 ** np.arange(g - 1, -1, -1.0), np.linspace(0.2, 0.6, g)
+    ws = hfk.new_workspace(hfk.workspace_bytes(n, g, "fp64"), dev)
+    hfk.fock(torch.tensor(s.xyz, device=dev), torch.tensor(s.dens, device=dev), e, c, 1e-10, workspace=ws)
+    return hfk.read_stats(ws)["tile_items"]
+
+
+def test_entry_of_few_primitives_leaves_builds_of_many_their_default(hfk_dev, tmp_path):
+    # five and six primitives on few atoms have a default of their own (one item per block)
+    hfk, torch, dev = hfk_dev
+    announce("tuning keys of the single-molecule build")
+    gs = (1, 3, 4, 5, 6)
+    untuned = {g: _tile(hfk, torch, dev, 20, g) for g in gs}
+    entry = dict(precision=0, size_bucket=5, strategy=2, variant=1, gpc=4, group_bras=1024, ket_copies=8)
+    hfk.load_tuning(_table(tmp_path / "g3.json", _arch(torch), single=[dict(entry, tile_items=16, ngauss=3)]))
+    for g in gs:
+        assert _tile(hfk, torch, dev, 20, g) == (16 if g <= 4 else untuned[g]), g
+    hfk.load_tuning(_table(tmp_path / "g6.json", _arch(torch), single=[dict(entry, tile_items=4, ngauss=6)]))
+    for g in gs:
+        assert _tile(hfk, torch, dev, 20, g) == (16 if g <= 4 else 4), g
+    # an entry without ngauss takes the place of every entry of its precision and size
+    hfk.load_tuning(_table(tmp_path / "any.json", _arch(torch), single=[dict(entry, tile_items=2)]))
+    assert all(_tile(hfk, torch, dev, 20, g) == 2 for g in gs)
+
+
+def test_tuned_entry_names_its_primitives(hfk_dev, tmp_path):
+    hfk, torch, dev = hfk_dev
+    s = random_cluster(12, 3, box=6.0)
+    X, D = torch.tensor(s.xyz, device=dev), torch.tensor(s.dens, device=dev)
+    path = str(tmp_path / "t.json")
+    announce("tuner: two contractions of one size")
+    hfk.tune(X, D, s.exps, s.coefs, 1e-10, cache_path=path)
+    hfk.tune(X, D, [6.0, 3.0, 1.5, 0.8, 0.4, 0.2], [0.1, 0.2, 0.3, 0.4, 0.3, 0.2], 1e-10, cache_path=path)
+    assert [(x["size_bucket"], x["ngauss"]) for x in json.load(open(path))["entries"]] == [(4, 3), (4, 6)]
