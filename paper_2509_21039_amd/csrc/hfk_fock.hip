@@ -326,14 +326,23 @@ template <typename R> struct FockSmem {
                (det ? stage_bytes : 0);
     }
 };
-constexpr size_t kCuLds = (size_t)160 << 10, kStaticLds = 256;   // a CU's LDS; what the kernel declares itself
+constexpr size_t kCuLds = (size_t)160 << 10;   // a CU's LDS
+
+// LDS to count beside the carve-up.  FP64: the block counter's slot at the dynamic part's alignment;
+// with it the runtime's occupancy query gives the same workgroups for every size from 100 to 6144
+// atoms (three primitives).  With 256 bytes, 1303 to 1316 atoms were taken to hold three
+// workgroups of four waves, not four, and ran eight waves (1303 at 4 bohr 11.7 ms for 11.4, at 6
+// bohr 1.49 for 1.35).  FP32 keeps 256: exact, 1091 to 1105 atoms would run four waves without the
+// rows of D, where eight with them are ahead (1092 at 4 bohr 4.99 ms and 4.52).
+static size_t lds_beside(int prec) { return prec == HFK_MIXED ? 256 : 16; }
 
 // Workgroups of nw waves that the LDS and the waves the registers allow (five per SIMD in FP64,
 // six in FP32) leave a CU.
 static int fock_groups(int64_t n, int prec, bool drows, int nw)
 {
     const size_t need = (prec == HFK_MIXED ? FockSmem<float>::total((int)n, true, false, drows, nw)
-                                           : FockSmem<double>::total((int)n, true, false, drows, nw)) + kStaticLds;
+                                           : FockSmem<double>::total((int)n, true, false, drows, nw)) +
+                        lds_beside(prec);
     const int by_lds = (int)(kCuLds / need), by_waves = (prec == HFK_MIXED ? 24 : 20) / nw;
     return by_lds < by_waves ? by_lds : by_waves;
 }
@@ -765,10 +774,14 @@ int fock_resident_groups(int g, int prec, int variant, int64_t n, bool atoms, bo
 
 // The LDS rows of F grow with the atoms, and with four waves sharing them fewer and fewer waves
 // fit on a CU (12 at 2016 atoms): wider workgroups share a pair of rows among more waves, and are
-// taken where more waves then fit (2016 atoms at 4 bohr: FP64 33.8 ms with four, 30.0 with eight,
-// mixed 25.0 and 16.4).  Where the count is the same four waves lose less at the end of a block
-// (1024 atoms at 3 bohr 28.2 against 29.0 ms), and widths that the four SIMDs don't share evenly
-// lose on both sides (five waves 31.1, six 37.8).
+// taken where more waves then fit.  FP64 at 4 bohr, ms with four waves and with eight: 1303 atoms
+// 11.4 / 11.7 (16 waves a CU either way, four lose less at the end of a block), 1400 (12 and 16)
+// 16.0 / 13.6, 2016 33.8 / 29.9; mixed 1092 4.99 / 4.52, 2016 24.9 / 16.3.  With eight and with
+// sixteen, thinly spread (7 bohr): FP64 3400 6.5 / 7.2 (16 waves either way), 3813 on 10.9 / 8.7,
+// 6144 27.1 / 21.6; mixed 4300 9.0 / 10.5, 4500 14.3 / 11.2; per-atom bases 3800 19.1 / 14.7.
+// Below 1 ms the last blocks show: mixed 1092 atoms at 6 bohr 0.78 ms with four, 0.81 with eight.
+// Widths that the four SIMDs don't share evenly lose on both sides (2016 atoms: five waves 31.1,
+// six 37.8).
 int fock_waves_per_group(int g, int prec, int variant, int64_t n, bool atoms, bool det)
 {
     if (g > 3 || det || (variant == 0 && !atoms)) return kWavesPerGroup;
