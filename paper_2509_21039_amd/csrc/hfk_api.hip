@@ -412,22 +412,39 @@ static int block_groups(const Layout &L, int groups)
 // wave four chunks of 64 kets of an item: the screened kets are packed across them and a bra's
 // rows are cleared and flushed once per 4096 or 8192 kets.  Small ones have too few such items
 // to go round, and a bra with 500 kets leaves two of its four waves idle: one chunk per wave
-// there.  The line is where the two cross, in pairs (us, four chunks against one): 32 atoms
-// 90 / 77, 64 atoms 245 / 239 (mixed 201 / 198), 128 atoms 1087 / 1106; per-atom bases 100
-// atoms 948 / 903; with five or six primitives a chunk is ten times as long and the line lies
-// higher: 45 atoms 926 / 559, 90 atoms 4964 / 4121.  The smallest FP64 systems have fewer
-// chunks than SIMDs: their waves share one chunk, each with every fourth bra primitive pair
-// (8 atoms 49 / 40; 20 atoms with six primitives 184 / 99, with three 53 / 55).  Mixed builds
-// don't split: partial FP32 sums would round differently.
+// there.  The lines are in pairs, where the two cross (us on a 2 bohr lattice, four chunks / one),
+// and lie higher the longer a chunk is (g^4 terms):
+//   g = 1        17 atoms 37 / 35, 23 42 / 44, 32 51 / 62; per-atom 17 56 / 53, 20 52.5 / 54.6
+//   g = 2        23 52.5 / 48.8, 25 53.1 / 52.0, 29 58 / 61, 32 62 / 68; mixed 25 51.2 / 51.3
+//   g = 3 FP64   64 240 / 230, 72 275 / 266, 76 300 / 299, 84 375 / 378, 128 1016 / 1032;
+//                per-atom 109 1151 / 1080, 128 1712 / 1696, 150 2803 / 2831
+//   g = 3 mixed  60 183 / 166, 64 201 / 190, 66 192 / 196; per-atom 64 232 / 221, 66 216 / 231
+//   g = 4        127 4159 / 4017, 170 11205 / 11017, mixed 150 3439 / 3406, 170 5238 / 5248
+//   g = 5, 6     45 653 / 530, 127 10880 / 10034, 170 28650 / 27024, mixed 12303 / 11929 (g = 6);
+//                nothing larger was timed
+// Thinner lattices cross within a few atoms of the same places (3 and 4 bohr: 32 atoms with g = 1 50 /
+// 61 and 45 / 53, 90 with g = 3 mixed 221 / 219 and 158 / 164, 170 with g = 6 7700 / 7202).
+static int64_t one_chunk_pairs(int g, int precision, bool atoms)
+{
+    if (g >= 4) return 14600;
+    if (g == 3) return precision == HFK_MIXED ? 2100 : (atoms ? 8256 : 3000);
+    return g == 2 ? 330 : 190;
+}
+
+// The smallest FP64 systems have fewer chunks than SIMDs: their waves share one chunk, each with
+// every fourth bra primitive pair, up to as many pairs (us, a chunk per wave / shared): g = 4 24
+// atoms 105 / 89, 27 113 / 105, 30 117 / 122; g = 6 27 235 / 160, 30 308 / 269; g = 3 8 atoms 50 /
+// 40, 14 50 / 46, 17 53 / 51, 20 52 / 56; g = 2 10 38 / 36, 12 39 / 40; g = 1 the same within 1 us.
+// Mixed builds don't split: partial FP32 sums would round differently.
+static int64_t shared_chunk_pairs(int g) { return g >= 4 ? 400 : (g == 3 ? 120 : 64); }
+
 static void set_items(Layout &L, int strat, int variant, int precision)
 {
     if (strat == HFK_STRATEGY_DETERMINISTIC) return;
     L.nw = fock_waves_per_group(L.g, precision, variant, L.n, L.atoms, false);
-    const int64_t one_chunk = L.g >= 5 ? 8192 : (L.atoms ? 6000 : 2500);
-    if (L.npair > one_chunk) return;
+    if (L.npair > one_chunk_pairs(L.g, precision, L.atoms)) return;
     L.sub = 1;
-    const int64_t shared = L.g >= 5 ? 400 : 64;
-    if (precision == HFK_FP64 && variant != 0 && L.npair <= shared) L.nsplit = kWavesPerGroup;
+    if (precision == HFK_FP64 && variant != 0 && L.npair <= shared_chunk_pairs(L.g)) L.nsplit = kWavesPerGroup;
 }
 
 // A tuned entry of this kind of call, else one of any kind, else the default with its waves and
@@ -958,6 +975,25 @@ hfk_status hfk_set_debug(int32_t on, double sym_tol)
     return HFK_OK;
 }
 
+// Pairs up to which the gradient kernel's items hold one chunk per wave, for the forward build's
+// reasons (us on a 2 bohr lattice, four chunks / one): g = 1 24 atoms 44 / 42, 40 60 / 60, 48 69 /
+// 70, 128 370 / 416; g = 2 100 633 / 621, 109 815 / 826, 128 1317 / 1346, mixed 72 165 / 159, 80 192
+// / 195, 128 677 / 732; g = 3 64 416 / 355, 128 2267 / 2224, 150 3636 / 3607, 200 8729 / 8929, mixed
+// 109 744 / 738, 128 1066 / 1070, 150 1668 / 1712; g = 4 128 10894 / 10582, 150 18243 / 17964, mixed
+// 7095 / 6997; g = 5, 6 50 2694 / 1813, 150 57471 / 53709, 199 138606 / 135634, mixed 29549 / 29496.
+// Per-atom bases cross within a few atoms of the same places.
+static int64_t one_chunk_pairs_grad(int g, int precision)
+{
+    const bool mixed = precision == HFK_MIXED;
+    switch (g) {
+    case 1: return 820;
+    case 2: return mixed ? 2630 : 5050;
+    case 3: return mixed ? 6000 : 8256;
+    case 4: return 11400;
+    default: return 20000;
+    }
+}
+
 // hfk_fock_grad and hfk_fock_grad_atoms (atoms: exps/coefs are per-atom rows).
 static hfk_status fock_grad_impl(bool atoms, int64_t natoms, const double *xyz, int32_t ngauss,
                                  const double *exps_host, const double *coefs_host, const double *dens, double tau,
@@ -985,10 +1021,7 @@ static hfk_status fock_grad_impl(bool atoms, int64_t natoms, const double *xyz, 
     Layout L = make_layout(natoms, ngauss, precision, 1, groups_cap(cus), atoms);
     if (workspace_bytes < L.total)
         return fail(HFK_ENOMEM, "workspace holds %zu bytes, %zu needed", workspace_bytes, L.total);
-    // items of one chunk per wave on small systems, for the forward build's reasons (us, four
-    // chunks against one: 20 atoms 132 / 82, 64 atoms 437 / 378, 128 atoms 2341 / 2309, mixed
-    // 1102 / 1113; 50 atoms with six primitives 2694 / 1813; 200 atoms 8729 / 8929)
-    L.sub = L.npair <= (ngauss >= 5 ? 20000 : (precision == HFK_MIXED ? 6000 : 8256)) ? 1 : kSubChunks;
+    L.sub = L.npair <= one_chunk_pairs_grad(ngauss, precision) ? 1 : kSubChunks;
     // the gradient kernel's blocks: eight items (sixteen small ones), groups of 1024 bras, unless
     // hfk_set_shape asks for another shape (the pull-back build below takes the forward's shape)
     set_shape(L, g_cfg_tile > 0 ? g_cfg_tile : (L.sub == 1 ? 2 * kGradTileItems : kGradTileItems),
