@@ -663,7 +663,7 @@ hfk_status diagonalise(Ctx &c, const ScfLayout &SL, char *ws, const double *Fx, 
 hfk_status info_status(Ctx &c, int info)
 {
     if (info == 0) return HFK_OK;
-    snprintf(c.msg, c.msglen, "dsyevd did not converge (info = %d)", info);
+    snprintf(c.msg, c.msglen, "the symmetric eigenproblem did not converge (info = %d)", info);
     return HFK_EHIP;
 }
 

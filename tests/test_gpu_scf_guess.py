@@ -44,3 +44,17 @@ def test_scf_from_a_guess_vs_oracle(n, guess):
     assert r["converged"] and rel(r["E"], ref["E"]) < 1e-10
     assert abs(r["D"].cpu().numpy() - ref["D"]).max() < 1e-7
     assert abs(r["eps"].cpu().numpy() - ref["eps"]).max() < 1e-7
+
+
+def test_eigenproblem_with_nan_names_no_library_routine():
+    # three atoms: the library's own one-workgroup eigenproblem, not the linear-algebra library's
+    import torch
+    import paper_2509_21039_amd as hfk
+    dev = torch.device("cuda:0")
+    xyz, Z, e, c = _chains(3)
+    announce("scf nan guess n=3")
+    with pytest.raises(hfk.HfkError) as err:
+        hfk.scf(torch.tensor(xyz, device=dev), Z, e, c, 2, 1e-9,
+                dens0=torch.full((3, 3), float("nan"), dtype=torch.float64, device=dev))
+    assert err.value.status == hfk.HFK_EHIP
+    assert "did not converge" in str(err.value) and "dsyevd" not in str(err.value)
