@@ -344,9 +344,8 @@ constexpr int kManyPrimitives = 5;
 // Groups of 1024 bras.  Eight shared ket-side Coulomb vectors: they stay cached where one per
 // workgroup does not (he512 FP64 68.0 against 69.2 ms, he1024 mixed 210.0 against 221.2 ms,
 // he128 2.12 against 2.19 ms).
-static TunedConfig default_config(int64_t n, int precision, int ngauss)
+static TunedConfig default_config(int64_t n, int ngauss)
 {
-    (void)precision;
     int tile = 2 * kTileItems;
     if (ngauss >= kManyPrimitives && n * (n + 1) / 2 <= 400) tile = 1;
     return TunedConfig{HFK_STRATEGY_ATOMIC, 1, n <= 64 ? 4 : 6, tile, kGroupBras, kDefaultKetCopies};
@@ -377,7 +376,7 @@ static bool lookup_tuned(const std::string &arch, int precision, int bucket, int
 
 static TunedConfig pick_config(int32_t strategy, int32_t precision, int64_t n, int32_t ngauss)
 {
-    TunedConfig c = default_config(n, precision, ngauss);
+    TunedConfig c = default_config(n, ngauss);
     if (g_force) {
         c = *g_force;
     } else {
@@ -1220,7 +1219,7 @@ static hfk_status fock_batched_impl(bool atoms, int64_t nmol, const int64_t *ato
         if (fit > 0 && gpc > fit) gpc = fit;
     }
     const BatchedShape shape{gpc, bc.block_items, bc.owned_bound, bc.waves};
-    e = launch_batched(L, b, ws, atom_off_host, xyz, dens_packed, tau, precision, fock_packed, e2, d_xyz, cus * gpc,
+    e = launch_batched(L, b, ws, xyz, dens_packed, tau, precision, fock_packed, e2, d_xyz, cus * gpc,
                        shape, st);
     if (e != hipSuccess) return hip_fail(e, "batched launch");
     note_last(workspace, stream);
@@ -1356,7 +1355,7 @@ hfk_status hfk_tune(int64_t natoms, const double *xyz, int32_t ngauss, const dou
     if (cus <= 0) return fail(HFK_EHIP, "no HIP device");
     const Layout L0 = make_layout(natoms, ngauss, precision, 0, groups_cap(cus));
     hfk_status err = HFK_OK;
-    TunedConfig best = default_config(natoms, precision, ngauss);
+    TunedConfig best = default_config(natoms, ngauss);
     if (ngauss > 4) best.variant = 1;
     TunedConfig cand;
     auto run = [&]() {

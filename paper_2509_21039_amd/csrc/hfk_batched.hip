@@ -923,11 +923,10 @@ hipError_t upload_batch_tables(const BLayout &L, char *ws, const int64_t *atom_o
     return e;
 }
 
-hipError_t launch_batched(const BLayout &L, const Basis &b, char *ws, const int64_t *atom_off_host, const double *xyz,
-                          const double *dens, double tau, int prec, double *fock, double *e2, double *d_xyz,
-                          int groups, const BatchedShape &shape, hipStream_t st)
+hipError_t launch_batched(const BLayout &L, const Basis &b, char *ws, const double *xyz, const double *dens, double tau,
+                          int prec, double *fock, double *e2, double *d_xyz, int groups, const BatchedShape &shape,
+                          hipStream_t st)
 {
-    (void)atom_off_host;
     const int64_t nmol = L.nmol;
     hipError_t e = hipSuccess;
     DevHeader *hdr = (DevHeader *)(ws + L.hdr);

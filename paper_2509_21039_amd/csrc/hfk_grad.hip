@@ -84,7 +84,6 @@ template <> struct GPrec<double> {
     static __device__ const double *bip(const GradArgs &a) { return a.bip; }
     static __device__ const double *bgw(const GradArgs &a) { return a.bgw; }
     static __device__ const double *rsg(const BasisDev *bd) { return bd->rsg; }
-    static __device__ double rsqrt(double x) { return rsqrt_fp64(x); }
 };
 template <> struct GPrec<float> {
     static __device__ const float *boys() { return kBoysG32.v; }
@@ -93,7 +92,6 @@ template <> struct GPrec<float> {
     static __device__ const float *bip(const GradArgs &a) { return a.bip_f; }
     static __device__ const float *bgw(const GradArgs &a) { return a.bgw_f; }
     static __device__ const float *rsg(const BasisDev *bd) { return bd->rsg_f; }
-    static __device__ float rsqrt(float x) { return rsqrt_fp32(x); }
 };
 
 template <int G, typename R, bool kAtoms = false>

@@ -261,9 +261,9 @@ struct BatchedShape {
 // Copies the per-molecule tables (atom counts, offsets) into the workspace and waits for
 // the copies (their host staging ends with the call).
 hipError_t upload_batch_tables(const BLayout &L, char *ws, const int64_t *atom_off_host, hipStream_t st);
-hipError_t launch_batched(const BLayout &L, const Basis &b, char *ws, const int64_t *atom_off_host, const double *xyz,
-                          const double *dens, double tau, int prec, double *fock, double *e2, double *d_xyz,
-                          int groups, const BatchedShape &shape, hipStream_t st);
+hipError_t launch_batched(const BLayout &L, const Basis &b, char *ws, const double *xyz, const double *dens, double tau,
+                          int prec, double *fock, double *e2, double *d_xyz, int groups, const BatchedShape &shape,
+                          hipStream_t st);
 int batched_resident_groups(int g, int prec, bool grad, bool atoms, int nmax, int waves);
 // Debug check of densities on the device (results in the header's dchk fields, which the
 // first launch clears): one row-major n x n matrix, or nmol matrices at mol_doff with sizes
@@ -276,10 +276,13 @@ hipError_t launch_dens_check_batched(DevHeader *hdr, int64_t nmol, const long lo
 // primitive quartet is at most u_ab u_cd: S_ab S_cd E(r) with E <= (2/sqrt(pi)) sqrt(rho) and
 // sqrt(rho) = sqrt(p q / (p + q)) <= (p q)^(1/4) / sqrt(2).  The tables hold the binary
 // exponent e with u < 2^e, and the quartet kernels leave out a primitive quartet when
-// e_ab + e_cd <= term_limit(tau, prec), that is when it is below 1e-10 min(tau, 1e-10): ten
-// decimal orders under the screen of whole quartets, and so little that the sums do not change
-// in FP64 beyond their own rounding.  With FP32 integrals the line is at 1e-6 min(tau, 1e-10):
-// a matrix element of 1e5 quartets moves by 1e-11 at most, where FP32 rounding leaves 1e-8.
+// e_ab + e_cd <= term_limit(tau, prec), that is when it is below 1e-10 min(tau, 1e-10), with FP32
+// integrals below 1e-6 min(tau, 1e-10).  Up to g^4 terms of a quartet can be left out, so an
+// element that sums N quartets moves by at most 4 max|D| N g^4 times the line: tau = 1e-10, N =
+// 1e5, three primitives 3e-13, and 3e-9 with FP32 integrals (six primitives 5e-12 and 5e-8).  What
+// builds move by is far less, since few terms lie near the line: FP64 within their own rounding
+// (G at 512 atoms by 2e-15 in the Frobenius norm, at 2016 by 1e-15), FP32 1e-11 at 1024 atoms and 3e-10 over
+// 500 clusters, where FP32 rounding leaves 4e-8.
 // tau = 0 leaves nothing out.
 constexpr int kTermNever = -30000;    // exponent of a zero bound (left out unless tau = 0)
 constexpr int kTermAlways = 15000;    // of a bound that is not finite (never left out)

@@ -19,9 +19,8 @@ __global__ __launch_bounds__(256) void k_prep_begin(Basis b, BasisDev *__restric
 {
     const int t = threadIdx.x;
     const int g = b.g, g2 = b.g2;
-    if (blockIdx.x > 0 || gridDim.x == 1) {
-        const int64_t at = (int64_t)(gridDim.x == 1 ? 0 : blockIdx.x - 1) * blockDim.x + t;
-        const int64_t step = (int64_t)(gridDim.x == 1 ? 1 : gridDim.x - 1) * blockDim.x;
+    if (blockIdx.x > 0) {
+        const int64_t at = (int64_t)(blockIdx.x - 1) * blockDim.x + t, step = (int64_t)(gridDim.x - 1) * blockDim.x;
         for (int64_t x = at; x < g2 * g2; x += step) {
             const int ab = (int)x / g2, cd = (int)x % g2;
             const double p = b.alpha[ab / g] + b.alpha[ab % g];
@@ -57,8 +56,8 @@ __global__ __launch_bounds__(256) void k_prep_begin(Basis b, BasisDev *__restric
         }
         for (int64_t x = at; x < nf; x += step) fzero[x] = 0.0;
         for (int64_t x = at; x < ncnt; x += step) cnt[x] = 0;
+        return;
     }
-    if (blockIdx.x > 0) return;
     // centroid and bounding box (block reductions)
     __shared__ double red[3][256], rmin[3][256], rmax[3][256];
     double s0 = 0, s1 = 0, s2 = 0;
