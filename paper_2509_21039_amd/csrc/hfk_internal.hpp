@@ -280,8 +280,8 @@ hipError_t launch_dens_check_batched(DevHeader *hdr, int64_t nmol, const long lo
 // integrals below 1e-6 min(tau, 1e-10).  Up to g^4 terms of a quartet can be left out, so an
 // element that sums N quartets moves by at most 4 max|D| N g^4 times the line: tau = 1e-10, N =
 // 1e5, three primitives 3e-13, and 3e-9 with FP32 integrals (six primitives 5e-12 and 5e-8).  What
-// builds move by is far less, since few terms lie near the line: FP64 within their own rounding
-// (G at 512 atoms by 2e-15 in the Frobenius norm, at 2016 by 1e-15), FP32 1e-11 at 1024 atoms and 3e-10 over
+// builds move by is far less, since few terms lie near the line: FP64 within their own rounding (G
+// in the Frobenius norm 2e-15 at 512 atoms, 1e-15 at 2016), FP32 1e-11 at 1024 atoms and 3e-10 over
 // 500 clusters, where FP32 rounding leaves 4e-8.
 // tau = 0 leaves nothing out.
 constexpr int kTermNever = -30000;    // exponent of a zero bound (left out unless tau = 0)

@@ -188,8 +188,10 @@ __global__ __launch_bounds__(256) void k_lincomb(int64_t n2, Coefs cf, const dou
 // Up to kSmallScf atoms the dense part of an iteration is two launches of one workgroup with its
 // matrices in LDS: the error matrix with the scalars the host needs, and the extrapolation, the
 // eigenproblem and the density.  The libraries' route is some 60 launches per iteration (the
-// eigensolver's reduction alone 35 of them at 36 atoms, 0.9 ms in all): 36 atoms 14.6 ms per
-// SCF, in one workgroup 3.6 ms.  The eigenproblem is solved by cyclic Jacobi rotations, n/2
+// eigensolver's reduction alone 35 of them at 36 atoms, 0.9 ms in all): per SCF 12 atoms 5.3 ms, in
+// one workgroup 1.3; 36 atoms 14.0 and 3.6; 48 23.7 and 6.7; 63 33.9 and 11.8.  The limit is what
+// the kernels are laid out for (three matrices of 64 rows take 100 KB of LDS); larger systems were
+// not tried in one workgroup.  The eigenproblem is solved by cyclic Jacobi rotations, n/2
 // disjoint ones at a time (round-robin pairing), which suits one workgroup: a round is one
 // division-and-root chain and one pass over 2 x 2 blocks.  Its start is the last eigenvectors,
 // so that few sweeps remain once the density settles.
