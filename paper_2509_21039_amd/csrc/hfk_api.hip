@@ -228,6 +228,9 @@ constexpr int kGradTileItems = 8;
 // Largest system of the deterministic strategy: every workgroup needs its own copies of F
 // and of the ket vector within the workspace budgets, and four wave copies of rows i, j in LDS.
 constexpr int64_t kMaxDetAtoms = 1024;
+// Its workgroups per CU: a sixth, which the LDS holds in mixed builds of up to 81 atoms, is one more
+// copy per CU to sum (64 atoms 1085 us with six, 964 with five; per-atom 1145 and 1015).
+constexpr int kDetGroupsPerCU = 5;
 
 // Deterministic strategy: every workgroup must own a copy of F and of the ket vector.
 static hfk_status det_groups(Layout &L)
@@ -392,7 +395,7 @@ static TunedConfig pick_config(int32_t strategy, int32_t precision, int64_t n, i
     if (ngauss > 4) c.variant = 1;   // the direct form is built for g <= 4 only
     if (strategy == HFK_STRATEGY_DETERMINISTIC) {
         // a fixed configuration, independent of tuning and overrides (capped at residency)
-        c = TunedConfig{HFK_STRATEGY_DETERMINISTIC, 1, kMaxGroupsPerCU,
+        c = TunedConfig{HFK_STRATEGY_DETERMINISTIC, 1, kDetGroupsPerCU,
                         precision == HFK_MIXED ? 2 * kTileItems : kTileItems, kGroupBras, 0};
     }
     return c;
